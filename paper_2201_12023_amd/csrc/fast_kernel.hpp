@@ -335,7 +335,7 @@ void recurrence_fast_kernel(
     // at most two columns ahead of the last one: rows up to K + 1, so KP + 2 rows would do.
     constexpr int ROWS = KP + FAST_ROWS_SLACK;
     extern __shared__ int32_t lds[];                   // Fprev [NC][ROWS][64] (+ Fnext if WI > 1)
-    __shared__ int32_t sh_tk[NWK * WI];
+    __shared__ int32_t sh_tk[1];
     __shared__ int32_t sh_skip[NWK * WI];
     // stage counts the early-stop table spans: 64, or 128 for more than 64 layers on more
     // than 64 devices (stage counts never exceed either)
@@ -380,15 +380,7 @@ void recurrence_fast_kernel(
     unsigned long long n_blocks_total = 0;
 
     for (;;) {
-        // Every thread issues the atomic (thread 0 adds 1, the others 0) and all read thread
-        // 0's return value.  No branch on the thread id may appear in this loop: it would be
-        // loop-invariant, the compiler splits the loop on it, and the lanes of one wave then
-        // run the persistent loop out of step with each other.
-        // (each wave parks its first lane's return value; wave 0's first lane is thread 0)
-        sh_tk[wid] = __builtin_amdgcn_readfirstlane(atomicAdd(ticket, tid == 0 ? 1 : 0));
-        __syncthreads();
-        const int tk = __builtin_amdgcn_readfirstlane(sh_tk[0]);
-        __syncthreads();
+        const int tk = draw_ticket(ticket, tid, sh_tk);
         if (tk >= n_groups) break;                     // the workgroup's only exit
         const int j0 = (descending ? (n_groups - 1 - tk) : tk) * ncand;
         int jj[NC];                                    // candidate indices (the last may repeat;
@@ -936,12 +928,9 @@ void recurrence_fast_kernel(
                 const int slot = owner ? jj[e] : dummy_idx;
                 Fmin[slot] = bestD;                        // all lanes, same value
                 Sbest[slot] = bestD >= DEV_INF ? 0 : sD;
-                if (prune) {                               // uniform; the minimum is idempotent
-                    const long long T = (owner && bestD < DEV_INF)
-                                            ? (long long)bestD + (long long)(p.B - 1) * (long long)c_given[e]
-                                            : (long long)INF_I64;
-                    atomicMin((long long *)&chunk_min[jj[e] / PRUNE_CHUNK], T);
-                }
+                if (prune && j0 + e < n && bestD < DEV_INF)    // uniform
+                    publish_min(&chunk_min[jj[e] / PRUNE_CHUNK],
+                                (int64_t)bestD + (int64_t)(p.B - 1) * (int64_t)c_given[e], tid);
             }
         }
         if (COUNT) n_blocks_total += n_blocks;

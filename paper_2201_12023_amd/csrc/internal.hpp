@@ -107,6 +107,31 @@ __device__ __forceinline__ int64_t wave_prefix_min_i64(int64_t v, int lane)
     return v;
 }
 
+// Next ticket of a work counter, drawn by one thread of the workgroup (`tid` == 0) and handed to all of
+// them through *sh.  Two barriers.  The thread id goes through an opaque register on every call: a
+// branch on it inside a persistent loop is otherwise loop-invariant, the compiler splits the loop on
+// it, and the lanes of one wave then run the loop out of step with each other.  (All threads adding 0 but
+// one needs no branch, but is 64 serial operations a wave on one address: 512 workgroups of sixteen
+// waves spent 65 us there before their first candidate.)
+__device__ __forceinline__ int draw_ticket(int32_t *ticket, int tid, int32_t *sh)
+{
+    int t = tid;
+    asm volatile("" : "+v"(t));
+    if (t == 0) *sh = atomicAdd(ticket, 1);
+    __syncthreads();
+    const int tk = __builtin_amdgcn_readfirstlane(*sh);
+    __syncthreads();
+    return tk;
+}
+
+// atomicMin by one thread of the workgroup (see draw_ticket)
+__device__ __forceinline__ void publish_min(int64_t *p, int64_t v, int tid)
+{
+    int t = tid;
+    asm volatile("" : "+v"(t));
+    if (t == 0) atomicMin((long long *)p, (long long)v);
+}
+
 // ---- host-side launchers (callers validate sizes first; none of these synchronises)
 
 constexpr int SORT_SLICES = 1024;        // one-wave slices of the radix sort
