@@ -50,11 +50,13 @@ struct alpa_dp {
     int fast_grid_max[3] = {0, 0, 0}, generic_grid_max = 0;   // [nc] for nc = 1, 2
 
     int32_t *d_table = nullptr, *d_sizes = nullptr, *d_recs = nullptr, *d_gmin = nullptr;
+    int32_t *d_bounds = nullptr;    // what the table says about every candidate (launch_table_bounds)
+    int32_t *d_bound_work = nullptr;
     PrepBuffers pb{};
     int32_t *d_distinct = nullptr;
     uint32_t *d_ncount = nullptr;   // [2]: distinct table values, distinct caller candidates
     int32_t *d_cand = nullptr, *d_rank = nullptr, *d_tmax_stage = nullptr;
-    int32_t *d_Fmin = nullptr, *d_Sbest = nullptr;
+    int32_t *d_Fmin = nullptr, *d_Sbest = nullptr, *d_knots = nullptr;
     int64_t *d_T = nullptr, *d_outT_stage = nullptr, *d_chunkmin = nullptr;
     int cand_cap = 0;               // capacity of the per-candidate arrays
     SolveState *d_state = nullptr;
@@ -142,6 +144,9 @@ static void free_sweep_arrays(alpa_dp *h)
     h->sw_cap = 0;
 }
 
+// one kernel recovers the layers of all winners of a sweep (else a launch per layer, winner by winner)
+static bool plan_slabs(const alpa_dp *h) { return h->fast_ok && h->p.D <= 64; }
+
 static int alloc_sweep_arrays(alpa_dp *h, int n_B)
 {
     free_sweep_arrays(h);
@@ -153,7 +158,7 @@ static int alloc_sweep_arrays(alpa_dp *h, int n_B)
     HIPCHK(hipMalloc(&h->d_sw_n, 2 * 4));
     HIPCHK(hipMalloc(&h->d_sw_state, n * sizeof(SolveState)));
     HIPCHK(hipMalloc(&h->d_sw_plans, n * sizeof(alpa_plan_t)));
-    if (h->fast_ok && h->p.D <= 64) {   // one slab of layers per B value; the general kernel (also
+    if (plan_slabs(h)) {                // one slab of layers per B value; the general kernel (also
                                         // used above 64 devices) reuses d_Fall
         const size_t slab = (size_t)(h->p.Smax + 1) * (size_t)(h->p.K + 2) * (h->p.D + 1);
         HIPCHK(hipMalloc(&h->d_sw_Fall, n * slab * 4));
@@ -201,7 +206,8 @@ extern "C" void alpa_dp_destroy(alpa_dp_t *h)
     free_sweep_arrays(h);
     (void)hipFree(h->d_table); (void)hipFree(h->d_sizes); (void)hipFree(h->d_recs); (void)hipFree(h->d_gmin);
     (void)hipFree(h->pb.hist); (void)hipFree(h->d_ncount); (void)hipFree(h->d_state); (void)hipFree(h->d_scratch);
-    (void)hipFree(h->d_Fall); (void)hipFree(h->d_tmpFS); (void)hipFree(h->d_plan_tmp); (void)hipFree(h->d_best_plan);
+    (void)hipFree(h->d_Fall); (void)hipFree(h->d_tmpFS); (void)hipFree(h->d_plan_tmp); (void)hipFree(h->d_best_plan); (void)hipFree(h->d_knots);
+    (void)hipFree(h->d_bounds); (void)hipFree(h->d_bound_work);
     for (auto &e : h->ev) if (e) (void)hipEventDestroy(e);
     (void)hipSetDevice(prev);
     delete h;
@@ -260,11 +266,15 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     HIPCHK(hipMalloc(&h->d_state, sizeof(SolveState)));
     HIPCHK(hipMemsetAsync(h->d_state, 0, sizeof(SolveState), h->stream));
     HIPCHK(hipMalloc(&h->d_tmpFS, 4 * 4));
+    HIPCHK(hipMalloc(&h->d_knots, 2 * REFINE_MAX_KNOTS * 4));
     HIPCHK(hipMalloc(&h->d_plan_tmp, sizeof(alpa_plan_t)));
     HIPCHK(hipMalloc(&h->d_best_plan, sizeof(alpa_plan_t)));
     HIPCHK(launch_init_best_plan(h->stream, h->d_best_plan));
     const size_t LS = (size_t)(K + 2) * (D + 1);
     HIPCHK(hipMalloc(&h->d_Fall, (size_t)(h->p.Smax + 1) * LS * 4));
+    HIPCHK(hipMalloc(&h->d_bounds, table_bounds_ints(h->p) * 4));
+    HIPCHK(hipMalloc(&h->d_bound_work, table_bounds_work(h->p) * 4));
+    HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
     // general kernel: two F layers per resident workgroup, at most 256 MiB in total
     int gg = h->n_cu * 4;
     while (gg > 1 && (size_t)gg * 2 * LS * 4 > (256ull << 20)) gg /= 2;
@@ -412,6 +422,7 @@ extern "C" int alpa_dp_restrict_equal_layers(alpa_dp_t *h)
         restore{prev, h->device};
     const int K = h->p.K, D = h->p.D, S = h->p.S;
     HIPCHK(launch_equal_layer_mask(h->stream, h->d_table, K, S));
+    HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
     if (h->fast_ok) {
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
     }
@@ -516,6 +527,24 @@ static int candidate_bound(const alpa_dp *h, bool have_list, int n_tmax)
     return std::min(h->n_distinct, n_tmax);
 }
 
+// How a list of at most `bound` candidates is evaluated.  Up to `all` candidates worth searching go in one
+// round: rounds wait for each other, and a round of the register/LDS kernel takes about as long for 256
+// candidates as for 2048 (64 layers on 16 x 8, 1024 candidates: 0.71 ms in one round, 0.96 in two; 64 layers
+// on 8 x 8, 4096: 1.47 in one, 0.58 in two).  In the general kernel, a workgroup per candidate, it is the
+// work that counts, from fewer on.
+static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool general)
+{
+    RefineBuffers rb{};
+    rb.knots[0] = h->d_knots;
+    rb.knots[1] = h->d_knots + REFINE_MAX_KNOTS;
+    rb.list = h->pb.keys[0];                       // free once the candidates are known
+    rb.all = general ? 512 : 2048;
+    rb.first_round = 256;                          // a candidate per compute unit
+    rb.budget = 512;
+    rb.rounds = bound <= rb.all ? 1 : bound <= 8192 ? 2 : 3;
+    return rb;
+}
+
 // n_B > 0: sweep over the B values in d_sw_B (Eq. 4 and the selection once per value, plans
 // to d_sw_plans); otherwise one solve with the handle's B.
 static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigned flags,
@@ -542,6 +571,11 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     const int prune = n_B > 0 ? 0 : prune_sel;
     hipStream_t st = h->stream;
 
+    const bool fast = h->fast_ok && !(flags & ALPA_DP_GENERIC);
+    const RefineBuffers rb = plan_rounds(h, bound, !fast);
+    // per-candidate results are wanted from every interval; a plan alone from few of them
+    const RefineQuery rq{n_B > 0 ? h->d_sw_B : nullptr, p.B, std::max(n_B, 1), prune,
+                         (n_B > 0 || !d_out_T) ? 1 : 0, h->d_bounds, p.Smax};
     HIPCHK(hipEventRecord(h->ev[0], st));
     HIPCHK(launch_init_state(st, h->d_state, h->d_chunkmin, bound / PRUNE_CHUNK + 1));
     if (have_list) {
@@ -555,12 +589,17 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     } else {
         int rc = queue_table_candidates(h);
         if (rc) return rc;
-        HIPCHK(launch_pick_candidates(st, h->d_distinct, h->d_ncount + 0, n_tmax, h->d_cand,
+        HIPCHK(launch_pick_candidates(st, h->d_distinct, h->d_ncount + 0, n_tmax, bound, h->d_cand,
                                       h->d_state, h->cand_cap));
     }
+    HIPCHK(launch_refine_begin(st, rq, h->d_cand, h->d_Fmin, h->d_Sbest, h->d_state, rb));
     HIPCHK(hipEventRecord(h->ev[1], st));
-    if (bound > 0) {
-        const bool fast = h->fast_ok && !(flags & ALPA_DP_GENERIC);
+    for (int round = 1; bound > 0 && round <= rb.rounds; ++round) {
+        const bool last = round == rb.rounds;
+        if (round > 1)
+            HIPCHK(launch_refine(st, rq, h->d_cand, h->d_Fmin, h->d_state, round - 1, last, rb));
+        // candidates of a round before the last are knots: none of them may be skipped
+        const int skip = last ? prune : 0;
         if (fast) {
             // One candidate per workgroup: seven waves per SIMD and two columns folded into one
             // three-operand minimum, which is faster than two candidates sharing their scalar
@@ -585,30 +624,51 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
             const int n_groups = (bound + per_wg - 1) / per_wg;
             const int grid = std::max(
                 1, std::min(n_groups, h->tune_grid ? h->tune_grid : h->fast_grid_max[nc]));
-            FastArgs fa{p, h->d_recs, h->d_sizes, h->d_cand, &h->d_state->n_cand,
-                        &h->d_state->ticket, &h->d_state->wave_relax, h->d_chunkmin, prune,
-                        /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cand_cap, nullptr, nullptr, h->d_gmin};
+            FastArgs fa{p, h->d_recs, h->d_sizes, h->d_cand, rb.list,
+                        &h->d_state->n_list, 0, INT32_MAX,
+                        &h->d_state->ticket, &h->d_state->wave_relax, h->d_chunkmin, skip,
+                        /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cand_cap, nullptr, nullptr, h->d_gmin, h->d_bounds};
             fa.grouped = group_dp;
+            // Short lists go to forms with more waves per candidate (two of sixteen or four of eight waves per
+            // compute unit instead of eight of four; 256 candidates of 64 layers on 8 x 8, t_max at the 20 %
+            // quantile: 127, 163 and 262 us), on 65..128 devices, at half the occupancy, up to one candidate per compute unit (16 x 8: 257
+            // against 536 us, but 760 against 714 for 1024).  How long a list is only the device knows:
+            // each launch does nothing unless the list is in its share.
+            const int most = last ? bound : std::max(rb.budget, round == 1 ? rb.all : 0);
+            const bool own_form = h->tune_nc || h->tune_no_groups >= 2 || h->tune_grid || h->tune_wg_per_cu;
+            if (!(flags & ALPA_DP_COUNT_WORK) && !own_form) {
+                fa.n_hi = wide ? h->n_cu : 2 * h->n_cu;
+                HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_FEW, nc, std::min(bound, fa.n_hi)));
+                fa.n_lo = fa.n_hi;
+                if (!wide && most > fa.n_lo) {
+                    fa.n_hi = 8 * h->n_cu;
+                    HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_MID, nc, std::min(bound, 4 * h->n_cu)));
+                    fa.n_lo = fa.n_hi;
+                }
+                fa.n_hi = INT32_MAX;
+            }
+            if (most > fa.n_lo)
             HIPCHK(launch_recurrence_fast(st, fa, (flags & ALPA_DP_COUNT_WORK) ? FAST_MODE_COUNT
                                                                               : FAST_MODE_BATCH,
                                           nc, grid));
         } else {
             const int grid = std::max(1, std::min(bound, h->generic_grid_max));
             HIPCHK(launch_recurrence_generic(st, p, h->d_table, h->d_sizes, h->d_cand,
-                                             &h->d_state->n_cand, &h->d_state->ticket,
-                                             h->d_chunkmin, prune, h->d_Fmin, h->d_Sbest,
-                                             h->d_scratch, 2, grid));
+                                             rb.list, &h->d_state->n_list, &h->d_state->ticket,
+                                             h->d_chunkmin, skip, h->d_Fmin, h->d_Sbest,
+                                             h->d_scratch, 2, h->d_bounds, grid));
         }
     }
     HIPCHK(hipEventRecord(h->ev[2], st));
     if (n_B > 0) {
         HIPCHK(launch_sweep_epilogue(st, h->d_sw_B, n_B, &h->d_state->n_cand, h->d_cand, h->d_Fmin,
                                      h->d_Sbest, h->d_sw_state, prune_sel, h->d_sw_c, h->d_sw_s));
-        if (h->fast_ok && p.D <= 64 && !(flags & ALPA_DP_GENERIC)) {
+        if (plan_slabs(h) && !(flags & ALPA_DP_GENERIC)) {
             const size_t slab = (size_t)(p.Smax + 1) * (size_t)(p.K + 2) * (p.D + 1);
-            FastArgs fa{p, h->d_recs, h->d_sizes, h->d_sw_c, h->d_sw_n, h->d_sw_n + 1,
+            FastArgs fa{p, h->d_recs, h->d_sizes, h->d_sw_c, nullptr, h->d_sw_n, 0, INT32_MAX,
+                        h->d_sw_n + 1,
                         &h->d_state->wave_relax, nullptr, 0, 0, h->d_sw_FS,
-                        h->d_sw_FS + (n_B + 1), n_B, h->d_sw_Fall, h->d_sw_s, h->d_gmin};
+                        h->d_sw_FS + (n_B + 1), n_B, h->d_sw_Fall, h->d_sw_s, h->d_gmin, nullptr};
             HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_PLAN, 1, std::min(n_B, h->n_cu)));
             HIPCHK(launch_plan_walk_many(st, p, h->d_table, h->d_sizes, h->d_sw_state,
                                          h->d_sw_Fall, slab, h->d_sw_plans, n_B));
@@ -632,10 +692,10 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                                 have_list ? n_tmax : bound, h->d_state, d_out_T));
     // every layer of the winning candidate (does nothing if there is none), then the walk
     if (h->fast_ok && p.D <= 64 && !(flags & ALPA_DP_GENERIC)) {
-        FastArgs fa{p, h->d_recs, h->d_sizes, &h->d_state->best_c,
-                    &h->d_state->plan_n, &h->d_state->plan_ticket, &h->d_state->wave_relax,
+        FastArgs fa{p, h->d_recs, h->d_sizes, &h->d_state->best_c, nullptr,
+                    &h->d_state->plan_n, 0, INT32_MAX, &h->d_state->plan_ticket, &h->d_state->wave_relax,
                     nullptr, 0, 0, h->d_tmpFS, h->d_tmpFS + 2, 1, h->d_Fall, &h->d_state->best_s,
-                    h->d_gmin};
+                    h->d_gmin, nullptr};
         HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_PLAN, 1, 1));
     } else {
         HIPCHK(launch_plan_layers(st, p, h->d_table, h->d_sizes, &h->d_state->best_c,

@@ -315,18 +315,19 @@ template <int NWK, int WI, int NC, bool DUMP, bool COUNT, bool WIDE = false, boo
 // to 80 as well and spill; asked for seven it stays within 64 of its own accord, which the
 // build step checks from the compiler's resource remarks.)
 __global__ __launch_bounds__(WAVE * NWK * WI)
-__attribute__((amdgpu_waves_per_eu((NC == 1 && WI == 1 && !DUMP && !WIDE && !GROUPED) ? 7 : 4)))
+__attribute__((amdgpu_waves_per_eu((NC == 1 && !DUMP && !WIDE && !GROUPED) ? 7 : 4)))
 void recurrence_fast_kernel(
     Problem p, const int32_t *__restrict__ recs_g, const int32_t *__restrict__ sizes_g,
-    const int32_t *__restrict__ cand, const int32_t *__restrict__ n_cand_p, int32_t *ticket,
+    const int32_t *__restrict__ cand, const int32_t *__restrict__ list,
+    const int32_t *__restrict__ n_list_p, int n_lo, int n_hi, int32_t *ticket,
     unsigned long long *wave_relax, int64_t *chunk_min, int prune, int descending,
     int32_t *__restrict__ Fmin, int32_t *__restrict__ Sbest, int dummy_idx,
     int32_t *__restrict__ F_all, const int32_t *__restrict__ s_top_p,
-    const int32_t *__restrict__ group_min, int group_dp)
+    const int32_t *__restrict__ group_min, const int32_t *__restrict__ s_bound, int group_dp)
 {
     static_assert((WI & (WI - 1)) == 0, "wave groups along the shape axis: a power of two");
     static_assert(!DUMP || NC == 1, "layer dump is for a single candidate");
-    static_assert(!WIDE || (NC == 2 && WI == 1 && !DUMP), "two windows use the two-candidate layout");
+    static_assert(!WIDE || (NC == 2 && !DUMP), "two windows use the two-candidate layout");
     static_assert(!GROUPED || (NC == 1 && WI == 1 && !DUMP && !WIDE), "lane groups: one-candidate form");
     constexpr int NCAND = WIDE ? 1 : NC;               // candidates per workgroup (not GROUPED)
     constexpr int NT = WAVE * NWK * WI;
@@ -369,7 +370,8 @@ void recurrence_fast_kernel(
     const int pk_cand_off = (lane >> 5) * ROWS * WAVE;
     const bool half1 = lane >= 32;
     const int32_t size_of_lane = sizes[min(lane, S - 1)];   // lane q holds a_q (S <= 64)
-    const int n = __builtin_amdgcn_readfirstlane(*n_cand_p);
+    const int n = __builtin_amdgcn_readfirstlane(*n_list_p);
+    if (n <= n_lo || n > n_hi) return;                 // the other form's share (whole grid)
     // GROUPED: lane = grp * DP + gl, group grp works for candidate j0 + grp on d - 1 = gl
     // (DP: a power of two, D <= DP <= 64, chosen by the host)
     const int DP = GROUPED ? group_dp : WAVE;
@@ -387,14 +389,15 @@ void recurrence_fast_kernel(
         int32_t c[NC], c_given[NC];                    //  both windows serve one candidate)
 #pragma unroll
         for (int e = 0; e < NC; ++e) {
-            jj[e] = WIDE ? j0 : min(j0 + e, n - 1);
+            const int pos = WIDE ? j0 : min(j0 + e, n - 1);
+            jj[e] = DUMP ? pos : __builtin_amdgcn_readfirstlane(list[pos]);
             c_given[e] = __builtin_amdgcn_readfirstlane(cand[jj[e]]);
             // as a filter every value from DEV_INF on is "no filter" (finite entries are far
             // below); clamped so that the sentinel entries themselves never pass it
             c[e] = min(c_given[e], DEV_INF - 1);
         }
         // GROUPED: every lane has its group's candidate; the scalar side works with the largest
-        const int jl = min(j0 + grp, n - 1);
+        const int jl = GROUPED ? list[min(j0 + grp, n - 1)] : 0;
         int32_t c_lane_given = 0, c_lane = 0, c_lo = 0;
         if constexpr (GROUPED) {
             c_lane_given = cand[jl];
@@ -467,9 +470,9 @@ void recurrence_fast_kernel(
             }
             }
         }
-        int32_t best[NC], sbest[NC];
+        int32_t best[NCAND], sbest[NCAND];
 #pragma unroll
-        for (int e = 0; e < NC; ++e) { best[e] = DEV_INF; sbest[e] = 0; }
+        for (int e = 0; e < NCAND; ++e) { best[e] = DEV_INF; sbest[e] = 0; }
         unsigned n_blocks = 0;
         // A launch that finds the records outside the L2 of its XCD (a first solve, or other
         // kernels since the last one) pays for it: the workgroups of an XCD walk the records
@@ -480,7 +483,7 @@ void recurrence_fast_kernel(
         // register that is never read; it stays reserved until the wait at the end of the ticket
         // (tied from asm to asm, so it keeps its place unless it is spilled: the build step
         // refuses a recurrence kernel that spills, to scratch or to accumulation registers).
-        constexpr bool WARM = FOLD;
+        constexpr bool WARM = FOLD && (WI == 1 || DUMP);
         // (more than 64 layers: the records of one candidate no longer fit the L2, every ticket
         // streams them in, so every ticket touches ahead)
         const bool warm_l2 = WARM && (NWK > 4 || tk < (int)gridDim.x);
@@ -851,7 +854,6 @@ void recurrence_fast_kernel(
                     }
             }
             __syncthreads();                           // every wave is done reading Fprev
-            int32_t f1[NC];
             if (WI == 1) {
 #pragma unroll
                 for (int e = 0; e < NC; ++e)
@@ -861,8 +863,6 @@ void recurrence_fast_kernel(
                         Fprev[(e * ROWS + rowB + u) * WAVE + lane] = acc[e][8 + u];
                     }
                 __syncthreads();
-#pragma unroll
-                for (int e = 0; e < NC; ++e) f1[e] = acc[e][0];   // F(s, first layer, .) in wave 0
             } else {
 #pragma unroll
                 for (int e = 0; e < NC; ++e)
@@ -873,12 +873,16 @@ void recurrence_fast_kernel(
                     }
                 __syncthreads();
                 int32_t *tmp = Fprev; Fprev = Fnext; Fnext = tmp;
-#pragma unroll
-                for (int e = 0; e < NC; ++e) f1[e] = Fprev[e * ROWS * WAVE + lane];   // row 0
             }
+            // F(s, first layer, all devices): row 0 of the layer at device count D (of the lane's group;
+            // else the same cell for every lane)
 #pragma unroll
-            for (int e = 0; e < NC; ++e)
-                if (f1[e] < best[e]) { best[e] = f1[e]; sbest[e] = s; }   // lowest s on ties
+            for (int e = 0; e < NCAND; ++e) {
+                int32_t f1 = Fprev[((WIDE ? (D - 1) / WAVE : e) * ROWS) * WAVE +
+                                         (GROUPED ? (lane & -DP) + D - 1 : (D - 1) & (WAVE - 1))];
+                if constexpr (!GROUPED) f1 = __builtin_amdgcn_readfirstlane(f1);
+                if (f1 < best[e]) { best[e] = f1; sbest[e] = s; }   // lowest s on ties
+            }
             if (DUMP) {
                 int32_t *Fs = F_out + (size_t)s * LS;
                 if (WI == 1) {
@@ -899,8 +903,21 @@ void recurrence_fast_kernel(
                 }
             }
         };
+        // No later layer can matter once the table's bound on them (s_bound[s]: the least F of more than
+        // s stages with no filter at all, so a lower bound for every candidate) has reached the best
+        // value so far: ties go to the lower s.
+        auto finished = [&](int s) {
+            if constexpr (DUMP) return false;
+            const int32_t bound = s_bound[s];
+            bool open = best[0] > bound;
+            if constexpr (NCAND > 1) open = open || best[NCAND - 1] > bound;
+            return __ballot(open) == 0;
+        };
         if (s_top >= 1) layer(1, std::true_type{});
-        for (int s = 2; s <= s_top; ++s) layer(s, std::false_type{});
+        for (int s = 2; s <= s_top; ++s) {
+            if (finished(s - 1)) break;
+            layer(s, std::false_type{});
+        }
         if constexpr (WARM) asm volatile("s_waitcnt vmcnt(0)" : "+v"(pf_touch) :: "memory");
         if constexpr (GROUPED) {
             // the lane of device count D in group grp holds F(s, first layer, all devices) of
@@ -916,14 +933,11 @@ void recurrence_fast_kernel(
                 atomicMin((long long *)&chunk_min[jl / PRUNE_CHUNK],
                           (long long)best[0] + (long long)(p.B - 1) * (long long)c_lane_given);
         } else {
-        // lane D-1 (of window (D-1)/64) holds F(s, first layer, all devices); wave 0 owns the
-            // results; a repeated last candidate goes to the spare slot
+        // wave 0 owns the results; a repeated last candidate goes to the spare slot
 #pragma unroll
             for (int e = 0; e < NCAND; ++e) {
-                const int32_t bv = (WIDE && D > WAVE) ? best[NC - 1] : best[e];
-                const int32_t sv = (WIDE && D > WAVE) ? sbest[NC - 1] : sbest[e];
-                const int32_t bestD = __builtin_amdgcn_readlane(bv, (D - 1) & (WAVE - 1));
-                const int32_t sD = __builtin_amdgcn_readlane(sv, (D - 1) & (WAVE - 1));
+                const int32_t bestD = __builtin_amdgcn_readfirstlane(best[e]);
+                const int32_t sD = __builtin_amdgcn_readfirstlane(sbest[e]);
                 const bool owner = (wid == 0) && (j0 + e < n);
                 const int slot = owner ? jj[e] : dummy_idx;
                 Fmin[slot] = bestD;                        // all lanes, same value
@@ -962,9 +976,9 @@ static hipError_t launch_one(hipStream_t st, const FastArgs &a, int grid)
     }
     hipLaunchKernelGGL((recurrence_fast_kernel<NWK, WI, NC, DUMP, COUNT, WIDE, GROUPED>), dim3(grid),
                        dim3(WAVE * NWK * WI), lds, st, a.p, a.recs,
-                       a.sizes, a.cand, a.n_cand_p, a.ticket, a.wave_relax, a.chunk_min, a.prune,
+                       a.sizes, a.cand, a.list, a.n_list_p, a.n_lo, a.n_hi, a.ticket, a.wave_relax, a.chunk_min, a.prune,
                        a.descending, a.Fmin, a.Sbest, a.dummy_idx, a.F_all, a.s_top_p, a.group_min,
-                       a.grouped);
+                       a.s_bound, a.grouped);
     return hipGetLastError();
 }
 
@@ -973,6 +987,12 @@ static hipError_t launch_nwk(hipStream_t st, const FastArgs &a, int mode, int nc
 {
     switch (mode) {
     case FAST_MODE_PLAN: return launch_one<NWK, plan_wi(NWK), 1, true, false>(st, a, grid);
+    case FAST_MODE_FEW:
+        if (a.p.D > WAVE) return launch_one<NWK, plan_wi(NWK), 2, false, false, true>(st, a, grid);
+        return launch_one<NWK, plan_wi(NWK), 1, false, false>(st, a, grid);
+    case FAST_MODE_MID:
+        if (a.p.D > WAVE) return launch_one<NWK, 2, 2, false, false, true>(st, a, grid);
+        return launch_one<NWK, 2, 1, false, false>(st, a, grid);
     case FAST_MODE_COUNT:
         if (a.p.D > WAVE) return launch_one<NWK, 1, 2, false, true, true>(st, a, grid);
         if (a.grouped) return launch_one<NWK, 1, 1, false, true, false, true>(st, a, grid);

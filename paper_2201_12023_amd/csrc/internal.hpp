@@ -29,7 +29,10 @@ struct SolveState {
     int32_t n_distinct;      // distinct finite table values seen by candidate preparation
     int32_t plan_n;          // 1 if a plan is to be recovered (a feasible winner exists)
     int32_t plan_ticket;     // ticket counter of the plan-recovery run
-    int32_t pad;
+    int32_t n_first;         // candidates [n_first, n_range) are searched (kernels_refine.hip)
+    int32_t n_range;
+    int32_t n_list;          // candidates to evaluate in the present round
+    int32_t n_knots;         // candidates evaluated so far
 };
 
 struct Problem {
@@ -154,10 +157,37 @@ hipError_t launch_distinct_by_bitmap(hipStream_t st, const int32_t *table, int K
                                      int32_t max_value, uint32_t *work, int32_t *out_unique,
                                      uint32_t *out_n_unique);
 size_t distinct_bitmap_words(int32_t max_value);
+
+// Rounds of evaluation (kernels_refine.hip)
+constexpr int REFINE_MAX_KNOTS = 4096;   // knots a refinement step takes in (LDS)
+struct RefineBuffers {
+    int32_t *knots[2];       // [REFINE_MAX_KNOTS] each: positions evaluated so far, ascending
+    int32_t *list;           // [candidate capacity] positions to evaluate in the present round
+    int all;                 // up to so many candidates worth searching: one round takes them all
+    int first_round;         // else: knots of the first round
+    int budget;              // points of a round that is neither the first nor the last
+    int rounds;              // launched; those behind one that has settled everything are empty
+};
+// What is asked of the candidates: per-candidate results, or the plan alone for one or several B values
+struct RefineQuery {
+    const int32_t *B_vals;   // device array of n_B values, or null: B
+    int B, n_B;
+    int prune;               // the early exit of Alg. 1 (one B value)
+    int plan_only;
+    const int32_t *bounds;   // launch_table_bounds
+    int Smax;
+};
+// `bound`: the host's upper bound of the number of candidates
 hipError_t launch_pick_candidates(hipStream_t st, const int32_t *distinct,
-                                  const uint32_t *n_distinct, int n_quantiles, int32_t *cand,
-                                  SolveState *state, int cap);
+                                  const uint32_t *n_distinct, int n_quantiles, int bound,
+                                  int32_t *cand, SolveState *state, int cap);
 hipError_t launch_set_candidates(hipStream_t st, const uint32_t *n_unique, SolveState *state);
+// first round: the range worth searching and its knots
+hipError_t launch_refine_begin(hipStream_t st, const RefineQuery &rq, const int32_t *cand, int32_t *Fmin,
+                               int32_t *Sbest, SolveState *state, const RefineBuffers &rb);
+// the step behind round `round` (1-based)
+hipError_t launch_refine(hipStream_t st, const RefineQuery &rq, const int32_t *cand, int32_t *Fmin,
+                         SolveState *state, int round, int last, const RefineBuffers &rb);
 hipError_t launch_rank_lookup(hipStream_t st, const int32_t *tmax, int n, const int32_t *unique,
                               const uint32_t *n_unique, int32_t *rank_of_orig);
 
@@ -180,13 +210,18 @@ int fast_group_min_stages(int K, int D);        // stage counts the early-stop t
 size_t fast_group_min_ints(int K, int D, int S);   // size of the early-stop table
 
 hipError_t launch_recurrence_generic(hipStream_t st, const Problem &p, const int32_t *table,
-                                     const int32_t *sizes, const int32_t *cand,
-                                     const int32_t *n_cand_p, int32_t *ticket, int64_t *chunk_min,
+                                     const int32_t *sizes, const int32_t *cand, const int32_t *list,
+                                     const int32_t *n_list_p, int32_t *ticket, int64_t *chunk_min,
                                      int prune, int32_t *Fmin, int32_t *Sbest, int32_t *scratch,
-                                     int n_layers, int grid);
+                                     int n_layers, const int32_t *s_bound, int grid);
 struct FastArgs {
     Problem p;
-    const int32_t *recs, *sizes, *cand, *n_cand_p;
+    const int32_t *recs, *sizes, *cand;
+    // positions in `cand` to evaluate, ascending, and their number (device memory); the plan mode
+    // takes candidates 0 .. *n_list_p - 1 instead.  The launch does nothing unless
+    // n_lo < *n_list_p <= n_hi.
+    const int32_t *list, *n_list_p;
+    int n_lo, n_hi;
     int32_t *ticket;
     unsigned long long *wave_relax;
     int64_t *chunk_min;
@@ -198,6 +233,7 @@ struct FastArgs {
     int32_t *F_all;
     const int32_t *s_top_p;
     const int32_t *group_min;   // early-stop table (launch_repack_fast)
+    const int32_t *s_bound;     // [Smax + 1]: the least unfiltered F of more than s stages (batch modes)
     // batch modes, at most 32 devices, one-candidate form: 0, or the width DP of the lane groups
     // (a power of two, D <= DP <= 32): 64 / DP candidates per workgroup
     int grouped = 0;
@@ -209,7 +245,7 @@ inline int fast_lane_group_width(int D)
     while (dp < D) dp <<= 1;
     return dp;
 }
-enum { FAST_MODE_BATCH = 0, FAST_MODE_COUNT = 1, FAST_MODE_PLAN = 2 };
+enum { FAST_MODE_BATCH = 0, FAST_MODE_COUNT = 1, FAST_MODE_PLAN = 2, FAST_MODE_FEW = 3, FAST_MODE_MID = 4 };
 hipError_t launch_recurrence_fast(hipStream_t st, const FastArgs &a, int mode, int nc, int grid);
 int fast_kernel_blocks_per_cu(int K, int nc);
 // the instances for 65-128 layers (kernels_fast_deep.hip)
@@ -220,6 +256,15 @@ int fast_kernel_blocks_per_cu_deep(int K, int nc);
 hipError_t launch_plan_layers(hipStream_t st, const Problem &p, const int32_t *table,
                               const int32_t *sizes, const int32_t *c_p, const int32_t *n_p,
                               const int32_t *s_top_p, int32_t *F_all);
+// bounds of the table (kernels_generic.hip): [0..Smax] the least unfiltered F of more than s stages, then
+// the smallest t_max with a plan and the stages of one; work: table_bounds_work() int32
+inline size_t table_bounds_ints(const Problem &p) { return (size_t)p.Smax + 3; }
+inline size_t table_bounds_work(const Problem &p)
+{
+    return 4 * (size_t)(p.K + 2) * (p.D + 1) + 2 * ((size_t)p.Smax + 1);
+}
+hipError_t launch_table_bounds(hipStream_t st, const Problem &p, const int32_t *table,
+                               const int32_t *sizes, int32_t *work, int32_t *bounds);
 hipError_t launch_epilogue(hipStream_t st, const Problem &p, const int32_t *cand,
                            const int32_t *Fmin, const int32_t *Sbest, SolveState *state, int prune,
                            int64_t *T);

@@ -47,7 +47,8 @@ __device__ __forceinline__ int32_t relax_cell(const Problem &p, const int32_t *_
 
 __device__ void fill_layers(const Problem &p, const int32_t *__restrict__ table,
                             const int32_t *__restrict__ sizes, int32_t c, int32_t *slot,
-                            int n_layers, int32_t *best_out, int32_t *sbest_out)
+                            int n_layers, const int32_t *__restrict__ s_bound, int32_t *best_out,
+                            int32_t *sbest_out)
 {
     const int K = p.K, D = p.D, S = p.S;
     const int LS = (K + 2) * (D + 1);
@@ -68,6 +69,7 @@ __device__ void fill_layers(const Problem &p, const int32_t *__restrict__ table,
         const int32_t f1 = cur[1 * (D + 1) + D];       // F(s, first layer, all devices)
         if (f1 < best) { best = f1; sbest = s; }       // lowest s on ties
         __syncthreads();
+        if (s_bound[s] >= best) break;                 // uniform: no later layer can be lower
     }
     *best_out = best;
     *sbest_out = sbest;
@@ -92,15 +94,16 @@ __device__ bool can_skip(const int64_t *chunk_min, int j, int32_t c, int B)
 constexpr int GENERIC_MAX_THREADS = 1024;
 __global__ __launch_bounds__(GENERIC_MAX_THREADS) void recurrence_generic_kernel(
     Problem p, const int32_t *__restrict__ table, const int32_t *__restrict__ sizes,
-    const int32_t *__restrict__ cand, const int32_t *__restrict__ n_cand_p, int32_t *ticket,
+    const int32_t *__restrict__ cand, const int32_t *__restrict__ list,
+    const int32_t *__restrict__ n_list_p, int32_t *ticket,
     int64_t *chunk_min, int prune, int32_t *__restrict__ Fmin, int32_t *__restrict__ Sbest,
-    int32_t *scratch, int n_layers)
+    int32_t *scratch, int n_layers, const int32_t *__restrict__ s_bound)
 {
     __shared__ int32_t sh_tk[GENERIC_MAX_THREADS];
     __shared__ int sh_skip[WAVE];
     const int LS = (p.K + 2) * (p.D + 1);
     int32_t *slot = scratch + (size_t)blockIdx.x * n_layers * LS;
-    const int n = *n_cand_p;
+    const int n = *n_list_p;
     for (;;) {
         // No branch on the thread id in this loop (it would be loop-invariant and the
         // compiler may split the loop on it, letting lanes of a wave run out of step):
@@ -108,9 +111,10 @@ __global__ __launch_bounds__(GENERIC_MAX_THREADS) void recurrence_generic_kernel
         // parks its return value and all read thread 0's.
         sh_tk[threadIdx.x] = atomicAdd(ticket, threadIdx.x == 0 ? 1 : 0);
         __syncthreads();
-        const int j = sh_tk[0];
+        const int tk = sh_tk[0];
         __syncthreads();
-        if (j >= n) break;                        // uniform exit: every wave reaches it
+        if (tk >= n) break;                       // uniform exit: every wave reaches it
+        const int j = list[tk];
         const int32_t c = cand[j];
         if (prune) {
             const bool sk = can_skip(chunk_min, j, c, p.B);    // same value in every wave
@@ -125,7 +129,7 @@ __global__ __launch_bounds__(GENERIC_MAX_THREADS) void recurrence_generic_kernel
             }
         }
         int32_t best, sbest;
-        fill_layers(p, table, sizes, c, slot, n_layers, &best, &sbest);
+        fill_layers(p, table, sizes, c, slot, n_layers, s_bound, &best, &sbest);
         Fmin[j] = best;                           // all threads, same value
         Sbest[j] = best >= DEV_INF ? 0 : sbest;
         if (prune && best < DEV_INF)              // uniform; the minimum is idempotent
@@ -185,6 +189,92 @@ __global__ __launch_bounds__(256) void plan_layer_kernel(
         for (int off = 32; off >= 1; off >>= 1) v = min(v, __shfl_xor(v, off, 64));
         if (lane == 0) cur[x] = v;
     }
+}
+
+// What a table says about every candidate at once, computed when the table is: the recurrence with no
+// filter (F), and with the largest latency of a plan in the place of their sum (G).  A filter only takes
+// terms away, so F(s, 1, D) bounds every candidate's layer s from below, and a candidate has a plan
+// exactly if it is at least the least G(s, 1, D).  One launch per layer, a wave per cell, its lanes over
+// the (last layer, shape) terms; F and G in two buffers each.  Bound by the launch (5 us a layer at 64
+// layers on 64 devices).
+__global__ __launch_bounds__(256) void bound_layer_kernel(Problem p, const int32_t *__restrict__ table,
+                                                          const int32_t *__restrict__ sizes, int s,
+                                                          const int32_t *__restrict__ F_prev,
+                                                          int32_t *__restrict__ F_cur,
+                                                          int32_t *__restrict__ at_end)
+{
+    const int K = p.K, D = p.D, S = p.S;
+    const int LS = (K + 2) * (D + 1);
+    const int32_t *G_prev = F_prev + LS;
+    int32_t *G_cur = F_cur + LS;
+    if (s == 0) {                                  // only F(0, K+1, 0) = G(0, K+1, 0) = 0
+        for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < 2 * LS; x += gridDim.x * blockDim.x)
+            F_cur[x] = (x == (K + 1) * (D + 1) || x == LS + (K + 1) * (D + 1)) ? 0 : DEV_INF;
+        return;
+    }
+    const int32_t *tab_s = table + (size_t)(s - 1) * K * K * S;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const int n_waves = (gridDim.x * blockDim.x) >> 6;
+    for (int x = wave; x < LS; x += n_waves) {
+        const int k = x / (D + 1), d = x - k * (D + 1);
+        int32_t v = DEV_INF, g = DEV_INF;
+        if (k >= 1 && k <= K - s + 1 && d >= s) {   // see relax_cell
+            const int i_first = (s == 1) ? K : k, i_last = K - s + 1;
+            const int n_terms = (i_last - i_first + 1) * S;
+            const int32_t *tp = tab_s + ((size_t)(k - 1) * K + (i_first - 1)) * S;
+            for (int j = lane; j < n_terms; j += WAVE) {
+                const int di = j / S, q = j - di * S;
+                const int a = sizes[q];
+                if (a > d) continue;
+                const int32_t t = tp[j];
+                if (t == INF_I32) continue;
+                const int at = (i_first + di + 1) * (D + 1) + d - a;
+                v = min(v, t + F_prev[at]);
+                g = min(g, max(t, G_prev[at]));
+            }
+        }
+        v = wave_min_i32(v);
+        g = wave_min_i32(g);
+        if (lane == 0) {
+            F_cur[x] = v;                          // (v <= DEV_INF: both sides of the sum are)
+            G_cur[x] = g;
+            if (x == (D + 1) + D) { at_end[2 * s] = v; at_end[2 * s + 1] = g; }
+        }
+    }
+}
+
+// bounds[s] = min over s' > s of F(s', 1, D), s = 0..Smax; bounds[Smax + 1] = the smallest t_max with a
+// plan (DEV_INF if there is none) and bounds[Smax + 2] = stages of a plan that it admits.
+__global__ __launch_bounds__(WAVE) void table_bounds_kernel(Problem p, const int32_t *__restrict__ at_end,
+                                                            int32_t *__restrict__ bounds)
+{
+    for (int s = threadIdx.x; s <= p.Smax; s += WAVE) {
+        int32_t m = DEV_INF;
+        for (int x = s + 1; x <= p.Smax; ++x) m = min(m, at_end[2 * x]);
+        bounds[s] = m;
+    }
+    int32_t g = DEV_INF, sg = 0;
+    for (int x = 1; x <= p.Smax; ++x) {            // all threads, same values
+        const int32_t v = at_end[2 * x + 1];
+        if (v < g) { g = v; sg = x; }
+    }
+    bounds[p.Smax + 1] = g;
+    bounds[p.Smax + 2] = sg;
+}
+
+// work: 4 layers of (K + 2)(D + 1) int32, then 2 (Smax + 1) more
+hipError_t launch_table_bounds(hipStream_t st, const Problem &p, const int32_t *table,
+                               const int32_t *sizes, int32_t *work, int32_t *bounds)
+{
+    const int LS = (p.K + 2) * (p.D + 1);
+    const int grid = std::min((LS + 3) / 4, 4096);     // four cells (waves) per block
+    int32_t *at_end = work + 4 * (size_t)LS;
+    for (int s = 0; s <= p.Smax; ++s)
+        hipLaunchKernelGGL(bound_layer_kernel, dim3(grid), dim3(256), 0, st, p, table, sizes, s,
+                           work + (size_t)((s + 1) & 1) * 2 * LS, work + (size_t)(s & 1) * 2 * LS, at_end);
+    hipLaunchKernelGGL(table_bounds_kernel, dim3(1), dim3(WAVE), 0, st, p, at_end, bounds);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- Eq. 4 + best selection
@@ -452,15 +542,16 @@ __global__ void init_best_plan_kernel(PlanDev *best)
 // ---------------------------------------------------------------- launchers
 
 hipError_t launch_recurrence_generic(hipStream_t st, const Problem &p, const int32_t *table,
-                                     const int32_t *sizes, const int32_t *cand,
-                                     const int32_t *n_cand_p, int32_t *ticket, int64_t *chunk_min,
+                                     const int32_t *sizes, const int32_t *cand, const int32_t *list,
+                                     const int32_t *n_list_p, int32_t *ticket, int64_t *chunk_min,
                                      int prune, int32_t *Fmin, int32_t *Sbest, int32_t *scratch,
-                                     int n_layers, int grid)
+                                     int n_layers, const int32_t *s_bound, int grid)
 {
     // a lone workgroup (a single candidate) gets the widest block
     const int threads = grid == 1 ? GENERIC_MAX_THREADS : 256;
     hipLaunchKernelGGL(recurrence_generic_kernel, dim3(grid), dim3(threads), 0, st, p, table, sizes,
-                       cand, n_cand_p, ticket, chunk_min, prune, Fmin, Sbest, scratch, n_layers);
+                       cand, list, n_list_p, ticket, chunk_min, prune, Fmin, Sbest, scratch, n_layers,
+                       s_bound);
     return hipGetLastError();
 }
 

@@ -309,28 +309,6 @@ __global__ __launch_bounds__(1024) void bitmap_write_kernel(const uint32_t *__re
 
 // ---------------------------------------------------------------- candidate lists
 
-__global__ void pick_candidates_kernel(const int32_t *__restrict__ distinct,
-                                       const uint32_t *__restrict__ n_distinct_p, int n_quantiles,
-                                       int32_t *__restrict__ cand, SolveState *state, int cap)
-{
-    const int n = (int)*n_distinct_p;
-    int C = (n_quantiles == 0 || n <= n_quantiles) ? n : n_quantiles;
-    if (C > cap) C = cap;
-    const bool all = (C == n);
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < C; j += gridDim.x * blockDim.x)
-        cand[j] = all ? distinct[j] : distinct[((long long)j * (n - 1)) / (n_quantiles - 1)];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        state->n_cand = C;
-        state->n_distinct = n;
-    }
-}
-
-__global__ void set_candidates_kernel(const uint32_t *__restrict__ n_unique_p, SolveState *state)
-{
-    state->n_cand = (int)*n_unique_p;
-    state->n_distinct = (int)*n_unique_p;
-}
-
 // rank_of_orig[j] = index of tmax[j] in the ascending distinct list (binary search)
 __global__ void rank_lookup_kernel(const int32_t *__restrict__ tmax, int n,
                                    const int32_t *__restrict__ unique,
@@ -415,24 +393,6 @@ size_t distinct_bitmap_words(int32_t max_value)
 {
     const size_t words = (size_t)max_value / 32 + 1;
     return words + (words + 1023) / 1024 + 1;
-}
-
-hipError_t launch_pick_candidates(hipStream_t st, const int32_t *distinct,
-                                  const uint32_t *n_distinct, int n_quantiles, int32_t *cand,
-                                  SolveState *state, int cap)
-{
-    int grid = (cap + 255) / 256;
-    if (grid > 1024) grid = 1024;
-    if (grid < 1) grid = 1;
-    hipLaunchKernelGGL(pick_candidates_kernel, dim3(grid), dim3(256), 0, st, distinct, n_distinct,
-                       n_quantiles, cand, state, cap);
-    return hipGetLastError();
-}
-
-hipError_t launch_set_candidates(hipStream_t st, const uint32_t *n_unique, SolveState *state)
-{
-    hipLaunchKernelGGL(set_candidates_kernel, dim3(1), dim3(1), 0, st, n_unique, state);
-    return hipGetLastError();
 }
 
 hipError_t launch_rank_lookup(hipStream_t st, const int32_t *tmax, int n, const int32_t *unique,

@@ -1,0 +1,315 @@
+// Which t_max candidates the recurrence is run for.
+//
+// F(s, k, d; t_max) of Eq. 3 is a minimum over the terms that pass the filter t_intra <= t_max, so
+// min_s F(s, 1, N*M; t_max) never grows with t_max: over the ascending candidate list it is a
+// staircase, and two evaluated candidates with the same value settle every candidate between
+// them.  The staircases of model-like tables have few steps (99 over the 4096 candidates of the
+// 64-layer expert workload on 8 x 8, 156 of 4096 and 223 of 7321 on the other two large ones), so the list is
+// evaluated in rounds: evenly spaced knots first, then points inside the intervals whose ends differ,
+// in the last round all of those.  What two knots cannot settle is evaluated; a table on which
+// every candidate has a value of its own is evaluated whole, in the last round.
+//
+// The winner of Eq. 4 is always an evaluated candidate: T* = F + (B - 1) t_max takes the lowest
+// t_max on ties, so within a step of the staircase the first candidate wins, and a candidate whose
+// predecessor has another value is never strictly inside an interval with equal ends.
+#include "internal.hpp"
+
+namespace alpa {
+
+constexpr int RF_THREADS = 1024;
+constexpr int RF_WAVES = RF_THREADS / WAVE;
+
+// Evenly spaced knot g of m over [0, n): both ends included.
+__device__ __forceinline__ int even_knot(int g, int m, int n)
+{
+    return m <= 1 ? 0 : (int)(((long long)g * (n - 1)) / (m - 1));
+}
+
+__global__ void pick_candidates_kernel(const int32_t *__restrict__ distinct,
+                                       const uint32_t *__restrict__ n_distinct_p, int n_quantiles,
+                                       int32_t *__restrict__ cand, SolveState *state, int cap)
+{
+    const int n = (int)*n_distinct_p;
+    int C = (n_quantiles == 0 || n <= n_quantiles) ? n : n_quantiles;
+    if (C > cap) C = cap;
+    const bool all = (C == n);
+    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < C; j += gridDim.x * blockDim.x)
+        cand[j] = all ? distinct[j] : distinct[((long long)j * (n - 1)) / (n_quantiles - 1)];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        state->n_cand = C;
+        state->n_distinct = n;
+    }
+}
+
+__global__ void set_candidates_kernel(const uint32_t *__restrict__ n_unique_p, SolveState *state)
+{
+    state->n_cand = (int)*n_unique_p;
+    state->n_distinct = (int)*n_unique_p;
+}
+
+// The range of candidates worth searching, and the first round's knots in it (one block).
+//   * Below the smallest t_max with a plan (bounds) every candidate is infeasible.
+//   * The first candidate j0 at or above it admits a plan of s stages, each at most that t_max, so
+//     T*(j0) <= U = s t_feas + (B - 1) t_max(j0): with the early exit of Alg. 1, nothing from the first
+//     candidate on with B t_max >= U is evaluated; where only the plan counts, a candidate
+//     with (least unfiltered F) + (B - 1) t_max >= U cannot win against j0.
+// The list is sorted as unsigned, so values below zero (only a device-side list can hold them) come last;
+// no entry passes them.
+__global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq, int all, int first_round,
+                                                                  const int32_t *__restrict__ cand,
+                                                                  int32_t *__restrict__ Fmin,
+                                                                  int32_t *__restrict__ Sbest,
+                                                                  SolveState *state,
+                                                                  int32_t *__restrict__ knots,
+                                                                  int32_t *__restrict__ list)
+{
+    __shared__ int sh_end;
+    const int C = state->n_cand;
+    const int64_t t_feas = rq.bounds[rq.Smax + 1], stages = rq.bounds[rq.Smax + 2];
+    int lo = 0, hi = C;                                // first index with a negative value
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (cand[mid] < 0) hi = mid; else lo = mid + 1;
+    }
+    const int n = lo;
+    lo = 0; hi = n;                                    // first index with a plan
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (cand[mid] >= t_feas) hi = mid; else lo = mid + 1;
+    }
+    const int j0 = t_feas >= DEV_INF ? n : lo;
+    if (threadIdx.x == 0) sh_end = (rq.prune || rq.plan_only) ? min(n, j0 + 1) : n;
+    __syncthreads();
+    if ((rq.prune || rq.plan_only) && j0 < n) {
+        for (int b = threadIdx.x; b < rq.n_B; b += RF_THREADS) {
+            const int64_t B = rq.B_vals ? rq.B_vals[b] : rq.B;
+            const int64_t U = stages * t_feas + (B - 1) * (int64_t)cand[j0];
+            const int64_t least = rq.bounds[0];
+            int x = j0 + 1, z = n;                     // first index in [x, z) that need not be looked at
+            while (x < z) {
+                const int mid = (x + z) >> 1;
+                const int64_t c = cand[mid];
+                if ((rq.prune && B * c >= U) || (rq.plan_only && least + (B - 1) * c >= U)) z = mid;
+                else x = mid + 1;
+            }
+            atomicMax(&sh_end, x);
+        }
+        __syncthreads();
+    }
+    const int end = sh_end;
+    const int m = end - j0 <= all ? end - j0 : first_round;
+    for (int j = threadIdx.x; j < m; j += RF_THREADS) {
+        const int k = j0 + even_knot(j, m, end - j0);
+        list[j] = k;
+        if (j < REFINE_MAX_KNOTS) knots[j] = k;
+    }
+    for (int j = threadIdx.x; j < j0; j += RF_THREADS) { Fmin[j] = DEV_INF; Sbest[j] = 0; }
+    for (int j = n + threadIdx.x; j < C; j += RF_THREADS) { Fmin[j] = DEV_INF; Sbest[j] = 0; }
+    // not evaluated, and not to be taken for a winner: a lower candidate has the lowest possible T here
+    // (with the early exit they lie behind it)
+    for (int j = end + threadIdx.x; j < n; j += RF_THREADS) { Fmin[j] = DEV_INF; Sbest[j] = 0; }
+    if (threadIdx.x == 0) {
+        state->n_first = j0;
+        state->n_range = end;
+        state->n_list = m;
+        state->n_knots = min(m, REFINE_MAX_KNOTS);
+    }
+}
+
+// Exclusive prefix sum of one value per thread over the block, and the block's total.
+__device__ __forceinline__ int block_scan(int v, int *sh, int &total)
+{
+    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x >> 6;
+    int x = v;
+#pragma unroll
+    for (int off = 1; off < WAVE; off <<= 1) {
+        const int o = __shfl_up(x, off, WAVE);
+        if (lane >= off) x += o;
+    }
+    __syncthreads();                                   // sh may still be read from the last call
+    if (lane == WAVE - 1) sh[w] = x;
+    __syncthreads();
+    int base = 0;
+    total = 0;
+#pragma unroll
+    for (int k = 0; k < RF_WAVES; ++k) {
+        const int t = sh[k];
+        base += k < w ? t : 0;
+        total += t;
+    }
+    return base + x - v;
+}
+
+// One step between two rounds (one block).  Reads F at the knots, decides which intervals between
+// neighbouring knots still need points, and writes the next round's list; `last`: that is every
+// point of those intervals, and the points of the others get their value here.
+//
+//   prune      the early exit of Alg. 1: nothing from the first index on at which
+//              the knots alone show B * t_max >= best so far is needed.
+//   plan_only  no per-candidate results are asked for: an interval is needed only if one of its points
+//              could still beat the best knot at or below it, i.e. its lower bound
+//              F(right end) + (B - 1) t_max(first point) is below that knot's T* for one of the B
+//              values.  The points of the others take the left end's F, an upper bound that
+//              leaves every prefix minimum (and with it the early exit) as it is.
+// Otherwise a step takes at most `budget` points, dealt to the intervals in proportion to their
+// lengths.
+__global__ __launch_bounds__(RF_THREADS) void refine_kernel(
+    RefineQuery rq, const int32_t *__restrict__ cand, int32_t *__restrict__ Fmin, SolveState *state,
+    int last, int budget, const int32_t *__restrict__ knots, int32_t *__restrict__ knots_out, int32_t *__restrict__ list)
+{
+    __shared__ int32_t kx[REFINE_MAX_KNOTS];           // knot positions
+    __shared__ int32_t kf[REFINE_MAX_KNOTS];           // F there
+    __shared__ int32_t kn[REFINE_MAX_KNOTS];           // points wanted right of the knot
+    __shared__ int sh[RF_WAVES];
+    __shared__ int sh_range;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid >> 6;
+    const int prune = rq.prune, plan_only = rq.plan_only;
+    const int m = state->n_knots;
+    int range = state->n_range;
+    for (int i = tid; i < m; i += RF_THREADS) {
+        const int x = knots[i];
+        kx[i] = x;
+        kf[i] = Fmin[x];
+    }
+    if (tid == 0) sh_range = range;
+    __syncthreads();
+    for (int i = tid; i < m; i += RF_THREADS)
+        kn[i] = (!plan_only && i + 1 < m && kf[i] != kf[i + 1]) ? kx[i + 1] - kx[i] - 1 : 0;
+    __syncthreads();
+    if (prune || plan_only) {
+        // a wave per B value (the waves without one sit this out)
+        for (int b = w; b < rq.n_B; b += RF_WAVES) {
+            const int64_t B = rq.B_vals ? rq.B_vals[b] : rq.B;
+            int64_t carry = INF_I64;
+            for (int i0 = 0; i0 < m; i0 += WAVE) {
+                const int i = i0 + lane;
+                int64_t t = INF_I64;
+                int64_t c = 0;
+                if (i < m) {
+                    c = cand[kx[i]];
+                    if (kf[i] < DEV_INF) t = (int64_t)kf[i] + (B - 1) * c;
+                }
+                const int64_t incl = min64(wave_prefix_min_i64(t, lane), carry);
+                if (plan_only && i + 1 < m && kf[i] != kf[i + 1] && kx[i + 1] - kx[i] > 1) {
+                    const int64_t lb = (int64_t)kf[i + 1] + (B - 1) * (int64_t)cand[kx[i] + 1];
+                    if (lb < incl) kn[i] = kx[i + 1] - kx[i] - 1;      // same value from any wave
+                }
+                if (prune) {
+                    // first knot at which the rule fires on the knots before it
+                    const int lo = __shfl_up(lo32(incl), 1, WAVE), hi = __shfl_up(hi32(incl), 1, WAVE);
+                    const int64_t excl = lane == 0 ? carry : i64_from(lo, hi);
+                    const uint64_t hit = __ballot(i < m && i > 0 && excl != INF_I64 && B * c >= excl);
+                    if (hit) {
+                        const int at = __ffsll((unsigned long long)hit) - 1;
+                        const int64_t e = i64_from(__shfl(lo32(excl), at, WAVE), __shfl(hi32(excl), at, WAVE));
+                        int a = kx[i0 + at - 1] + 1, z = kx[i0 + at];   // it fires in [a, z]
+                        while (a < z) {
+                            const int mid = (a + z) >> 1;
+                            if (B * (int64_t)cand[mid] >= e) z = mid; else a = mid + 1;
+                        }
+                        sh_range = a;                  // one B value with the early exit
+                        break;
+                    }
+                }
+                carry = i64_from(__shfl(lo32(incl), WAVE - 1, WAVE), __shfl(hi32(incl), WAVE - 1, WAVE));
+            }
+        }
+        __syncthreads();
+        range = min(range, sh_range);
+    }
+    // how many points each interval gets, and where they go
+    int mine = 0;
+    for (int i = tid; i < m; i += RF_THREADS) {
+        const int g = max(0, min(kn[i], range - kx[i] - 1));
+        kn[i] = g;
+        mine += g;
+    }
+    int total;
+    (void)block_scan(mine, sh, total);
+    const bool everything = last || total <= budget;
+    int list_base = 0, len_base = 0;
+    for (int i0 = 0; i0 < m; i0 += RF_THREADS) {
+        const int i = i0 + tid;
+        const int g = i < m ? kn[i] : 0;
+        int t0, t1;
+        const int before = len_base + block_scan(g, sh, t0);
+        int take = g;
+        if (!everything)                               // (all intervals together: `budget` points)
+            take = (int)(((long long)(before + g) * budget) / total) -
+                   (int)(((long long)before * budget) / total);
+        const int at = list_base + block_scan(take, sh, t1);
+        if (i < m) {
+            // a short share is written here; longer ones by whole waves below
+            kn[i] = take;
+            if (!last) knots_out[i + at] = kx[i];
+            for (int u = 0; u < take && take <= 4; ++u) {
+                const int j = everything ? kx[i] + 1 + u
+                                         : kx[i] + (int)(((long long)(g + 1) * (u + 1)) / (take + 1));
+                list[at + u] = j;
+                if (!last) knots_out[i + at + 1 + u] = j;
+            }
+        }
+        // (a wave's lanes hold 64 neighbouring intervals; its long ones one after the other)
+        for (uint64_t todo = __ballot(take > 4); todo; todo &= todo - 1) {
+            const int l = __ffsll((unsigned long long)todo) - 1;
+            const int tk = __shfl(take, l, WAVE), ap = __shfl(at, l, WAVE), gp = __shfl(g, l, WAVE);
+            const int s = i0 + w * WAVE + l, x = kx[s];
+            for (int u = lane; u < tk; u += WAVE) {
+                const int j = everything ? x + 1 + u : x + (int)(((long long)(gp + 1) * (u + 1)) / (tk + 1));
+                list[ap + u] = j;
+                if (!last) knots_out[s + ap + 1 + u] = j;
+            }
+        }
+        len_base += t0;
+        list_base += t1;
+    }
+    if (last) {
+        // every point that no round evaluates: its interval's ends agree, or it cannot matter
+        __syncthreads();
+        for (int i = w; i + 1 < m; i += RF_WAVES) {
+            if (kn[i] != 0) continue;
+            const int end = min(kx[i + 1], range);
+            for (int j = kx[i] + 1 + lane; j < end; j += WAVE) Fmin[j] = kf[i];
+        }
+    }
+    if (tid == 0) {
+        state->n_range = range;
+        state->n_list = list_base;
+        state->n_knots = last ? m : m + list_base;
+        state->ticket = 0;
+    }
+}
+
+hipError_t launch_pick_candidates(hipStream_t st, const int32_t *distinct,
+                                  const uint32_t *n_distinct, int n_quantiles, int bound,
+                                  int32_t *cand, SolveState *state, int cap)
+{
+    const int grid = std::max(1, std::min((bound + 255) / 256, 1024));
+    hipLaunchKernelGGL(pick_candidates_kernel, dim3(grid), dim3(256), 0, st, distinct, n_distinct,
+                       n_quantiles, cand, state, cap);
+    return hipGetLastError();
+}
+
+hipError_t launch_set_candidates(hipStream_t st, const uint32_t *n_unique, SolveState *state)
+{
+    hipLaunchKernelGGL(set_candidates_kernel, dim3(1), dim3(1), 0, st, n_unique, state);
+    return hipGetLastError();
+}
+
+hipError_t launch_refine_begin(hipStream_t st, const RefineQuery &rq, const int32_t *cand, int32_t *Fmin,
+                               int32_t *Sbest, SolveState *state, const RefineBuffers &rb)
+{
+    hipLaunchKernelGGL(refine_begin_kernel, dim3(1), dim3(RF_THREADS), 0, st, rq, rb.all, rb.first_round, cand, Fmin,
+                       Sbest, state, rb.knots[0], rb.list);
+    return hipGetLastError();
+}
+
+hipError_t launch_refine(hipStream_t st, const RefineQuery &rq, const int32_t *cand, int32_t *Fmin,
+                         SolveState *state, int round, int last, const RefineBuffers &rb)
+{
+    hipLaunchKernelGGL(refine_kernel, dim3(1), dim3(RF_THREADS), 0, st, rq, cand, Fmin, state, last, rb.budget,
+                       rb.knots[(round - 1) & 1], rb.knots[round & 1], rb.list);
+    return hipGetLastError();
+}
+
+}  // namespace alpa
