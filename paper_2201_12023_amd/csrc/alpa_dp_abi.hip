@@ -50,6 +50,9 @@ struct alpa_dp {
     int fast_grid_max[3] = {0, 0, 0}, generic_grid_max = 0;   // [nc] for nc = 1, 2
 
     int32_t *d_table = nullptr, *d_sizes = nullptr, *d_recs = nullptr, *d_gmin = nullptr;
+    int32_t *d_rowrecs = nullptr, *d_rowends = nullptr;
+    bool row_ok = false;
+    int row_grid = 0;
     int32_t *d_bounds = nullptr;    // what the table says about every candidate (launch_table_bounds)
     int32_t *d_bound_work = nullptr;
     PrepBuffers pb{};
@@ -145,7 +148,7 @@ static void free_sweep_arrays(alpa_dp *h)
 }
 
 // one kernel recovers the layers of all winners of a sweep (else a launch per layer, winner by winner)
-static bool plan_slabs(const alpa_dp *h) { return h->fast_ok && h->p.D <= 64; }
+static bool plan_slabs(const alpa_dp *h) { return (h->row_ok || h->fast_ok) && h->p.D <= 64; }
 
 static int alloc_sweep_arrays(alpa_dp *h, int n_B)
 {
@@ -207,7 +210,7 @@ extern "C" void alpa_dp_destroy(alpa_dp_t *h)
     (void)hipFree(h->d_table); (void)hipFree(h->d_sizes); (void)hipFree(h->d_recs); (void)hipFree(h->d_gmin);
     (void)hipFree(h->pb.hist); (void)hipFree(h->d_ncount); (void)hipFree(h->d_state); (void)hipFree(h->d_scratch);
     (void)hipFree(h->d_Fall); (void)hipFree(h->d_tmpFS); (void)hipFree(h->d_plan_tmp); (void)hipFree(h->d_best_plan); (void)hipFree(h->d_knots);
-    (void)hipFree(h->d_bounds); (void)hipFree(h->d_bound_work);
+    (void)hipFree(h->d_rowrecs); (void)hipFree(h->d_bounds); (void)hipFree(h->d_bound_work); (void)hipFree(h->d_rowends);
     for (auto &e : h->ev) if (e) (void)hipEventDestroy(e);
     (void)hipSetDevice(prev);
     delete h;
@@ -280,9 +283,17 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     while (gg > 1 && (size_t)gg * 2 * LS * 4 > (256ull << 20)) gg /= 2;
     h->generic_grid_max = gg;
     HIPCHK(hipMalloc(&h->d_scratch, (size_t)gg * 2 * LS * 4));
+    // 65-128 layers on up to 64 devices and 129-256 devices
+    h->row_ok = (K > 64 || D > 128) && row_serves(K, D, S);
+    if (h->row_ok) {
+        HIPCHK(hipMalloc(&h->d_rowrecs, row_table_ints(K, h->p.Smax, S) * 4));
+        HIPCHK(hipMalloc(&h->d_rowends, row_ends_ints(K, h->p.Smax, S) * 4));
+        HIPCHK(launch_repack_row(h->stream, h->d_table, K, h->p.Smax, S, h->d_rowrecs, h->d_rowends));
+        h->row_grid = h->n_cu * row_blocks_per_cu(K, D, S);
+    }
     // register/LDS kernel
     // above 64 devices: one candidate per workgroup, the two-window form of the kernel
-    h->fast_ok = K <= 128 && D <= 128;
+    h->fast_ok = !h->row_ok && K <= 128 && D <= 128;
     if (h->fast_ok) {
         h->KP = 16 * ((K + 15) / 16);
         HIPCHK(hipMalloc(&h->d_recs, fast_table_ints(K, S) * 4));
@@ -423,6 +434,8 @@ extern "C" int alpa_dp_restrict_equal_layers(alpa_dp_t *h)
     const int K = h->p.K, D = h->p.D, S = h->p.S;
     HIPCHK(launch_equal_layer_mask(h->stream, h->d_table, K, S));
     HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
+    if (h->row_ok)
+        HIPCHK(launch_repack_row(h->stream, h->d_table, K, h->p.Smax, S, h->d_rowrecs, h->d_rowends));
     if (h->fast_ok) {
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
     }
@@ -530,15 +543,15 @@ static int candidate_bound(const alpa_dp *h, bool have_list, int n_tmax)
 // How a list of at most `bound` candidates is evaluated.  Up to `all` candidates worth searching go in one
 // round: rounds wait for each other, and a round of the register/LDS kernel takes about as long for 256
 // candidates as for 2048 (64 layers on 16 x 8, 1024 candidates: 0.71 ms in one round, 0.96 in two; 64 layers
-// on 8 x 8, 4096: 1.47 in one, 0.58 in two).  In the general kernel, a workgroup per candidate, it is the
-// work that counts, from fewer on.
-static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool general)
+// on 8 x 8, 4096: 1.47 in one, 0.58 in two).  Where every candidate keeps a compute unit busy by itself (the
+// row kernel's sizes) the work counts from fewer on (128 layers, 1024 candidates: 2.28 in one, 1.53 in two).
+static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool one_per_cu)
 {
     RefineBuffers rb{};
     rb.knots[0] = h->d_knots;
     rb.knots[1] = h->d_knots + REFINE_MAX_KNOTS;
     rb.list = h->pb.keys[0];                       // free once the candidates are known
-    rb.all = general ? 512 : 2048;
+    rb.all = one_per_cu ? 512 : 2048;
     rb.first_round = 256;                          // a candidate per compute unit
     rb.budget = 512;
     rb.rounds = bound <= rb.all ? 1 : bound <= 8192 ? 2 : 3;
@@ -572,6 +585,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     hipStream_t st = h->stream;
 
     const bool fast = h->fast_ok && !(flags & ALPA_DP_GENERIC);
+    const bool row = h->row_ok && !(flags & ALPA_DP_GENERIC);
     const RefineBuffers rb = plan_rounds(h, bound, !fast);
     // per-candidate results are wanted from every interval; a plan alone from few of them
     const RefineQuery rq{n_B > 0 ? h->d_sw_B : nullptr, p.B, std::max(n_B, 1), prune,
@@ -600,7 +614,15 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
             HIPCHK(launch_refine(st, rq, h->d_cand, h->d_Fmin, h->d_state, round - 1, last, rb));
         // candidates of a round before the last are knots: none of them may be skipped
         const int skip = last ? prune : 0;
-        if (fast) {
+        if (row) {
+            FastArgs fa{p, nullptr, h->d_sizes, h->d_cand, rb.list, &h->d_state->n_list, 0, INT32_MAX,
+                        &h->d_state->ticket, &h->d_state->wave_relax, h->d_chunkmin, skip,
+                        /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cand_cap, nullptr, nullptr,
+                        nullptr, h->d_bounds};
+            HIPCHK(launch_recurrence_row(st, fa, h->d_rowrecs, h->d_rowends,
+                                         (flags & ALPA_DP_COUNT_WORK) ? FAST_MODE_COUNT : FAST_MODE_BATCH,
+                                         std::max(1, std::min(bound, h->row_grid))));
+        } else if (fast) {
             // One candidate per workgroup: seven waves per SIMD and two columns folded into one
             // three-operand minimum, which is faster than two candidates sharing their scalar
             // loads and lanes at four waves per SIMD (workload 4: 4.40 against 4.66 ms); the
@@ -669,7 +691,11 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                         h->d_sw_n + 1,
                         &h->d_state->wave_relax, nullptr, 0, 0, h->d_sw_FS,
                         h->d_sw_FS + (n_B + 1), n_B, h->d_sw_Fall, h->d_sw_s, h->d_gmin, nullptr};
-            HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_PLAN, 1, std::min(n_B, h->n_cu)));
+            if (row)
+                HIPCHK(launch_recurrence_row(st, fa, h->d_rowrecs, h->d_rowends, FAST_MODE_PLAN,
+                                             std::min(n_B, h->n_cu)));
+            else
+                HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_PLAN, 1, std::min(n_B, h->n_cu)));
             HIPCHK(launch_plan_walk_many(st, p, h->d_table, h->d_sizes, h->d_sw_state,
                                          h->d_sw_Fall, slab, h->d_sw_plans, n_B));
         } else {
@@ -691,7 +717,13 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         HIPCHK(launch_scatter_T(st, h->d_T, have_list ? h->d_rank : nullptr,
                                 have_list ? n_tmax : bound, h->d_state, d_out_T));
     // every layer of the winning candidate (does nothing if there is none), then the walk
-    if (h->fast_ok && p.D <= 64 && !(flags & ALPA_DP_GENERIC)) {
+    if (row && p.D <= 64) {
+        FastArgs fa{p, nullptr, h->d_sizes, &h->d_state->best_c, nullptr,
+                    &h->d_state->plan_n, 0, INT32_MAX, &h->d_state->plan_ticket, &h->d_state->wave_relax,
+                    nullptr, 0, 0, h->d_tmpFS, h->d_tmpFS + 2, 1, h->d_Fall, &h->d_state->best_s,
+                    nullptr, nullptr};
+        HIPCHK(launch_recurrence_row(st, fa, h->d_rowrecs, h->d_rowends, FAST_MODE_PLAN, 1));
+    } else if (h->fast_ok && p.D <= 64 && !(flags & ALPA_DP_GENERIC)) {
         FastArgs fa{p, h->d_recs, h->d_sizes, &h->d_state->best_c, nullptr,
                     &h->d_state->plan_n, 0, INT32_MAX, &h->d_state->plan_ticket, &h->d_state->wave_relax,
                     nullptr, 0, 0, h->d_tmpFS, h->d_tmpFS + 2, 1, h->d_Fall, &h->d_state->best_s,

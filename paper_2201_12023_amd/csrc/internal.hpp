@@ -252,6 +252,16 @@ int fast_kernel_blocks_per_cu(int K, int nc);
 hipError_t launch_recurrence_fast_deep(hipStream_t st, const FastArgs &a, int mode, int nc, int grid);
 int fast_kernel_blocks_per_cu_deep(int K, int nc);
 
+// a workgroup per candidate, t_intra by row broadcast (kernels_row.hip)
+bool row_serves(int K, int D, int S);
+int row_blocks_per_cu(int K, int D, int S);
+size_t row_table_ints(int K, int Smax, int S);
+size_t row_ends_ints(int K, int Smax, int S);
+hipError_t launch_repack_row(hipStream_t st, const int32_t *table, int K, int Smax, int S,
+                             int32_t *recs, int32_t *ends);
+hipError_t launch_recurrence_row(hipStream_t st, const FastArgs &f, const int32_t *recs,
+                                 const int32_t *ends, int mode, int grid);
+
 // plan recovery of one candidate, a launch per layer (general sizes)
 hipError_t launch_plan_layers(hipStream_t st, const Problem &p, const int32_t *table,
                               const int32_t *sizes, const int32_t *c_p, const int32_t *n_p,

@@ -108,3 +108,33 @@ def test_bound_on_late_layers(size):
             _same_plan(plan, p_ref)
         finally:
             B.alpa_dp_destroy(h)
+
+
+# the sizes of the kernel with a workgroup per candidate: 65-128 layers, 129-256 devices; one, odd and even numbers of
+# half-blocks of 8 layers, device counts at the edges of 16, 32, 64 and their multiples, many shapes
+ROW_CASES = [(65, 1, 2), (72, 1, 16), (73, 3, 8), (96, 4, 8), (121, 5, 4), (128, 8, 8), (128, 1, 1), (88, 60, 1),
+             (1, 17, 8), (8, 24, 8), (9, 32, 8), (17, 12, 16), (23, 60, 4), (40, 31, 8), (48, 16, 16), (54, 16, 16)]
+
+
+@pytest.mark.parametrize("size", ROW_CASES, ids=lambda s: f"K{s[0]}-{s[1]}x{s[2]}")
+@pytest.mark.parametrize("inf_frac", [0.0, 0.6])
+def test_workgroup_per_candidate_sizes(size, inf_frac):
+    K, N, M = size
+    w = W.random_problem(K + 7 * N, K, N, M, inf_frac=inf_frac, value_hi=9000)
+    cand = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), 12)
+    cand = np.unique(np.concatenate([cand, cand[:3] // 2, [2**31 - 2]])).astype(np.int32)
+    h = B.alpa_dp_create(w.table, K, N, M, w.B, w.shapes)
+    try:
+        for prune in (False, True):
+            T_ref, p_ref = oracle.solve_parallel(w.table, N, M, w.B, w.shapes, cand, prune, 8)
+            flags = B.ALPA_DP_PRUNE if prune else 0
+            for extra in (0, B.ALPA_DP_COUNT_WORK):
+                T, plan = B.alpa_dp_solve(h, cand, flags=flags | extra)
+                assert np.array_equal(T, T_ref)
+                _same_plan(plan, p_ref)
+        Bs = [1, 40]
+        for Bv, plan in zip(Bs, B.alpa_dp_solve_sweep(h, cand, Bs)):
+            _, p_ref = oracle.solve_parallel(w.table, N, M, Bv, w.shapes, cand, False, 8)
+            _same_plan(plan, p_ref)
+    finally:
+        B.alpa_dp_destroy(h)
