@@ -278,8 +278,9 @@ const char *alpa_dp_last_error(void);
  *   out_ms        NULL, or receives the device time of the kernels (HIP events).
  *
  * Errors: EINVAL (null pointer, K or L outside 1..ALPA_CLUSTER_MAX_OPS, bad edge, negative
- * figure, delta_ppm out of range), EOVERFLOW (the limits above), ENOMEM (8 K^2 + 4 L K bytes
- * of device memory are needed), EHIP.
+ * figure, delta_ppm out of range), EOVERFLOW (the limits above), ENOMEM (8 K W + 4 L K +
+ * 16 K min(L, 128) bytes of device memory are needed, W <= K the largest number of consecutive
+ * operators within the FLOP bound), EHIP.
  */
 #define ALPA_CLUSTER_MAX_OPS 4096
 int alpa_cluster_layers(const int32_t *flop, int K, const int32_t *edge_src,
@@ -309,7 +310,7 @@ int alpa_cluster_layers_exact(const int32_t *flop, int K, const int32_t *edge_sr
  * results; inputs and outputs are DEVICE pointers owned by the caller, the call only queues
  * kernels on `hip_stream` (a hipStream_t, NULL = the null stream) and returns; it calls no
  * hipMalloc / hipFree, copies nothing and does not synchronise.  The work memory is a fixed
- * array in the library's device image (about 3.2 MB per device, held until the process ends),
+ * array in the library's device image (about 4.4 MB per device, held until the process ends),
  * which limits K and L to ALPA_CLUSTER_STATIC_MAX_OPS.
  *
  *   d_flop, d_edge_src, d_edge_dst, d_edge_bytes   as for alpa_cluster_layers, device memory.

@@ -62,17 +62,14 @@ static int cluster_layers_impl(const int32_t *flop, int K, const int32_t *edge_s
     const int64_t cap = ((1000000ll + delta_ppm) * total) / ((int64_t)L * 1000000ll);
 
     hipStream_t st = nullptr;
-    DevBuf d_flop, d_src, d_dst, d_nb, d_Ct, d_chunk, d_pf, d_GV, d_arg, d_out, d_first;
-    const size_t E = (size_t)num_edges, Kp = (size_t)K + 1;
+    DevBuf d_flop, d_src, d_dst, d_nb, d_work, d_out, d_first;
+    const size_t E = (size_t)num_edges;
+    const int width = cluster_band_width(flop, K, cap);
     HIPCHK(d_flop.alloc((size_t)K * 4));
     HIPCHK(d_src.alloc(E * 4));
     HIPCHK(d_dst.alloc(E * 4));
     HIPCHK(d_nb.alloc(E * 8));
-    HIPCHK(d_Ct.alloc((size_t)K * K * 8));
-    HIPCHK(d_chunk.alloc(cluster_chunk_rows(K) * K * 8));
-    HIPCHK(d_pf.alloc(Kp * 8));
-    HIPCHK(d_GV.alloc(4 * Kp * 8));
-    HIPCHK(d_arg.alloc((size_t)L * Kp * 4));
+    HIPCHK(d_work.alloc(cluster_work_i64(K, L, width) * 8));
     HIPCHK(d_out.alloc(2 * 8));
     HIPCHK(d_first.alloc(((size_t)L + 1) * 4));
     HIPCHK(hipMemcpyAsync(d_flop.p, flop, (size_t)K * 4, hipMemcpyHostToDevice, st));
@@ -88,10 +85,9 @@ static int cluster_layers_impl(const int32_t *flop, int K, const int32_t *edge_s
         guard{ev0, ev1};
     HIPCHK(hipEventRecord(ev0, st));
     HIPCHK(launch_cluster(st, d_flop.as<int32_t>(), d_src.as<int32_t>(), d_dst.as<int32_t>(),
-                          d_nb.as<int64_t>(), num_edges, K, L, cap, d_Ct.as<int64_t>(),
-                          d_chunk.as<int64_t>(), d_pf.as<int64_t>(), d_GV.as<int64_t>(),
-                          d_arg.as<int32_t>(), d_out.as<int64_t>(), d_first.as<int32_t>(), nullptr, 0,
-                          exact));
+                          d_nb.as<int64_t>(), num_edges, K, L, cap, width,
+                          cluster_work(d_work.as<int64_t>(), K, L, width), d_out.as<int64_t>(),
+                          d_first.as<int32_t>(), nullptr, 0, exact));
     HIPCHK(hipEventRecord(ev1, st));
     int64_t res[2] = {0, 0};
     HIPCHK(hipMemcpyAsync(res, d_out.p, sizeof(res), hipMemcpyDeviceToHost, st));
@@ -124,12 +120,12 @@ extern "C" int alpa_cluster_layers_exact(const int32_t *flop, int K, const int32
 // ---------------------------------------------------------------- no allocation on the call
 
 // Work memory of alpa_cluster_layers_static: what alpa_cluster_layers allocates per call, at
-// the sizes of ALPA_CLUSTER_STATIC_MAX_OPS operators and layers, in int64 units:
-// Ct [K*K], chunk [ceil(K/64)*K], pf [K+1], GV [4*(K+1)], ctl [8], arg [L*(K+1)] int32.
+// the sizes of ALPA_CLUSTER_STATIC_MAX_OPS operators and layers with every operator feasible as
+// first one, in int64 units (cluster_work_i64), and the two words of the argument checks.
 namespace {
 constexpr size_t SMAX = ALPA_CLUSTER_STATIC_MAX_OPS;
-constexpr size_t SCRATCH_I64 = SMAX * SMAX + ((SMAX + 63) / 64) * SMAX + (SMAX + 1) +
-                               4 * (SMAX + 1) + 8 + (SMAX * (SMAX + 1) + 1) / 2;
+constexpr size_t SCRATCH_I64 = SMAX * SMAX + 2 * 129 * (SMAX + 1) + (SMAX + 1) + SMAX + 8 +
+                               ((SMAX + 1) * (SMAX + 1) + 3) / 2 + 8;
 }
 // Every device the library runs on holds its own copy of this array until the process ends.  In
 // host code the name is only a handle for hipGetSymbolAddress; kernels get the address below.
@@ -165,17 +161,13 @@ extern "C" int alpa_cluster_layers_static(const int32_t *d_flop, int K, const in
         g_scratch_known[dev] = true;
     }
     int64_t *base = g_scratch_of_device[dev];
-    const size_t Ks = (size_t)K;
-    int64_t *Ct = base;
-    int64_t *chunk = Ct + Ks * Ks;
-    int64_t *pf = chunk + cluster_chunk_rows(K) * Ks;
-    int64_t *GV = pf + (Ks + 1);
-    int64_t *ctl = GV + 4 * (Ks + 1);
-    int32_t *arg = (int32_t *)(ctl + 8);
-    // Everything the kernels read from the work memory they have written in this call (Ct is
-    // cleared by a fill kernel, not a memset, so that the call can be recorded into a graph).
+    if (cluster_work_i64(K, L, K) + 8 > SCRATCH_I64)
+        return fail(ALPA_DP_EINVAL, "fixed work memory too small");        // (cannot be at the sizes above)
+    int64_t *ctl = base;
+    // Everything the kernels read from the work memory they have written in this call (cleared by
+    // kernels, not a memset, so that the call can be recorded into a graph).
     HIPCHK(launch_cluster((hipStream_t)hip_stream, d_flop, d_edge_src, d_edge_dst, d_edge_bytes,
-                          num_edges, K, L, /*cap=*/0, Ct, chunk, pf, GV, arg, d_out, d_out_first_op,
-                          ctl, delta_ppm));
+                          num_edges, K, L, /*cap=*/0, /*width=*/K, cluster_work(base + 8, K, L, K), d_out,
+                          d_out_first_op, ctl, delta_ppm));
     return ALPA_DP_OK;
 }

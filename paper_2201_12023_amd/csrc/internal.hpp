@@ -294,17 +294,23 @@ hipError_t launch_plan_walk_many(hipStream_t st, const Problem &p, const int32_t
 hipError_t launch_init_state(hipStream_t st, SolveState *state, int64_t *chunk_min, int n_chunks);
 hipError_t launch_init_best_plan(hipStream_t st, void *best_plan);
 
-// operator clustering (Eq. 6); buffers: Ct [K*K], chunk [cluster_chunk_rows(K)*K], pf [K+1],
-// GV [4*(K+1)] (int64), arg [L*(K+1)], out [2] (G, V), first_op [L+1].  ctl == nullptr: the
+// operator clustering (Eq. 6).  Work memory, see kernels_cluster.hip: band [width][K], rows G and V of one
+// launch, pf and win [K + 1], tot [K], arg [L][K + 1].
+struct ClusterWork {
+    int64_t *band, *G, *V, *pf, *tot, *keep;
+    int32_t *win, *arg, *meta;
+};
+size_t cluster_work_i64(int K, int L, int width);
+ClusterWork cluster_work(int64_t *base, int K, int L, int width);
+int cluster_band_width(const int32_t *flop, int K, int64_t cap);
+// width: at least the largest number of feasible first operators (K if unknown).  ctl == nullptr: the
 // caller has checked the inputs and passes the FLOP bound `cap`.  ctl != nullptr ([2] int64):
 // the inputs are checked and the bound is computed from delta_ppm on the device, out is [3]
 // (G, V, status) and `cap` is ignored.  exact != 0 (host-checked inputs only): a second run of
 // the recurrence minimises V over every clustering that reaches G(K, L).
 hipError_t launch_cluster(hipStream_t st, const int32_t *flop, const int32_t *src,
                           const int32_t *dst, const int64_t *nbytes, int E, int K, int L,
-                          int64_t cap, int64_t *Ct, int64_t *chunk, int64_t *pf, int64_t *GV,
-                          int32_t *arg, int64_t *out, int32_t *first_op, int64_t *ctl = nullptr,
-                          int delta_ppm = 0, int exact = 0);
-size_t cluster_chunk_rows(int K);
+                          int64_t cap, int width, const ClusterWork &w, int64_t *out,
+                          int32_t *first_op, int64_t *ctl = nullptr, int delta_ppm = 0, int exact = 0);
 
 }  // namespace alpa

@@ -1,0 +1,46 @@
+"""GPU parity of operator clustering at the sizes where its row kernel changes form: one tile of prefix
+lengths and several (the last one ragged), one lane per candidate and many, windows beyond what a
+lane keeps in registers, more layers than rows of one launch.  Whole numbers, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2201_12023_amd import binding as B
+from paper_2201_12023_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+# seed, operators, edges, layers, delta (ppm), largest FLOP figure
+CASES = [(1, 1, 0, 1, 0, 9), (2, 63, 200, 5, 500000, 9), (3, 64, 200, 64, 10**9, 9), (4, 65, 300, 9, 300000, 40),
+         (5, 511, 2000, 20, 500000, 9), (6, 512, 2000, 3, 200000, 9), (7, 513, 2000, 20, 500000, 9),
+         (8, 576, 3000, 128, 10**6, 5), (9, 577, 3000, 129, 10**6, 5), (10, 700, 1500, 257, 2 * 10**6, 3),
+         (11, 640, 4000, 2, 0, 1), (12, 900, 6000, 4, 10**9, 9), (13, 520, 0, 7, 500000, 0), (14, 600, 900, 300, 0, 50)]
+
+
+def _edges(seed, K, E, hi):
+    return W.random_op_graph(seed, K, E, flop_hi=hi)
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"K{c[1]}-L{c[3]}")
+@pytest.mark.parametrize("rule", ["cell", "exact", "static"])
+def test_tiles_and_windows(case, rule):
+    import torch
+    seed, K, E, L, delta, hi = case
+    if rule == "static" and max(K, L) > B.CLUSTER_STATIC_MAX_OPS:
+        pytest.skip("beyond the fixed work memory")
+    g = _edges(seed, K, E, hi)
+    args = (g.flop, g.src, g.dst, g.nbytes)
+    want = (oracle.cluster_exact if rule == "exact" else oracle.cluster)(*args, L, delta)
+    for _ in range(2):                              # the second call finds the first one's work memory
+        if rule == "static":
+            out = torch.zeros(3, dtype=torch.int64, device="cuda")
+            first = torch.zeros(L + 1, dtype=torch.int32, device="cuda")
+            B.alpa_cluster_layers_static(*[torch.from_numpy(a).cuda() for a in args], L, delta, out, first)
+            comm, sumsq, status = out.tolist()
+            assert status == 0
+            got = (comm, sumsq, first.tolist() if comm != B.INF_I64 else [])
+        else:
+            call = B.alpa_cluster_layers_exact if rule == "exact" else B.alpa_cluster_layers
+            r = call(*args, L, delta)
+            got = (r["comm"], r["sumsq"], r["first_op"])
+        assert got == want
