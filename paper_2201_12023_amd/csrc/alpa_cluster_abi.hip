@@ -2,8 +2,10 @@
 #include "../../include/alpa_dp.h"
 #include "internal.hpp"
 
+#include <algorithm>
+#include <memory>
+#include <new>
 #include <string>
-#include <vector>
 
 using namespace alpa;
 
@@ -62,37 +64,41 @@ static int cluster_layers_impl(const int32_t *flop, int K, const int32_t *edge_s
     const int64_t cap = ((1000000ll + delta_ppm) * total) / ((int64_t)L * 1000000ll);
 
     hipStream_t st = nullptr;
-    DevBuf d_flop, d_src, d_dst, d_nb, d_work, d_out, d_first;
+    // inputs, results and work memory are parts of one allocation (each costs tens of microseconds, and so does
+    // its release); the edges go up in one copy, the results come down in one
     const size_t E = (size_t)num_edges;
     const int width = cluster_band_width(flop, K, cap);
-    HIPCHK(d_flop.alloc((size_t)K * 4));
-    HIPCHK(d_src.alloc(E * 4));
-    HIPCHK(d_dst.alloc(E * 4));
-    HIPCHK(d_nb.alloc(E * 8));
-    HIPCHK(d_work.alloc(cluster_work_i64(K, L, width) * 8));
-    HIPCHK(d_out.alloc(2 * 8));
-    HIPCHK(d_first.alloc(((size_t)L + 1) * 4));
-    HIPCHK(hipMemcpyAsync(d_flop.p, flop, (size_t)K * 4, hipMemcpyHostToDevice, st));
+    const size_t in64 = E + (2 * E + (size_t)K + 1) / 2, out64 = 2 + ((size_t)L + 2) / 2;
+    DevBuf mem;
+    HIPCHK(mem.alloc((in64 + out64 + cluster_work_i64(K, L, width)) * 8));
+    std::unique_ptr<int64_t[]> stage(new (std::nothrow) int64_t[std::max(in64, out64)]);
+    if (!stage) return fail(ALPA_DP_ENOMEM, "host allocation failed");
+    int64_t *s_nb = stage.get();
+    int32_t *s_src = (int32_t *)(s_nb + E), *s_dst = s_src + E, *s_flop = s_dst + E;
     if (E) {
-        HIPCHK(hipMemcpyAsync(d_src.p, edge_src, E * 4, hipMemcpyHostToDevice, st));
-        HIPCHK(hipMemcpyAsync(d_dst.p, edge_dst, E * 4, hipMemcpyHostToDevice, st));
-        HIPCHK(hipMemcpyAsync(d_nb.p, edge_bytes, E * 8, hipMemcpyHostToDevice, st));
+        std::copy(edge_bytes, edge_bytes + E, s_nb);
+        std::copy(edge_src, edge_src + E, s_src);
+        std::copy(edge_dst, edge_dst + E, s_dst);
     }
+    std::copy(flop, flop + K, s_flop);
+    int64_t *d_nb = mem.as<int64_t>(), *d_out = d_nb + in64, *d_work = d_out + out64;
+    const int32_t *d_src = (const int32_t *)(d_nb + E), *d_dst = d_src + E, *d_flop = d_dst + E;
+    int32_t *d_first = (int32_t *)(d_out + 2);
+    HIPCHK(hipMemcpyAsync(d_nb, stage.get(), in64 * 8, hipMemcpyHostToDevice, st));
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     HIPCHK(hipEventCreate(&ev0));
     HIPCHK(hipEventCreate(&ev1));
     struct EvGuard { hipEvent_t a, b; ~EvGuard() { (void)hipEventDestroy(a); (void)hipEventDestroy(b); } }
         guard{ev0, ev1};
     HIPCHK(hipEventRecord(ev0, st));
-    HIPCHK(launch_cluster(st, d_flop.as<int32_t>(), d_src.as<int32_t>(), d_dst.as<int32_t>(),
-                          d_nb.as<int64_t>(), num_edges, K, L, cap, width,
-                          cluster_work(d_work.as<int64_t>(), K, L, width), d_out.as<int64_t>(),
-                          d_first.as<int32_t>(), nullptr, 0, exact));
+    HIPCHK(launch_cluster(st, d_flop, d_src, d_dst, d_nb, num_edges, K, L, cap, width,
+                          cluster_work(d_work, K, L, width), d_out, d_first, nullptr, 0, exact));
     HIPCHK(hipEventRecord(ev1, st));
-    int64_t res[2] = {0, 0};
-    HIPCHK(hipMemcpyAsync(res, d_out.p, sizeof(res), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(out_first_op, d_first.p, ((size_t)L + 1) * 4, hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(stage.get(), d_out, out64 * 8, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
+    const int64_t *res = stage.get();
+    const int32_t *first = (const int32_t *)(res + 2);
+    std::copy(first, first + L + 1, out_first_op);
     *out_comm = res[0];
     *out_sumsq = res[1];
     if (out_ms) HIPCHK(hipEventElapsedTime(out_ms, ev0, ev1));

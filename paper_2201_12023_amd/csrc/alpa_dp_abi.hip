@@ -49,6 +49,11 @@ struct alpa_dp {
     int KP = 0;
     int fast_grid_max[3] = {0, 0, 0}, generic_grid_max = 0;   // [nc] for nc = 1, 2
 
+    // One allocation per group of arrays (an allocation and its release cost tens of microseconds each):
+    // what lives as long as the handle, the work area of the distinct table values, the per-candidate arrays,
+    // and those of a sweep.  The pointers below are parts of these.
+    void *arena = nullptr, *key_arena = nullptr, *cand_arena = nullptr, *sweep_arena = nullptr;
+    void *distinct_arena = nullptr;
     int32_t *d_table = nullptr, *d_sizes = nullptr, *d_recs = nullptr, *d_gmin = nullptr;
     int32_t *d_rowrecs = nullptr, *d_rowends = nullptr;
     bool row_ok = false;
@@ -59,7 +64,7 @@ struct alpa_dp {
     int32_t *d_distinct = nullptr;
     uint32_t *d_ncount = nullptr;   // [2]: distinct table values, distinct caller candidates
     int32_t *d_cand = nullptr, *d_rank = nullptr, *d_tmax_stage = nullptr;
-    int32_t *d_Fmin = nullptr, *d_Sbest = nullptr, *d_knots = nullptr;
+    int32_t *d_Fmin = nullptr, *d_Sbest = nullptr, *d_knots = nullptr, *d_list = nullptr;
     int64_t *d_T = nullptr, *d_outT_stage = nullptr, *d_chunkmin = nullptr;
     int cand_cap = 0;               // capacity of the per-candidate arrays
     SolveState *d_state = nullptr;
@@ -81,70 +86,79 @@ struct alpa_dp {
     int fast_per_cu[3] = {0, 0, 0};  // resident workgroups per compute unit, [nc]
 };
 
-static void free_candidate_arrays(alpa_dp *h)
+// Parts of one allocation: `layout` names them twice, first to count, then to place them.
+struct Carver {
+    char *base = nullptr;
+    size_t used = 0;
+    template <class T> void operator()(T *&p, size_t n)
+    {
+        p = base ? (T *)(base + used) : nullptr;
+        used += (n * sizeof(T) + 255) & ~(size_t)255;
+    }
+};
+
+// All or nothing: after a failure *arena and every pointer of the layout are null.
+template <class Layout>
+static int carve(void **arena, Layout layout)
 {
-    (void)hipFree(h->pb.keys[0]); (void)hipFree(h->pb.keys[1]); (void)hipFree(h->pb.block_cnt);
-    (void)hipFree(h->d_cand); (void)hipFree(h->d_rank); (void)hipFree(h->d_tmax_stage);
-    (void)hipFree(h->d_Fmin); (void)hipFree(h->d_Sbest); (void)hipFree(h->d_T); (void)hipFree(h->d_outT_stage);
-    (void)hipFree(h->d_chunkmin); (void)hipFree(h->d_distinct);
-    h->pb.keys[0] = h->pb.keys[1] = nullptr; h->pb.block_cnt = nullptr;
-    h->d_cand = h->d_rank = h->d_tmax_stage = h->d_Fmin = h->d_Sbest = h->d_distinct = nullptr;
-    h->d_T = h->d_outT_stage = h->d_chunkmin = nullptr;
-    h->cand_cap = 0;
-    h->pb.cap = 0;
+    (void)hipFree(*arena);
+    *arena = nullptr;
+    Carver count;
+    layout(count);
+    HIPCHK(hipMalloc(arena, count.used));
+    Carver place{(char *)*arena};
+    layout(place);
+    return ALPA_DP_OK;
 }
 
-// Per-candidate arrays for up to `cap` keys / candidates.  All or nothing: after a failure
-// every pointer is null and both capacities are 0, so the next solve tries again (and fails
-// with ENOMEM again rather than launching on short buffers).
+// Work area of the sorts (of the table's values or of a caller's list) for up to `cap` keys
+static int alloc_key_arrays(alpa_dp *h, int cap)
+{
+    const size_t c = (size_t)cap;
+    h->pb.cap = 0;
+    const int rc = carve(&h->key_arena, [&](Carver &take) {
+        take(h->pb.keys[0], c);
+        take(h->pb.keys[1], c);
+        take(h->pb.block_cnt, c / 4096 + 2);
+    });
+    if (rc) return rc;
+    h->pb.cap = cap;
+    return ALPA_DP_OK;
+}
+
+// Per-candidate arrays for up to `cap` candidates; after a failure the capacity is 0, so the next solve
+// tries again (and fails with ENOMEM again rather than launching on short buffers).
 static int alloc_candidate_arrays(alpa_dp *h, int cap)
 {
-    free_candidate_arrays(h);
     const size_t c = (size_t)cap;
-    auto body = [&]() -> int {
-        HIPCHK(hipMalloc(&h->pb.keys[0], c * 4));
-        HIPCHK(hipMalloc(&h->pb.keys[1], c * 4));
-        HIPCHK(hipMalloc(&h->pb.block_cnt, (c / 4096 + 2) * 4));
-        HIPCHK(hipMalloc(&h->d_distinct, c * 4));
-        HIPCHK(hipMalloc(&h->d_cand, c * 4));
-        HIPCHK(hipMalloc(&h->d_rank, c * 4));
-        HIPCHK(hipMalloc(&h->d_tmax_stage, c * 4));
-        HIPCHK(hipMalloc(&h->d_Fmin, (c + 1) * 4));      // + one spare slot (see FastArgs)
-        HIPCHK(hipMalloc(&h->d_Sbest, (c + 1) * 4));
-        HIPCHK(hipMalloc(&h->d_T, c * 8));
-        HIPCHK(hipMalloc(&h->d_outT_stage, c * 8));
-        HIPCHK(hipMalloc(&h->d_chunkmin, (c / PRUNE_CHUNK + 2) * 8));
-        return ALPA_DP_OK;
-    };
-    const int rc = body();
-    if (rc != ALPA_DP_OK) {
-        free_candidate_arrays(h);
-        return rc;
-    }
-    h->pb.cap = cap;
+    h->cand_cap = 0;
+    const int rc = carve(&h->cand_arena, [&](Carver &take) {
+        take(h->d_cand, c);
+        take(h->d_list, c);
+        take(h->d_rank, c);
+        take(h->d_tmax_stage, c);
+        take(h->d_Fmin, c + 1);                    // + one spare slot (see FastArgs)
+        take(h->d_Sbest, c + 1);
+        take(h->d_T, c);
+        take(h->d_outT_stage, c);
+        take(h->d_chunkmin, c / PRUNE_CHUNK + 2);
+    });
+    if (rc) return rc;
     h->cand_cap = cap;
     return ALPA_DP_OK;
 }
 
-// Capacity every solve needs: the table's keys for the sort of its values, and the caller's
-// list if that is longer.
+// Capacity every solve needs: the distinct table values, and the caller's list if that is longer.
 static int ensure_candidate_arrays(alpa_dp *h, int n_list)
 {
-    const int need = std::max(std::max(h->n_table_keys, 1024), n_list);
-    if (h->cand_cap >= need) return ALPA_DP_OK;
+    const int need = std::max(std::max(h->n_distinct, 1024), n_list);
+    const bool cands = h->cand_cap < need, keys = h->pb.cap < n_list;
+    if (!cands && !keys) return ALPA_DP_OK;
     HIPCHK(hipStreamSynchronize(h->stream));
-    return alloc_candidate_arrays(h, need);
-}
-
-static void free_sweep_arrays(alpa_dp *h)
-{
-    (void)hipFree(h->d_sw_B); (void)hipFree(h->d_sw_c); (void)hipFree(h->d_sw_s);
-    (void)hipFree(h->d_sw_FS); (void)hipFree(h->d_sw_n); (void)hipFree(h->d_sw_state);
-    (void)hipFree(h->d_sw_Fall); (void)hipFree(h->d_sw_plans);
-    h->d_sw_B = h->d_sw_c = h->d_sw_s = h->d_sw_FS = h->d_sw_n = h->d_sw_Fall = nullptr;
-    h->d_sw_state = nullptr;
-    h->d_sw_plans = nullptr;
-    h->sw_cap = 0;
+    int rc = ALPA_DP_OK;
+    if (keys) rc = alloc_key_arrays(h, n_list);
+    if (!rc && cands) rc = alloc_candidate_arrays(h, need);
+    return rc;
 }
 
 // one kernel recovers the layers of all winners of a sweep (else a launch per layer, winner by winner)
@@ -152,20 +166,21 @@ static bool plan_slabs(const alpa_dp *h) { return (h->row_ok || h->fast_ok) && h
 
 static int alloc_sweep_arrays(alpa_dp *h, int n_B)
 {
-    free_sweep_arrays(h);
     const size_t n = (size_t)n_B;
-    HIPCHK(hipMalloc(&h->d_sw_B, n * 4));
-    HIPCHK(hipMalloc(&h->d_sw_c, n * 4));
-    HIPCHK(hipMalloc(&h->d_sw_s, n * 4));
-    HIPCHK(hipMalloc(&h->d_sw_FS, 2 * (n + 1) * 4));
-    HIPCHK(hipMalloc(&h->d_sw_n, 2 * 4));
-    HIPCHK(hipMalloc(&h->d_sw_state, n * sizeof(SolveState)));
-    HIPCHK(hipMalloc(&h->d_sw_plans, n * sizeof(alpa_plan_t)));
-    if (plan_slabs(h)) {                // one slab of layers per B value; the general kernel (also
-                                        // used above 64 devices) reuses d_Fall
-        const size_t slab = (size_t)(h->p.Smax + 1) * (size_t)(h->p.K + 2) * (h->p.D + 1);
-        HIPCHK(hipMalloc(&h->d_sw_Fall, n * slab * 4));
-    }
+    h->sw_cap = 0;
+    const int rc = carve(&h->sweep_arena, [&](Carver &take) {
+        take(h->d_sw_B, n);
+        take(h->d_sw_c, n);
+        take(h->d_sw_s, n);
+        take(h->d_sw_FS, 2 * (n + 1));
+        take(h->d_sw_n, 2);
+        take(h->d_sw_state, n);
+        take(h->d_sw_plans, n);
+        // one slab of layers per B value; the general kernel (also used above 64 devices) reuses d_Fall
+        if (plan_slabs(h))
+            take(h->d_sw_Fall, n * ((size_t)(h->p.Smax + 1) * (size_t)(h->p.K + 2) * (h->p.D + 1)));
+    });
+    if (rc) return rc;
     h->sw_cap = n_B;
     return ALPA_DP_OK;
 }
@@ -177,16 +192,25 @@ static int bits_for(uint32_t v)
     return b;
 }
 
+static bool distinct_by_bitmap(const alpa_dp *h)
+{
+    return h->max_finite >= 0 && h->max_finite < DISTINCT_BITMAP_MAX && !h->tune_sort;
+}
+
 // distinct finite table values -> d_distinct, count -> d_ncount[0]
 static int queue_table_candidates(alpa_dp *h)
 {
     // small values: one bit per value instead of a sort (the second key buffer is the work area)
-    if (h->max_finite >= 0 && h->max_finite < DISTINCT_BITMAP_MAX && !h->tune_sort &&
-        distinct_bitmap_words(h->max_finite) <= (size_t)h->pb.cap) {
+    if (distinct_by_bitmap(h)) {
         HIPCHK(launch_distinct_by_bitmap(h->stream, h->d_table, h->p.K, h->p.S, h->max_finite,
                                          (uint32_t *)h->pb.keys[1], h->d_distinct,
                                          h->d_ncount + 0));
         return ALPA_DP_OK;
+    }
+    if (h->pb.cap < h->n_table_keys) {               // (the sort was asked for behind the back of create)
+        HIPCHK(hipStreamSynchronize(h->stream));
+        const int rc = alloc_key_arrays(h, h->n_table_keys);
+        if (rc) return rc;
     }
     const int32_t inf_key = h->max_finite + 1;
     HIPCHK(launch_gather_table_values(h->stream, h->d_table, h->p.K, h->p.S, inf_key,
@@ -205,12 +229,8 @@ extern "C" void alpa_dp_destroy(alpa_dp_t *h)
     (void)hipGetDevice(&prev);
     (void)hipSetDevice(h->device);
     (void)hipStreamSynchronize(h->stream);
-    free_candidate_arrays(h);
-    free_sweep_arrays(h);
-    (void)hipFree(h->d_table); (void)hipFree(h->d_sizes); (void)hipFree(h->d_recs); (void)hipFree(h->d_gmin);
-    (void)hipFree(h->pb.hist); (void)hipFree(h->d_ncount); (void)hipFree(h->d_state); (void)hipFree(h->d_scratch);
-    (void)hipFree(h->d_Fall); (void)hipFree(h->d_tmpFS); (void)hipFree(h->d_plan_tmp); (void)hipFree(h->d_best_plan); (void)hipFree(h->d_knots);
-    (void)hipFree(h->d_rowrecs); (void)hipFree(h->d_bounds); (void)hipFree(h->d_bound_work); (void)hipFree(h->d_rowends);
+    (void)hipFree(h->arena); (void)hipFree(h->key_arena); (void)hipFree(h->cand_arena);
+    (void)hipFree(h->sweep_arena); (void)hipFree(h->distinct_arena);
     for (auto &e : h->ev) if (e) (void)hipEventDestroy(e);
     (void)hipSetDevice(prev);
     delete h;
@@ -246,58 +266,58 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
 {
     const int K = h->p.K, S = h->p.S, D = h->p.D;
     HIPCHK(hipGetDevice(&h->device));
-    hipDeviceProp_t prop;
-    HIPCHK(hipGetDeviceProperties(&prop, h->device));
-    h->n_cu = prop.multiProcessorCount;
+    HIPCHK(hipDeviceGetAttribute(&h->n_cu, hipDeviceAttributeMultiprocessorCount, h->device));
     for (auto &e : h->ev) HIPCHK(hipEventCreate(&e));
-    const size_t tbytes = (size_t)K * K * K * S * 4;
-    HIPCHK(hipMalloc(&h->d_table, tbytes));
-    {
-        int rc = fill_table();
-        if (rc) return rc;
-    }
-    if (h->max_finite >= 0 && (long long)K * h->max_finite >= (1ll << 30))
-        return fail(ALPA_DP_EOVERFLOW, "K * largest finite latency >= 2^30");
-    h->key_bits_table = bits_for((uint32_t)(h->max_finite + 1));
-    h->n_table_keys = K * (K * (K + 1) / 2) * S;
-    HIPCHK(hipMalloc(&h->d_sizes, (size_t)S * 4));
-    HIPCHK(hipMemcpyAsync(h->d_sizes, sizes.data(), (size_t)S * 4, hipMemcpyHostToDevice,
-                          h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));      // `sizes` may go away after the return
-    HIPCHK(hipMalloc(&h->pb.hist, (SORT_RADIX * SORT_SLICES + SORT_RADIX) * 4));   // counts + totals
-    HIPCHK(hipMalloc(&h->d_ncount, 2 * 4));
-    HIPCHK(hipMalloc(&h->d_state, sizeof(SolveState)));
-    HIPCHK(hipMemsetAsync(h->d_state, 0, sizeof(SolveState), h->stream));
-    HIPCHK(hipMalloc(&h->d_tmpFS, 4 * 4));
-    HIPCHK(hipMalloc(&h->d_knots, 2 * REFINE_MAX_KNOTS * 4));
-    HIPCHK(hipMalloc(&h->d_plan_tmp, sizeof(alpa_plan_t)));
-    HIPCHK(hipMalloc(&h->d_best_plan, sizeof(alpa_plan_t)));
-    HIPCHK(launch_init_best_plan(h->stream, h->d_best_plan));
     const size_t LS = (size_t)(K + 2) * (D + 1);
-    HIPCHK(hipMalloc(&h->d_Fall, (size_t)(h->p.Smax + 1) * LS * 4));
-    HIPCHK(hipMalloc(&h->d_bounds, table_bounds_ints(h->p) * 4));
-    HIPCHK(hipMalloc(&h->d_bound_work, table_bounds_work(h->p) * 4));
-    HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
     // general kernel: two F layers per resident workgroup, at most 256 MiB in total
     int gg = h->n_cu * 4;
     while (gg > 1 && (size_t)gg * 2 * LS * 4 > (256ull << 20)) gg /= 2;
     h->generic_grid_max = gg;
-    HIPCHK(hipMalloc(&h->d_scratch, (size_t)gg * 2 * LS * 4));
-    // 65-128 layers on up to 64 devices and 129-256 devices
+    // 65-128 layers on up to 64 devices and 129-256 devices: a workgroup per candidate; other sizes up to 128
+    // layers on 128 devices: the register/LDS kernel (above 64 devices in its two-window form)
     h->row_ok = (K > 64 || D > 128) && row_serves(K, D, S);
+    h->fast_ok = !h->row_ok && K <= 128 && D <= 128;
+    int rc = carve(&h->arena, [&](Carver &take) {
+        take(h->d_table, (size_t)K * K * K * S);
+        take(h->d_sizes, S);
+        take(h->pb.hist, SORT_RADIX * SORT_SLICES + SORT_RADIX);   // counts + totals
+        take(h->d_ncount, 2);
+        take(h->d_state, 1);
+        take(h->d_tmpFS, 4);
+        take(h->d_knots, 2 * REFINE_MAX_KNOTS);
+        take(h->d_plan_tmp, 1);
+        take(h->d_best_plan, 1);
+        take(h->d_Fall, (size_t)(h->p.Smax + 1) * LS);
+        take(h->d_bounds, table_bounds_ints(h->p));
+        take(h->d_bound_work, table_bounds_work(h->p));
+        take(h->d_scratch, (size_t)gg * 2 * LS);
+        if (h->row_ok) {
+            take(h->d_rowrecs, row_table_ints(K, h->p.Smax, S));
+            take(h->d_rowends, row_ends_ints(K, h->p.Smax, S));
+        }
+        if (h->fast_ok) {
+            take(h->d_recs, fast_table_ints(K, S));
+            take(h->d_gmin, fast_group_min_ints(K, D, S));
+        }
+    });
+    if (rc) return rc;
+    rc = fill_table();
+    if (rc) return rc;
+    if (h->max_finite >= 0 && (long long)K * h->max_finite >= (1ll << 30))
+        return fail(ALPA_DP_EOVERFLOW, "K * largest finite latency >= 2^30");
+    h->key_bits_table = bits_for((uint32_t)(h->max_finite + 1));
+    h->n_table_keys = K * (K * (K + 1) / 2) * S;
+    HIPCHK(hipMemcpyAsync(h->d_sizes, sizes.data(), (size_t)S * 4, hipMemcpyHostToDevice,
+                          h->stream));            // (the call ends with a synchronisation)
+    HIPCHK(hipMemsetAsync(h->d_state, 0, sizeof(SolveState), h->stream));
+    HIPCHK(launch_init_best_plan(h->stream, h->d_best_plan));
+    HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
     if (h->row_ok) {
-        HIPCHK(hipMalloc(&h->d_rowrecs, row_table_ints(K, h->p.Smax, S) * 4));
-        HIPCHK(hipMalloc(&h->d_rowends, row_ends_ints(K, h->p.Smax, S) * 4));
         HIPCHK(launch_repack_row(h->stream, h->d_table, K, h->p.Smax, S, h->d_rowrecs, h->d_rowends));
         h->row_grid = h->n_cu * row_blocks_per_cu(K, D, S);
     }
-    // register/LDS kernel
-    // above 64 devices: one candidate per workgroup, the two-window form of the kernel
-    h->fast_ok = !h->row_ok && K <= 128 && D <= 128;
     if (h->fast_ok) {
         h->KP = 16 * ((K + 15) / 16);
-        HIPCHK(hipMalloc(&h->d_recs, fast_table_ints(K, S) * 4));
-        HIPCHK(hipMalloc(&h->d_gmin, fast_group_min_ints(K, D, S) * 4));
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
         for (int nc = 1; nc <= 2; ++nc) {
             int per_cu = fast_kernel_blocks_per_cu(K, nc);
@@ -306,7 +326,14 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
             h->fast_grid_max[nc] = h->n_cu * per_cu;
         }
     }
-    int rc2 = ensure_candidate_arrays(h, 0);
+    // the bitmap of the distinct values needs a few words, their sort every entry
+    int rc2 = alloc_key_arrays(h, distinct_by_bitmap(h)
+                                      ? std::max(1024, (int)distinct_bitmap_words(h->max_finite))
+                                      : h->n_table_keys);
+    if (rc2) return rc2;
+    rc2 = carve(&h->distinct_arena, [&](Carver &take) {
+        take(h->d_distinct, (size_t)std::min<long long>(h->n_table_keys, (long long)h->max_finite + 2));
+    });
     if (rc2) return rc2;
     // length of the full candidate list
     rc2 = queue_table_candidates(h);
@@ -315,7 +342,7 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     HIPCHK(hipMemcpyAsync(&nd, h->d_ncount, 4, hipMemcpyDeviceToHost, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     h->n_distinct = (int)nd;
-    return ALPA_DP_OK;
+    return ensure_candidate_arrays(h, 0);
 }
 
 template <class FillTable>
@@ -350,22 +377,16 @@ extern "C" int alpa_dp_create(alpa_dp_t **out, const int32_t *cost_table, int K,
     return create_handle(out, K, N, M, B, sizes, [&](alpa_dp *h) -> int {
         // the range check of the used part of the table (no negative latency; largest finite
         // entry for the overflow proof) is a reduction on the device copy
-        int32_t *d_range = nullptr;
-        auto body = [&]() -> int {
-            HIPCHK(hipMalloc(&d_range, 2 * 4));
-            HIPCHK(hipMemcpyAsync(h->d_table, cost_table, (size_t)K * K * K * S * 4,
-                                  hipMemcpyHostToDevice, h->stream));
-            HIPCHK(launch_table_range(h->stream, h->d_table, K, S, d_range));
-            int32_t range[2] = {0, -1};
-            HIPCHK(hipMemcpyAsync(range, d_range, sizeof(range), hipMemcpyDeviceToHost, h->stream));
-            HIPCHK(hipStreamSynchronize(h->stream));
-            if (range[0] < 0) return fail(ALPA_DP_EINVAL, "negative latency in cost_table");
-            h->max_finite = range[1];
-            return ALPA_DP_OK;
-        };
-        const int rc2 = body();
-        (void)hipFree(d_range);
-        return rc2;
+        int32_t *d_range = h->d_tmpFS;             // (free until the first solve)
+        HIPCHK(hipMemcpyAsync(h->d_table, cost_table, (size_t)K * K * K * S * 4,
+                              hipMemcpyHostToDevice, h->stream));
+        HIPCHK(launch_table_range(h->stream, h->d_table, K, S, d_range));
+        int32_t range[2] = {0, -1};
+        HIPCHK(hipMemcpyAsync(range, d_range, sizeof(range), hipMemcpyDeviceToHost, h->stream));
+        HIPCHK(hipStreamSynchronize(h->stream));
+        if (range[0] < 0) return fail(ALPA_DP_EINVAL, "negative latency in cost_table");
+        h->max_finite = range[1];
+        return ALPA_DP_OK;
     });
 }
 
@@ -399,13 +420,12 @@ extern "C" int alpa_dp_create_from_profiles(alpa_dp_t **out, const int32_t *t_l,
     if (mem_device >= (1ll << 62)) return fail(ALPA_DP_EINVAL, "mem_device too large");
     return create_handle(out, K, N, M, B, sizes, [&](alpa_dp *h) -> int {
         const size_t n = (size_t)K * K * S * O;
-        int32_t *d_t = nullptr, *d_max = nullptr;
+        void *inputs = nullptr;
+        int32_t *d_t = nullptr, *d_max = h->d_tmpFS;    // (free until the first solve)
         int64_t *d_ms = nullptr, *d_ma = nullptr;
         auto body = [&]() -> int {
-            HIPCHK(hipMalloc(&d_t, n * 4));
-            HIPCHK(hipMalloc(&d_ms, n * 8));
-            HIPCHK(hipMalloc(&d_ma, n * 8));
-            HIPCHK(hipMalloc(&d_max, 4));
+            const int rc1 = carve(&inputs, [&](Carver &take) { take(d_t, n); take(d_ms, n); take(d_ma, n); });
+            if (rc1) return rc1;
             HIPCHK(hipMemcpyAsync(d_t, t_l, n * 4, hipMemcpyHostToDevice, h->stream));
             HIPCHK(hipMemcpyAsync(d_ms, mem_stage, n * 8, hipMemcpyHostToDevice, h->stream));
             HIPCHK(hipMemcpyAsync(d_ma, mem_act, n * 8, hipMemcpyHostToDevice, h->stream));
@@ -418,7 +438,7 @@ extern "C" int alpa_dp_create_from_profiles(alpa_dp_t **out, const int32_t *t_l,
             return ALPA_DP_OK;
         };
         const int rc2 = body();
-        (void)hipFree(d_t); (void)hipFree(d_ms); (void)hipFree(d_ma); (void)hipFree(d_max);
+        (void)hipFree(inputs);
         return rc2;
     });
 }
@@ -550,7 +570,7 @@ static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool one_per_cu)
     RefineBuffers rb{};
     rb.knots[0] = h->d_knots;
     rb.knots[1] = h->d_knots + REFINE_MAX_KNOTS;
-    rb.list = h->pb.keys[0];                       // free once the candidates are known
+    rb.list = h->d_list;
     rb.all = one_per_cu ? 512 : 2048;
     rb.first_round = 256;                          // a candidate per compute unit
     rb.budget = 512;
