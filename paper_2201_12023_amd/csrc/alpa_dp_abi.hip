@@ -60,6 +60,7 @@ struct alpa_dp {
     int row_grid = 0;
     int32_t *d_bounds = nullptr;    // what the table says about every candidate (launch_table_bounds)
     int32_t *d_bound_work = nullptr;
+    bool have_bounds = false;       // of the present table: computed by the first solve that needs them
     PrepBuffers pb{};
     int32_t *d_distinct = nullptr;
     uint32_t *d_ncount = nullptr;   // [2]: distinct table values, distinct caller candidates
@@ -311,7 +312,6 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
                           h->stream));            // (the call ends with a synchronisation)
     HIPCHK(hipMemsetAsync(h->d_state, 0, sizeof(SolveState), h->stream));
     HIPCHK(launch_init_best_plan(h->stream, h->d_best_plan));
-    HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
     if (h->row_ok) {
         HIPCHK(launch_repack_row(h->stream, h->d_table, K, h->p.Smax, S, h->d_rowrecs, h->d_rowends));
         h->row_grid = h->n_cu * row_blocks_per_cu(K, D, S);
@@ -453,7 +453,9 @@ extern "C" int alpa_dp_restrict_equal_layers(alpa_dp_t *h)
         restore{prev, h->device};
     const int K = h->p.K, D = h->p.D, S = h->p.S;
     HIPCHK(launch_equal_layer_mask(h->stream, h->d_table, K, S));
-    HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
+    // (a graph recorded after the first solve reads the bounds and does not compute them)
+    if (h->have_bounds)
+        HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
     if (h->row_ok)
         HIPCHK(launch_repack_row(h->stream, h->d_table, K, h->p.Smax, S, h->d_rowrecs, h->d_rowends));
     if (h->fast_ok) {
@@ -625,6 +627,13 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         if (rc) return rc;
         HIPCHK(launch_pick_candidates(st, h->d_distinct, h->d_ncount + 0, n_tmax, bound, h->d_cand,
                                       h->d_state, h->cand_cap));
+    }
+    if (!h->have_bounds) {
+        HIPCHK(launch_table_bounds(st, p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
+        // (recorded into a graph, they are there only after its replay)
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        HIPCHK(hipStreamIsCapturing(st, &capture));
+        h->have_bounds = capture == hipStreamCaptureStatusNone;
     }
     HIPCHK(launch_refine_begin(st, rq, h->d_cand, h->d_Fmin, h->d_Sbest, h->d_state, rb));
     HIPCHK(hipEventRecord(h->ev[1], st));

@@ -138,3 +138,58 @@ def test_workgroup_per_candidate_sizes(size, inf_frac):
             _same_plan(plan, p_ref)
     finally:
         B.alpa_dp_destroy(h)
+
+
+@pytest.mark.parametrize("solved_before", [False, True])
+@pytest.mark.parametrize("size", [(12, 2, 4), (70, 2, 2), (20, 18, 8)], ids=lambda s: f"K{s[0]}-{s[1]}x{s[2]}")
+def test_bounds_follow_the_table(size, solved_before):
+    """What is known of a table is computed by its first solve, and again when the table changes."""
+    K, N, M = size
+    w = _table(31 + K, K, N, M, 20_000, 0.1)
+    h = B.alpa_dp_create(w.table, K, N, M, 9, w.shapes)
+    try:
+        if solved_before:
+            B.alpa_dp_solve(h, None, 40, B.ALPA_DP_PRUNE)
+        B.alpa_dp_restrict_equal_layers(h)
+        masked = oracle.equal_layer_table(w.table)
+        cand = oracle.quantiles(oracle.all_candidates(masked, w.shapes), 40)
+        for prune in (True, False):
+            T_ref, p_ref = oracle.solve_parallel(masked, N, M, 9, w.shapes, cand, prune, 8)
+            T, plan = B.alpa_dp_solve(h, None, 40, B.ALPA_DP_PRUNE if prune else 0)
+            assert np.array_equal(T, T_ref)
+            _same_plan(plan, p_ref)
+    finally:
+        B.alpa_dp_destroy(h)
+
+
+def test_first_solve_recorded_into_a_graph():
+    """The first solve of a table as a graph: the replays compute what they need, and so does an eager solve
+    made before the first replay."""
+    import torch
+    w = _table(51, 14, 2, 8, 20_000, 0.1)
+    cand = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), 300)
+    T_ref, p_ref = oracle.solve_parallel(w.table, 2, 8, 9, w.shapes, cand, False, 8)
+    h = B.alpa_dp_create(w.table, 14, 2, 8, 9, w.shapes)
+    try:
+        stream = torch.cuda.Stream()
+        d_T = torch.zeros(len(cand), dtype=torch.int64, device="cuda")
+        d_plan = torch.zeros(B.PLAN_BYTES, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        B.alpa_dp_set_stream(h, stream)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            B.alpa_dp_solve_dev(h, None, 300, 0, d_T, d_plan)
+        for replay in range(4):
+            T, plan = B.alpa_dp_solve(h, None, 300, 0)             # eager, on the same buffers
+            assert np.array_equal(T, T_ref)
+            _same_plan(plan, p_ref)
+            d_T.zero_()
+            d_plan.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(stream):
+                graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(d_T.cpu().numpy(), T_ref)
+            _same_plan(B.plan_from_bytes(d_plan.cpu().numpy().tobytes()), p_ref)
+    finally:
+        B.alpa_dp_destroy(h)
