@@ -152,7 +152,8 @@ int alpa_dp_set_B(alpa_dp_t *h, int B);
  * library's own choice.  Errors: EINVAL (null handle, unknown key, value out of range).
  */
 #define ALPA_DP_TUNE_CANDIDATES_PER_WG 1  /* 1 or 2 t_max candidates per workgroup of the
-                                             register/LDS kernel (own choice: 1)                 */
+                                             register/LDS kernel (own choice: 1, with more waves
+                                             for short lists)                                   */
 #define ALPA_DP_TUNE_DISTINCT_BY_SORT  2  /* 1: distinct table values by the radix sort also where
                                              the presence bitmap applies                        */
 #define ALPA_DP_TUNE_WG_PER_CU         3  /* upper bound on resident workgroups per compute unit */
@@ -211,9 +212,9 @@ int alpa_dp_solve_dev(alpa_dp_t *h, const int32_t *d_tmax, int n_tmax, unsigned 
  * candidate list and Eq. 4 plus the selection run once per B value.
  *
  *   tmax, n_tmax  as for alpa_dp_solve (HOST pointer or NULL).
- *   flags     ALPA_DP_GENERIC as for alpa_dp_solve.  ALPA_DP_PRUNE: every candidate is
- *             still evaluated (the early exit of Alg. 1 depends on B); the rule is applied
- *             per B value afterwards, so that out_plans[b].n_evaluated and every other
+ *   flags     ALPA_DP_GENERIC as for alpa_dp_solve.  ALPA_DP_PRUNE: the early
+ *             exit of Alg. 1 depends on B, so the rule is applied per B value
+ *             after the recurrence, so that out_plans[b].n_evaluated and every other
  *             field equal those of alpa_dp_solve with B = B_values[b] and the same flags.
  *   B_values  HOST array of n_B values, each >= 1, 1 <= n_B <= ALPA_DP_MAX_SWEEP.
  *   out_plans HOST array of n_B plans, caller-owned; out_plans[b] is the best plan for
