@@ -50,9 +50,9 @@ struct alpa_dp {
     int fast_grid_max[3] = {0, 0, 0}, generic_grid_max = 0;   // [nc] for nc = 1, 2
 
     // One allocation per group of arrays (an allocation and its release cost tens of microseconds each):
-    // what lives as long as the handle, the work area of the distinct table values, the per-candidate arrays,
-    // and those of a sweep.  The pointers below are parts of these.
-    void *arena = nullptr, *key_arena = nullptr, *cand_arena = nullptr, *sweep_arena = nullptr;
+    // what lives as long as the handle, the sort's keys with the per-candidate arrays, and those of a
+    // sweep.  The pointers below are parts of these.
+    void *arena = nullptr, *cand_arena = nullptr, *sweep_arena = nullptr;
     void *distinct_arena = nullptr;
     int32_t *d_table = nullptr, *d_sizes = nullptr, *d_recs = nullptr, *d_gmin = nullptr;
     int32_t *d_rowrecs = nullptr, *d_rowends = nullptr;
@@ -112,28 +112,16 @@ static int carve(void **arena, Layout layout)
     return ALPA_DP_OK;
 }
 
-// Work area of the sorts (of the table's values or of a caller's list) for up to `cap` keys
-static int alloc_key_arrays(alpa_dp *h, int cap)
-{
-    const size_t c = (size_t)cap;
-    h->pb.cap = 0;
-    const int rc = carve(&h->key_arena, [&](Carver &take) {
-        take(h->pb.keys[0], c);
-        take(h->pb.keys[1], c);
-        take(h->pb.block_cnt, c / 4096 + 2);
-    });
-    if (rc) return rc;
-    h->pb.cap = cap;
-    return ALPA_DP_OK;
-}
-
-// Per-candidate arrays for up to `cap` candidates; after a failure the capacity is 0, so the next solve
+// Keys and per-candidate arrays for up to `cap` of them; after a failure the capacity is 0, so the next solve
 // tries again (and fails with ENOMEM again rather than launching on short buffers).
 static int alloc_candidate_arrays(alpa_dp *h, int cap)
 {
     const size_t c = (size_t)cap;
-    h->cand_cap = 0;
+    h->cand_cap = h->pb.cap = 0;
     const int rc = carve(&h->cand_arena, [&](Carver &take) {
+        take(h->pb.keys[0], c);
+        take(h->pb.keys[1], c);
+        take(h->pb.block_cnt, c / 4096 + 2);
         take(h->d_cand, c);
         take(h->d_list, c);
         take(h->d_rank, c);
@@ -145,21 +133,24 @@ static int alloc_candidate_arrays(alpa_dp *h, int cap)
         take(h->d_chunkmin, c / PRUNE_CHUNK + 2);
     });
     if (rc) return rc;
-    h->cand_cap = cap;
+    h->cand_cap = h->pb.cap = cap;
     return ALPA_DP_OK;
 }
 
-// Capacity every solve needs: the distinct table values, and the caller's list if that is longer.
+static bool distinct_by_bitmap(const alpa_dp *h)
+{
+    return h->max_finite >= 0 && h->max_finite < DISTINCT_BITMAP_MAX && !h->tune_sort;
+}
+
+// Capacity every solve needs: the distinct table values and what finds them (the words of a bitmap, or a key
+// per table entry for the sort), and the caller's list if that is longer.
 static int ensure_candidate_arrays(alpa_dp *h, int n_list)
 {
-    const int need = std::max(std::max(h->n_distinct, 1024), n_list);
-    const bool cands = h->cand_cap < need, keys = h->pb.cap < n_list;
-    if (!cands && !keys) return ALPA_DP_OK;
+    int need = std::max(std::max(h->n_distinct, 1024), n_list);
+    need = std::max(need, distinct_by_bitmap(h) ? (int)distinct_bitmap_words(h->max_finite) : h->n_table_keys);
+    if (h->cand_cap >= need) return ALPA_DP_OK;
     HIPCHK(hipStreamSynchronize(h->stream));
-    int rc = ALPA_DP_OK;
-    if (keys) rc = alloc_key_arrays(h, n_list);
-    if (!rc && cands) rc = alloc_candidate_arrays(h, need);
-    return rc;
+    return alloc_candidate_arrays(h, need);
 }
 
 // one kernel recovers the layers of all winners of a sweep (else a launch per layer, winner by winner)
@@ -193,25 +184,17 @@ static int bits_for(uint32_t v)
     return b;
 }
 
-static bool distinct_by_bitmap(const alpa_dp *h)
-{
-    return h->max_finite >= 0 && h->max_finite < DISTINCT_BITMAP_MAX && !h->tune_sort;
-}
-
 // distinct finite table values -> d_distinct, count -> d_ncount[0]
 static int queue_table_candidates(alpa_dp *h)
 {
+    const int rc = ensure_candidate_arrays(h, 0);  // (they are gone after a failed attempt to grow them)
+    if (rc) return rc;
     // small values: one bit per value instead of a sort (the second key buffer is the work area)
     if (distinct_by_bitmap(h)) {
         HIPCHK(launch_distinct_by_bitmap(h->stream, h->d_table, h->p.K, h->p.S, h->max_finite,
                                          (uint32_t *)h->pb.keys[1], h->d_distinct,
                                          h->d_ncount + 0));
         return ALPA_DP_OK;
-    }
-    if (h->pb.cap < h->n_table_keys) {               // (the sort was asked for behind the back of create)
-        HIPCHK(hipStreamSynchronize(h->stream));
-        const int rc = alloc_key_arrays(h, h->n_table_keys);
-        if (rc) return rc;
     }
     const int32_t inf_key = h->max_finite + 1;
     HIPCHK(launch_gather_table_values(h->stream, h->d_table, h->p.K, h->p.S, inf_key,
@@ -230,7 +213,7 @@ extern "C" void alpa_dp_destroy(alpa_dp_t *h)
     (void)hipGetDevice(&prev);
     (void)hipSetDevice(h->device);
     (void)hipStreamSynchronize(h->stream);
-    (void)hipFree(h->arena); (void)hipFree(h->key_arena); (void)hipFree(h->cand_arena);
+    (void)hipFree(h->arena); (void)hipFree(h->cand_arena);
     (void)hipFree(h->sweep_arena); (void)hipFree(h->distinct_arena);
     for (auto &e : h->ev) if (e) (void)hipEventDestroy(e);
     (void)hipSetDevice(prev);
@@ -326,12 +309,7 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
             h->fast_grid_max[nc] = h->n_cu * per_cu;
         }
     }
-    // the bitmap of the distinct values needs a few words, their sort every entry
-    int rc2 = alloc_key_arrays(h, distinct_by_bitmap(h)
-                                      ? std::max(1024, (int)distinct_bitmap_words(h->max_finite))
-                                      : h->n_table_keys);
-    if (rc2) return rc2;
-    rc2 = carve(&h->distinct_arena, [&](Carver &take) {
+    int rc2 = carve(&h->distinct_arena, [&](Carver &take) {
         take(h->d_distinct, (size_t)std::min<long long>(h->n_table_keys, (long long)h->max_finite + 2));
     });
     if (rc2) return rc2;

@@ -1,0 +1,224 @@
+// Host-side test driver: the library's own host code over a HIP runtime that is made up here.  The
+// executable defines every HIP function that libalpa_dp.so imports, so no GPU and no driver is touched
+// and no kernel runs: allocations are addresses in a reserved range that is never used twice, and a
+// launch is its kernel's name and its pointer arguments.  That shows, on the CPU, what a call would have
+// the GPU read and write: arguments that are null, or that lie in memory already given back.
+//
+//   g++ -std=c++17 -rdynamic -o driver tests/fake_hip_driver.cpp -Iinclude libalpa_dp.so
+//   ./driver <scenario>          prints OK, or what is wrong (exit status 1)
+#include "../include/alpa_dp.h"
+
+#include <cxxabi.h>
+#include <sys/mman.h>
+
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+using Stream = void *;
+struct Dim3 { uint32_t x, y, z; };
+constexpr int OK = 0, INVALID = 1, OUT_OF_MEMORY = 2, CAPTURE_UNSUPPORTED = 900;
+constexpr int D2H = 2;
+
+struct Block { size_t bytes; bool live; };
+struct Launch { std::string kernel; std::vector<std::pair<uintptr_t, std::string>> pointers; };
+
+struct Runtime {
+    uintptr_t base = 0, next = 0;
+    std::map<uintptr_t, Block> blocks;             // by first address
+    std::map<const void *, std::string> kernels;   // host stub -> demangled name
+    std::vector<Launch> launches;
+    bool capturing = false;
+    int waits_for_capture = 0;                     // synchronisation, allocation or release in a capture
+    int mallocs = 0, syncs = 0;
+    int fail_malloc_in = -1;                       // the n-th allocation from now on fails
+    int32_t n_distinct = 100, largest = 5000;      // what the kernels would have found in the table
+    Dim3 grid{}, block{};
+    size_t shared = 0;
+    Stream stream = nullptr;
+};
+static Runtime &rt()
+{
+    static Runtime r;
+    if (!r.base) {
+        r.base = (uintptr_t)mmap(nullptr, 1ull << 40, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+        r.next = r.base;
+    }
+    return r;
+}
+static const Block *block_of(uintptr_t p)
+{
+    auto it = rt().blocks.upper_bound(p);
+    if (it == rt().blocks.begin()) return nullptr;
+    --it;
+    return p < it->first + it->second.bytes ? &it->second : nullptr;
+}
+
+extern "C" {
+void **__hipRegisterFatBinary(const void *) { static void *h; return &h; }
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+void __hipRegisterFunction(void **, const void *stub, char *, const char *name, unsigned, void *, void *, void *,
+                           void *, int *)
+{
+    int status = 0;
+    char *d = abi::__cxa_demangle(name, nullptr, nullptr, &status);
+    rt().kernels[stub] = d ? d : name;
+    free(d);
+}
+int __hipPushCallConfiguration(Dim3 grid, Dim3 block, size_t shared, Stream st)
+{
+    rt().grid = grid; rt().block = block; rt().shared = shared; rt().stream = st;
+    return OK;
+}
+int __hipPopCallConfiguration(Dim3 *grid, Dim3 *block, size_t *shared, Stream *st)
+{
+    *grid = rt().grid; *block = rt().block; *shared = rt().shared; *st = rt().stream;
+    return OK;
+}
+int hipLaunchKernel(const void *stub, Dim3, Dim3, void **args, size_t, Stream)
+{
+    const std::string &sig = rt().kernels[stub];
+    Launch l;
+    const size_t open = sig.rfind('(');
+    l.kernel = sig.substr(0, open);
+    std::string params = sig.substr(open + 1, sig.size() - open - 2);
+    for (size_t n = 0, at = 0; at <= params.size(); ++n) {
+        size_t comma = params.find(',', at);
+        if (comma == std::string::npos) comma = params.size();
+        const std::string type = params.substr(at, comma - at);
+        if (type.find('*') != std::string::npos) l.pointers.push_back({*(uintptr_t *)args[n], type});
+        at = comma + 1;
+    }
+    rt().launches.push_back(l);
+    return OK;
+}
+int hipMalloc(void **p, size_t bytes)
+{
+    if (rt().capturing) { ++rt().waits_for_capture; return CAPTURE_UNSUPPORTED; }
+    ++rt().mallocs;
+    if (rt().fail_malloc_in >= 0 && rt().fail_malloc_in-- == 0) { *p = nullptr; return OUT_OF_MEMORY; }
+    *p = (void *)rt().next;
+    rt().blocks[rt().next] = {bytes, true};
+    rt().next += (bytes + 4096) & ~(size_t)4095;
+    return OK;
+}
+int hipFree(void *p)
+{
+    if (!p) return OK;
+    if (rt().capturing) { ++rt().waits_for_capture; return CAPTURE_UNSUPPORTED; }
+    auto it = rt().blocks.find((uintptr_t)p);
+    if (it == rt().blocks.end() || !it->second.live) { printf("release of something that is not allocated\n"); exit(1); }
+    it->second.live = false;
+    return OK;
+}
+int hipMemcpyAsync(void *dst, const void *src, size_t bytes, int kind, Stream)
+{
+    Launch l{"memcpy", {}};
+    for (const void *p : {(const void *)dst, src})
+        if (block_of((uintptr_t)p)) l.pointers.push_back({(uintptr_t)p, "void*"});
+    rt().launches.push_back(l);
+    if (kind != D2H) return OK;
+    memset(dst, 0, bytes);
+    if (bytes == 4) memcpy(dst, &rt().n_distinct, 4);
+    if (bytes == 8) ((int32_t *)dst)[1] = rt().largest;
+    return OK;
+}
+int hipMemsetAsync(void *, int, size_t, Stream) { return OK; }
+int hipStreamSynchronize(Stream)
+{
+    if (rt().capturing) { ++rt().waits_for_capture; return CAPTURE_UNSUPPORTED; }
+    ++rt().syncs;
+    return OK;
+}
+int hipStreamIsCapturing(Stream, int *status) { *status = rt().capturing ? 1 : 0; return OK; }
+int hipGetDevice(int *d) { *d = 0; return OK; }
+int hipSetDevice(int) { return OK; }
+int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return OK; }
+int hipEventCreate(void **e) { *e = e; return OK; }
+int hipEventDestroy(void *) { return OK; }
+int hipEventRecord(void *, Stream) { return OK; }
+int hipEventSynchronize(void *) { return OK; }
+int hipEventElapsedTime(float *ms, void *, void *) { *ms = 1; return OK; }
+int hipFuncSetAttribute(const void *, int, int) { return OK; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) { *n = 8; return OK; }
+int hipGetLastError(void) { return OK; }
+const char *hipGetErrorString(int e) { return e == OUT_OF_MEMORY ? "out of memory" : "error"; }
+int hipGetSymbolAddress(void **, const void *) { return INVALID; }
+int hipGetDevicePropertiesR0600(void *, int) { return INVALID; }
+}
+
+static int bad = 0;
+#define CHECK(cond, ...) do { if (!(cond)) { printf(__VA_ARGS__); printf(" [%s]\n", #cond); ++bad; } } while (0)
+
+// Every pointer of the launches from number `from` on lies in memory that is allocated now.
+static void check_launches(size_t from, size_t to, const char *what)
+{
+    for (size_t n = from; n < to; ++n) {
+        const Launch &l = rt().launches[n];
+        for (auto &[p, type] : l.pointers) {
+            const Block *b = block_of(p);
+            if (b) CHECK(b->live, "%s: %s: a %s in memory that was given back", what, l.kernel.c_str(), type.c_str());
+            // the work areas of the candidate list are never optional
+            else if (l.kernel.find("bitmap_") != std::string::npos || l.kernel.find("radix_") != std::string::npos ||
+                     l.kernel.find("gather_") != std::string::npos)
+                CHECK(p != 0, "%s: %s: a %s is null", what, l.kernel.c_str(), type.c_str());
+        }
+    }
+}
+
+// 12 layers on 2 x 8: 12 * 78 * 5 = 4680 table entries, 100 distinct values of up to 5000
+constexpr int K = 12, N = 2, M = 8, S = 5, ENTRIES = K * (K * (K + 1) / 2) * S;
+static alpa_dp_t *create()
+{
+    static std::vector<int32_t> table((size_t)K * K * K * S, 7);
+    const alpa_shape_t shapes[S] = {{1, 1}, {1, 2}, {1, 4}, {1, 8}, {2, 8}};
+    alpa_dp_t *h = nullptr;
+    const int rc = alpa_dp_create(&h, table.data(), K, N, M, 8, shapes, S);
+    if (rc) { printf("create: %d %s\n", rc, alpa_dp_last_error()); exit(1); }
+    return h;
+}
+
+// a reported ENOMEM leaves a handle that works, or says ENOMEM again
+static void out_of_memory()
+{
+    for (int big : {0, 1}) {                       // values for the bitmap, and for the sort
+        rt().largest = big ? 1 << 24 : 5000;
+        for (int nth = 0; nth < 2; ++nth) {
+            alpa_dp_t *h = create();
+            std::vector<int32_t> list(3 * ENTRIES, 9);
+            alpa_plan_t plan;
+            rt().fail_malloc_in = nth;
+            const int rc = alpa_dp_solve(h, list.data(), (int)list.size(), 0, nullptr, &plan);
+            const bool failed = rt().fail_malloc_in < 0;
+            rt().fail_malloc_in = -1;
+            CHECK(rc == (failed ? ALPA_DP_ENOMEM : 0), "long list, allocation %d fails: %d", nth, rc);
+            const size_t from = rt().launches.size();
+            CHECK(alpa_dp_solve(h, nullptr, 0, 0, nullptr, &plan) == 0, "solve after it");
+            CHECK(alpa_dp_restrict_equal_layers(h) == 0, "restriction after it");
+            CHECK(alpa_dp_best(h, &plan) == 0, "best after it");
+            check_launches(from, rt().launches.size(), "after a failed allocation");
+            // the same with the restriction first
+            rt().fail_malloc_in = nth;
+            (void)alpa_dp_solve(h, list.data(), (int)list.size(), 0, nullptr, &plan);
+            rt().fail_malloc_in = -1;
+            const size_t next = rt().launches.size();
+            CHECK(alpa_dp_restrict_equal_layers(h) == 0, "restriction after a second one");
+            check_launches(next, rt().launches.size(), "restriction after a failed allocation");
+            alpa_dp_destroy(h);
+        }
+    }
+}
+
+int main(int argc, char **argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "out_of_memory") out_of_memory();
+    else { printf("unknown scenario\n"); return 1; }
+    if (!bad) printf("OK\n");
+    return bad ? 1 : 0;
+}
