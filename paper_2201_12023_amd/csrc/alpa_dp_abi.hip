@@ -137,17 +137,15 @@ static int alloc_candidate_arrays(alpa_dp *h, int cap)
     return ALPA_DP_OK;
 }
 
-static bool distinct_by_bitmap(const alpa_dp *h)
-{
-    return h->max_finite >= 0 && h->max_finite < DISTINCT_BITMAP_MAX && !h->tune_sort;
-}
-
-// Capacity every solve needs: the distinct table values and what finds them (the words of a bitmap, or a key
-// per table entry for the sort), and the caller's list if that is longer.
+// Capacity every solve needs: an entry of the table each (the sort of its values takes them all), the words
+// of the bitmap that takes the sort's place, and the caller's list if that is longer.  Sized by the entries
+// and not by the distinct values, so that a list of ordinary length finds room: a solve on the
+// caller's stream neither allocates nor waits, and can be recorded into a graph.
 static int ensure_candidate_arrays(alpa_dp *h, int n_list)
 {
-    int need = std::max(std::max(h->n_distinct, 1024), n_list);
-    need = std::max(need, distinct_by_bitmap(h) ? (int)distinct_bitmap_words(h->max_finite) : h->n_table_keys);
+    int need = std::max(std::max(h->n_table_keys, 1024), n_list);
+    if (h->max_finite >= 0 && h->max_finite < DISTINCT_BITMAP_MAX)
+        need = std::max(need, (int)distinct_bitmap_words(h->max_finite));
     if (h->cand_cap >= need) return ALPA_DP_OK;
     HIPCHK(hipStreamSynchronize(h->stream));
     return alloc_candidate_arrays(h, need);
@@ -182,6 +180,11 @@ static int bits_for(uint32_t v)
     int b = 1;
     while (b < 32 && (v >> b)) ++b;
     return b;
+}
+
+static bool distinct_by_bitmap(const alpa_dp *h)
+{
+    return h->max_finite >= 0 && h->max_finite < DISTINCT_BITMAP_MAX && !h->tune_sort;
 }
 
 // distinct finite table values -> d_distinct, count -> d_ncount[0]
@@ -320,7 +323,7 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     HIPCHK(hipMemcpyAsync(&nd, h->d_ncount, 4, hipMemcpyDeviceToHost, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     h->n_distinct = (int)nd;
-    return ensure_candidate_arrays(h, 0);
+    return ALPA_DP_OK;
 }
 
 template <class FillTable>

@@ -182,6 +182,7 @@ static alpa_dp_t *create()
     if (rc) { printf("create: %d %s\n", rc, alpa_dp_last_error()); exit(1); }
     return h;
 }
+static void *device_array(size_t bytes) { void *p; hipMalloc(&p, bytes); return p; }
 
 // a reported ENOMEM leaves a handle that works, or says ENOMEM again
 static void out_of_memory()
@@ -214,10 +215,37 @@ static void out_of_memory()
     }
 }
 
+// a solve on device pointers with a list of up to as many values as the table has entries only queues work:
+// no allocation, no wait, also recorded into a graph as the handle's first call
+static void ordinary_lists()
+{
+    for (int sort : {0, 1})
+        for (int n : {0, 1025, 2000, ENTRIES}) {
+            for (int capture : {1, 0}) {
+                alpa_dp_t *h = create();
+                CHECK(alpa_dp_set_tuning(h, ALPA_DP_TUNE_DISTINCT_BY_SORT, sort) == 0, "tuning");
+                auto *d_list = (int32_t *)device_array((size_t)ENTRIES * 4);
+                auto *d_T = (int64_t *)device_array((size_t)ENTRIES * 8);
+                rt().capturing = capture;
+                rt().waits_for_capture = rt().mallocs = rt().syncs = 0;
+                const size_t from = rt().launches.size();
+                const int rc = alpa_dp_solve_dev(h, n ? d_list : nullptr, n, 0, d_T, nullptr);
+                rt().capturing = false;
+                CHECK(rc == 0, "list of %d, sort %d, capture %d: %d (%s)", n, sort, capture, rc, alpa_dp_last_error());
+                CHECK(rt().waits_for_capture + rt().mallocs + rt().syncs == 0,
+                      "list of %d, sort %d, capture %d: %d allocations, %d waits, %d of them in the capture", n, sort,
+                      capture, rt().mallocs, rt().syncs, rt().waits_for_capture);
+                check_launches(from, rt().launches.size(), "ordinary list");
+                alpa_dp_destroy(h);
+            }
+        }
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "out_of_memory") out_of_memory();
+    else if (what == "ordinary_lists") ordinary_lists();
     else { printf("unknown scenario\n"); return 1; }
     if (!bad) printf("OK\n");
     return bad ? 1 : 0;
