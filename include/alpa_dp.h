@@ -202,6 +202,12 @@ int alpa_dp_solve(alpa_dp_t *h, const int32_t *tmax, int n_tmax, unsigned flags,
  * with the sizes given for alpa_dp_solve; they must stay valid until the stream has
  * run the work.  Candidates are not range-checked (values outside [0, INT32_MAX) give
  * T* = ALPA_DP_INF_I64 or unfiltered results for that candidate, never a fault).
+ * A list longer than any before it may allocate; the call waits only if device memory is too short for that.
+ *
+ * It may be recorded into a HIP graph on the handle's stream.  The graph solves the handle's table as it is
+ * when it is replayed, with the B it was recorded with, and uses memory that the handle keeps until it is
+ * destroyed: any other call may be made between replays, on the same stream or ordered with it.
+ * alpa_dp_candidates describes the last call, not a replay.
  */
 int alpa_dp_solve_dev(alpa_dp_t *h, const int32_t *d_tmax, int n_tmax, unsigned flags,
                       int64_t *d_out_T, alpa_plan_t *d_out_plan);

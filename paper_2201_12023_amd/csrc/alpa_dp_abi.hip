@@ -36,6 +36,23 @@ extern "C" __attribute__((visibility("hidden"))) int alpa_dp_set_error_(int code
                         std::string(#expr) + ": " + hipGetErrorString(e_));                 \
     } while (0)
 
+// A group of arrays that grows with the candidate lists.  The arrays it has outgrown stay where they are to
+// the end of the handle: a solve that is queued, or recorded into a graph, still uses them, so growing
+// neither waits nor releases anything.  The room at least doubles, so what is kept is less than what is in use.
+struct GrowingArena {
+    void *mem = nullptr;
+    int cap = 0;
+    void *kept[32] = {};
+    int n_kept = 0;
+    void release()
+    {
+        (void)hipFree(mem);
+        while (n_kept) (void)hipFree(kept[--n_kept]);
+        mem = nullptr;
+        cap = 0;
+    }
+};
+
 struct alpa_dp {
     Problem p{};
     int device = 0;
@@ -50,10 +67,11 @@ struct alpa_dp {
     int fast_grid_max[3] = {0, 0, 0}, generic_grid_max = 0;   // [nc] for nc = 1, 2
 
     // One allocation per group of arrays (an allocation and its release cost tens of microseconds each):
-    // what lives as long as the handle, the sort's keys with the per-candidate arrays, and those of a
+    // what lives as long as the handle, the keys of the sorts, the per-candidate arrays, and those of a
     // sweep.  The pointers below are parts of these.
-    void *arena = nullptr, *cand_arena = nullptr, *sweep_arena = nullptr;
-    void *distinct_arena = nullptr;
+    void *arena = nullptr, *sweep_arena = nullptr, *distinct_arena = nullptr;
+    GrowingArena keys, cands;
+    bool recorded = false;          // a solve has been recorded into a graph
     int32_t *d_table = nullptr, *d_sizes = nullptr, *d_recs = nullptr, *d_gmin = nullptr;
     int32_t *d_rowrecs = nullptr, *d_rowends = nullptr;
     bool row_ok = false;
@@ -67,7 +85,6 @@ struct alpa_dp {
     int32_t *d_cand = nullptr, *d_rank = nullptr, *d_tmax_stage = nullptr;
     int32_t *d_Fmin = nullptr, *d_Sbest = nullptr, *d_knots = nullptr, *d_list = nullptr;
     int64_t *d_T = nullptr, *d_outT_stage = nullptr, *d_chunkmin = nullptr;
-    int cand_cap = 0;               // capacity of the per-candidate arrays
     SolveState *d_state = nullptr;
     int32_t *d_scratch = nullptr, *d_Fall = nullptr, *d_tmpFS = nullptr;
     alpa_plan_t *d_plan_tmp = nullptr, *d_best_plan = nullptr;
@@ -106,49 +123,121 @@ static int carve(void **arena, Layout layout)
     *arena = nullptr;
     Carver count;
     layout(count);
-    HIPCHK(hipMalloc(arena, count.used));
+    const hipError_t e = hipMalloc(arena, count.used);
+    if (e != hipSuccess) (void)hipGetLastError();  // reported here, not to be found by the next launch
+    HIPCHK(e);
     Carver place{(char *)*arena};
     layout(place);
     return ALPA_DP_OK;
 }
 
-// Keys and per-candidate arrays for up to `cap` of them; after a failure the capacity is 0, so the next solve
-// tries again (and fails with ENOMEM again rather than launching on short buffers).
-static int alloc_candidate_arrays(alpa_dp *h, int cap)
+// Work area of the sorts (of the table's values or of a caller's list) for `c` keys; for the values of a
+// table it holds a bitmap instead
+static void key_layout(alpa_dp *h, size_t c, Carver &take)
 {
-    const size_t c = (size_t)cap;
-    h->cand_cap = h->pb.cap = 0;
-    const int rc = carve(&h->cand_arena, [&](Carver &take) {
-        take(h->pb.keys[0], c);
-        take(h->pb.keys[1], c);
-        take(h->pb.block_cnt, c / 4096 + 2);
-        take(h->d_cand, c);
-        take(h->d_list, c);
-        take(h->d_rank, c);
-        take(h->d_tmax_stage, c);
-        take(h->d_Fmin, c + 1);                    // + one spare slot (see FastArgs)
-        take(h->d_Sbest, c + 1);
-        take(h->d_T, c);
-        take(h->d_outT_stage, c);
-        take(h->d_chunkmin, c / PRUNE_CHUNK + 2);
-    });
-    if (rc) return rc;
-    h->cand_cap = h->pb.cap = cap;
+    take(h->pb.keys[0], c);
+    take(h->pb.keys[1], c);
+    take(h->pb.block_cnt, c / 4096 + 2);
+}
+
+// Per-candidate arrays for `c` candidates
+static void candidate_layout(alpa_dp *h, size_t c, Carver &take)
+{
+    take(h->d_cand, c);
+    take(h->d_list, c);
+    take(h->d_rank, c);
+    take(h->d_tmax_stage, c);
+    take(h->d_Fmin, c + 1);                        // + one spare slot (see FastArgs)
+    take(h->d_Sbest, c + 1);
+    take(h->d_T, c);
+    take(h->d_outT_stage, c);
+    take(h->d_chunkmin, c / PRUNE_CHUNK + 2);
+}
+
+// Is the handle's stream being recorded into a graph?  (The null stream never is, and asking about it while
+// another one is recorded is an error.)
+static int stream_is_recorded(const alpa_dp *h, bool *yes)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (h->stream) HIPCHK(hipStreamIsCapturing(h->stream, &status));
+    *yes = status != hipStreamCaptureStatusNone;
     return ALPA_DP_OK;
 }
 
-// Capacity every solve needs: an entry of the table each (the sort of its values takes them all), the words
-// of the bitmap that takes the sort's place, and the caller's list if that is longer.  Sized by the entries
-// and not by the distinct values, so that a list of ordinary length finds room: a solve on the
-// caller's stream neither allocates nor waits, and can be recorded into a graph.
+typedef void (*ArenaLayout)(alpa_dp *, size_t, Carver &);
+
+static hipError_t new_arrays(alpa_dp *h, GrowingArena &g, int cap, ArenaLayout layout)
+{
+    Carver count;
+    layout(h, (size_t)cap, count);
+    void *fresh = nullptr;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;    // an allocation is no part of a recording
+    hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+    if (e == hipSuccess) {
+        e = hipMalloc(&fresh, count.used);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    if (e != hipSuccess) {                         // (the pointers are null now: see grow)
+        (void)hipGetLastError();                   // handled by the caller, not to be found by the next launch
+        return e;
+    }
+    Carver place{(char *)fresh};
+    layout(h, (size_t)cap, place);
+    if (g.mem) g.kept[g.n_kept++] = g.mem;
+    g.mem = fresh;
+    g.cap = cap;
+    return hipSuccess;
+}
+
+// Room for `need` entries.  A failure leaves the group as it was; where memory is short and no graph needs the
+// outgrown arrays they are released first, and then a failure leaves a capacity of 0, so that the next
+// solve tries again.
+static int grow(alpa_dp *h, GrowingArena &g, int need, ArenaLayout layout)
+{
+    if (g.cap >= need) return ALPA_DP_OK;
+    bool recorded = false;
+    const int rc = stream_is_recorded(h, &recorded);
+    if (rc) return rc;
+    const int roomy = (int)std::max<long long>(need, std::min<long long>(2ll * g.cap, INT32_MAX - 4096));
+    hipError_t e = new_arrays(h, g, roomy, layout);
+    if (e == hipErrorOutOfMemory && !recorded && !h->recorded) {
+        HIPCHK(hipStreamSynchronize(h->stream));
+        g.release();
+        e = new_arrays(h, g, need, layout);
+    }
+    if (e != hipSuccess) {
+        Carver back{(char *)g.mem};                // (all null if there is nothing to go back to)
+        layout(h, (size_t)g.cap, back);
+        return fail(e == hipErrorOutOfMemory ? ALPA_DP_ENOMEM : ALPA_DP_EHIP,
+                    std::string("arrays for ") + std::to_string(need) + " candidates: " + hipGetErrorString(e));
+    }
+    return ALPA_DP_OK;
+}
+
+static bool distinct_by_bitmap(const alpa_dp *h)
+{
+    return h->max_finite >= 0 && h->max_finite < DISTINCT_BITMAP_MAX && !h->tune_sort;
+}
+
+// From the start there is room for lists of ordinary length (both groups together stay below 2 MiB, from where
+// on an allocation and its release take longer: room for every entry of the table made a planning call of 32
+// layers on 4 x 8 773 instead of 680 us).
+constexpr int ORDINARY_LIST = 16384;
+static int ordinary_list(const alpa_dp *h) { return std::min(std::max(h->n_table_keys, 1024), ORDINARY_LIST); }
+
+// Keys for a list of n_list and for what finds the table's values: the words of a bitmap, or a key per entry
+static int ensure_keys(alpa_dp *h, int n_list)
+{
+    const int find = distinct_by_bitmap(h) ? (int)distinct_bitmap_words(h->max_finite) : h->n_table_keys;
+    return grow(h, h->keys, std::max(std::max(find, n_list), ordinary_list(h)), key_layout);
+}
+
+// Everything that a solve needs: keys, and per-candidate arrays for the distinct table values or the caller's list
 static int ensure_candidate_arrays(alpa_dp *h, int n_list)
 {
-    int need = std::max(std::max(h->n_table_keys, 1024), n_list);
-    if (h->max_finite >= 0 && h->max_finite < DISTINCT_BITMAP_MAX)
-        need = std::max(need, (int)distinct_bitmap_words(h->max_finite));
-    if (h->cand_cap >= need) return ALPA_DP_OK;
-    HIPCHK(hipStreamSynchronize(h->stream));
-    return alloc_candidate_arrays(h, need);
+    const int rc = ensure_keys(h, n_list);
+    if (rc) return rc;
+    return grow(h, h->cands, std::max(std::max(h->n_distinct, n_list), ordinary_list(h)), candidate_layout);
 }
 
 // one kernel recovers the layers of all winners of a sweep (else a launch per layer, winner by winner)
@@ -182,15 +271,10 @@ static int bits_for(uint32_t v)
     return b;
 }
 
-static bool distinct_by_bitmap(const alpa_dp *h)
-{
-    return h->max_finite >= 0 && h->max_finite < DISTINCT_BITMAP_MAX && !h->tune_sort;
-}
-
 // distinct finite table values -> d_distinct, count -> d_ncount[0]
 static int queue_table_candidates(alpa_dp *h)
 {
-    const int rc = ensure_candidate_arrays(h, 0);  // (they are gone after a failed attempt to grow them)
+    const int rc = ensure_keys(h, 0);
     if (rc) return rc;
     // small values: one bit per value instead of a sort (the second key buffer is the work area)
     if (distinct_by_bitmap(h)) {
@@ -216,8 +300,9 @@ extern "C" void alpa_dp_destroy(alpa_dp_t *h)
     (void)hipGetDevice(&prev);
     (void)hipSetDevice(h->device);
     (void)hipStreamSynchronize(h->stream);
-    (void)hipFree(h->arena); (void)hipFree(h->cand_arena);
-    (void)hipFree(h->sweep_arena); (void)hipFree(h->distinct_arena);
+    (void)hipFree(h->arena); (void)hipFree(h->sweep_arena); (void)hipFree(h->distinct_arena);
+    h->keys.release();
+    h->cands.release();
     for (auto &e : h->ev) if (e) (void)hipEventDestroy(e);
     (void)hipSetDevice(prev);
     delete h;
@@ -323,7 +408,7 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     HIPCHK(hipMemcpyAsync(&nd, h->d_ncount, 4, hipMemcpyDeviceToHost, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     h->n_distinct = (int)nd;
-    return ALPA_DP_OK;
+    return ensure_candidate_arrays(h, 0);
 }
 
 template <class FillTable>
@@ -576,10 +661,13 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     if (prev != h->device) HIPCHK(hipSetDevice(h->device));
     struct Restore { int prev, cur; ~Restore() { if (prev != cur) (void)hipSetDevice(prev); } }
         restore{prev, h->device};
+    bool recorded = false;
     {
-        const int rc = ensure_candidate_arrays(h, have_list ? n_tmax : 0);
+        int rc = ensure_candidate_arrays(h, have_list ? n_tmax : 0);
+        if (!rc) rc = stream_is_recorded(h, &recorded);
         if (rc) return rc;
     }
+    if (recorded) h->recorded = true;
     const int bound = candidate_bound(h, have_list, n_tmax);
     const int prune_sel = (flags & ALPA_DP_PRUNE) ? 1 : 0;
     // Skipping a candidate while the recurrence runs is decided with one B; a sweep
@@ -607,14 +695,11 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         int rc = queue_table_candidates(h);
         if (rc) return rc;
         HIPCHK(launch_pick_candidates(st, h->d_distinct, h->d_ncount + 0, n_tmax, bound, h->d_cand,
-                                      h->d_state, h->cand_cap));
+                                      h->d_state, h->cands.cap));
     }
     if (!h->have_bounds) {
         HIPCHK(launch_table_bounds(st, p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
-        // (recorded into a graph, they are there only after its replay)
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        HIPCHK(hipStreamIsCapturing(st, &capture));
-        h->have_bounds = capture == hipStreamCaptureStatusNone;
+        h->have_bounds = !recorded;                // (recorded, they are there only after the graph's replay)
     }
     HIPCHK(launch_refine_begin(st, rq, h->d_cand, h->d_Fmin, h->d_Sbest, h->d_state, rb));
     HIPCHK(hipEventRecord(h->ev[1], st));
@@ -627,7 +712,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         if (row) {
             FastArgs fa{p, nullptr, h->d_sizes, h->d_cand, rb.list, &h->d_state->n_list, 0, INT32_MAX,
                         &h->d_state->ticket, &h->d_state->wave_relax, h->d_chunkmin, skip,
-                        /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cand_cap, nullptr, nullptr,
+                        /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cands.cap, nullptr, nullptr,
                         nullptr, h->d_bounds};
             HIPCHK(launch_recurrence_row(st, fa, h->d_rowrecs, h->d_rowends,
                                          (flags & ALPA_DP_COUNT_WORK) ? FAST_MODE_COUNT : FAST_MODE_BATCH,
@@ -659,7 +744,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
             FastArgs fa{p, h->d_recs, h->d_sizes, h->d_cand, rb.list,
                         &h->d_state->n_list, 0, INT32_MAX,
                         &h->d_state->ticket, &h->d_state->wave_relax, h->d_chunkmin, skip,
-                        /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cand_cap, nullptr, nullptr, h->d_gmin, h->d_bounds};
+                        /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cands.cap, nullptr, nullptr, h->d_gmin, h->d_bounds};
             fa.grouped = group_dp;
             // Short lists go to forms with more waves per candidate (two of sixteen or four of eight waves per
             // compute unit instead of eight of four; 256 candidates of 64 layers on 8 x 8, t_max at the 20 %

@@ -21,8 +21,8 @@
 
 using Stream = void *;
 struct Dim3 { uint32_t x, y, z; };
-constexpr int OK = 0, INVALID = 1, OUT_OF_MEMORY = 2, CAPTURE_UNSUPPORTED = 900;
-constexpr int D2H = 2;
+constexpr int OK = 0, INVALID = 1, OUT_OF_MEMORY = 2, CAPTURE_UNSUPPORTED = 900, CAPTURE_IMPLICIT = 906;
+constexpr int D2H = 2, MODE_GLOBAL = 0, MODE_RELAXED = 2;
 
 struct Block { size_t bytes; bool live; };
 struct Launch { std::string kernel; std::vector<std::pair<uintptr_t, std::string>> pointers; };
@@ -33,9 +33,10 @@ struct Runtime {
     std::map<const void *, std::string> kernels;   // host stub -> demangled name
     std::vector<Launch> launches;
     bool capturing = false;
+    int mode = MODE_GLOBAL, last_error = OK;
     int waits_for_capture = 0;                     // synchronisation, allocation or release in a capture
     int mallocs = 0, syncs = 0;
-    int fail_malloc_in = -1;                       // the n-th allocation from now on fails
+    int fail_from = 0, fail_to = 0, failed = 0;    // the allocations [from, to) fail
     int32_t n_distinct = 100, largest = 5000;      // what the kernels would have found in the table
     Dim3 grid{}, block{};
     size_t shared = 0;
@@ -99,9 +100,9 @@ int hipLaunchKernel(const void *stub, Dim3, Dim3, void **args, size_t, Stream)
 }
 int hipMalloc(void **p, size_t bytes)
 {
-    if (rt().capturing) { ++rt().waits_for_capture; return CAPTURE_UNSUPPORTED; }
-    ++rt().mallocs;
-    if (rt().fail_malloc_in >= 0 && rt().fail_malloc_in-- == 0) { *p = nullptr; return OUT_OF_MEMORY; }
+    if (rt().capturing && rt().mode != MODE_RELAXED) { ++rt().waits_for_capture; return CAPTURE_UNSUPPORTED; }
+    const int n = rt().mallocs++;
+    if (n >= rt().fail_from && n < rt().fail_to) { ++rt().failed; *p = nullptr; return rt().last_error = OUT_OF_MEMORY; }
     *p = (void *)rt().next;
     rt().blocks[rt().next] = {bytes, true};
     rt().next += (bytes + 4096) & ~(size_t)4095;
@@ -135,7 +136,11 @@ int hipStreamSynchronize(Stream)
     ++rt().syncs;
     return OK;
 }
-int hipStreamIsCapturing(Stream, int *status) { *status = rt().capturing ? 1 : 0; return OK; }
+int hipStreamIsCapturing(Stream st, int *status)
+{
+    *status = st && rt().capturing ? 1 : 0;
+    return !st && rt().capturing ? CAPTURE_IMPLICIT : OK;
+}
 int hipGetDevice(int *d) { *d = 0; return OK; }
 int hipSetDevice(int) { return OK; }
 int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return OK; }
@@ -146,10 +151,19 @@ int hipEventSynchronize(void *) { return OK; }
 int hipEventElapsedTime(float *ms, void *, void *) { *ms = 1; return OK; }
 int hipFuncSetAttribute(const void *, int, int) { return OK; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) { *n = 8; return OK; }
-int hipGetLastError(void) { return OK; }
+int hipGetLastError(void) { const int e = rt().last_error; rt().last_error = OK; return e; }
+int hipThreadExchangeStreamCaptureMode(int *mode) { std::swap(rt().mode, *mode); return OK; }
 const char *hipGetErrorString(int e) { return e == OUT_OF_MEMORY ? "out of memory" : "error"; }
 int hipGetSymbolAddress(void **, const void *) { return INVALID; }
 int hipGetDevicePropertiesR0600(void *, int) { return INVALID; }
+}
+
+// from the next allocation but `skip` on, `n` of them fail
+static void fail_mallocs(int skip, int n)
+{
+    rt().fail_from = rt().mallocs + skip;
+    rt().fail_to = rt().fail_from + n;
+    rt().failed = 0;
 }
 
 static int bad = 0;
@@ -180,6 +194,7 @@ static alpa_dp_t *create()
     alpa_dp_t *h = nullptr;
     const int rc = alpa_dp_create(&h, table.data(), K, N, M, 8, shapes, S);
     if (rc) { printf("create: %d %s\n", rc, alpa_dp_last_error()); exit(1); }
+    CHECK(alpa_dp_set_stream(h, (void *)0x1000) == 0, "stream");   // (the null stream cannot be recorded)
     return h;
 }
 static void *device_array(size_t bytes) { void *p; hipMalloc(&p, bytes); return p; }
@@ -193,10 +208,10 @@ static void out_of_memory()
             alpa_dp_t *h = create();
             std::vector<int32_t> list(3 * ENTRIES, 9);
             alpa_plan_t plan;
-            rt().fail_malloc_in = nth;
+            fail_mallocs(nth, 9);
             const int rc = alpa_dp_solve(h, list.data(), (int)list.size(), 0, nullptr, &plan);
-            const bool failed = rt().fail_malloc_in < 0;
-            rt().fail_malloc_in = -1;
+            const bool failed = rt().failed > 0;
+            fail_mallocs(0, 0);
             CHECK(rc == (failed ? ALPA_DP_ENOMEM : 0), "long list, allocation %d fails: %d", nth, rc);
             const size_t from = rt().launches.size();
             CHECK(alpa_dp_solve(h, nullptr, 0, 0, nullptr, &plan) == 0, "solve after it");
@@ -204,9 +219,9 @@ static void out_of_memory()
             CHECK(alpa_dp_best(h, &plan) == 0, "best after it");
             check_launches(from, rt().launches.size(), "after a failed allocation");
             // the same with the restriction first
-            rt().fail_malloc_in = nth;
+            fail_mallocs(nth, 9);
             (void)alpa_dp_solve(h, list.data(), (int)list.size(), 0, nullptr, &plan);
-            rt().fail_malloc_in = -1;
+            fail_mallocs(0, 0);
             const size_t next = rt().launches.size();
             CHECK(alpa_dp_restrict_equal_layers(h) == 0, "restriction after a second one");
             check_launches(next, rt().launches.size(), "restriction after a failed allocation");
@@ -241,11 +256,94 @@ static void ordinary_lists()
         }
 }
 
+static size_t live_bytes()
+{
+    size_t n = 0;
+    for (auto &b : rt().blocks) n += b.second.live ? b.second.bytes : 0;
+    return n;
+}
+
+// a graph's kernels keep their memory, whatever the handle is asked for afterwards
+static void recorded_solve()
+{
+    const size_t before = live_bytes();
+    alpa_dp_t *h = create();
+    std::vector<int32_t> list(200 * ENTRIES, 9);
+    alpa_plan_t plan;
+    auto eager = [&](int n) { return alpa_dp_solve(h, list.data(), n, 0, nullptr, &plan); };
+    const size_t at_first = live_bytes();
+    const size_t from = rt().launches.size();
+    rt().capturing = true;
+    CHECK(alpa_dp_solve_dev(h, nullptr, 0, 0, nullptr, nullptr) == 0, "recorded solve: %s", alpa_dp_last_error());
+    rt().capturing = false;
+    const size_t to = rt().launches.size();
+    for (int n : {2, 5, 6, 9, 17, 18, 40}) {
+        const size_t mine = rt().launches.size();
+        CHECK(eager(n * ENTRIES) == 0, "list of %d times the entries", n);
+        check_launches(mine, rt().launches.size(), "eager solve");
+        check_launches(from, to, "replay after a longer list");
+    }
+    // what has been outgrown is less than what is in use, and that at most twice the longest list
+    CHECK(live_bytes() - at_first < (size_t)2 * 2 * 40 * ENTRIES * 50, "%zu bytes held", live_bytes() - at_first);
+    fail_mallocs(0, 9);
+    CHECK(eager(200 * ENTRIES) == ALPA_DP_ENOMEM, "no room");
+    fail_mallocs(0, 0);
+    check_launches(from, to, "replay after a failed attempt");
+    const size_t mine = rt().launches.size();
+    CHECK(eager(40 * ENTRIES) == 0, "list that has found room before");
+    check_launches(mine, rt().launches.size(), "eager solve after a failed attempt");
+    alpa_dp_destroy(h);
+    CHECK(live_bytes() == before, "%zu bytes left by destroy", live_bytes() - before);
+}
+
+// a list of any length only queues work on the caller's stream, recorded or not: the arrays grow without a wait
+static void long_lists()
+{
+    for (int capture : {1, 0}) {
+        alpa_dp_t *h = create();
+        auto *d_list = (int32_t *)device_array((size_t)100 * ENTRIES * 4);
+        auto *d_T = (int64_t *)device_array((size_t)100 * ENTRIES * 8);
+        rt().capturing = capture;
+        rt().waits_for_capture = rt().syncs = 0;
+        const size_t from = rt().launches.size();
+        for (int n : {1, 10, 100, 2}) {
+            const int rc = alpa_dp_solve_dev(h, d_list, n * ENTRIES, 0, d_T, nullptr);
+            CHECK(rc == 0, "list of %d times the entries, capture %d: %d (%s)", n, capture, rc, alpa_dp_last_error());
+        }
+        rt().capturing = false;
+        CHECK(rt().waits_for_capture + rt().syncs == 0, "capture %d: %d waits, %d in the capture", capture, rt().syncs,
+              rt().waits_for_capture);
+        check_launches(from, rt().launches.size(), "long lists");
+        CHECK(rt().mode == MODE_GLOBAL, "the thread's capture mode is left changed");
+        alpa_dp_destroy(h);
+    }
+}
+
+// memory too short for old and new arrays together: without a graph the old ones make room
+static void short_memory()
+{
+    alpa_dp_t *h = create();
+    std::vector<int32_t> list(9 * ENTRIES, 9);
+    alpa_plan_t plan;
+    for (int nth : {0, 1}) {
+        fail_mallocs(nth, 1);
+        const size_t from = rt().launches.size();
+        CHECK(alpa_dp_solve(h, list.data(), (4 + 5 * nth) * ENTRIES, 0, nullptr, &plan) == 0, "allocation %d fails: %s",
+              nth, alpa_dp_last_error());
+        fail_mallocs(0, 0);
+        check_launches(from, rt().launches.size(), "solve in short memory");
+    }
+    alpa_dp_destroy(h);
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "out_of_memory") out_of_memory();
     else if (what == "ordinary_lists") ordinary_lists();
+    else if (what == "recorded_solve") recorded_solve();
+    else if (what == "long_lists") long_lists();
+    else if (what == "short_memory") short_memory();
     else { printf("unknown scenario\n"); return 1; }
     if (!bad) printf("OK\n");
     return bad ? 1 : 0;

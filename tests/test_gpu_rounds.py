@@ -193,3 +193,73 @@ def test_first_solve_recorded_into_a_graph():
             _same_plan(B.plan_from_bytes(d_plan.cpu().numpy().tobytes()), p_ref)
     finally:
         B.alpa_dp_destroy(h)
+
+
+def test_recorded_solve_outlives_longer_lists():
+    """A recorded solve, then eager ones with lists that the handle's arrays have to grow for, replays in
+    between: the graph's kernels still find their memory."""
+    import torch
+    w = _table(52, 14, 2, 8, 20_000, 0.1)
+    cand = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), 300)
+    T_ref, p_ref = oracle.solve_parallel(w.table, 2, 8, 9, w.shapes, cand, False, 8)
+    rng = np.random.default_rng(4)
+    h = B.alpa_dp_create(w.table, 14, 2, 8, 9, w.shapes)
+    try:
+        stream = torch.cuda.Stream()
+        d_T = torch.zeros(len(cand), dtype=torch.int64, device="cuda")
+        d_plan = torch.zeros(B.PLAN_BYTES, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        B.alpa_dp_set_stream(h, stream)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            B.alpa_dp_solve_dev(h, None, 300, 0, d_T, d_plan)
+        for length in (2000, 7350, 20_000, 90_000):      # the table has 7350 entries
+            mine = rng.choice(cand, length).astype(np.int32)
+            T, _ = B.alpa_dp_solve(h, mine)
+            assert np.array_equal(T, T_ref[np.searchsorted(cand, mine)])
+            # whatever took the place of outgrown memory would be written by the graph
+            guard = torch.full((1 << 20,), 77, dtype=torch.int32, device="cuda")
+            d_T.zero_()
+            d_plan.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(stream):
+                graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(d_T.cpu().numpy(), T_ref)
+            _same_plan(B.plan_from_bytes(d_plan.cpu().numpy().tobytes()), p_ref)
+            assert bool((guard == 77).all())
+    finally:
+        B.alpa_dp_destroy(h)
+
+
+def test_long_list_recorded_as_the_first_call():
+    """The handle's arrays grow while its stream is recorded."""
+    import torch
+    w = _table(53, 14, 2, 8, 20_000, 0.1)
+    cand = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), 300)
+    T_ref, p_ref = oracle.solve_parallel(w.table, 2, 8, 9, w.shapes, cand, False, 8)
+    mine = np.random.default_rng(5).choice(cand, 50_000).astype(np.int32)
+    mine[: len(cand)] = cand
+    h = B.alpa_dp_create(w.table, 14, 2, 8, 9, w.shapes)
+    try:
+        stream = torch.cuda.Stream()
+        d_mine = torch.from_numpy(mine).cuda()
+        d_T = torch.zeros(len(mine), dtype=torch.int64, device="cuda")
+        d_plan = torch.zeros(B.PLAN_BYTES, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        B.alpa_dp_set_stream(h, stream)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            B.alpa_dp_solve_dev(h, d_mine, len(mine), 0, d_T, d_plan)
+        for replay in range(3):
+            T, _ = B.alpa_dp_solve(h, cand)                         # eager, in between
+            assert np.array_equal(T, T_ref)
+            d_T.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(stream):
+                graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(d_T.cpu().numpy(), T_ref[np.searchsorted(cand, mine)])
+            _same_plan(B.plan_from_bytes(d_plan.cpu().numpy().tobytes()), p_ref)
+    finally:
+        B.alpa_dp_destroy(h)
