@@ -34,7 +34,10 @@ __global__ __launch_bounds__(CL_THREADS) void cluster_prefix_kernel(
     extern __shared__ int64_t sh[];                  // [K + 1] prefix sums
     __shared__ int64_t part[CL_THREADS];
     __shared__ int sh_max;
-    if (ctl) cap = ctl[1];                           // bound computed on the device (cluster_check_kernel)
+    // Bound computed on the device (cluster_check_kernel).  Inputs that it has refused have no feasible first
+    // operator anywhere: with a negative figure a row value could be any number, NOT_YET among them.
+    const bool refused = ctl && ctl[0] != 0;
+    if (ctl) cap = ctl[1];
     const int t = threadIdx.x;
     const int per = (K + CL_THREADS - 1) / CL_THREADS;
     const int lo = min(K, t * per), hi = min(K, lo + per);
@@ -66,8 +69,9 @@ __global__ __launch_bounds__(CL_THREADS) void cluster_prefix_kernel(
             const int mid = (a + b) >> 1;
             if (sh[mid] >= need) b = mid; else a = mid + 1;
         }
-        win[n] = n - a;
-        widest = max(widest, n - a);
+        const int feasible = refused ? 0 : n - a;
+        win[n] = feasible;
+        widest = max(widest, feasible);
     }
     atomicMax(&sh_max, widest);
     __syncthreads();

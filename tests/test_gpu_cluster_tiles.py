@@ -44,3 +44,20 @@ def test_tiles_and_windows(case, rule):
             r = call(*args, L, delta)
             got = (r["comm"], r["sumsq"], r["first_op"])
         assert got == want
+
+
+def test_refused_figures_reach_no_wait():
+    """Negative FLOP figures, refused by the check on the device, whose wrapped sum of squares over the first
+    four operators is -1: the value by which a row says that it is not there yet, in a tile that the
+    next one waits for."""
+    import torch
+    f = [3122172103, 2200318541, 3694363990, 2942074529]
+    assert sum(x * x for x in f) % 2**64 == 2**64 - 1
+    flop = np.array([x - 2**32 for x in f] + [-1] * 146, dtype=np.int32)
+    none32, none64 = torch.zeros(0, dtype=torch.int32).cuda(), torch.zeros(0, dtype=torch.int64).cuda()
+    for L in (5, 140):
+        out = torch.zeros(3, dtype=torch.int64, device="cuda")
+        first = torch.zeros(L + 1, dtype=torch.int32, device="cuda")
+        B.alpa_cluster_layers_static(torch.from_numpy(flop).cuda(), none32, none32, none64, L, 500000, out, first)
+        torch.cuda.synchronize()
+        assert out.tolist() == [B.INF_I64, 0, -1] and first.tolist() == [-1] * (L + 1)
