@@ -326,9 +326,12 @@ int alpa_cluster_layers_exact(const int32_t *flop, int K, const int32_t *edge_sr
  *                   on the host and this call makes on the device: 0, ALPA_DP_EINVAL (negative
  *                   figure, bad edge) or ALPA_DP_EOVERFLOW; if not 0 the other outputs are
  *                   those of "no clustering" (INF, 0, -1 ...).  A bad edge is never written.
+ *                   ALPA_DP_EHIP: see overlapping calls, next.
  *   d_out_first_op  int32 [L + 1].
  * All calls on one device share the one work array: calls that may run at the same time on a
- * device (different streams, different threads) race; serialise them.  Results are valid once
+ * device (different streams, different threads) race; serialise them.  Overlapping calls give
+ * wrong numbers, or the status ALPA_DP_EHIP, seconds later, if one has waited for a value that
+ * another has overwritten.  Results are valid once
  * the stream has run the work; the input arrays must stay unchanged until then.
  *
  * Errors (returned at once, nothing queued): EINVAL (null pointer, K or L < 1 or above

@@ -35,7 +35,8 @@ int fail(int code, const std::string &msg) { return alpa_dp_set_error_(code, msg
 static int cluster_layers_impl(const int32_t *flop, int K, const int32_t *edge_src,
                                const int32_t *edge_dst, const int64_t *edge_bytes, int num_edges,
                                int L, int delta_ppm, int64_t *out_comm, int64_t *out_sumsq,
-                               int32_t *out_first_op, float *out_ms, int exact)
+                               int32_t *out_first_op, float *out_ms, int exact,
+                               unsigned max_spins = CLUSTER_MAX_SPINS)
 {
     if (!flop || !out_comm || !out_sumsq || !out_first_op)
         return fail(ALPA_DP_EINVAL, "null argument");
@@ -68,7 +69,7 @@ static int cluster_layers_impl(const int32_t *flop, int K, const int32_t *edge_s
     // its release); the edges go up in one copy, the results come down in one
     const size_t E = (size_t)num_edges;
     const int width = cluster_band_width(flop, K, cap);
-    const size_t in64 = E + (2 * E + (size_t)K + 1) / 2, out64 = 2 + ((size_t)L + 2) / 2;
+    const size_t in64 = E + (2 * E + (size_t)K + 1) / 2, out64 = 3 + ((size_t)L + 2) / 2;
     DevBuf mem;
     HIPCHK(mem.alloc((in64 + out64 + cluster_work_i64(K, L, width)) * 8));
     std::unique_ptr<int64_t[]> stage(new (std::nothrow) int64_t[std::max(in64, out64)]);
@@ -83,7 +84,7 @@ static int cluster_layers_impl(const int32_t *flop, int K, const int32_t *edge_s
     std::copy(flop, flop + K, s_flop);
     int64_t *d_nb = mem.as<int64_t>(), *d_out = d_nb + in64, *d_work = d_out + out64;
     const int32_t *d_src = (const int32_t *)(d_nb + E), *d_dst = d_src + E, *d_flop = d_dst + E;
-    int32_t *d_first = (int32_t *)(d_out + 2);
+    int32_t *d_first = (int32_t *)(d_out + 3);
     HIPCHK(hipMemcpyAsync(d_nb, stage.get(), in64 * 8, hipMemcpyHostToDevice, st));
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     HIPCHK(hipEventCreate(&ev0));
@@ -92,12 +93,13 @@ static int cluster_layers_impl(const int32_t *flop, int K, const int32_t *edge_s
         guard{ev0, ev1};
     HIPCHK(hipEventRecord(ev0, st));
     HIPCHK(launch_cluster(st, d_flop, d_src, d_dst, d_nb, num_edges, K, L, cap, width,
-                          cluster_work(d_work, K, L, width), d_out, d_first, nullptr, 0, exact));
+                          cluster_work(d_work, K, L, width), d_out, d_first, nullptr, 0, exact, max_spins));
     HIPCHK(hipEventRecord(ev1, st));
     HIPCHK(hipMemcpyAsync(stage.get(), d_out, out64 * 8, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     const int64_t *res = stage.get();
-    const int32_t *first = (const int32_t *)(res + 2);
+    if (res[2] != 0) return fail(ALPA_DP_EHIP, "a wait between workgroups has run out");
+    const int32_t *first = (const int32_t *)(res + 3);
     std::copy(first, first + L + 1, out_first_op);
     *out_comm = res[0];
     *out_sumsq = res[1];
@@ -121,6 +123,17 @@ extern "C" int alpa_cluster_layers_exact(const int32_t *flop, int K, const int32
 {
     return cluster_layers_impl(flop, K, edge_src, edge_dst, edge_bytes, num_edges, L, delta_ppm,
                                out_comm, out_sumsq, out_first_op, out_ms, 1);
+}
+
+// alpa_cluster_layers with waits between workgroups of at most max_spins looks, for the test of a wait that runs out
+// (not in the public header)
+extern "C" int alpa_cluster_layers_waiting_(const int32_t *flop, int K, const int32_t *edge_src,
+                                            const int32_t *edge_dst, const int64_t *edge_bytes,
+                                            int num_edges, int L, int delta_ppm, int exact, unsigned max_spins,
+                                            int64_t *out_comm, int64_t *out_sumsq, int32_t *out_first_op)
+{
+    return cluster_layers_impl(flop, K, edge_src, edge_dst, edge_bytes, num_edges, L, delta_ppm,
+                               out_comm, out_sumsq, out_first_op, nullptr, exact, max_spins);
 }
 
 // ---------------------------------------------------------------- no allocation on the call

@@ -305,12 +305,16 @@ ClusterWork cluster_work(int64_t *base, int K, int L, int width);
 int cluster_band_width(const int32_t *flop, int K, int64_t cap);
 // width: at least the largest number of feasible first operators (K if unknown).  ctl == nullptr: the
 // caller has checked the inputs and passes the FLOP bound `cap`.  ctl != nullptr ([2] int64):
-// the inputs are checked and the bound is computed from delta_ppm on the device, out is [3]
-// (G, V, status) and `cap` is ignored.  exact != 0 (host-checked inputs only): a second run of
-// the recurrence minimises V over every clustering that reaches G(K, L).
+// the inputs are checked and the bound is computed from delta_ppm on the device, and `cap` is
+// ignored.  out is [3]: G, V, status.  exact != 0 (host-checked inputs only): a second run of
+// the recurrence minimises V over every clustering that reaches G(K, L).  max_spins: how often a wait
+// between workgroups looks for its value before it gives up (about 0.5 us a look; waits take a few, unless
+// another call writes the same work memory).
+constexpr unsigned CLUSTER_MAX_SPINS = 1u << 23;
 hipError_t launch_cluster(hipStream_t st, const int32_t *flop, const int32_t *src,
                           const int32_t *dst, const int64_t *nbytes, int E, int K, int L,
                           int64_t cap, int width, const ClusterWork &w, int64_t *out,
-                          int32_t *first_op, int64_t *ctl = nullptr, int delta_ppm = 0, int exact = 0);
+                          int32_t *first_op, int64_t *ctl = nullptr, int delta_ppm = 0, int exact = 0,
+                          unsigned max_spins = CLUSTER_MAX_SPINS);
 
 }  // namespace alpa

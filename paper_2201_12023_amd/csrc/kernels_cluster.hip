@@ -26,7 +26,8 @@ constexpr int ROWS_PER_LAUNCH = 128;
 constexpr int64_t NOT_YET = -1;        // no value of a row is negative
 
 // pf[x] = FLOP of operators 0..x-1 (int64); win[n] = number of feasible first operators of a layer that ends
-// with the n-th (1-based); meta[0] = the largest of them (at least 1), meta[1] = work counter.  One block.
+// with the n-th (1-based); meta[0] = the largest of them (at least 1), meta[1] = work counter, meta[2] = a wait
+// has run out.  One block.
 __global__ __launch_bounds__(CL_THREADS) void cluster_prefix_kernel(
     const int32_t *__restrict__ flop, int K, int64_t cap, const int64_t *__restrict__ ctl,
     int64_t *__restrict__ pf, int32_t *__restrict__ win, int64_t *__restrict__ tot, int32_t *__restrict__ meta)
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(CL_THREADS) void cluster_prefix_kernel(
     }
     atomicMax(&sh_max, widest);
     __syncthreads();
-    if (t == 0) { meta[0] = sh_max; meta[1] = 0; }
+    if (t == 0) { meta[0] = sh_max; meta[1] = 0; meta[2] = 0; }
 }
 
 __global__ void cluster_zero_band_kernel(int64_t *__restrict__ band, int K, const int32_t *__restrict__ meta)
@@ -184,10 +185,19 @@ __device__ __forceinline__ void lex_step(Lex &a)
     if (lex_less(o, a)) a = o;
 }
 
-__device__ __forceinline__ int64_t await(const int64_t *p)
+// The value at p once it is there.  Every wait of a call that has the work memory to itself ends by itself (see
+// cluster_rows_kernel); what another call overwrites may never come, so after max_spins looks, or once some
+// wait has run out (*lost), the caller goes on without it and the call reports it.  (A clock in the place of
+// the count is 2 % of the whole call.)
+__device__ __forceinline__ int64_t await(const int64_t *p, int32_t *lost, unsigned max_spins)
 {
     int64_t v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    while (v == NOT_YET) {
+    for (unsigned spin = 0; v == NOT_YET; ++spin) {
+        if (spin >= max_spins ||
+            (spin % 64 == 63 && __hip_atomic_load(lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+            __hip_atomic_store(lost, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return INF_I64;
+        }
         __builtin_amdgcn_s_sleep(1);
         v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -206,7 +216,7 @@ template <bool EXACT>
 __global__ __launch_bounds__(CL_THREADS) void cluster_rows_kernel(
     const int64_t *__restrict__ band, const int64_t *__restrict__ pf, const int32_t *__restrict__ win, int K,
     int rows, int64_t *G, int64_t *V, int32_t *__restrict__ arg, int32_t *meta,
-    const int64_t *__restrict__ gstar_p)
+    const int64_t *__restrict__ gstar_p, unsigned max_spins)
 {
     constexpr int T = CL_TILE, GL = CL_LANES, KEEP = CL_KEEP;
     extern __shared__ int64_t sh[];
@@ -228,7 +238,8 @@ __global__ __launch_bounds__(CL_THREADS) void cluster_rows_kernel(
         if (!EXACT) sG[x] = G[m];
         sV[x] = V[m];
     }
-    const int width = n <= K ? win[n] : 0;
+    // (no further back than the tile reads, whatever another call may have left in `win`)
+    const int width = n <= K ? min(win[n], n - base) : 0;
     const int64_t pn = pf[min(n, K)];
     const int64_t gstar = EXACT ? *gstar_p : 0;
     __syncthreads();
@@ -249,8 +260,8 @@ __global__ __launch_bounds__(CL_THREADS) void cluster_rows_kernel(
             for (int x = threadIdx.x; x < halo; x += CL_THREADS) {
                 const int m = base + x;
                 // G(0, r) of a positive number of layers is infinite; nobody owns it
-                if (!EXACT) sG[x] = m == 0 ? INF_I64 : await(&G[(r - 1) * ld + m]);
-                sV[x] = m == 0 ? (EXACT ? INF_I64 : 0) : await(&V[(r - 1) * ld + m]);
+                if (!EXACT) sG[x] = m == 0 ? INF_I64 : await(&G[(r - 1) * ld + m], &meta[2], max_spins);
+                sV[x] = m == 0 ? (EXACT ? INF_I64 : 0) : await(&V[(r - 1) * ld + m], &meta[2], max_spins);
             }
         __syncthreads();
         Lex best{INF_I64, 0, 0};
@@ -360,18 +371,19 @@ __global__ __launch_bounds__(1024) void cluster_check_kernel(
     }
 }
 
-// out[0] = G(K, L), out[1] = V(K, L); first_op[0..L] by walking arg back (one thread).  With
-// ctl (device-resident inputs) also out[2] = ctl[0], the status of the argument checks, and
-// "no clustering" is reported if that is not 0.
+// out[0] = G(K, L), out[1] = V(K, L); first_op[0..L] by walking arg back (one thread).  out[2] = 0, or ctl[0], the
+// status of the argument checks (device-resident inputs), or -4 (ALPA_DP_EHIP) if a wait has run out; "no
+// clustering" is reported if that is not 0.
 __global__ void cluster_walk_kernel(const int64_t *__restrict__ G, const int64_t *__restrict__ V,
                                     const int32_t *__restrict__ arg, int K, int L,
-                                    const int64_t *__restrict__ ctl, int64_t *__restrict__ out,
-                                    int32_t *__restrict__ first_op)
+                                    const int64_t *__restrict__ ctl, const int32_t *__restrict__ meta,
+                                    int64_t *__restrict__ out, int32_t *__restrict__ first_op)
 {
     // G: G(K, L); V: the sum of squares that goes with it (exact mode: W(K, L))
     if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    if (ctl) out[2] = ctl[0];
-    const int64_t g = (ctl && ctl[0] != 0) ? INF_I64 : *G;
+    const int64_t status = ctl && ctl[0] != 0 ? ctl[0] : meta[2] != 0 ? -4 : 0;
+    out[2] = status;
+    const int64_t g = status != 0 ? INF_I64 : *G;
     out[0] = g;
     out[1] = g == INF_I64 ? 0 : *V;
     if (g == INF_I64) {
@@ -382,13 +394,14 @@ __global__ void cluster_walk_kernel(const int64_t *__restrict__ G, const int64_t
     first_op[L] = K;
     for (int r = L; r >= 1; --r) {
         const int i = arg[(size_t)(r - 1) * (K + 1) + n];
-        first_op[r - 1] = i - 1;
-        n = i - 1;
+        n = min(max(i - 1, 0), K);                   // (i is in 1..n unless another call wrote here)
+        first_op[r - 1] = n;
     }
 }
 
 template <bool EXACT>
-static hipError_t launch_rows(hipStream_t st, const ClusterWork &w, int K, int rows, int width, int32_t *arg)
+static hipError_t launch_rows(hipStream_t st, const ClusterWork &w, int K, int rows, int width, int32_t *arg,
+                              unsigned max_spins)
 {
     constexpr int T = CL_TILE;
     const size_t lds = (size_t)3 * (std::min(width, K) + T + 1) * sizeof(int64_t);
@@ -398,12 +411,13 @@ static hipError_t launch_rows(hipStream_t st, const ClusterWork &w, int K, int r
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((cluster_rows_kernel<EXACT>), dim3((K + T - 1) / T), dim3(CL_THREADS), lds, st, w.band,
-                       w.pf, w.win, K, rows, w.G, w.V, arg, w.meta, w.keep);
+                       w.pf, w.win, K, rows, w.G, w.V, arg, w.meta, w.keep, max_spins);
     return hipGetLastError();
 }
 
 template <bool EXACT>
-static hipError_t launch_run(hipStream_t st, const ClusterWork &w, int K, int L, int width, int32_t *arg)
+static hipError_t launch_run(hipStream_t st, const ClusterWork &w, int K, int L, int width, int32_t *arg,
+                             unsigned max_spins)
 {
     const size_t ld = (size_t)K + 1;
     int done = 0, last = 0;
@@ -411,7 +425,7 @@ static hipError_t launch_run(hipStream_t st, const ClusterWork &w, int K, int L,
         const int rows = std::min(ROWS_PER_LAUNCH, L - done);
         hipLaunchKernelGGL(cluster_begin_rows_kernel, dim3((K + 64) / 64), dim3(64), 0, st, w.G, w.V, K, rows,
                            done == 0 ? 1 : 0, EXACT ? 1 : 0, last, w.meta);
-        const hipError_t e = launch_rows<EXACT>(st, w, K, rows, width, arg + done * ld);
+        const hipError_t e = launch_rows<EXACT>(st, w, K, rows, width, arg + done * ld, max_spins);
         if (e != hipSuccess) return e;
         done += rows;
         last = rows;
@@ -422,7 +436,8 @@ static hipError_t launch_run(hipStream_t st, const ClusterWork &w, int K, int L,
 hipError_t launch_cluster(hipStream_t st, const int32_t *flop, const int32_t *src,
                           const int32_t *dst, const int64_t *nbytes, int E, int K, int L,
                           int64_t cap, int width, const ClusterWork &w, int64_t *out,
-                          int32_t *first_op, int64_t *ctl, int delta_ppm, int exact)
+                          int32_t *first_op, int64_t *ctl, int delta_ppm, int exact,
+                          unsigned max_spins)
 {
     if (ctl)
         hipLaunchKernelGGL(cluster_check_kernel, dim3(1), dim3(1024), 0, st, flop, K, src, dst,
@@ -437,17 +452,17 @@ hipError_t launch_cluster(hipStream_t st, const int32_t *flop, const int32_t *sr
                            nbytes, E, K, w.band, w.tot, w.meta);
     hipLaunchKernelGGL(cluster_band_in_kernel, dim3((K + 63) / 64), dim3(64), 0, st, w.band, w.tot, K, w.meta);
     hipLaunchKernelGGL(cluster_band_sum_kernel, dim3((K + 63) / 64), dim3(64), 0, st, w.band, K, w.meta);
-    hipError_t e = launch_run<false>(st, w, K, L, width, w.arg);
+    hipError_t e = launch_run<false>(st, w, K, L, width, w.arg, max_spins);
     if (e != hipSuccess) return e;
     const size_t ld = (size_t)K + 1;
     const size_t end = (size_t)((L - 1) % ROWS_PER_LAUNCH + 1) * ld + K;   // (K, L) in the last launch's rows
     if (exact) {
         hipLaunchKernelGGL(cluster_keep_kernel, dim3(1), dim3(1), 0, st, w.G + end, w.keep);
-        e = launch_run<true>(st, w, K, L, width, w.arg);
+        e = launch_run<true>(st, w, K, L, width, w.arg, max_spins);
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(cluster_walk_kernel, dim3(1), dim3(WAVE), 0, st, exact ? w.keep : w.G + end, w.V + end,
-                       w.arg, K, L, (const int64_t *)ctl, out, first_op);
+                       w.arg, K, L, (const int64_t *)ctl, w.meta, out, first_op);
     return hipGetLastError();
 }
 

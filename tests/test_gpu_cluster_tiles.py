@@ -61,3 +61,22 @@ def test_refused_figures_reach_no_wait():
         B.alpa_cluster_layers_static(torch.from_numpy(flop).cuda(), none32, none32, none64, L, 500000, out, first)
         torch.cuda.synchronize()
         assert out.tolist() == [B.INF_I64, 0, -1] and first.tolist() == [-1] * (L + 1)
+
+
+@pytest.mark.parametrize("exact", [0, 1])
+def test_a_wait_that_runs_out_is_reported(exact):
+    """With no time to wait in, the first value that is not there yet ends the call with a status; with the usual
+    time the same call, on the memory that the first one gave back, is right."""
+    import ctypes
+    g = W.make_op_graph(3, 60)                       # 12 tiles, 31 rows that wait
+    L, first = 32, np.zeros(33, np.int32)
+    comm, sumsq = ctypes.c_int64(), ctypes.c_int64()
+    ptr = lambda a: ctypes.c_void_p(a.ctypes.data)
+    rc = B.load().alpa_cluster_layers_waiting_(ptr(g.flop), g.K, ptr(g.src), ptr(g.dst), ptr(g.nbytes), len(g.src), L,
+                                               500000, exact, 0, ctypes.byref(comm),
+                                               ctypes.byref(sumsq), ptr(first))
+    assert rc == -4 and b"wait" in B.load().alpa_dp_last_error()
+    call = B.alpa_cluster_layers_exact if exact else B.alpa_cluster_layers
+    r = call(g.flop, g.src, g.dst, g.nbytes, L, 500000)
+    want = (oracle.cluster_exact if exact else oracle.cluster)(g.flop, g.src, g.dst, g.nbytes, L, 500000)
+    assert (r["comm"], r["sumsq"], r["first_op"]) == want
