@@ -77,8 +77,9 @@ struct alpa_dp {
     bool row_ok = false;
     int row_grid = 0;
     int32_t *d_bounds = nullptr;    // what the table says about every candidate (launch_table_bounds)
+    int32_t *d_no_bounds = nullptr; // the same layout, saying nothing
     int32_t *d_bound_work = nullptr;
-    bool have_bounds = false;       // of the present table: computed by the first solve that needs them
+    bool have_bounds = false;       // of the present table: computed by the first solve that wants them
     PrepBuffers pb{};
     int32_t *d_distinct = nullptr;
     uint32_t *d_ncount = nullptr;   // [2]: distinct table values, distinct caller candidates
@@ -351,7 +352,7 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     h->fast_ok = !h->row_ok && K <= 128 && D <= 128;
     int rc = carve(&h->arena, [&](Carver &take) {
         take(h->d_table, (size_t)K * K * K * S);
-        take(h->d_sizes, S);
+        take(h->d_sizes, S + table_bounds_ints(h->p));             // d_no_bounds behind it
         take(h->pb.hist, SORT_RADIX * SORT_SLICES + SORT_RADIX);   // counts + totals
         take(h->d_ncount, 2);
         take(h->d_state, 1);
@@ -379,8 +380,12 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
         return fail(ALPA_DP_EOVERFLOW, "K * largest finite latency >= 2^30");
     h->key_bits_table = bits_for((uint32_t)(h->max_finite + 1));
     h->n_table_keys = K * (K * (K + 1) / 2) * S;
-    HIPCHK(hipMemcpyAsync(h->d_sizes, sizes.data(), (size_t)S * 4, hipMemcpyHostToDevice,
-                          h->stream));            // (the call ends with a synchronisation)
+    // (the call ends with a synchronisation: `up` may go away after the return)
+    std::vector<int32_t> up(sizes);
+    up.insert(up.end(), table_bounds_ints(h->p), -1);
+    up[S + h->p.Smax + 1] = 0;                     // any t_max may have a plan, of an unknown number of stages
+    h->d_no_bounds = h->d_sizes + S;
+    HIPCHK(hipMemcpyAsync(h->d_sizes, up.data(), up.size() * 4, hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipMemsetAsync(h->d_state, 0, sizeof(SolveState), h->stream));
     HIPCHK(launch_init_best_plan(h->stream, h->d_best_plan));
     if (h->row_ok) {
@@ -633,17 +638,31 @@ static int candidate_bound(const alpa_dp *h, bool have_list, int n_tmax)
 // candidates as for 2048 (64 layers on 16 x 8, 1024 candidates: 0.71 ms in one round, 0.96 in two; 64 layers
 // on 8 x 8, 4096: 1.47 in one, 0.58 in two).  Where every candidate keeps a compute unit busy by itself (the
 // row kernel's sizes) the work counts from fewer on (128 layers, 1024 candidates: 2.28 in one, 1.53 in two).
-static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool one_per_cu)
+// Without the bounds the problem is small and one round takes everything.
+static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool one_per_cu, bool with_bounds)
 {
     RefineBuffers rb{};
     rb.knots[0] = h->d_knots;
     rb.knots[1] = h->d_knots + REFINE_MAX_KNOTS;
     rb.list = h->d_list;
-    rb.all = one_per_cu ? 512 : 2048;
+    rb.all = !with_bounds ? INT32_MAX : one_per_cu ? 512 : 2048;
     rb.first_round = 256;                          // a candidate per compute unit
     rb.budget = 512;
     rb.rounds = bound <= rb.all ? 1 : bound <= 8192 ? 2 : 3;
     return rb;
+}
+
+// Does a solve of at most `bound` candidates use the table's bounds?  They cost the first solve that does a launch
+// per stage count (3.5 us each), and save what is left out of the recurrence, on every solve.  A small problem's first
+// solve goes without: 24 layers on 2 x 8, 512 candidates, 133 us without and 160 with them (165 before there
+// were bounds), 12 on 1 x 8 97 and 108 (105); they pay at once at 64 layers (1 x 8, 512 candidates: 192 without,
+// 138 with) and for more work (40 layers on 1 x 8, all 5050 values: 185 and 163).  A table that is solved
+// again is worth them: the same sizes then take 101, 84, 95 and 133 us.  A recorded solve would compute them on every replay.
+static bool wants_bounds(const alpa_dp *h, int bound, bool recorded)
+{
+    if (h->have_bounds || (h->any_solve && !recorded)) return true;
+    const double work = (double)bound * h->p.K * h->p.K * h->p.S * h->p.D;   // about ten per cell-update and stage count
+    return h->p.K >= 64 || work >= 8e7;
 }
 
 // n_B > 0: sweep over the B values in d_sw_B (Eq. 4 and the selection once per value, plans
@@ -677,10 +696,12 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
 
     const bool fast = h->fast_ok && !(flags & ALPA_DP_GENERIC);
     const bool row = h->row_ok && !(flags & ALPA_DP_GENERIC);
-    const RefineBuffers rb = plan_rounds(h, bound, !fast);
+    const bool with_bounds = wants_bounds(h, bound, recorded);
+    const RefineBuffers rb = plan_rounds(h, bound, !fast, with_bounds);
+    const int32_t *bounds = with_bounds ? h->d_bounds : h->d_no_bounds;
     // per-candidate results are wanted from every interval; a plan alone from few of them
     const RefineQuery rq{n_B > 0 ? h->d_sw_B : nullptr, p.B, std::max(n_B, 1), prune,
-                         (n_B > 0 || !d_out_T) ? 1 : 0, h->d_bounds, p.Smax};
+                         (n_B > 0 || !d_out_T) ? 1 : 0, bounds, p.Smax};
     HIPCHK(hipEventRecord(h->ev[0], st));
     HIPCHK(launch_init_state(st, h->d_state, h->d_chunkmin, bound / PRUNE_CHUNK + 1));
     if (have_list) {
@@ -697,7 +718,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         HIPCHK(launch_pick_candidates(st, h->d_distinct, h->d_ncount + 0, n_tmax, bound, h->d_cand,
                                       h->d_state, h->cands.cap));
     }
-    if (!h->have_bounds) {
+    if (with_bounds && !h->have_bounds) {
         HIPCHK(launch_table_bounds(st, p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
         h->have_bounds = !recorded;                // (recorded, they are there only after the graph's replay)
     }
@@ -713,7 +734,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
             FastArgs fa{p, nullptr, h->d_sizes, h->d_cand, rb.list, &h->d_state->n_list, 0, INT32_MAX,
                         &h->d_state->ticket, &h->d_state->wave_relax, h->d_chunkmin, skip,
                         /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cands.cap, nullptr, nullptr,
-                        nullptr, h->d_bounds};
+                        nullptr, bounds};
             HIPCHK(launch_recurrence_row(st, fa, h->d_rowrecs, h->d_rowends,
                                          (flags & ALPA_DP_COUNT_WORK) ? FAST_MODE_COUNT : FAST_MODE_BATCH,
                                          std::max(1, std::min(bound, h->row_grid))));
@@ -744,7 +765,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
             FastArgs fa{p, h->d_recs, h->d_sizes, h->d_cand, rb.list,
                         &h->d_state->n_list, 0, INT32_MAX,
                         &h->d_state->ticket, &h->d_state->wave_relax, h->d_chunkmin, skip,
-                        /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cands.cap, nullptr, nullptr, h->d_gmin, h->d_bounds};
+                        /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cands.cap, nullptr, nullptr, h->d_gmin, bounds};
             fa.grouped = group_dp;
             // Short lists go to forms with more waves per candidate (two of sixteen or four of eight waves per
             // compute unit instead of eight of four; 256 candidates of 64 layers on 8 x 8, t_max at the 20 %
@@ -757,7 +778,10 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                 fa.n_hi = wide ? h->n_cu : 2 * h->n_cu;
                 HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_FEW, nc, std::min(bound, fa.n_hi)));
                 fa.n_lo = fa.n_hi;
-                if (!wide && most > fa.n_lo) {
+                // (a first solve without bounds on 9..16 devices has lists of unequal candidates: the lane groups
+                // of the batch form, 24 layers on 2 x 8, 1500 candidates: 175 against 219 us)
+                const bool to_groups = grouped && !with_bounds && p.D <= 16;
+                if (!wide && !to_groups && most > fa.n_lo) {
                     fa.n_hi = 8 * h->n_cu;
                     HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_MID, nc, std::min(bound, 4 * h->n_cu)));
                     fa.n_lo = fa.n_hi;
@@ -773,7 +797,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
             HIPCHK(launch_recurrence_generic(st, p, h->d_table, h->d_sizes, h->d_cand,
                                              rb.list, &h->d_state->n_list, &h->d_state->ticket,
                                              h->d_chunkmin, skip, h->d_Fmin, h->d_Sbest,
-                                             h->d_scratch, 2, h->d_bounds, grid));
+                                             h->d_scratch, 2, bounds, grid));
         }
     }
     HIPCHK(hipEventRecord(h->ev[2], st));

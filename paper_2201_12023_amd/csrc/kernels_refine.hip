@@ -53,6 +53,7 @@ __global__ void set_candidates_kernel(const uint32_t *__restrict__ n_unique_p, S
 //     T*(j0) <= U = s t_feas + (B - 1) t_max(j0): with the early exit of Alg. 1, nothing from the first
 //     candidate on with B t_max >= U is evaluated; where only the plan counts, a candidate
 //     with (least unfiltered F) + (B - 1) t_max >= U cannot win against j0.
+// (Where the bounds say nothing, t_feas is 0 and `stages` negative: everything is searched.)
 // The list is sorted as unsigned, so values below zero (only a device-side list can hold them) come last;
 // no entry passes them.
 __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq, int all, int first_round,
@@ -83,7 +84,7 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
     if ((rq.prune || rq.plan_only) && j0 < n) {
         for (int b = threadIdx.x; b < rq.n_B; b += RF_THREADS) {
             const int64_t B = rq.B_vals ? rq.B_vals[b] : rq.B;
-            const int64_t U = stages * t_feas + (B - 1) * (int64_t)cand[j0];
+            const int64_t U = stages < 0 ? INF_I64 : stages * t_feas + (B - 1) * (int64_t)cand[j0];
             const int64_t least = rq.bounds[0];
             int x = j0 + 1, z = n;                     // first index in [x, z) that need not be looked at
             while (x < z) {

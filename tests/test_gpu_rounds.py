@@ -263,3 +263,57 @@ def test_long_list_recorded_as_the_first_call():
             _same_plan(B.plan_from_bytes(d_plan.cpu().numpy().tobytes()), p_ref)
     finally:
         B.alpa_dp_destroy(h)
+
+
+@pytest.mark.parametrize("form", list(FORMS))
+@pytest.mark.parametrize("size", [(3, 1, 2, 0), (12, 1, 8, 0), (24, 2, 8, 513), (14, 2, 8, 4000), (20, 4, 8, 600), (9, 8, 8, 300),
+                                  (8, 10, 8, 300), (7, 17, 8, 40), (66, 1, 2, 300)],
+                         ids=lambda s: f"K{s[0]}-{s[1]}x{s[2]}-n{s[3]}")
+def test_first_and_later_solves_of_a_table(size, form):
+    """A small problem's first solve does without the bounds, the second computes them, the third finds them:
+    the same results from a new handle's first three calls, whatever they ask for, and from a recorded one."""
+    import torch
+    K, N, M, n = size
+    w = _table(61 + K, K, N, M, 250_000, 0.15)
+    cand = oracle.all_candidates(w.table, w.shapes)
+    if n and len(cand) > n:
+        cand = oracle.quantiles(cand, n)
+    ref = {p: oracle.solve_parallel(w.table, N, M, 11, w.shapes, cand, p, 8) for p in (False, True)}
+    calls = {"T": lambda h, f: B.alpa_dp_solve(h, None, n, f),
+             "plan": lambda h, f: B.alpa_dp_solve(h, None, n, f, want_T=False),
+             "list": lambda h, f: B.alpa_dp_solve(h, cand, flags=f),
+             "sweep": lambda h, f: (None, B.alpa_dp_solve_sweep(h, None, [11, 3], n_tmax=n, flags=f)[0])}
+    for first in calls:
+        for prune in (False, True):
+            flags = FORMS[form] | (B.ALPA_DP_PRUNE if prune else 0)
+            h = B.alpa_dp_create(w.table, K, N, M, 11, w.shapes)
+            try:
+                for call in (first, "T", first):
+                    T, plan = calls[call](h, flags)
+                    if T is not None:
+                        assert np.array_equal(T, ref[prune][0])
+                    _same_plan(plan, ref[prune][1])
+            finally:
+                B.alpa_dp_destroy(h)
+    h = B.alpa_dp_create(w.table, K, N, M, 11, w.shapes)
+    try:
+        stream = torch.cuda.Stream()
+        d_T = torch.zeros(len(cand), dtype=torch.int64, device="cuda")
+        d_plan = torch.zeros(B.PLAN_BYTES, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        B.alpa_dp_set_stream(h, stream)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            B.alpa_dp_solve_dev(h, None, n, FORMS[form], d_T, d_plan)
+        for replay in range(3):
+            d_T.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(stream):
+                graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(d_T.cpu().numpy(), ref[False][0])
+            _same_plan(B.plan_from_bytes(d_plan.cpu().numpy().tobytes()), ref[False][1])
+            T, plan = B.alpa_dp_solve(h, None, n, FORMS[form])
+            assert np.array_equal(T, ref[False][0])
+    finally:
+        B.alpa_dp_destroy(h)
