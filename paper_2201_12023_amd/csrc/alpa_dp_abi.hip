@@ -778,9 +778,12 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                 fa.n_hi = wide ? h->n_cu : 2 * h->n_cu;
                 HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_FEW, nc, std::min(bound, fa.n_hi)));
                 fa.n_lo = fa.n_hi;
-                // (a first solve without bounds on 9..16 devices has lists of unequal candidates: the lane groups
-                // of the batch form, 24 layers on 2 x 8, 1500 candidates: 175 against 219 us)
-                const bool to_groups = grouped && !with_bounds && p.D <= 16;
+                // On meshes that use few of a wave's lanes the lane groups of the batch form take what is beyond
+                // the first form's share: up to 8 devices (1024 candidates, recurrence alone: 24 layers on 1 x 4
+                // 10 against 27 us, 48 on 1 x 8 11 and 30, 40 on 1 x 8 63 and 54), up to 16 if nothing is
+                // left out, in a first solve without bounds (24 on 2 x 8, 1500: 175 against 219 in all); else
+                // 16 devices are as fast or faster with eight waves (64 on 2 x 8: 126 against 139).
+                const bool to_groups = grouped && p.D <= (with_bounds ? 8 : 16);
                 if (!wide && !to_groups && most > fa.n_lo) {
                     fa.n_hi = 8 * h->n_cu;
                     HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_MID, nc, std::min(bound, 4 * h->n_cu)));

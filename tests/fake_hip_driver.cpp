@@ -185,18 +185,21 @@ static void check_launches(size_t from, size_t to, const char *what)
     }
 }
 
-// 12 layers on 2 x 8: 12 * 78 * 5 = 4680 table entries, 100 distinct values of up to 5000
-constexpr int K = 12, N = 2, M = 8, S = 5, ENTRIES = K * (K * (K + 1) / 2) * S;
-static alpa_dp_t *create()
+static alpa_dp_t *create_problem(int K, int N, int M)
 {
-    static std::vector<int32_t> table((size_t)K * K * K * S, 7);
-    const alpa_shape_t shapes[S] = {{1, 1}, {1, 2}, {1, 4}, {1, 8}, {2, 8}};
+    std::vector<alpa_shape_t> shapes;
+    for (int m = 1; m <= M; m *= 2) shapes.push_back({1, m});
+    for (int n = 2; n <= N; ++n) shapes.push_back({n, M});
+    std::vector<int32_t> table((size_t)K * K * K * shapes.size(), 7);
     alpa_dp_t *h = nullptr;
-    const int rc = alpa_dp_create(&h, table.data(), K, N, M, 8, shapes, S);
+    const int rc = alpa_dp_create(&h, table.data(), K, N, M, 8, shapes.data(), (int)shapes.size());
     if (rc) { printf("create: %d %s\n", rc, alpa_dp_last_error()); exit(1); }
     CHECK(alpa_dp_set_stream(h, (void *)0x1000) == 0, "stream");   // (the null stream cannot be recorded)
     return h;
 }
+// 12 layers on 2 x 8: 12 * 78 * 5 = 4680 table entries, 100 distinct values of up to 5000
+constexpr int K = 12, N = 2, M = 8, ENTRIES = K * (K * (K + 1) / 2) * 5;
+static alpa_dp_t *create() { return create_problem(K, N, M); }
 static void *device_array(size_t bytes) { void *p; hipMalloc(&p, bytes); return p; }
 
 // a reported ENOMEM leaves a handle that works, or says ENOMEM again
@@ -336,6 +339,71 @@ static void short_memory()
     alpa_dp_destroy(h);
 }
 
+// which kernels a solve of n quantiles (0: all 5000 values) launches, each name between blanks
+static std::string kernels_of(alpa_dp_t *h, int n)
+{
+    const size_t from = rt().launches.size();
+    CHECK(alpa_dp_solve_dev(h, nullptr, n, 0, (int64_t *)device_array(8 * 5000), nullptr) == 0, "solve");
+    std::string all = " ";
+    for (size_t x = from; x < rt().launches.size(); ++x) {
+        std::string k = rt().launches[x].kernel;
+        k.erase(0, k.rfind("alpa::") + 6);
+        for (char c : k) if (c != ' ') all += c;
+        all += " ";
+    }
+    return all;
+}
+
+// which form of the recurrence serves which sizes and lists, and when a table's bounds are computed
+static void routes()
+{
+    rt().n_distinct = 5000;
+    struct { int K, N, M, n; const char *has, *has_not; } cases[] = {
+        // up to 8 devices: beyond two candidates per compute unit in lane groups, not with eight waves each
+        {24, 1, 4, 1500, " recurrence_fast_kernel<2,1,1,false,false,false,true> ", "recurrence_fast_kernel<2,2,1,false"},
+        {40, 2, 4, 2048, " recurrence_fast_kernel<3,1,1,false,false,false,true> ", "recurrence_fast_kernel<3,2,1,false"},
+        {64, 1, 2, 600, " recurrence_fast_kernel<4,1,1,false,false,false,true> ", "recurrence_fast_kernel<4,2,1,false"},
+        {24, 3, 4, 1500, " recurrence_fast_kernel<2,2,1,false,false,false,false> ", "recurrence_row"},
+        {64, 8, 8, 1500, " recurrence_fast_kernel<4,2,1,false,false,false,false> ", "recurrence_row"},
+        {64, 1, 2, 512, " recurrence_fast_kernel<4,4,1,false,false,false,false> ", "false,true> "},
+    };
+    for (auto &c : cases) {
+        alpa_dp_t *h = create_problem(c.K, c.N, c.M);
+        (void)kernels_of(h, c.n);
+        const std::string k = kernels_of(h, c.n);  // with the bounds
+        CHECK(k.find(c.has) != std::string::npos, "%d layers on %dx%d, %d: no%sin%s", c.K, c.N, c.M, c.n, c.has, k.c_str());
+        CHECK(k.find(c.has_not) == std::string::npos, "%d layers on %dx%d, %d: %s in%s", c.K, c.N, c.M, c.n, c.has_not,
+              k.c_str());
+        alpa_dp_destroy(h);
+    }
+    // bounds: by the first solve, or by the second; never recorded into a small problem's graph
+    struct { int K, N, M, n, by; } bounds[] = {{8, 1, 4, 0, 2}, {24, 2, 8, 1000, 2}, {40, 1, 8, 512, 2}, {64, 1, 2, 300, 1},
+                                               {64, 8, 8, 300, 1}, {48, 8, 8, 2000, 1}, {24, 8, 8, 5000, 1}};
+    for (auto &c : bounds) {
+        alpa_dp_t *h = create_problem(c.K, c.N, c.M);
+        rt().capturing = true;
+        const bool recorded = kernels_of(h, c.n).find("bound_layer") != std::string::npos;
+        rt().capturing = false;
+        CHECK(recorded == (c.by == 1), "%d layers on %dx%d, %d: bounds in the graph: %d", c.K, c.N, c.M, c.n, recorded);
+        alpa_dp_destroy(h);
+        h = create_problem(c.K, c.N, c.M);
+        for (int restricted = 0; restricted < 2; ++restricted) {
+            for (int solve = 1; solve <= 3; ++solve) {
+                const bool found = kernels_of(h, c.n).find("bound_layer") != std::string::npos;
+                CHECK(found == (solve == c.by && !restricted), "%d layers on %dx%d, %d: solve %d, bounds %d", c.K, c.N, c.M,
+                      c.n, solve, found);
+            }
+            const size_t from = rt().launches.size();
+            CHECK(alpa_dp_restrict_equal_layers(h) == 0, "restriction");
+            bool again = false;                    // (they are there: the restriction computes them anew)
+            for (size_t x = from; x < rt().launches.size(); ++x)
+                again |= rt().launches[x].kernel.find("bound_layer") != std::string::npos;
+            CHECK(again, "%d layers on %dx%d: bounds of the old table", c.K, c.N, c.M);
+        }
+        alpa_dp_destroy(h);
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -344,6 +412,7 @@ int main(int argc, char **argv)
     else if (what == "recorded_solve") recorded_solve();
     else if (what == "long_lists") long_lists();
     else if (what == "short_memory") short_memory();
+    else if (what == "routes") routes();
     else { printf("unknown scenario\n"); return 1; }
     if (!bad) printf("OK\n");
     return bad ? 1 : 0;

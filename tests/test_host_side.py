@@ -1,5 +1,5 @@
-"""A handle's device memory, looked at without a GPU: the library's host code runs over a HIP runtime made
-up in tests/fake_hip_driver.cpp, which notes every allocation and every kernel's pointer arguments."""
+"""A handle's device memory and the kernels that a call launches, looked at without a GPU: the library's host code
+runs over a HIP runtime made up in tests/fake_hip_driver.cpp, which notes every allocation and every launch."""
 import os
 import shutil
 import subprocess
@@ -23,8 +23,8 @@ def driver(tmp_path_factory):
     return str(out)
 
 
-@pytest.mark.parametrize("scenario", ["out_of_memory", "ordinary_lists", "recorded_solve", "long_lists", "short_memory"])
-def test_handle_memory(driver, scenario):
+@pytest.mark.parametrize("scenario", ["out_of_memory", "ordinary_lists", "recorded_solve", "long_lists", "short_memory", "routes"])
+def test_host_side_of_a_handle(driver, scenario):
     env = dict(os.environ)
     env["LD_LIBRARY_PATH"] = os.path.dirname(B.LIB_PATH) + ":" + env.get("LD_LIBRARY_PATH", "")
     r = subprocess.run([driver, scenario], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, env=env,
