@@ -346,9 +346,14 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     int gg = h->n_cu * 4;
     while (gg > 1 && (size_t)gg * 2 * LS * 4 > (256ull << 20)) gg /= 2;
     h->generic_grid_max = gg;
-    // 65-128 layers on up to 64 devices and 129-256 devices: a workgroup per candidate; other sizes up to 128
-    // layers on 128 devices: the register/LDS kernel (above 64 devices in its two-window form)
-    h->row_ok = (K > 64 || D > 128) && row_serves(K, D, S);
+    // A workgroup per candidate (the row kernel) where its layers fit in LDS: 129-256 devices, and from 65 layers on (up to
+    // 138 layers on 8 x 8, 86 on 16 x 8, 240 on 2 x 8).  Not up to 128 layers on 1 or 2 devices and 96 on 3 or 4, where
+    // most lanes of a wave have nothing to do and lane groups of the register/LDS kernel are faster (2048 candidates:
+    // 72 layers on 1 x 2 152 against 176 us, on 1 x 4 180 and 199, 96 on 1 x 4 229 and 248; 128 on 1 x 4 355 and 371, but 422 and 380 for
+    // 6000; 72 on 2 x 4, 6000: 306 and 257).  Beyond 128 layers the other choice is the general kernel (240 on
+    // 2 x 8, 1024 candidates: 0.9 against 50 ms).
+    const bool groups_serve = K <= 128 && (D <= 2 || (D <= 4 && K <= 96));
+    h->row_ok = (D > 128 || (K > 64 && !groups_serve)) && row_serves(K, D, S);
     h->fast_ok = !h->row_ok && K <= 128 && D <= 128;
     int rc = carve(&h->arena, [&](Carver &take) {
         take(h->d_table, (size_t)K * K * K * S);

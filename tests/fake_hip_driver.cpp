@@ -366,6 +366,19 @@ static void routes()
         {24, 3, 4, 1500, " recurrence_fast_kernel<2,2,1,false,false,false,false> ", "recurrence_row"},
         {64, 8, 8, 1500, " recurrence_fast_kernel<4,2,1,false,false,false,false> ", "recurrence_row"},
         {64, 1, 2, 512, " recurrence_fast_kernel<4,4,1,false,false,false,false> ", "false,true> "},
+        // a workgroup per candidate: from 65 layers on, but not on the smallest meshes, and where the layers fit in LDS
+        {72, 1, 2, 2048, " recurrence_fast_kernel<5,1,1,false,false,false,true> ", "recurrence_row"},
+        {128, 1, 2, 2048, " recurrence_fast_kernel<8,1,1,false,false,false,true> ", "recurrence_row"},
+        {96, 1, 4, 2048, " recurrence_fast_kernel<6,1,1,false,false,false,true> ", "recurrence_row"},
+        {97, 3, 1, 2048, " recurrence_row_kernel<81,false,false> ", "recurrence_fast"},
+        {65, 5, 1, 2048, " recurrence_row_kernel<81,false,false> ", "recurrence_fast"},
+        {72, 2, 4, 2048, " recurrence_row_kernel<81,false,false> ", "recurrence_fast"},
+        {129, 1, 2, 300, " recurrence_row_kernel<81,false,false> ", "recurrence_generic"},
+        {138, 8, 8, 300, " recurrence_row_kernel<129,false,false> ", "recurrence_generic"},
+        {139, 8, 8, 300, " recurrence_generic_kernel ", "recurrence_row"},
+        {100, 64, 1, 300, " recurrence_fast_kernel<7,2,1,false,false,false,false> ", "recurrence_row"},
+        {86, 16, 8, 300, " recurrence_row_kernel<193,false,false> ", "recurrence_fast"},
+        {48, 32, 8, 300, " recurrence_row_kernel<321,false,false> ", "recurrence_generic"},
     };
     for (auto &c : cases) {
         alpa_dp_t *h = create_problem(c.K, c.N, c.M);
