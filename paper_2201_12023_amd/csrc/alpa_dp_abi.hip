@@ -796,10 +796,8 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                 }
                 fa.n_hi = INT32_MAX;
             }
-            if (most > fa.n_lo)
-            HIPCHK(launch_recurrence_fast(st, fa, (flags & ALPA_DP_COUNT_WORK) ? FAST_MODE_COUNT
-                                                                              : FAST_MODE_BATCH,
-                                          nc, grid));
+            const int form = (flags & ALPA_DP_COUNT_WORK) ? FAST_MODE_COUNT : FAST_MODE_BATCH;
+            if (most > fa.n_lo) HIPCHK(launch_recurrence_fast(st, fa, form, nc, grid));
         } else {
             const int grid = std::max(1, std::min(bound, h->generic_grid_max));
             HIPCHK(launch_recurrence_generic(st, p, h->d_table, h->d_sizes, h->d_cand,

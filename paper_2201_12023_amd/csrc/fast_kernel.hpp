@@ -990,8 +990,8 @@ static hipError_t launch_nwk(hipStream_t st, const FastArgs &a, int mode, int nc
     case FAST_MODE_FEW:
         if (a.p.D > WAVE) return launch_one<NWK, plan_wi(NWK), 2, false, false, true>(st, a, grid);
         return launch_one<NWK, plan_wi(NWK), 1, false, false>(st, a, grid);
-    case FAST_MODE_MID:
-        if (a.p.D > WAVE) return launch_one<NWK, 2, 2, false, false, true>(st, a, grid);
+    case FAST_MODE_MID:                            // (up to 64 devices: see the caller)
+        if (a.p.D > WAVE) return hipErrorInvalidValue;
         return launch_one<NWK, 2, 1, false, false>(st, a, grid);
     case FAST_MODE_COUNT:
         if (a.p.D > WAVE) return launch_one<NWK, 1, 2, false, true, true>(st, a, grid);

@@ -141,10 +141,9 @@ constexpr int SORT_SLICES = 1024;        // one-wave slices of the radix sort
 constexpr int SORT_RADIX = 256;          // 8-bit digits
 
 struct PrepBuffers {
-    int32_t *keys[2];        // [cap] each
+    int32_t *keys[2];        // [capacity] each
     uint32_t *hist;          // [SORT_RADIX * SORT_SLICES] slice counts + [SORT_RADIX] digit totals
-    uint32_t *block_cnt;     // [cap / 4096 + 2]
-    int cap;
+    uint32_t *block_cnt;     // [capacity / 4096 + 2]
 };
 
 hipError_t launch_gather_table_values(hipStream_t st, const int32_t *table, int K, int S,
