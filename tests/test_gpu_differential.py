@@ -1,7 +1,8 @@
-"""Differential test on the GPU: the register/LDS recurrence kernel against the general one (which
+"""Differential test on the GPU: the tuned recurrence kernels against the general one (which
 the parity tests pin to the oracle at the same sizes) on a few hundred seeded random problems —
 layer counts 1..128, every mesh of up to 128 devices, unstructured and formula tables, all three
-ways of giving candidates, pruning on and off, one and two candidates per workgroup.  A mismatch
+ways of giving candidates, pruning on and off, one and two candidates per workgroup (the register/LDS
+kernel: up to 64 layers, and beyond on the smallest meshes).  A mismatch
 is then settled by the oracle: every tenth case is also checked against it directly."""
 import numpy as np
 import pytest

@@ -428,25 +428,29 @@ def test_full_size_workloads_against_stored_oracle_results(idx):
         B.alpa_dp_destroy(h)
 
 
-def test_general_kernel_on_a_mesh_larger_than_64_devices():
-    """N*M = 80 and K = 66 are outside the register/LDS kernel; the general one serves."""
+@pytest.mark.parametrize("kernel", list(KERNELS))
+def test_deep_model_on_a_mesh_larger_than_64_devices(kernel):
+    """N*M = 80 and K = 66: a workgroup per candidate (layers recovered by the general kernel), and the general
+    kernel on request."""
     w = W.random_problem(77, 66, 10, 8, inf_frac=0.3, value_hi=900)
     allc = oracle.all_candidates(w.table, w.shapes)
     cand = oracle.quantiles(allc, 8)
     T_ref, p_ref = oracle.solve_parallel(w.table, w.N, w.M, w.B, w.shapes, cand, False, 8)
     h = B.alpa_dp_create(w.table, w.K, w.N, w.M, w.B, w.shapes)
     try:
-        T, plan = B.alpa_dp_solve(h, cand)
+        T, plan = B.alpa_dp_solve(h, cand, flags=KERNELS[kernel])
         assert (T == T_ref).all()
         _same_plan(plan, p_ref)
     finally:
         B.alpa_dp_destroy(h)
 
 
+@pytest.mark.parametrize("kernel", list(KERNELS))
 @pytest.mark.parametrize("case", [(91, 256, 1, 2), (92, 5, 32, 32), (93, 40, 16, 16)],
                          ids=["K256-1x2", "K5-32x32", "K40-16x16"])
-def test_general_kernel_at_the_size_limits(case):
-    """The largest K (256), the largest mesh (1024 devices, 37 shapes) and one in between."""
+def test_size_limits(case, kernel):
+    """The largest K (256) and the largest mesh (1024 devices, 37 shapes), which only the general kernel serves,
+    and a size in between, which it serves on request."""
     seed, K, N, M = case
     w = W.random_problem(seed, K, N, M, inf_frac=0.2, value_hi=3000)
     cand = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), 6)
@@ -454,7 +458,7 @@ def test_general_kernel_at_the_size_limits(case):
         T_ref, p_ref = oracle.solve_parallel(w.table, w.N, w.M, w.B, w.shapes, cand, prune, 6)
         h = B.alpa_dp_create(w.table, w.K, w.N, w.M, w.B, w.shapes)
         try:
-            T, plan = B.alpa_dp_solve(h, cand, flags=B.ALPA_DP_PRUNE if prune else 0)
+            T, plan = B.alpa_dp_solve(h, cand, flags=KERNELS[kernel] | (B.ALPA_DP_PRUNE if prune else 0))
             assert (T == T_ref).all()
             _same_plan(plan, p_ref)
         finally:
@@ -584,8 +588,8 @@ def test_meshes_of_65_to_128_devices(case, kernel):
             B.alpa_dp_destroy(h)
 
 
-DEEP_CASES = [  # seed, K, N, M: 65..128 layers (5-8 waves per workgroup), the last four on
-    # 65..128 devices (two windows, stage counts up to 128)
+DEEP_CASES = [  # seed, K, N, M: 65..128 layers (all but the one-device case by a workgroup per candidate), the last
+    # four on 65..128 devices (stage counts up to 128; from 92 layers on two windows of the register/LDS kernel)
     (70, 65, 4, 8), (71, 80, 8, 8), (72, 96, 2, 8), (73, 128, 8, 8), (74, 100, 1, 8),
     (75, 113, 4, 16), (76, 128, 3, 4), (77, 81, 1, 1),
     (78, 70, 9, 8), (79, 100, 16, 8), (80, 128, 2, 64), (81, 128, 16, 8),
@@ -639,15 +643,17 @@ def test_plans_of_many_stages(case, kernel):
         B.alpa_dp_destroy(h)
 
 
-@pytest.mark.parametrize("nc", [1, 2])
-@pytest.mark.parametrize("case", [(1, 128, 8, 8), (2, 96, 4, 8), (3, 72, 2, 8)],
-                         ids=lambda c: f"s{c[0]}-K{c[1]}-{c[2]}x{c[3]}")
-def test_deep_formula_tables(case, nc):
-    """Structured tables (monotone in the stage span, memory-bound infeasibility) are where
-    the early stop of the column loops and the packed two-candidate passes take effect."""
-    seed, K, N, M = case
+@pytest.mark.parametrize("case", [(1, 128, 8, 8, 0), (2, 96, 4, 8, 0), (3, 72, 2, 8, 0), (4, 128, 1, 2, 1), (4, 128, 1, 2, 2),
+                                  (5, 96, 1, 4, 1), (5, 96, 1, 4, 2), (6, 99, 64, 1, 1), (6, 99, 64, 1, 2)],
+                         ids=lambda c: f"s{c[0]}-K{c[1]}-{c[2]}x{c[3]}-nc{c[4]}")
+def test_deep_formula_tables(case):
+    """Structured tables (monotone in the stage span, memory-bound infeasibility) are where the early stops
+    take effect: those of the kernel with a workgroup per candidate, and, on the smallest meshes and with
+    many shapes, the column loops and the packed two-candidate passes of the register/LDS kernel (nc: candidates
+    per workgroup, which only that kernel knows)."""
+    seed, K, N, M, nc = case
     w = W.deep_model_problem(seed, K, N, M)
-    cand_ref = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), 121)
+    cand_ref = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), 121 if N < 64 else 9)
     for prune in (False, True):
         T_ref, p_ref = oracle.solve_parallel(w.table, w.N, w.M, w.B, w.shapes, cand_ref, prune, 8)
         assert (T_ref < oracle.INF64).any()

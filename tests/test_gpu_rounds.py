@@ -110,16 +110,21 @@ def test_bound_on_late_layers(size):
             B.alpa_dp_destroy(h)
 
 
-# the sizes of the kernel with a workgroup per candidate: 65-128 layers, 129-256 devices; one, odd and even numbers of
-# half-blocks of 8 layers, device counts at the edges of 16, 32, 64 and their multiples, many shapes
-ROW_CASES = [(65, 1, 2), (72, 1, 16), (73, 3, 8), (96, 4, 8), (121, 5, 4), (128, 8, 8), (128, 1, 1), (88, 60, 1),
-             (1, 17, 8), (8, 24, 8), (9, 32, 8), (17, 12, 16), (23, 60, 4), (40, 31, 8), (48, 16, 16), (54, 16, 16)]
+# the sizes of the kernel with a workgroup per candidate: 65 layers and more (beyond 128: the third scale of its row ends),
+# 129-256 devices; one, odd and even numbers of half-blocks of 8 layers, device counts at the edges of 16, 32, 64 and
+# their multiples, many shapes; the largest layer counts that fit in LDS
+ROW_CASES = [(65, 3, 2), (72, 1, 16), (73, 3, 8), (96, 4, 8), (121, 5, 4), (128, 8, 8), (97, 1, 4), (88, 60, 1),
+             (66, 10, 8), (86, 16, 8),
+             (1, 17, 8), (8, 24, 8), (9, 32, 8), (17, 12, 16), (23, 60, 4), (40, 31, 8), (48, 16, 16), (54, 16, 16),
+             (129, 1, 2), (244, 1, 1), (191, 1, 4), (240, 2, 8), (195, 4, 8), (130, 8, 8), (138, 8, 8)]
 
 
 @pytest.mark.parametrize("size", ROW_CASES, ids=lambda s: f"K{s[0]}-{s[1]}x{s[2]}")
 @pytest.mark.parametrize("inf_frac", [0.0, 0.6])
 def test_workgroup_per_candidate_sizes(size, inf_frac):
     K, N, M = size
+    if K > 128 and N * M > 16 and inf_frac:
+        pytest.skip("one share of infinite entries for the sizes that take the oracle longest")
     w = W.random_problem(K + 7 * N, K, N, M, inf_frac=inf_frac, value_hi=9000)
     cand = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), 12)
     cand = np.unique(np.concatenate([cand, cand[:3] // 2, [2**31 - 2]])).astype(np.int32)
@@ -135,6 +140,40 @@ def test_workgroup_per_candidate_sizes(size, inf_frac):
         Bs = [1, 40]
         for Bv, plan in zip(Bs, B.alpa_dp_solve_sweep(h, cand, Bs)):
             _, p_ref = oracle.solve_parallel(w.table, N, M, Bv, w.shapes, cand, False, 8)
+            _same_plan(plan, p_ref)
+    finally:
+        B.alpa_dp_destroy(h)
+
+
+# sizes of 65-128 layers that stay with the register/LDS kernel: the smallest meshes, and up to 64 devices with so many
+# shapes that the other kernel's rows do not fit in LDS; lists in the share of each of its forms (sixteen and eight
+# waves per candidate, four; lane groups)
+DEEP_CASES = [(65, 1, 1), (65, 1, 2), (128, 1, 1), (72, 1, 2), (81, 3, 1), (96, 1, 4), (112, 2, 1), (128, 1, 2), (99, 64, 1), (120, 32, 2)]
+
+
+@pytest.mark.parametrize("size", DEEP_CASES, ids=lambda s: f"K{s[0]}-{s[1]}x{s[2]}")
+def test_deep_models_in_the_register_kernel(size):
+    K, N, M = size
+    w = W.random_problem(K + N, K, N, M, inf_frac=0.3, value_hi=9000)
+    few = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), 5)
+    h = B.alpa_dp_create(w.table, K, N, M, w.B, w.shapes)
+    try:
+        for prune in (0, B.ALPA_DP_PRUNE):
+            T_ref, p_ref = oracle.solve_parallel(w.table, N, M, w.B, w.shapes, few, bool(prune), 8)
+            for n in (5, 300, 700, 2500):
+                T_gen, p_gen = B.alpa_dp_solve(h, None, n, prune | B.ALPA_DP_GENERIC)
+                for key, value in ((B.ALPA_DP_TUNE_CANDIDATES_PER_WG, 0), (B.ALPA_DP_TUNE_CANDIDATES_PER_WG, 1),
+                                   (B.ALPA_DP_TUNE_CANDIDATES_PER_WG, 2), (B.ALPA_DP_TUNE_LANE_GROUPS, 1)):
+                    B.alpa_dp_set_tuning(h, key, value)
+                    for extra in (0, B.ALPA_DP_COUNT_WORK):
+                        T, plan = B.alpa_dp_solve(h, None, n, prune | extra)
+                        assert np.array_equal(T, T_gen) and plan == p_gen, (n, key, value, extra)
+                    B.alpa_dp_set_tuning(h, key, 0)
+                if n == 5:
+                    assert np.array_equal(T_gen, T_ref)
+                    _same_plan(p_gen, p_ref)
+        for Bv, plan in zip([1, 40], B.alpa_dp_solve_sweep(h, few, [1, 40])):
+            _, p_ref = oracle.solve_parallel(w.table, N, M, Bv, w.shapes, few, False, 8)
             _same_plan(plan, p_ref)
     finally:
         B.alpa_dp_destroy(h)
