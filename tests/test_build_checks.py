@@ -3,6 +3,7 @@ from paper_2201_12023_amd import build as B
 
 BATCH = "_ZN4alpa22recurrence_fast_kernelILi4ELi1ELi1ELb0ELb0ELb0ELb0EEEvNS_7ProblemEPKi"
 PLAN = "_ZN4alpa22recurrence_fast_kernelILi4ELi4ELi1ELb1ELb0ELb0ELb0EEEvNS_7ProblemEPKi"
+ROW = "_ZN4alpa21recurrence_row_kernelILi129ELb0ELb0EEEvNS_7RowArgsE"
 OTHER = "_ZN4alpa15epilogue_kernelENS_7ProblemEPKi"
 
 
@@ -33,6 +34,12 @@ def test_batch_instance_must_keep_eight_waves_and_no_scratch():
     # scratch memory nor to accumulation registers
     assert len(B.check_resources(B.parse_resource_remarks(remarks(PLAN, 72, 12, 7)))) == 1
     assert len(B.check_resources(B.parse_resource_remarks(remarks(PLAN, 72, 0, 7, agprs=4)))) == 1
+
+
+def test_row_kernel_must_keep_eight_waves_and_no_spills():
+    check = lambda *r: len(B.check_resources(B.parse_resource_remarks(remarks(ROW, *r))))
+    assert check(57, 0, 8) == 0
+    assert check(68, 0, 7) == check(64, 24, 8) == check(64, 0, 8, 4) == 1
 
 
 ASM_HEAD = "\t.text\n_ZN4alpa22recurrence_fast_kernelILi4ELi1ELi1ELb0ELb0ELb0ELb0EEEvNS_7ProblemE: ; @x\n"
