@@ -35,19 +35,17 @@ HEADLINE = 4
 
 
 def stored_counter_figures(workload):
-    """HBM bytes per launch and issued-VALU fraction of the recurrence kernel as last measured
-    with rocprofv3 --pmc: two 'key: value' lines in the counter summary under profiles/, which
+    """HBM bytes and issued-VALU fraction of a solve's recurrence rounds as last measured
+    with rocprofv3 --pmc: two 'key: value' lines in the summary under profiles/, which
     also names the commit it was taken at.  (None, None, None) if there is no such summary."""
-    path = os.path.join(ROOT, "profiles", f"recurrence_fast_kernel_workload{workload}_counters.md")
+    path = os.path.join(ROOT, "profiles", f"workload{workload}.md")
     if not os.path.exists(path):
         return None, None, None
     text = open(path).read()
-    tr = re.search(r"^traffic_bytes_per_launch:\s*([0-9.eE+]+)", text, re.M)
+    tr = re.search(r"^traffic_bytes_per_solve:\s*([0-9.eE+]+)", text, re.M)
     fi = re.search(r"^valu_issued_fraction:\s*([0-9.eE+-]+)", text, re.M)
     co = re.search(r"^measured_at_commit:\s*(\w+)", text, re.M)
-    tc = re.search(r"^traffic_measured_at_commit:\s*(\w+)", text, re.M)
-    return (float(tr.group(1)) if tr else None, float(fi.group(1)) if fi else None,
-            (tc or co).group(1) if (tc or co) else None)
+    return float(tr.group(1)) if tr else None, float(fi.group(1)) if fi else None, co.group(1) if co else None
 
 
 def main():
@@ -282,7 +280,7 @@ def main():
                      "peak_measured": valu_measured / 1e12 if valu_measured else None,
                      "frac_of_measured": achieved / valu_measured if valu_measured else None,
                      "traffic": traffic, "traffic_kind": "stored rocprofv3 --pmc measurement "
-                     "(profiles/) of a launch over the whole list, not taken by this run" if traffic else None,
+                     "(profiles/) of one solve's rounds, not taken by this run" if traffic else None,
                      "traffic_measured_at_commit": commit,
                      "kernel": "recurrence_fast_kernel", "kernel_ms_avg": head["rec_avg"]},
         "extra": extra,

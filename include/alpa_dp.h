@@ -149,7 +149,10 @@ int alpa_dp_set_B(alpa_dp_t *h, int B);
 /*
  * Tuning of the launch shape; cites no passage of the paper because no result depends on it
  * (the parity tests run every setting against the same oracle values).  value 0 restores the
- * library's own choice.  Errors: EINVAL (null handle, unknown key, value out of range).
+ * library's own choice.  All keys but DISTINCT_BY_SORT are about the register/LDS kernel and without
+ * effect where another one serves: 129 devices or more, and from 65 layers on all but up to 128
+ * layers on 1 or 2 devices, 96 on 3 or 4, and sizes whose layers do not fit in LDS (more than 138 layers
+ * on 8 x 8, 86 on 16 x 8).  Errors: EINVAL (null handle, unknown key, value out of range).
  */
 #define ALPA_DP_TUNE_CANDIDATES_PER_WG 1  /* 1 or 2 t_max candidates per workgroup of the
                                              register/LDS kernel (own choice: 1, with more waves
@@ -228,8 +231,8 @@ int alpa_dp_solve_dev(alpa_dp_t *h, const int32_t *d_tmax, int n_tmax, unsigned 
  *
  * The handle's own B and the running best of alpa_dp_best() are not touched.  Blocking.
  * On the first call (and when n_B grows) device memory for n_B sets of layers is
- * allocated: n_B * (min(K, N*M) + 1) * (K + 2) * (N*M + 1) * 4 bytes when K <= 128 and
- * N*M <= 64 (one set, reused, otherwise).  Errors: EINVAL (null pointers, n_B or a B value
+ * allocated: n_B * (min(K, N*M) + 1) * (K + 2) * (N*M + 1) * 4 bytes when N*M <= 64 and K <= 128, or
+ * more layers as long as they fit in LDS (138 on 8 x 8, 244 on 1 x 1); one set, reused, otherwise.  Errors: EINVAL (null pointers, n_B or a B value
  * out of range, and the candidate-list errors of alpa_dp_solve), ENOMEM, EHIP.
  */
 #define ALPA_DP_MAX_SWEEP 256

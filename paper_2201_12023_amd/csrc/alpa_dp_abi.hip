@@ -744,9 +744,10 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                                          (flags & ALPA_DP_COUNT_WORK) ? FAST_MODE_COUNT : FAST_MODE_BATCH,
                                          std::max(1, std::min(bound, h->row_grid))));
         } else if (fast) {
-            // One candidate per workgroup: seven waves per SIMD and two columns folded into one
+            // One candidate per workgroup: eight waves per SIMD and two columns folded into one
             // three-operand minimum, which is faster than two candidates sharing their scalar
-            // loads and lanes at four waves per SIMD (workload 4: 4.40 against 4.66 ms); the
+            // loads and lanes at four waves per SIMD (64 layers on 8 x 8, 4096 candidates, this form for
+            // lists of every length: 0.98 against 1.78 ms of recurrence; 48 layers 0.53 and 0.92); the
             // two-candidate form stays available through the tuning call.
             int nc = 1;
             if (h->tune_nc) nc = h->tune_nc;
@@ -754,7 +755,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
             if (wide) nc = 2;
             // Small meshes: groups of lanes, each with a candidate of its own: as many groups as
             // the mesh allows (less work in total, and fewer, lonelier workgroups, which on these
-            // small problems matters as much: workload 2 takes 0.11 instead of 0.15 ms).  Not for
+            // small problems matters as much; both sides at `to_groups` below).  Not for
             // lists so short that every candidate gets a compute unit of its own anyway.
             int group_dp = 0;
             if (p.D <= 32 && nc == 1 && h->tune_no_groups != 1 &&

@@ -3,8 +3,8 @@
 // workgroup per t_max candidate, threads over the cells (k, d) of a layer s, every cell
 // scanning its (last layer, shape) terms in tie-break order; F layers live in global
 // memory.  Problems of up to 128 layers on up to 128 devices normally run through the
-// register/LDS kernel (fast_kernel.hpp) or, beyond 64 layers and up to 256 devices, the row kernel
-// (kernels_row.hip); this one serves the remaining sizes.  Where those kernels do not recover the
+// register/LDS kernel (fast_kernel.hpp) or, from 65 layers on and up to 256 devices, as long as its layers fit in
+// LDS, the row kernel (kernels_row.hip); this one serves the remaining sizes.  Where those kernels do not recover the
 // winner's layers themselves (more than 64 devices), and for the
 // remaining sizes, plan_layer_kernel does, one launch per layer.
 #include "internal.hpp"
@@ -192,13 +192,13 @@ __global__ __launch_bounds__(256) void plan_layer_kernel(
     }
 }
 
-// What a table says about every candidate at once, computed by its first solve: the recurrence with no
+// What a table says about every candidate at once, computed by the first solve that wants it: the recurrence with no
 // filter (F), and with the largest latency of a plan in the place of their sum (G).  A filter only takes
 // terms away, so F(s, 1, D) bounds every candidate's layer s from below, and a candidate has a plan
 // exactly if it is at least the least G(s, 1, D).  One launch per layer, a wave per cell, its lanes over
-// the (last layer, shape) terms; F and G in two buffers each.  Bound by the launch (5 us a layer at 64
-// layers on 64 devices; 24 layers on 2 x 8 take 57 us this way and 150 in one workgroup with a thread per
-// cell, which walks all of a cell's terms alone).
+// the (last layer, shape) terms; F and G in two buffers each.  Bound by the launch and by the division per term
+// (3.3 us a layer at 24 layers on 2 x 8, 5.9 at 64 on 8 x 8, 13 at 128 on 8 x 8, 14.5 at 48 on 32 x 8; 24 layers on 2 x 8
+// take 59 us this way and 150 in one workgroup with a thread per cell, which walks all of a cell's terms alone).
 __global__ __launch_bounds__(256) void bound_layer_kernel(Problem p, const int32_t *__restrict__ table,
                                                           const int32_t *__restrict__ sizes, int s,
                                                           const int32_t *__restrict__ F_prev,
