@@ -1,7 +1,7 @@
 // Walk through every entry point of the C ABI on nine problem sizes (both recurrence kernels,
 // every flag, the B sweep, table construction, the equal-layer restriction, placement,
 // operator clustering, two error paths), meant to be built with the host code under
-// AddressSanitizer and run on a GPU machine:
+// AddressSanitizer and run on a machine with the GPU:
 //
 //   hipcc --offload-arch=gfx950 -O1 -g -std=c++17 -Xarch_host -fsanitize=address \
 //         -Xclang -target-feature -Xclang -packed-fp32-ops -Iinclude \

@@ -1,5 +1,5 @@
 """The host-side memory-checking driver (tests/asan_driver.cpp) walks through every entry point
-of the C ABI; it is run by hand on a GPU machine under AddressSanitizer.  Here it is at least
+of the C ABI; it is run by hand on a machine with the GPU, under AddressSanitizer.  Here it is at least
 compiled (host pass only, against the header) so that it cannot fall behind the ABI."""
 import os
 import shutil
