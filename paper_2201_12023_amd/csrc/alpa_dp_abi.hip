@@ -658,16 +658,23 @@ static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool one_per_cu, b
 }
 
 // Does a solve of at most `bound` candidates use the table's bounds?  They cost the first solve that does a launch
-// per stage count (3.5 us each), and save what is left out of the recurrence, on every solve.  A small problem's first
-// solve goes without: 24 layers on 2 x 8, 512 candidates, 133 us without and 160 with them (165 before there
-// were bounds), 12 on 1 x 8 97 and 108 (105); they pay at once at 64 layers (1 x 8, 512 candidates: 192 without,
-// 138 with) and for more work (40 layers on 1 x 8, all 5050 values: 185 and 163).  A table that is solved
-// again is worth them: the same sizes then take 101, 84, 95 and 133 us.  A recorded solve would compute them on every replay.
+// per stage count (3.3 to 6 us each on up to 64 devices), and save what is left out of the recurrence, on every solve.  A
+// small problem's first solve goes without (us before there were bounds, with them, without):
+//   24 layers on 2 x 8, 512 candidates  165, 160, 133      40 layers on 8 x 8, 40 candidates   512, 402, 390
+//   12 on 1 x 8, all 475                105, 108,  97      64 on 4 x 8, 130                    437, 482, 391
+//   40 on 2 x 8, 12                     184, 158, 156      48 on 1 x 2, all 2705               102, 115, 109
+// and not where they pay at once: deeper models on 3..16 devices, where a candidate stops early (64 layers on
+// 2 x 8, 12 candidates: 223, 161, 218) and on 64 (56 on 8 x 8, 12: 770, 587, 644), more than 64 devices, where a
+// layer costs more (28 on 16 x 8, 40: 759, 436, 466; 26 on 12 x 16, 23: 569 with, 687 without), and more work (40 on
+// 1 x 8, all 5050: 194, 163, 185; 52 on 3 x 8, 400: 329, 307, 321).  A table that is solved again is worth them:
+// 24 layers on 2 x 8 then take 101 us, 12 on 1 x 8 84.  A recorded solve would compute them on every replay.
 static bool wants_bounds(const alpa_dp *h, int bound, bool recorded)
 {
     if (h->have_bounds || (h->any_solve && !recorded)) return true;
-    const double work = (double)bound * h->p.K * h->p.K * h->p.S * h->p.D;   // about ten per cell-update and stage count
-    return h->p.K >= 64 || work >= 8e7;
+    const int K = h->p.K, D = h->p.D;
+    const int most_layers = D <= 2 ? 64 : D <= 16 ? 40 : D <= 48 ? 64 : D <= 64 ? 40 : 0;
+    const double work = (double)bound * K * K * h->p.S * D;    // about ten per cell-update and stage count
+    return K > most_layers || work >= (D > 16 ? 1.3e8 : 8e7);
 }
 
 // n_B > 0: sweep over the B values in d_sw_B (Eq. 4 and the selection once per value, plans

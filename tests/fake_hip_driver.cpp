@@ -390,8 +390,9 @@ static void routes()
         alpa_dp_destroy(h);
     }
     // bounds: by the first solve, or by the second; never recorded into a small problem's graph
-    struct { int K, N, M, n, by; } bounds[] = {{8, 1, 4, 0, 2}, {24, 2, 8, 1000, 2}, {40, 1, 8, 512, 2}, {64, 1, 2, 300, 1},
-                                               {64, 8, 8, 300, 1}, {48, 8, 8, 2000, 1}, {24, 8, 8, 5000, 1}};
+    struct { int K, N, M, n, by; } bounds[] = {{8, 1, 4, 0, 2}, {24, 2, 8, 1000, 2}, {40, 1, 8, 512, 2}, {64, 1, 2, 300, 2},
+                                               {64, 2, 8, 12, 1}, {56, 4, 8, 130, 2}, {40, 8, 8, 12, 2}, {56, 8, 8, 12, 1},
+                                               {26, 12, 16, 23, 1}, {6, 16, 8, 12, 1}, {64, 8, 8, 300, 1}, {48, 8, 8, 2000, 1}, {24, 8, 8, 5000, 1}};
     for (auto &c : bounds) {
         alpa_dp_t *h = create_problem(c.K, c.N, c.M);
         rt().capturing = true;
