@@ -73,9 +73,9 @@ struct alpa_dp {
     GrowingArena keys, cands;
     bool recorded = false;          // a solve has been recorded into a graph
     int32_t *d_table = nullptr, *d_sizes = nullptr, *d_recs = nullptr, *d_gmin = nullptr;
-    int32_t *d_rowrecs = nullptr, *d_rowends = nullptr;
-    bool row_ok = false;
-    int row_grid = 0;
+    int32_t *d_bandrecs = nullptr, *d_bandends = nullptr, *d_bandthr = nullptr;
+    bool band_ok = false;
+    BandShape band{};
     int32_t *d_bounds = nullptr;    // what the table says about every candidate (launch_table_bounds)
     int32_t *d_no_bounds = nullptr; // the same layout, saying nothing
     int32_t *d_bound_work = nullptr;
@@ -92,7 +92,7 @@ struct alpa_dp {
     // sweep over B (allocated on first use, for up to sw_cap values)
     int sw_cap = 0;
     int32_t *d_sw_B = nullptr, *d_sw_c = nullptr, *d_sw_s = nullptr, *d_sw_FS = nullptr;
-    int32_t *d_sw_n = nullptr;      // [2]: number of B values, ticket of the plan-recovery run
+    int32_t *d_sw_n = nullptr;      // [chunk][2]: number of B values, ticket of the plan-recovery run
     SolveState *d_sw_state = nullptr;
     int32_t *d_sw_Fall = nullptr;
     alpa_plan_t *d_sw_plans = nullptr;
@@ -242,7 +242,14 @@ static int ensure_candidate_arrays(alpa_dp *h, int n_list)
 }
 
 // one kernel recovers the layers of all winners of a sweep (else a launch per layer, winner by winner)
-static bool plan_slabs(const alpa_dp *h) { return (h->row_ok || h->fast_ok) && h->p.D <= 64; }
+static bool plan_slabs(const alpa_dp *h) { return h->band_ok || (h->fast_ok && h->p.D <= 64); }
+
+// int32 of one winner's layers, and the winners whose layers are kept at a time (up to 1 GiB of them)
+static size_t slab_ints(const alpa_dp *h) { return (size_t)(h->p.Smax + 1) * (size_t)(h->p.K + 2) * (h->p.D + 1); }
+static int sweep_chunk(const alpa_dp *h, int n_B)
+{
+    return (int)std::max<size_t>(1, std::min<size_t>(n_B, (1ull << 28) / slab_ints(h)));
+}
 
 static int alloc_sweep_arrays(alpa_dp *h, int n_B)
 {
@@ -253,12 +260,12 @@ static int alloc_sweep_arrays(alpa_dp *h, int n_B)
         take(h->d_sw_c, n);
         take(h->d_sw_s, n);
         take(h->d_sw_FS, 2 * (n + 1));
-        take(h->d_sw_n, 2);
+        take(h->d_sw_n, 2 * n);
         take(h->d_sw_state, n);
         take(h->d_sw_plans, n);
-        // one slab of layers per B value; the general kernel (also used above 64 devices) reuses d_Fall
+        // one slab of layers per B value of a chunk; the general kernel reuses d_Fall
         if (plan_slabs(h))
-            take(h->d_sw_Fall, n * ((size_t)(h->p.Smax + 1) * (size_t)(h->p.K + 2) * (h->p.D + 1)));
+            take(h->d_sw_Fall, sweep_chunk(h, n_B) * slab_ints(h));
     });
     if (rc) return rc;
     h->sw_cap = n_B;
@@ -289,6 +296,17 @@ static int queue_table_candidates(alpa_dp *h)
                                       h->pb.keys[0]));
     HIPCHK(launch_sort_dedup(h->stream, h->pb, h->n_table_keys, h->key_bits_table, inf_key,
                              h->d_distinct, h->d_ncount + 0));
+    return ALPA_DP_OK;
+}
+
+// what the table says about every candidate -> d_bounds
+static int queue_bounds(alpa_dp *h)
+{
+    if (h->band_ok)
+        HIPCHK(launch_band_bounds(h->stream, h->d_table, h->d_sizes, h->p, h->max_finite, h->d_bound_work, h->d_bandthr,
+                                  h->d_bounds));
+    else
+        HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
     return ALPA_DP_OK;
 }
 
@@ -346,15 +364,17 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     int gg = h->n_cu * 4;
     while (gg > 1 && (size_t)gg * 2 * LS * 4 > (256ull << 20)) gg /= 2;
     h->generic_grid_max = gg;
-    // A workgroup per candidate (the row kernel) where its layers fit in LDS: 129-256 devices, and from 65 layers on (up to
-    // 138 layers on 8 x 8, 86 on 16 x 8, 240 on 2 x 8).  Not up to 128 layers on 1 or 2 devices and 96 on 3 or 4, where
-    // most lanes of a wave have nothing to do and lane groups of the register/LDS kernel are faster (2048 candidates:
-    // 72 layers on 1 x 2 152 against 176 us, on 1 x 4 180 and 199, 96 on 1 x 4 229 and 248; 128 on 1 x 4 355 and 371, but 422 and 380 for
-    // 6000; 72 on 2 x 4, 6000: 306 and 257).  Beyond 128 layers the other choice is the general kernel (240 on
-    // 2 x 8, 1024 candidates: 0.9 against 50 ms).
-    const bool groups_serve = K <= 128 && (D <= 2 || (D <= 4 && K <= 96));
-    h->row_ok = (D > 128 || (K > 64 && !groups_serve)) && row_serves(K, D, S);
-    h->fast_ok = !h->row_ok && K <= 128 && D <= 128;
+    // The band kernel, a workgroup per candidate, wherever its layers fit in LDS (up to 243 layers on 8 x 8, 123 on
+    // 16 x 8, 59 on 32 x 8).  On small meshes most lanes of its waves have nothing to do, and the register/LDS kernel takes
+    // several candidates to a wave.  What the band kernel wants to know of a table (band_thresholds_kernel) costs a first
+    // solve more than it saves there, so that one stays on up to 4 devices (us, first solve and later ones: 128 layers on 1 x 4,
+    // 1000 candidates: 241 and 212 against 321 and 199) and on up to 8 with up to 64 layers (64 on 1 x 8,
+    // 2048: 252 and 215 against 298 and 190; but 72 on 2 x 4, 2048: 288 and 241 against 280 and 195).  It also takes
+    // what is left up to 128 devices, the general kernel the rest.
+    const bool groups_serve = K <= 128 && (D <= 4 || (D <= 8 && K <= 64));
+    h->band = band_shape(K, D, S, sizes.data());
+    h->band_ok = !groups_serve && h->band.nbuf != 0;
+    h->fast_ok = !h->band_ok && K <= 128 && D <= 128;
     int rc = carve(&h->arena, [&](Carver &take) {
         take(h->d_table, (size_t)K * K * K * S);
         take(h->d_sizes, S + table_bounds_ints(h->p));             // d_no_bounds behind it
@@ -366,12 +386,13 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
         take(h->d_plan_tmp, 1);
         take(h->d_best_plan, 1);
         take(h->d_Fall, (size_t)(h->p.Smax + 1) * LS);
-        take(h->d_bounds, table_bounds_ints(h->p));
-        take(h->d_bound_work, table_bounds_work(h->p));
+        take(h->d_bounds, table_bounds_ints(h->p) + (h->band_ok ? BAND_TOTALS : 0));
+        take(h->d_bound_work, h->band_ok ? band_least_ints(K, S) : table_bounds_work(h->p));
         take(h->d_scratch, (size_t)gg * 2 * LS);
-        if (h->row_ok) {
-            take(h->d_rowrecs, row_table_ints(K, h->p.Smax, S));
-            take(h->d_rowends, row_ends_ints(K, h->p.Smax, S));
+        if (h->band_ok) {
+            take(h->d_bandrecs, band_table_ints(K, h->p.Smax, S));
+            take(h->d_bandends, band_ends_ints(K, h->p.Smax, S));
+            take(h->d_bandthr, band_thresholds_ints(K, D));
         }
         if (h->fast_ok) {
             take(h->d_recs, fast_table_ints(K, S));
@@ -389,14 +410,13 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     std::vector<int32_t> up(sizes);
     up.insert(up.end(), table_bounds_ints(h->p), -1);
     up[S + h->p.Smax + 1] = 0;                     // any t_max may have a plan, of an unknown number of stages
+    up[S + h->p.Smax + 3] = DEV_INF;
     h->d_no_bounds = h->d_sizes + S;
     HIPCHK(hipMemcpyAsync(h->d_sizes, up.data(), up.size() * 4, hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipMemsetAsync(h->d_state, 0, sizeof(SolveState), h->stream));
     HIPCHK(launch_init_best_plan(h->stream, h->d_best_plan));
-    if (h->row_ok) {
-        HIPCHK(launch_repack_row(h->stream, h->d_table, K, h->p.Smax, S, h->d_rowrecs, h->d_rowends));
-        h->row_grid = h->n_cu * row_blocks_per_cu(K, D, S);
-    }
+    if (h->band_ok)
+        HIPCHK(launch_repack_band(h->stream, h->d_table, K, h->p.Smax, S, h->d_bandrecs, h->d_bandends));
     if (h->fast_ok) {
         h->KP = 16 * ((K + 15) / 16);
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
@@ -530,10 +550,12 @@ extern "C" int alpa_dp_restrict_equal_layers(alpa_dp_t *h)
     const int K = h->p.K, D = h->p.D, S = h->p.S;
     HIPCHK(launch_equal_layer_mask(h->stream, h->d_table, K, S));
     // (a graph recorded after the first solve reads the bounds and does not compute them)
-    if (h->have_bounds)
-        HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
-    if (h->row_ok)
-        HIPCHK(launch_repack_row(h->stream, h->d_table, K, h->p.Smax, S, h->d_rowrecs, h->d_rowends));
+    if (h->have_bounds) {
+        const int rcb = queue_bounds(h);
+        if (rcb) return rcb;
+    }
+    if (h->band_ok)
+        HIPCHK(launch_repack_band(h->stream, h->d_table, K, h->p.Smax, S, h->d_bandrecs, h->d_bandends));
     if (h->fast_ok) {
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
     }
@@ -640,9 +662,9 @@ static int candidate_bound(const alpa_dp *h, bool have_list, int n_tmax)
 
 // How a list of at most `bound` candidates is evaluated.  Up to `all` candidates worth searching go in one
 // round: rounds wait for each other, and a round of the register/LDS kernel takes about as long for 256
-// candidates as for 2048 (64 layers on 16 x 8, 1024 candidates: 0.71 ms in one round, 0.96 in two; 64 layers
-// on 8 x 8, 4096: 1.47 in one, 0.58 in two).  Where every candidate keeps a compute unit busy by itself (the
-// row kernel's sizes) the work counts from fewer on (128 layers, 1024 candidates: 2.28 in one, 1.53 in two).
+// candidates as for 2048 (64 layers on 1 x 8 in lane groups).  Where every candidate keeps a compute unit busy by itself
+// (the band kernel) the work counts from fewer on (us in one round and in two: 64 layers on 16 x 8, 1024
+// candidates: 2235 and 1367; 48 on 8 x 8, 2048: 716 and 337; but 24 on 2 x 8, 1500: 175 and 177).
 // Without the bounds the problem is small and one round takes everything.
 static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool one_per_cu, bool with_bounds)
 {
@@ -657,24 +679,19 @@ static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool one_per_cu, b
     return rb;
 }
 
-// Does a solve of at most `bound` candidates use the table's bounds?  They cost the first solve that does a launch
-// per stage count (3.3 to 6 us each on up to 64 devices), and save what is left out of the recurrence, on every solve.  A
-// small problem's first solve goes without (us before there were bounds, with them, without):
-//   24 layers on 2 x 8, 512 candidates  165, 160, 133      40 layers on 8 x 8, 40 candidates   512, 402, 390
-//   12 on 1 x 8, all 475                105, 108,  97      64 on 4 x 8, 130                    437, 482, 391
-//   40 on 2 x 8, 12                     184, 158, 156      48 on 1 x 2, all 2705               102, 115, 109
-// and not where they pay at once: deeper models on 3..16 devices, where a candidate stops early (64 layers on
-// 2 x 8, 12 candidates: 223, 161, 218) and on 64 (56 on 8 x 8, 12: 770, 587, 644), more than 64 devices, where a
-// layer costs more (28 on 16 x 8, 40: 759, 436, 466; 26 on 12 x 16, 23: 569 with, 687 without), and more work (40 on
-// 1 x 8, all 5050: 194, 163, 185; 52 on 3 x 8, 400: 329, 307, 321).  A table that is solved again is worth them:
-// 24 layers on 2 x 8 then take 101 us, 12 on 1 x 8 84.  A recorded solve would compute them on every replay.
+// Does a solve of at most `bound` candidates use the table's bounds?  The band kernel lives on them.  For the
+// others they cost the first solve that does a launch per stage count (3.3 to 6 us each), and save what is left out of the
+// recurrence, on every solve.  A small problem's first solve goes without (us before there were bounds, with them, without):
+//   12 layers on 1 x 8, all 475    105, 108,  97         48 on 1 x 2, all 2705    102, 115, 109
+// and not where they pay at once (40 on 1 x 8, all 5050: 194, 163, 185).  A table that is solved again is worth them:
+// 12 layers on 1 x 8 then take 84 us.  A recorded solve would compute them on every replay.
 static bool wants_bounds(const alpa_dp *h, int bound, bool recorded)
 {
-    if (h->have_bounds || (h->any_solve && !recorded)) return true;
+    if (h->have_bounds || (h->any_solve && !recorded) || h->band_ok) return true;
     const int K = h->p.K, D = h->p.D;
-    const int most_layers = D <= 2 ? 64 : D <= 16 ? 40 : D <= 48 ? 64 : D <= 64 ? 40 : 0;
+    const int most_layers = D <= 2 ? 64 : D <= 8 ? 40 : 0;
     const double work = (double)bound * K * K * h->p.S * D;    // about ten per cell-update and stage count
-    return K > most_layers || work >= (D > 16 ? 1.3e8 : 8e7);
+    return K > most_layers || work >= 8e7;
 }
 
 // n_B > 0: sweep over the B values in d_sw_B (Eq. 4 and the selection once per value, plans
@@ -707,13 +724,14 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     hipStream_t st = h->stream;
 
     const bool fast = h->fast_ok && !(flags & ALPA_DP_GENERIC);
-    const bool row = h->row_ok && !(flags & ALPA_DP_GENERIC);
+    const bool band = h->band_ok && !(flags & ALPA_DP_GENERIC);
     const bool with_bounds = wants_bounds(h, bound, recorded);
     const RefineBuffers rb = plan_rounds(h, bound, !fast, with_bounds);
     const int32_t *bounds = with_bounds ? h->d_bounds : h->d_no_bounds;
     // per-candidate results are wanted from every interval; a plan alone from few of them
     const RefineQuery rq{n_B > 0 ? h->d_sw_B : nullptr, p.B, std::max(n_B, 1), prune,
-                         (n_B > 0 || !d_out_T) ? 1 : 0, bounds, p.Smax};
+                         (n_B > 0 || !d_out_T) ? 1 : 0, bounds, p.Smax,
+                         h->band_ok ? bounds + table_bounds_ints(p) : nullptr, h->max_finite};
     HIPCHK(hipEventRecord(h->ev[0], st));
     HIPCHK(launch_init_state(st, h->d_state, h->d_chunkmin, bound / PRUNE_CHUNK + 1));
     if (have_list) {
@@ -731,7 +749,8 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                                       h->d_state, h->cands.cap));
     }
     if (with_bounds && !h->have_bounds) {
-        HIPCHK(launch_table_bounds(st, p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
+        const int rc = queue_bounds(h);
+        if (rc) return rc;
         h->have_bounds = !recorded;                // (recorded, they are there only after the graph's replay)
     }
     HIPCHK(launch_refine_begin(st, rq, h->d_cand, h->d_Fmin, h->d_Sbest, h->d_state, rb));
@@ -742,28 +761,27 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
             HIPCHK(launch_refine(st, rq, h->d_cand, h->d_Fmin, h->d_state, round - 1, last, rb));
         // candidates of a round before the last are knots: none of them may be skipped
         const int skip = last ? prune : 0;
-        if (row) {
+        if (band) {
             FastArgs fa{p, nullptr, h->d_sizes, h->d_cand, rb.list, &h->d_state->n_list, 0, INT32_MAX,
                         &h->d_state->ticket, &h->d_state->wave_relax, h->d_chunkmin, skip,
                         /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cands.cap, nullptr, nullptr,
                         nullptr, bounds};
-            HIPCHK(launch_recurrence_row(st, fa, h->d_rowrecs, h->d_rowends,
-                                         (flags & ALPA_DP_COUNT_WORK) ? FAST_MODE_COUNT : FAST_MODE_BATCH,
-                                         std::max(1, std::min(bound, h->row_grid))));
+            HIPCHK(launch_recurrence_band(st, fa, h->band, h->d_bandrecs, h->d_bandends, h->d_bandthr, h->max_finite,
+                                          (flags & ALPA_DP_COUNT_WORK) ? FAST_MODE_COUNT : FAST_MODE_BATCH,
+                                          std::max(1, std::min(bound, h->n_cu))));
         } else if (fast) {
             // One candidate per workgroup: eight waves per SIMD and two columns folded into one
             // three-operand minimum, which is faster than two candidates sharing their scalar
-            // loads and lanes at four waves per SIMD (64 layers on 8 x 8, 4096 candidates, this form for
-            // lists of every length: 0.98 against 1.78 ms of recurrence; 48 layers 0.53 and 0.92); the
-            // two-candidate form stays available through the tuning call.
+            // loads and lanes at four waves per SIMD; the two-candidate form stays available through the
+            // tuning call.
             int nc = 1;
             if (h->tune_nc) nc = h->tune_nc;
             const bool wide = p.D > 64;            // two windows of device counts, one candidate
             if (wide) nc = 2;
             // Small meshes: groups of lanes, each with a candidate of its own: as many groups as
             // the mesh allows (less work in total, and fewer, lonelier workgroups, which on these
-            // small problems matters as much; both sides at `to_groups` below).  Not for
-            // lists so short that every candidate gets a compute unit of its own anyway.
+            // small problems matters as much).  Not for lists so short that every candidate gets a compute unit
+            // of its own anyway.
             int group_dp = 0;
             if (p.D <= 32 && nc == 1 && h->tune_no_groups != 1 &&
                 (bound > h->n_cu || h->tune_no_groups >= 2)) {
@@ -780,28 +798,18 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                         &h->d_state->ticket, &h->d_state->wave_relax, h->d_chunkmin, skip,
                         /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cands.cap, nullptr, nullptr, h->d_gmin, bounds};
             fa.grouped = group_dp;
-            // Short lists go to forms with more waves per candidate (two of sixteen or four of eight waves per
-            // compute unit instead of eight of four; 256 candidates of 64 layers on 8 x 8, t_max at the 20 %
-            // quantile: 127, 163 and 262 us), on 65..128 devices, at half the occupancy, up to one candidate per compute unit (16 x 8: 257
+            // Short lists go to a form with more waves per candidate (up to 1024 threads), up to two candidates per
+            // compute unit, on 65..128 devices, at half the occupancy, up to one (64 layers on 16 x 8: 257
             // against 536 us, but 760 against 714 for 1024).  How long a list is only the device knows:
-            // each launch does nothing unless the list is in its share.
+            // each launch does nothing unless the list is in its share.  What is beyond goes to the lane groups (1024
+            // candidates, recurrence alone: 24 layers on 1 x 4 10 us, 27 in a form of eight waves a candidate; 48 on
+            // 1 x 8 11 and 30, 40 on 1 x 8 63 and 54).
             const int most = last ? bound : std::max(rb.budget, round == 1 ? rb.all : 0);
             const bool own_form = h->tune_nc || h->tune_no_groups >= 2 || h->tune_grid || h->tune_wg_per_cu;
             if (!(flags & ALPA_DP_COUNT_WORK) && !own_form) {
                 fa.n_hi = wide ? h->n_cu : 2 * h->n_cu;
                 HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_FEW, nc, std::min(bound, fa.n_hi)));
                 fa.n_lo = fa.n_hi;
-                // On meshes that use few of a wave's lanes the lane groups of the batch form take what is beyond
-                // the first form's share: up to 8 devices (1024 candidates, recurrence alone: 24 layers on 1 x 4
-                // 10 against 27 us, 48 on 1 x 8 11 and 30, 40 on 1 x 8 63 and 54), up to 16 if nothing is
-                // left out, in a first solve without bounds (24 on 2 x 8, 1500: 175 against 219 in all); else
-                // 16 devices are as fast or faster with eight waves (64 on 2 x 8: 126 against 139).
-                const bool to_groups = grouped && p.D <= (with_bounds ? 8 : 16);
-                if (!wide && !to_groups && most > fa.n_lo) {
-                    fa.n_hi = 8 * h->n_cu;
-                    HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_MID, nc, std::min(bound, 4 * h->n_cu)));
-                    fa.n_lo = fa.n_hi;
-                }
                 fa.n_hi = INT32_MAX;
             }
             const int form = (flags & ALPA_DP_COUNT_WORK) ? FAST_MODE_COUNT : FAST_MODE_BATCH;
@@ -819,18 +827,21 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         HIPCHK(launch_sweep_epilogue(st, h->d_sw_B, n_B, &h->d_state->n_cand, h->d_cand, h->d_Fmin,
                                      h->d_Sbest, h->d_sw_state, prune_sel, h->d_sw_c, h->d_sw_s));
         if (plan_slabs(h) && !(flags & ALPA_DP_GENERIC)) {
-            const size_t slab = (size_t)(p.Smax + 1) * (size_t)(p.K + 2) * (p.D + 1);
-            FastArgs fa{p, h->d_recs, h->d_sizes, h->d_sw_c, nullptr, h->d_sw_n, 0, INT32_MAX,
-                        h->d_sw_n + 1,
-                        &h->d_state->wave_relax, nullptr, 0, 0, h->d_sw_FS,
-                        h->d_sw_FS + (n_B + 1), n_B, h->d_sw_Fall, h->d_sw_s, h->d_gmin, nullptr};
-            if (row)
-                HIPCHK(launch_recurrence_row(st, fa, h->d_rowrecs, h->d_rowends, FAST_MODE_PLAN,
-                                             std::min(n_B, h->n_cu)));
-            else
-                HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_PLAN, 1, std::min(n_B, h->n_cu)));
-            HIPCHK(launch_plan_walk_many(st, p, h->d_table, h->d_sizes, h->d_sw_state,
-                                         h->d_sw_Fall, slab, h->d_sw_plans, n_B));
+            const int chunk = sweep_chunk(h, n_B);
+            for (int b = 0, x = 0; b < n_B; b += chunk, ++x) {
+                const int n = std::min(chunk, n_B - b);
+                FastArgs fa{p, h->d_recs, h->d_sizes, h->d_sw_c + b, nullptr, h->d_sw_n + 2 * x, 0, INT32_MAX,
+                            h->d_sw_n + 2 * x + 1,
+                            &h->d_state->wave_relax, nullptr, 0, 0, h->d_sw_FS,
+                            h->d_sw_FS + (n_B + 1), n_B, h->d_sw_Fall, h->d_sw_s + b, h->d_gmin, bounds};
+                if (band)
+                    HIPCHK(launch_recurrence_band(st, fa, h->band, h->d_bandrecs, h->d_bandends, h->d_bandthr, h->max_finite,
+                                                  FAST_MODE_PLAN, std::min(n, h->n_cu)));
+                else
+                    HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_PLAN, 1, std::min(n, h->n_cu)));
+                HIPCHK(launch_plan_walk_many(st, p, h->d_table, h->d_sizes, h->d_sw_state + b,
+                                             h->d_sw_Fall, slab_ints(h), h->d_sw_plans + b, n));
+            }
         } else {
             for (int b = 0; b < n_B; ++b) {        // one slab of layers, reused in stream order
                 SolveState *sb = h->d_sw_state + b;
@@ -850,12 +861,12 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         HIPCHK(launch_scatter_T(st, h->d_T, have_list ? h->d_rank : nullptr,
                                 have_list ? n_tmax : bound, h->d_state, d_out_T));
     // every layer of the winning candidate (does nothing if there is none), then the walk
-    if (row && p.D <= 64) {
+    if (band) {
         FastArgs fa{p, nullptr, h->d_sizes, &h->d_state->best_c, nullptr,
                     &h->d_state->plan_n, 0, INT32_MAX, &h->d_state->plan_ticket, &h->d_state->wave_relax,
                     nullptr, 0, 0, h->d_tmpFS, h->d_tmpFS + 2, 1, h->d_Fall, &h->d_state->best_s,
-                    nullptr, nullptr};
-        HIPCHK(launch_recurrence_row(st, fa, h->d_rowrecs, h->d_rowends, FAST_MODE_PLAN, 1));
+                    nullptr, bounds};
+        HIPCHK(launch_recurrence_band(st, fa, h->band, h->d_bandrecs, h->d_bandends, h->d_bandthr, h->max_finite, FAST_MODE_PLAN, 1));
     } else if (h->fast_ok && p.D <= 64 && !(flags & ALPA_DP_GENERIC)) {
         FastArgs fa{p, h->d_recs, h->d_sizes, &h->d_state->best_c, nullptr,
                     &h->d_state->plan_n, 0, INT32_MAX, &h->d_state->plan_ticket, &h->d_state->wave_relax,
@@ -964,8 +975,12 @@ extern "C" int alpa_dp_solve_sweep(alpa_dp_t *h, const int32_t *tmax, int n_tmax
         rc = alloc_sweep_arrays(h, n_B);
         if (rc) return rc;
     }
-    const int32_t head[2] = {n_B, 0};
-    HIPCHK(hipMemcpyAsync(h->d_sw_n, head, sizeof(head), hipMemcpyHostToDevice, h->stream));
+    std::vector<int32_t> head;                     // of every chunk
+    for (int b = 0, chunk = sweep_chunk(h, n_B); b < n_B; b += chunk) {
+        head.push_back(std::min(chunk, n_B - b));
+        head.push_back(0);
+    }
+    HIPCHK(hipMemcpyAsync(h->d_sw_n, head.data(), head.size() * 4, hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipMemcpyAsync(h->d_sw_B, B_values, (size_t)n_B * 4, hipMemcpyHostToDevice, h->stream));
     rc = solve_dev_impl(h, d_tmax, n_tmax, flags, nullptr, nullptr, key_bits, n_B);
     if (rc) {

@@ -1,6 +1,7 @@
 // Register/LDS recurrence kernel (Eq. 3) for K <= 128 layers on N*M <= 64 devices, and on up
-// to 128 devices in a two-window form (see WIDE below).  A header: the instances for up to 64
-// and for 65-128 layers are compiled in two translation units (kernels_fast.hip,
+// to 128 devices in a two-window form (see WIDE below).  It runs on meshes of up to 8 devices (several
+// candidates to a wave, see GROUPED) and where the band kernel's lists do not fit in LDS.  A header: the
+// instances for up to 64 and for 65-128 layers are compiled in two translation units (kernels_fast.hip,
 // kernels_fast_deep.hip).
 //
 // Mapping.  One workgroup evaluates one t_max candidate at a time (persistent workgroups
@@ -990,9 +991,6 @@ static hipError_t launch_nwk(hipStream_t st, const FastArgs &a, int mode, int nc
     case FAST_MODE_FEW:
         if (a.p.D > WAVE) return launch_one<NWK, plan_wi(NWK), 2, false, false, true>(st, a, grid);
         return launch_one<NWK, plan_wi(NWK), 1, false, false>(st, a, grid);
-    case FAST_MODE_MID:                            // (up to 64 devices: see the caller)
-        if (a.p.D > WAVE) return hipErrorInvalidValue;
-        return launch_one<NWK, 2, 1, false, false>(st, a, grid);
     case FAST_MODE_COUNT:
         if (a.p.D > WAVE) return launch_one<NWK, 1, 2, false, true, true>(st, a, grid);
         if (a.grouped) return launch_one<NWK, 1, 1, false, true, false, true>(st, a, grid);

@@ -157,6 +157,18 @@ hipError_t launch_distinct_by_bitmap(hipStream_t st, const int32_t *table, int K
                                      uint32_t *out_n_unique);
 size_t distinct_bitmap_words(int32_t max_value);
 
+// What is known of a table for certain values of t_max (kernels_band.hip): the thresholds, from no filter at all
+// and the largest latency down, sixteen an octave.
+constexpr int BAND_THRESHOLDS = 120;
+__host__ __device__ __forceinline__ int32_t band_threshold(int32_t max_finite, int j)
+{
+    if (j == 0) return DEV_INF - 1;
+    return (int32_t)(((int64_t)max_finite * (32 - ((j - 1) & 15)) >> 5) >> ((j - 1) >> 4)) + 1;
+}
+// behind the bounds (launch_band_bounds): a lower bound on F for each threshold and the least largest stage; then the sum and the
+// largest latency of a plan for each
+constexpr int BAND_TOTALS = 3 * BAND_THRESHOLDS + 1;
+
 // Rounds of evaluation (kernels_refine.hip)
 constexpr int REFINE_MAX_KNOTS = 4096;   // knots a refinement step takes in (LDS)
 struct RefineBuffers {
@@ -175,6 +187,8 @@ struct RefineQuery {
     int plan_only;
     const int32_t *bounds;   // launch_table_bounds
     int Smax;
+    const int32_t *thr;      // BAND_TOTALS numbers of launch_band_bounds, or null
+    int32_t max_finite;
 };
 // `bound`: the host's upper bound of the number of candidates
 hipError_t launch_pick_candidates(hipStream_t st, const int32_t *distinct,
@@ -244,22 +258,32 @@ inline int fast_lane_group_width(int D)
     while (dp < D) dp <<= 1;
     return dp;
 }
-enum { FAST_MODE_BATCH = 0, FAST_MODE_COUNT = 1, FAST_MODE_PLAN = 2, FAST_MODE_FEW = 3, FAST_MODE_MID = 4 };
+enum { FAST_MODE_BATCH = 0, FAST_MODE_COUNT = 1, FAST_MODE_PLAN = 2, FAST_MODE_FEW = 3 };
 hipError_t launch_recurrence_fast(hipStream_t st, const FastArgs &a, int mode, int nc, int grid);
 int fast_kernel_blocks_per_cu(int K, int nc);
 // the instances for 65-128 layers (kernels_fast_deep.hip)
 hipError_t launch_recurrence_fast_deep(hipStream_t st, const FastArgs &a, int mode, int nc, int grid);
 int fast_kernel_blocks_per_cu_deep(int K, int nc);
 
-// a workgroup per candidate, t_intra by row broadcast (kernels_row.hip)
-bool row_serves(int K, int D, int S);
-int row_blocks_per_cu(int K, int D, int S);
-size_t row_table_ints(int K, int Smax, int S);
-size_t row_ends_ints(int K, int Smax, int S);
-hipError_t launch_repack_row(hipStream_t st, const int32_t *table, int K, int Smax, int S,
-                             int32_t *recs, int32_t *ends);
-hipError_t launch_recurrence_row(hipStream_t st, const FastArgs &f, const int32_t *recs,
-                                 const int32_t *ends, int mode, int grid);
+// a workgroup per candidate, t_intra in bands by row broadcast (kernels_band.hip)
+struct BandShape {
+    int nbuf;                // F buffers in LDS; 0: the problem does not fit
+    int W;                   // windows of 64 device counts
+    int ahead, cap;          // layers whose work lists are made at a time; units a layer can have
+    int lens_at, bounds_at, lds_ints;   // in int32: where a candidate's stage lengths and its windows are kept; all of the LDS
+};
+BandShape band_shape(int K, int D, int S, const int32_t *sizes);
+size_t band_table_ints(int K, int Smax, int S);
+size_t band_ends_ints(int K, int Smax, int S);
+hipError_t launch_repack_band(hipStream_t st, const int32_t *table, int K, int Smax, int S,
+                              int32_t *recs, int32_t *ends);
+// what the table says about candidates: launch_table_bounds' place for these sizes
+size_t band_least_ints(int K, int S);
+size_t band_thresholds_ints(int K, int D);
+hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const int32_t *sizes, const Problem &p, int32_t max_finite,
+                              int32_t *work, int32_t *thr, int32_t *bounds);
+hipError_t launch_recurrence_band(hipStream_t st, const FastArgs &f, const BandShape &b, const int32_t *recs,
+                                  const int32_t *ends, const int32_t *thr, int32_t max_finite, int mode, int grid);
 
 // plan recovery of one candidate, a launch per layer (general sizes)
 hipError_t launch_plan_layers(hipStream_t st, const Problem &p, const int32_t *table,
@@ -267,7 +291,7 @@ hipError_t launch_plan_layers(hipStream_t st, const Problem &p, const int32_t *t
                               const int32_t *s_top_p, int32_t *F_all);
 // bounds of the table (kernels_generic.hip): [0..Smax] the least unfiltered F of more than s stages, then
 // the smallest t_max with a plan and the stages of one; work: table_bounds_work() int32
-inline size_t table_bounds_ints(const Problem &p) { return (size_t)p.Smax + 3; }
+inline size_t table_bounds_ints(const Problem &p) { return (size_t)p.Smax + 4; }
 inline size_t table_bounds_work(const Problem &p)
 {
     return 4 * (size_t)(p.K + 2) * (p.D + 1) + 2 * ((size_t)p.Smax + 1);

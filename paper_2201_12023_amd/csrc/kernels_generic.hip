@@ -2,11 +2,9 @@
 // selection, and plan recovery.  The recurrence here is the straightforward one: one
 // workgroup per t_max candidate, threads over the cells (k, d) of a layer s, every cell
 // scanning its (last layer, shape) terms in tie-break order; F layers live in global
-// memory.  Problems of up to 128 layers on up to 128 devices normally run through the
-// register/LDS kernel (fast_kernel.hpp) or, from 65 layers on and up to 256 devices, as long as its layers fit in
-// LDS, the row kernel (kernels_row.hip); this one serves the remaining sizes.  Where those kernels do not recover the
-// winner's layers themselves (more than 64 devices), and for the
-// remaining sizes, plan_layer_kernel does, one launch per layer.
+// memory.  Most problems run through the band kernel (kernels_band.hip) or, on small meshes, the
+// register/LDS kernel (fast_kernel.hpp), which also recover the winner's layers; this one serves
+// what their LDS does not hold, and plan_layer_kernel recovers the layers there, one launch per layer.
 #include "internal.hpp"
 
 namespace alpa {
@@ -263,6 +261,7 @@ __global__ __launch_bounds__(WAVE) void table_bounds_kernel(Problem p, const int
     }
     bounds[p.Smax + 1] = g;
     bounds[p.Smax + 2] = sg;
+    bounds[p.Smax + 3] = DEV_INF;                  // (from which t_max on F hardly changes: not known)
 }
 
 // work: 4 layers of (K + 2)(D + 1) int32, then 2 (Smax + 1) more
@@ -458,18 +457,21 @@ __global__ __launch_bounds__(WAVE) void plan_walk_kernel(Problem p, const int32_
     bool ok = true;
     while (s > 0) {
         const int32_t want = F_all[(size_t)s * LS + k * (D + 1) + d];
-        const int n_terms = (K - k + 1) * S;
+        // the last stage ends with layer K and takes all devices; in front of s - 1 others a stage leaves a
+        // layer and a device to each (nothing else is read: the layers may hold only what can be reached)
+        const int i_first = s == 1 ? K : k;
+        const int n_terms = (K - s + 1 - i_first + 1) * S;
         int found = -1;
         for (int x0 = 0; x0 < n_terms && found < 0; x0 += WAVE) {
             const int x = x0 + lane;
             bool hit = false;
             if (x < n_terms) {
-                const int i = k + x / S, q = x % S;
+                const int i = i_first + x / S, q = x % S;
                 const int a = sizes[q];
-                if (a <= d) {
+                if (s == 1 ? a == d : a < d) {
                     const int32_t t = table[(((size_t)(s - 1) * K + (k - 1)) * K + (i - 1)) * S + q];
                     if (t != INF_I32 && t <= c) {
-                        const int32_t f = F_all[(size_t)(s - 1) * LS + (i + 1) * (D + 1) + (d - a)];
+                        const int32_t f = s == 1 ? 0 : F_all[(size_t)(s - 1) * LS + (i + 1) * (D + 1) + (d - a)];
                         hit = f < DEV_INF && t + f == want;
                     }
                 }
@@ -478,7 +480,7 @@ __global__ __launch_bounds__(WAVE) void plan_walk_kernel(Problem p, const int32_
             if (hm) found = x0 + __ffsll((unsigned long long)hm) - 1;
         }
         if (found < 0 || want >= DEV_INF) { ok = false; break; }   // cannot happen for a consistent F
-        const int i = k + found / S, q = found % S;
+        const int i = i_first + found / S, q = found % S;
         sh.first_layer[stage] = k - 1;                 // all lanes, same value
         sh.shape_idx[stage] = q;
         ++stage;

@@ -47,6 +47,27 @@ __global__ void set_candidates_kernel(const uint32_t *__restrict__ n_unique_p, S
     state->n_distinct = (int)*n_unique_p;
 }
 
+// first index of the ascending candidates with a value of at least v (n: none)
+__device__ __forceinline__ int first_at_least(const int32_t *__restrict__ cand, int n, int32_t v)
+{
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (cand[mid] >= v) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+}
+
+// first index in [lo, hi) with B * value >= U (hi: none)
+__device__ __forceinline__ int first_product(const int32_t *__restrict__ cand, int lo, int hi, int64_t B, int64_t U)
+{
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (B * (int64_t)cand[mid] >= U) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+}
+
 // The range of candidates worth searching, and the first round's knots in it (one block).
 //   * Below the smallest t_max with a plan (bounds) every candidate is infeasible.
 //   * The first candidate j0 at or above it admits a plan of s stages, each at most that t_max, so
@@ -64,7 +85,8 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
                                                                   int32_t *__restrict__ knots,
                                                                   int32_t *__restrict__ list)
 {
-    __shared__ int sh_end;
+    __shared__ int sh_end, sh_first;
+    __shared__ int32_t sh_sum[BAND_THRESHOLDS], sh_x[BAND_THRESHOLDS], sh_c[BAND_THRESHOLDS], sh_lo[BAND_THRESHOLDS];
     const int C = state->n_cand;
     const int64_t t_feas = rq.bounds[rq.Smax + 1], stages = rq.bounds[rq.Smax + 2];
     int lo = 0, hi = C;                                // first index with a negative value
@@ -78,10 +100,74 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
         const int mid = (lo + hi) >> 1;
         if (cand[mid] >= t_feas) hi = mid; else lo = mid + 1;
     }
-    const int j0 = t_feas >= DEV_INF ? n : lo;
-    if (threadIdx.x == 0) sh_end = (rq.prune || rq.plan_only) ? min(n, j0 + 1) : n;
+    int j0 = t_feas >= DEV_INF ? n : lo;
+    if (threadIdx.x == 0) {
+        sh_end = (rq.prune || rq.plan_only) ? min(n, j0 + 1) : n;
+        sh_first = rq.plan_only && rq.thr ? n : j0;
+    }
     __syncthreads();
-    if ((rq.prune || rq.plan_only) && j0 < n) {
+    if ((rq.prune || rq.plan_only) && rq.thr && j0 < n) {
+        // Plans are known (of sum s and largest stage m: T* of the first candidate c that is not below m is at
+        // most s + (B - 1) c), and for every candidate a lower bound on F.
+        for (int t = threadIdx.x; t < BAND_THRESHOLDS; t += RF_THREADS) {
+            const int32_t sum = rq.thr[BAND_THRESHOLDS + 1 + 2 * t], largest = rq.thr[BAND_THRESHOLDS + 2 + 2 * t];
+            const int32_t above = band_threshold(rq.max_finite, t + 1 < BAND_THRESHOLDS ? t + 1 : t);
+            const int x = first_at_least(cand, n, largest);
+            sh_sum[t] = x < n ? sum : DEV_INF;
+            sh_x[t] = min(x, n - 1);
+            sh_c[t] = cand[min(x, n - 1)];
+            // candidates that take threshold t: from sh_lo[t] on, up to the threshold
+            sh_lo[t] = max(j0, t + 1 < BAND_THRESHOLDS ? first_at_least(cand, n, above + 1) : 0);
+        }
+        __syncthreads();
+        const int lane = threadIdx.x & (WAVE - 1);
+        for (int b = threadIdx.x >> 6; b < rq.n_B; b += RF_WAVES) {        // a wave per B value
+            const int64_t B = rq.B_vals ? rq.B_vals[b] : rq.B;
+            int64_t U = INF_I64;
+            for (int t = lane; t < BAND_THRESHOLDS; t += WAVE)
+                if (sh_sum[t] < DEV_INF) U = min64(U, sh_sum[t] + (B - 1) * (int64_t)sh_c[t]);
+            U = wave_min_i64(U);
+            int at = n;                                // the lowest candidate known to reach U
+            for (int t = lane; t < BAND_THRESHOLDS; t += WAVE)
+                if (sh_sum[t] < DEV_INF && sh_sum[t] + (B - 1) * (int64_t)sh_c[t] == U) at = min(at, sh_x[t]);
+            at = wave_min_i32(at);
+            // with the early exit nothing behind the first B t_max >= U is looked at; where only the plan counts, nothing that
+            // cannot get below U (nor reach it before `at`): then nothing else can set the early exit off either, as B t_max < U
+            // for every candidate in front of `at`
+            int first = n, end = j0 + 1;
+            if (U == INF_I64) {
+                first = j0;
+                end = n;
+            } else {
+                const int stop = rq.prune ? max(at + 1, first_product(cand, at + 1, n, B, U)) : n;
+                end = stop;
+                if (rq.plan_only) {
+                    end = min(at + 1, n);
+                    for (int t = lane; t < BAND_THRESHOLDS; t += WAVE) {
+                        const int lo_t = sh_lo[t], hi_t = min(stop, t == 0 ? n : sh_lo[t - 1]);
+                        const int64_t least = rq.thr[t];
+                        if (lo_t >= hi_t || least >= DEV_INF || least + (B - 1) * (int64_t)cand[lo_t] > U) continue;
+                        first = min(first, lo_t);
+                        int x = lo_t, z = hi_t;        // first index that cannot get to U
+                        while (x < z) {
+                            const int mid = (x + z) >> 1;
+                            if (least + (B - 1) * (int64_t)cand[mid] > U) z = mid; else x = mid + 1;
+                        }
+                        end = max(end, x);
+                    }
+                    first = min(first, at);
+                }
+            }
+            first = wave_min_i32(first);
+            end = -wave_min_i32(-end);
+            if (lane == 0) {
+                atomicMin(&sh_first, first);
+                atomicMax(&sh_end, end);
+            }
+        }
+        __syncthreads();
+        j0 = max(j0, min(sh_first, sh_end - 1));
+    } else if ((rq.prune || rq.plan_only) && j0 < n) {
         for (int b = threadIdx.x; b < rq.n_B; b += RF_THREADS) {
             const int64_t B = rq.B_vals ? rq.B_vals[b] : rq.B;
             const int64_t U = stages < 0 ? INF_I64 : stages * t_feas + (B - 1) * (int64_t)cand[j0];
@@ -98,9 +184,17 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
         __syncthreads();
     }
     const int end = sh_end;
-    const int m = end - j0 <= all ? end - j0 : first_round;
+    // knots: evenly up to where the table says that F hardly changes any more, and the last candidate
+    lo = j0; hi = max(j0, end - 1);
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (cand[mid] >= rq.bounds[rq.Smax + 3]) hi = mid; else lo = mid + 1;
+    }
+    const int span = lo + 1 - j0, rest = lo + 1 < end ? 1 : 0;
+    const bool whole = end - j0 <= all;
+    const int m = whole ? end - j0 : min(first_round, span + rest);
     for (int j = threadIdx.x; j < m; j += RF_THREADS) {
-        const int k = j0 + even_knot(j, m, end - j0);
+        const int k = whole ? j0 + j : j == m - 1 && rest ? end - 1 : j0 + even_knot(j, m - rest, span);
         list[j] = k;
         if (j < REFINE_MAX_KNOTS) knots[j] = k;
     }

@@ -363,22 +363,23 @@ static void routes()
         {24, 1, 4, 1500, " recurrence_fast_kernel<2,1,1,false,false,false,true> ", "recurrence_fast_kernel<2,2,1,false"},
         {40, 2, 4, 2048, " recurrence_fast_kernel<3,1,1,false,false,false,true> ", "recurrence_fast_kernel<3,2,1,false"},
         {64, 1, 2, 600, " recurrence_fast_kernel<4,1,1,false,false,false,true> ", "recurrence_fast_kernel<4,2,1,false"},
-        {24, 3, 4, 1500, " recurrence_fast_kernel<2,2,1,false,false,false,false> ", "recurrence_row"},
-        {64, 8, 8, 1500, " recurrence_fast_kernel<4,2,1,false,false,false,false> ", "recurrence_row"},
         {64, 1, 2, 512, " recurrence_fast_kernel<4,4,1,false,false,false,false> ", "false,true> "},
-        // a workgroup per candidate: from 65 layers on, but not on the smallest meshes, and where the layers fit in LDS
-        {72, 1, 2, 2048, " recurrence_fast_kernel<5,1,1,false,false,false,true> ", "recurrence_row"},
-        {128, 1, 2, 2048, " recurrence_fast_kernel<8,1,1,false,false,false,true> ", "recurrence_row"},
-        {96, 1, 4, 2048, " recurrence_fast_kernel<6,1,1,false,false,false,true> ", "recurrence_row"},
-        {97, 3, 1, 2048, " recurrence_row_kernel<81,false,false> ", "recurrence_fast"},
-        {65, 5, 1, 2048, " recurrence_row_kernel<81,false,false> ", "recurrence_fast"},
-        {72, 2, 4, 2048, " recurrence_row_kernel<81,false,false> ", "recurrence_fast"},
-        {129, 1, 2, 300, " recurrence_row_kernel<81,false,false> ", "recurrence_generic"},
-        {138, 8, 8, 300, " recurrence_row_kernel<129,false,false> ", "recurrence_generic"},
-        {139, 8, 8, 300, " recurrence_generic_kernel ", "recurrence_row"},
-        {100, 64, 1, 300, " recurrence_fast_kernel<7,2,1,false,false,false,false> ", "recurrence_row"},
-        {86, 16, 8, 300, " recurrence_row_kernel<193,false,false> ", "recurrence_fast"},
-        {48, 32, 8, 300, " recurrence_row_kernel<321,false,false> ", "recurrence_generic"},
+        {72, 1, 2, 2048, " recurrence_fast_kernel<5,1,1,false,false,false,true> ", "recurrence_band"},
+        {128, 1, 2, 2048, " recurrence_fast_kernel<8,1,1,false,false,false,true> ", "recurrence_band"},
+        {96, 1, 4, 2048, " recurrence_fast_kernel<6,1,1,false,false,false,true> ", "recurrence_band"},
+        {97, 3, 1, 2048, " recurrence_fast_kernel<7,1,1,false,false,false,true> ", "recurrence_band"},
+        // a workgroup per candidate: on more than 4 devices from 65 layers on, on more than 8, and where the layers fit in LDS
+        {24, 3, 4, 1500, " recurrence_band_kernel<64,4,false,false> ", "recurrence_fast"},
+        {64, 8, 8, 1500, " recurrence_band_kernel<64,4,false,false> ", "recurrence_fast"},
+        {65, 5, 1, 2048, " recurrence_band_kernel<64,8,false,false> ", "recurrence_fast"},
+        {72, 2, 4, 2048, " recurrence_band_kernel<64,8,false,false> ", "recurrence_fast"},
+        {129, 1, 2, 300, " recurrence_band_kernel<64,0,false,false> ", "recurrence_generic"},
+        {139, 8, 8, 300, " recurrence_band_kernel<64,0,false,false> ", "recurrence_generic"},
+        {100, 64, 1, 300, " recurrence_band_kernel<64,8,false,false> ", "recurrence_fast"},
+        {86, 16, 8, 300, " recurrence_band_kernel<128,0,false,false> ", "recurrence_fast"},
+        {59, 32, 8, 300, " recurrence_band_kernel<256,0,false,false> ", "recurrence_generic"},
+        {60, 32, 8, 300, " recurrence_generic_kernel ", "recurrence_band"},
+        {124, 16, 8, 300, " recurrence_fast_kernel<8,1,2,false,false,true,false> ", "recurrence_band"},
     };
     for (auto &c : cases) {
         alpa_dp_t *h = create_problem(c.K, c.N, c.M);
@@ -390,20 +391,24 @@ static void routes()
         alpa_dp_destroy(h);
     }
     // bounds: by the first solve, or by the second; never recorded into a small problem's graph
-    struct { int K, N, M, n, by; } bounds[] = {{8, 1, 4, 0, 2}, {24, 2, 8, 1000, 2}, {40, 1, 8, 512, 2}, {64, 1, 2, 300, 2},
-                                               {64, 2, 8, 12, 1}, {56, 4, 8, 130, 2}, {40, 8, 8, 12, 2}, {56, 8, 8, 12, 1},
-                                               {26, 12, 16, 23, 1}, {6, 16, 8, 12, 1}, {64, 8, 8, 300, 1}, {48, 8, 8, 2000, 1}, {24, 8, 8, 5000, 1}};
+    struct { int K, N, M, n, by; } bounds[] = {{8, 1, 4, 0, 2}, {24, 2, 8, 1000, 1}, {40, 1, 8, 512, 2}, {64, 1, 2, 300, 2},
+                                               {64, 2, 8, 12, 1}, {56, 4, 8, 130, 1}, {40, 8, 8, 12, 1}, {56, 8, 8, 12, 1},
+                                               {26, 12, 16, 23, 1}, {6, 16, 8, 12, 1}, {64, 8, 8, 300, 1}, {48, 8, 8, 2000, 1}, {24, 8, 8, 5000, 1},
+                                               {40, 1, 8, 2048, 1}, {50, 1, 8, 12, 1}};
+    auto bounds_in = [](const std::string &k) {
+        return k.find("bound_layer") != std::string::npos || k.find("band_thresholds") != std::string::npos;
+    };
     for (auto &c : bounds) {
         alpa_dp_t *h = create_problem(c.K, c.N, c.M);
         rt().capturing = true;
-        const bool recorded = kernels_of(h, c.n).find("bound_layer") != std::string::npos;
+        const bool recorded = bounds_in(kernels_of(h, c.n));
         rt().capturing = false;
         CHECK(recorded == (c.by == 1), "%d layers on %dx%d, %d: bounds in the graph: %d", c.K, c.N, c.M, c.n, recorded);
         alpa_dp_destroy(h);
         h = create_problem(c.K, c.N, c.M);
         for (int restricted = 0; restricted < 2; ++restricted) {
             for (int solve = 1; solve <= 3; ++solve) {
-                const bool found = kernels_of(h, c.n).find("bound_layer") != std::string::npos;
+                const bool found = bounds_in(kernels_of(h, c.n));
                 CHECK(found == (solve == c.by && !restricted), "%d layers on %dx%d, %d: solve %d, bounds %d", c.K, c.N, c.M,
                       c.n, solve, found);
             }
@@ -411,7 +416,7 @@ static void routes()
             CHECK(alpa_dp_restrict_equal_layers(h) == 0, "restriction");
             bool again = false;                    // (they are there: the restriction computes them anew)
             for (size_t x = from; x < rt().launches.size(); ++x)
-                again |= rt().launches[x].kernel.find("bound_layer") != std::string::npos;
+                again |= bounds_in(rt().launches[x].kernel);
             CHECK(again, "%d layers on %dx%d: bounds of the old table", c.K, c.N, c.M);
         }
         alpa_dp_destroy(h);
