@@ -217,7 +217,9 @@ static int grow(alpa_dp *h, GrowingArena &g, int need, ArenaLayout layout)
 
 static bool distinct_by_bitmap(const alpa_dp *h)
 {
-    return h->max_finite >= 0 && h->max_finite < DISTINCT_BITMAP_MAX && !h->tune_sort;
+    // (a bitmap of more words than there are keys costs more than the sort's smallest passes)
+    return h->max_finite >= 0 && h->max_finite < DISTINCT_BITMAP_MAX && !h->tune_sort &&
+           (h->max_finite < DISTINCT_LOCAL_MAX || h->max_finite / 32 < h->n_table_keys);
 }
 
 // From the start there is room for lists of ordinary length (both groups together stay below 2 MiB, from where
@@ -279,13 +281,14 @@ static int bits_for(uint32_t v)
     return b;
 }
 
-// distinct finite table values -> d_distinct, count -> d_ncount[0]
-static int queue_table_candidates(alpa_dp *h)
+// distinct finite table values -> d_distinct, count -> d_ncount[0]; `cleared`: the bitmap (in the second key buffer)
+static int queue_table_candidates(alpa_dp *h, bool cleared = false)
 {
     const int rc = ensure_keys(h, 0);
     if (rc) return rc;
     // small values: one bit per value instead of a sort (the second key buffer is the work area)
     if (distinct_by_bitmap(h)) {
+        if (!cleared) HIPCHK(launch_bitmap_clear(h->stream, (uint32_t *)h->pb.keys[1], h->max_finite));
         HIPCHK(launch_distinct_by_bitmap(h->stream, h->d_table, h->p.K, h->p.S, h->max_finite,
                                          (uint32_t *)h->pb.keys[1], h->d_distinct,
                                          h->d_ncount + 0));
@@ -733,8 +736,12 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                          (n_B > 0 || !d_out_T) ? 1 : 0, bounds, p.Smax,
                          h->band_ok ? bounds + table_bounds_ints(p) : nullptr, h->max_finite};
     HIPCHK(hipEventRecord(h->ev[0], st));
-    HIPCHK(launch_init_state(st, h->d_state, h->d_chunkmin, bound / PRUNE_CHUNK + 1));
-    if (have_list) {
+    const bool bitmap = !have_list && distinct_by_bitmap(h);
+    HIPCHK(launch_init_state(st, h->d_state, h->d_chunkmin, bound / PRUNE_CHUNK + 1, (uint32_t *)h->pb.keys[1],
+                             bitmap ? h->max_finite / 32 + 1 : 0));
+    if (have_list && n_tmax <= LIST_SORT_MAX) {
+        HIPCHK(launch_list_sort(st, d_tmax, n_tmax, h->d_cand, h->d_ncount + 1, h->d_state, d_out_T ? h->d_rank : nullptr));
+    } else if (have_list) {
         HIPCHK(hipMemcpyAsync(h->pb.keys[0], d_tmax, (size_t)n_tmax * 4, hipMemcpyDeviceToDevice,
                               st));
         HIPCHK(launch_sort_dedup(st, h->pb, n_tmax, key_bits, /*drop_key=*/-1, h->d_cand,
@@ -743,7 +750,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         if (d_out_T)
             HIPCHK(launch_rank_lookup(st, d_tmax, n_tmax, h->d_cand, h->d_ncount + 1, h->d_rank));
     } else {
-        int rc = queue_table_candidates(h);
+        int rc = queue_table_candidates(h, bitmap);
         if (rc) return rc;
         HIPCHK(launch_pick_candidates(st, h->d_distinct, h->d_ncount + 0, n_tmax, bound, h->d_cand,
                                       h->d_state, h->cands.cap));

@@ -150,8 +150,14 @@ hipError_t launch_gather_table_values(hipStream_t st, const int32_t *table, int 
                                       int32_t inf_key, int32_t *out_keys);
 hipError_t launch_sort_dedup(hipStream_t st, PrepBuffers &pb, int n, int key_bits,
                              int32_t drop_key, int32_t *out_unique, uint32_t *out_n_unique);
-// values below this many bits' worth go through the presence bitmap instead of the sort
-constexpr int32_t DISTINCT_BITMAP_MAX = 1 << 19;
+// Values up to these go through a presence bitmap instead of the sort: one in LDS (64 KiB), merged into the global
+// one, or the global one alone.
+constexpr int32_t DISTINCT_LOCAL_MAX = 1 << 19, DISTINCT_BITMAP_MAX = 1 << 25;
+hipError_t launch_bitmap_clear(hipStream_t st, uint32_t *work, int32_t max_value);
+// lists up to this long are sorted by one block
+constexpr int LIST_SORT_MAX = 8192;
+hipError_t launch_list_sort(hipStream_t st, const int32_t *tmax, int n, int32_t *out_unique, uint32_t *out_n_unique,
+                            SolveState *state, int32_t *rank_of_orig);
 hipError_t launch_distinct_by_bitmap(hipStream_t st, const int32_t *table, int K, int S,
                                      int32_t max_value, uint32_t *work, int32_t *out_unique,
                                      uint32_t *out_n_unique);
@@ -314,7 +320,7 @@ hipError_t launch_sweep_epilogue(hipStream_t st, const int32_t *B_vals, int n_B,
 hipError_t launch_plan_walk_many(hipStream_t st, const Problem &p, const int32_t *table,
                                  const int32_t *sizes, SolveState *states, const int32_t *F_all,
                                  size_t slab, void *plans, int n);
-hipError_t launch_init_state(hipStream_t st, SolveState *state, int64_t *chunk_min, int n_chunks);
+hipError_t launch_init_state(hipStream_t st, SolveState *state, int64_t *chunk_min, int n_chunks, uint32_t *clear, int words);
 hipError_t launch_init_best_plan(hipStream_t st, void *best_plan);
 
 // operator clustering (Eq. 6).  Work memory, see kernels_cluster.hip: band [width][K], rows G and V of one

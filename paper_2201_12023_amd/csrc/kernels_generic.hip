@@ -518,7 +518,8 @@ __global__ void copy_plan_kernel(const PlanDev *src, PlanDev *dst)
         ((int32_t *)dst)[x] = ((const int32_t *)src)[x];
 }
 
-__global__ void init_state_kernel(SolveState *state, int64_t *chunk_min, int n_chunks)
+// (and `words` of a bitmap to clear)
+__global__ void init_state_kernel(SolveState *state, int64_t *chunk_min, int n_chunks, uint32_t *clear, int words)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t == 0) {
@@ -533,6 +534,7 @@ __global__ void init_state_kernel(SolveState *state, int64_t *chunk_min, int n_c
         state->plan_ticket = 0;
     }
     for (int x = t; x < n_chunks; x += gridDim.x * blockDim.x) chunk_min[x] = INF_I64;
+    for (int x = t; x < words; x += gridDim.x * blockDim.x) clear[x] = 0;
 }
 
 __global__ void init_best_plan_kernel(PlanDev *best)
@@ -625,12 +627,10 @@ hipError_t launch_plan_walk_many(hipStream_t st, const Problem &p, const int32_t
     return hipGetLastError();
 }
 
-hipError_t launch_init_state(hipStream_t st, SolveState *state, int64_t *chunk_min, int n_chunks)
+hipError_t launch_init_state(hipStream_t st, SolveState *state, int64_t *chunk_min, int n_chunks, uint32_t *clear, int words)
 {
-    int grid = (n_chunks + 255) / 256;
-    if (grid < 1) grid = 1;
-    if (grid > 256) grid = 256;
-    hipLaunchKernelGGL(init_state_kernel, dim3(grid), dim3(256), 0, st, state, chunk_min, n_chunks);
+    const int grid = std::max(1, std::min((std::max(n_chunks, words / 4) + 255) / 256, 256));
+    hipLaunchKernelGGL(init_state_kernel, dim3(grid), dim3(256), 0, st, state, chunk_min, n_chunks, clear, words);
     return hipGetLastError();
 }
 

@@ -225,9 +225,8 @@ __global__ __launch_bounds__(1024) void dedup_write_kernel(const int32_t *__rest
 
 // ---------------------------------------------------------------- distinct values by bitmap
 //
-// SortedAndFilter of Alg. 1 for tables whose finite values are small integers (below
-// DISTINCT_BITMAP_MAX, so that the bitmap fits a workgroup's 64 KiB of LDS): instead of sorting every entry, each finite entry sets one bit of a
-// presence bitmap and the set bits are listed in order; the result is the same ascending list
+// SortedAndFilter of Alg. 1 for tables whose finite values are small integers: instead of sorting every entry, each finite
+// entry sets one bit of a presence bitmap and the set bits are listed in order; the result is the same ascending list
 // of distinct values.
 
 __global__ void bitmap_clear_kernel(uint32_t *__restrict__ bm, int words)
@@ -236,26 +235,40 @@ __global__ void bitmap_clear_kernel(uint32_t *__restrict__ bm, int words)
         bm[x] = 0u;
 }
 
-// Every block marks its share of the table in a bitmap of its own in LDS (most entries repeat
-// values the block has already seen) and then merges the words it touched into the global one.
+// A thread takes a stage and shape for eight numbers of stages behind it, with all loads in flight, and leaves out what
+// repeats the one before: of a model whose stages run at their fastest wherever they fit, most entries do.  LOCAL: a block
+// marks a bitmap of its own in LDS and then merges the words it touched into the global one (up to 64 KiB); else the
+// global one is marked directly.  Bound by reading the table (128 layers on 8 x 8, 126 MB: 80 us with
+// an entry at a time).
+template <bool LOCAL>
 __global__ __launch_bounds__(1024) void bitmap_mark_kernel(const int32_t *__restrict__ table, int K,
                                                            int S, int words,
                                                            uint32_t *__restrict__ bm)
 {
-    extern __shared__ uint32_t lbm[];             // [words]
-    for (int x = threadIdx.x; x < words; x += blockDim.x) lbm[x] = 0u;
-    __syncthreads();
-    const long long total = (long long)K * K * K * S;
-    for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
-         e += (long long)gridDim.x * blockDim.x) {
-        const long long r = e / S;
-        const int i = (int)(r % K), k = (int)((r / K) % K);
-        if (i < k) continue;
-        const int32_t t = table[e];
-        if (t == INF_I32) continue;
-        const uint32_t bit = 1u << (t & 31);
-        if (!(lbm[t >> 5] & bit)) atomicOr(&lbm[t >> 5], bit);   // a stale 0 only costs the atomic
+    extern __shared__ uint32_t lbm[];             // [words] if LOCAL
+    if (LOCAL) {
+        for (int x = threadIdx.x; x < words; x += blockDim.x) lbm[x] = 0u;
+        __syncthreads();
     }
+    const int n = K * K * S, total = n * ((K + 7) / 8);    // (256 layers, 64 shapes: 1.3e8)
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < total; x += gridDim.x * blockDim.x) {
+        const int ch = x / n, e = x - ch * n, r = e / S, k = r / K;
+        if (r - k * K < k) continue;               // (last layer in front of the first)
+        const int32_t *t = table + (size_t)ch * 8 * n + e;
+        int32_t v[8], prev = INF_I32;
+#pragma unroll
+        for (int y = 0; y < 8; ++y) v[y] = ch * 8 + y < K ? t[(size_t)y * n] : INF_I32;
+#pragma unroll
+        for (int y = 0; y < 8; ++y) {
+            if (v[y] != INF_I32 && v[y] != prev) {
+                const uint32_t bit = 1u << (v[y] & 31);
+                if (!LOCAL) atomicOr(&bm[v[y] >> 5], bit);
+                else if (!(lbm[v[y] >> 5] & bit)) atomicOr(&lbm[v[y] >> 5], bit);   // a stale 0 only costs the atomic
+            }
+            prev = v[y];
+        }
+    }
+    if (!LOCAL) return;
     __syncthreads();
     for (int x = threadIdx.x; x < words; x += blockDim.x) {
         const uint32_t v = lbm[x];
@@ -281,29 +294,107 @@ __global__ __launch_bounds__(1024) void bitmap_count_kernel(const uint32_t *__re
     }
 }
 
+// Lists the bits of words [1024 b, 1024 b + 1024) behind those of the words in front, which the block counts itself: from the
+// blocks' counts, or from the words where they are few (up to 16 blocks: one launch instead of three).
 __global__ __launch_bounds__(1024) void bitmap_write_kernel(const uint32_t *__restrict__ bm,
                                                             int words,
-                                                            const uint32_t *__restrict__ block_off,
-                                                            int32_t *__restrict__ unique)
+                                                            const uint32_t *__restrict__ block_cnt, int counted,
+                                                            int32_t *__restrict__ unique,
+                                                            uint32_t *__restrict__ n_unique)
 {
-    __shared__ uint32_t part[1024];
-    const int t = threadIdx.x;
+    __shared__ uint32_t wsum[16], wfront[16];
+    const int t = threadIdx.x, lane = t & 63;
     const int x = blockIdx.x * 1024 + t;
-    uint32_t w = x < words ? bm[x] : 0u;
+    uint32_t w = x < words ? bm[x] : 0u, front = 0;
+    if (counted)
+        for (int b = t; b < (int)blockIdx.x; b += 1024) front += block_cnt[b];
+    else
+        for (int y = t; y < (int)blockIdx.x * 1024; y += 1024) front += __popc(bm[y]);
     const uint32_t c = __popc(w);
-    part[t] = c;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        uint32_t o = (t >= off) ? part[t - off] : 0u;
-        __syncthreads();
-        part[t] += o;
-        __syncthreads();
+    uint32_t upto = c;                             // bits up to this lane's word
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(upto, off, 64);
+        if (lane >= off) upto += o;
     }
-    uint32_t pos = block_off[blockIdx.x] + part[t] - c;
+    for (int off = 32; off >= 1; off >>= 1) front += __shfl_xor(front, off, 64);
+    if (lane == 63) { wsum[t >> 6] = upto; wfront[t >> 6] = front; }
+    __syncthreads();
+    uint32_t pos = upto - c;
+    for (int y = 0; y < 16; ++y) pos += wfront[y] + (y < (t >> 6) ? wsum[y] : 0u);
+    if (blockIdx.x == gridDim.x - 1 && t == 1023) *n_unique = pos + c;
     while (w) {                                   // set bits, lowest first
         const int b = __ffs(w) - 1;
         unique[pos++] = (x << 5) + b;
         w &= w - 1;
+    }
+}
+
+// ---------------------------------------------------------------- short lists
+//
+// A caller's list of up to LIST_SORT_MAX values in one block: sorted in LDS (bitonic), the first of each run kept, and every
+// value's place among them (rank_of_orig, if wanted).  1500 values: 16 launches of the radix sort take
+// 55 us, and it three more for the places.
+__global__ __launch_bounds__(1024) void list_sort_kernel(const int32_t *__restrict__ tmax, int n, int N2,
+                                                         int32_t *__restrict__ unique, uint32_t *__restrict__ n_unique,
+                                                         SolveState *state, int32_t *__restrict__ rank_of_orig)
+{
+    extern __shared__ uint32_t keys[];             // [N2] keys, [N2] their places among the distinct ones
+    __shared__ uint32_t wsum[16];
+    const int t = threadIdx.x, lane = t & 63;
+    uint32_t *const place = keys + N2;
+    for (int x = t; x < N2; x += 1024) keys[x] = x < n ? (uint32_t)tmax[x] : ~0u;
+    __syncthreads();
+    for (int size = 2; size <= N2; size <<= 1)
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            for (int x = t; x < N2 / 2; x += 1024) {
+                const int lo = 2 * x - (x & (stride - 1)), hi = lo + stride;
+                const uint32_t a = keys[lo], b = keys[hi];
+                if ((a > b) == ((lo & size) == 0)) { keys[lo] = b; keys[hi] = a; }
+            }
+            // pairs up to 64 apart stay in the 128 keys of one wave, also in the next step
+            const int next = stride > 1 ? stride >> 1 : size;
+            if (max(stride, next) > 64) __syncthreads();
+            else {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+    __syncthreads();
+    const int per = (N2 + 1023) / 1024, from = t * per;    // (N2 is a power of two: 1, 2, 4 or 8)
+    uint32_t c = 0;
+    for (int x = from; x < min(from + per, n); ++x) c += x == 0 || keys[x - 1] != keys[x];
+    uint32_t upto = c;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(upto, off, 64);
+        if (lane >= off) upto += o;
+    }
+    if (lane == 63) wsum[t >> 6] = upto;
+    __syncthreads();
+    uint32_t pos = upto - c, all = 0;
+    for (int y = 0; y < 16; ++y) {
+        if (y < (t >> 6)) pos += wsum[y];
+        all += wsum[y];
+    }
+    for (int x = from; x < min(from + per, n); ++x) {
+        const bool head = x == 0 || keys[x - 1] != keys[x];
+        if (head) unique[pos++] = (int32_t)keys[x];
+        place[x] = pos - 1;
+    }
+    if (t == 0) {
+        *n_unique = all;
+        state->n_cand = (int)all;
+        state->n_distinct = (int)all;
+    }
+    if (!rank_of_orig) return;
+    __syncthreads();
+    for (int j = t; j < n; j += 1024) {
+        const uint32_t v = (uint32_t)tmax[j];
+        int lo = 0, hi = n - 1;                    // the first key that is not below (there is one)
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (keys[mid] < v) lo = mid + 1; else hi = mid;
+        }
+        rank_of_orig[j] = (int32_t)place[lo];
     }
 }
 
@@ -367,9 +458,32 @@ hipError_t launch_sort_dedup(hipStream_t st, PrepBuffers &pb, int n, int key_bit
     return hipGetLastError();
 }
 
+// A list of n <= LIST_SORT_MAX values on the device: its ascending distinct values, their number (also to the state), and
+// each value's place among them (rank_of_orig may be null)
+hipError_t launch_list_sort(hipStream_t st, const int32_t *tmax, int n, int32_t *out_unique, uint32_t *out_n_unique,
+                            SolveState *state, int32_t *rank_of_orig)
+{
+    int N2 = 2;
+    while (N2 < n) N2 <<= 1;
+    const size_t lds = (size_t)2 * N2 * 4;
+    if (lds > 32 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void *)list_sort_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(list_sort_kernel, dim3(1), dim3(1024), lds, st, tmax, n, N2, out_unique, out_n_unique, state, rank_of_orig);
+    return hipGetLastError();
+}
+
+hipError_t launch_bitmap_clear(hipStream_t st, uint32_t *work, int32_t max_value)
+{
+    const int words = max_value / 32 + 1;
+    hipLaunchKernelGGL(bitmap_clear_kernel, dim3(std::min((words + 1023) / 1024, 256)), dim3(1024), 0, st, work, words);
+    return hipGetLastError();
+}
+
 // Ascending distinct finite values of the table's entries with last >= first layer, all known
-// to be <= max_value < DISTINCT_BITMAP_MAX, to out_unique and their count to *out_n_unique.
-// `work` holds the bitmap and the block counts: distinct_bitmap_words(max_value) uint32.
+// to be <= max_value, to out_unique and their count to *out_n_unique.
+// `work` holds the bitmap, which is clear, and the block counts: distinct_bitmap_words(max_value) uint32.
 hipError_t launch_distinct_by_bitmap(hipStream_t st, const int32_t *table, int K, int S,
                                      int32_t max_value, uint32_t *work, int32_t *out_unique,
                                      uint32_t *out_n_unique)
@@ -377,15 +491,17 @@ hipError_t launch_distinct_by_bitmap(hipStream_t st, const int32_t *table, int K
     const int words = max_value / 32 + 1;
     const int nb = (words + 1023) / 1024;
     uint32_t *bm = work, *block_cnt = work + words;
-    hipLaunchKernelGGL(bitmap_clear_kernel, dim3(std::min(nb, 256)), dim3(1024), 0, st, bm, words);
-    const long long total = (long long)K * K * K * S;
-    const int grid = (int)std::min<long long>((total + 8191) / 8192, 256);
-    hipLaunchKernelGGL(bitmap_mark_kernel, dim3(grid), dim3(1024), (size_t)words * 4, st, table, K,
-                       S, words, bm);
-    hipLaunchKernelGGL(bitmap_count_kernel, dim3(nb), dim3(1024), 0, st, bm, words, block_cnt);
-    hipLaunchKernelGGL(scan_u32_kernel, dim3(1), dim3(1024), 0, st, block_cnt, nb, out_n_unique);
-    hipLaunchKernelGGL(bitmap_write_kernel, dim3(nb), dim3(1024), 0, st, bm, words, block_cnt,
-                       out_unique);
+    const int total = K * K * S * ((K + 7) / 8);
+    if (max_value < DISTINCT_LOCAL_MAX)
+        hipLaunchKernelGGL(bitmap_mark_kernel<true>, dim3(std::min((total + 1023) / 1024, 256)), dim3(1024), (size_t)words * 4,
+                           st, table, K, S, words, bm);
+    else
+        hipLaunchKernelGGL(bitmap_mark_kernel<false>, dim3(std::min((total + 1023) / 1024, 2048)), dim3(1024), 0, st, table, K,
+                           S, words, bm);
+    const bool few = nb <= 16;
+    if (!few) hipLaunchKernelGGL(bitmap_count_kernel, dim3(nb), dim3(1024), 0, st, bm, words, block_cnt);
+    hipLaunchKernelGGL(bitmap_write_kernel, dim3(nb), dim3(1024), 0, st, bm, words, block_cnt, few ? 0 : 1, out_unique,
+                       out_n_unique);
     return hipGetLastError();
 }
 
