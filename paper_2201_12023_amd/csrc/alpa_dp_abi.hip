@@ -760,7 +760,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         if (rc) return rc;
         h->have_bounds = !recorded;                // (recorded, they are there only after the graph's replay)
     }
-    HIPCHK(launch_refine_begin(st, rq, h->d_cand, h->d_Fmin, h->d_Sbest, h->d_state, rb));
+    HIPCHK(launch_refine_begin(st, rq, h->d_cand, h->d_state, rb));
     HIPCHK(hipEventRecord(h->ev[1], st));
     for (int round = 1; bound > 0 && round <= rb.rounds; ++round) {
         const bool last = round == rb.rounds;
@@ -831,7 +831,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     }
     HIPCHK(hipEventRecord(h->ev[2], st));
     if (n_B > 0) {
-        HIPCHK(launch_sweep_epilogue(st, h->d_sw_B, n_B, &h->d_state->n_cand, h->d_cand, h->d_Fmin,
+        HIPCHK(launch_sweep_epilogue(st, h->d_sw_B, n_B, h->d_state, h->d_cand, h->d_Fmin,
                                      h->d_Sbest, h->d_sw_state, prune_sel, h->d_sw_c, h->d_sw_s));
         if (plan_slabs(h) && !(flags & ALPA_DP_GENERIC)) {
             const int chunk = sweep_chunk(h, n_B);
@@ -863,10 +863,9 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         h->timed = true;
         return ALPA_DP_OK;
     }
-    HIPCHK(launch_epilogue(st, p, h->d_cand, h->d_Fmin, h->d_Sbest, h->d_state, prune_sel, h->d_T));
-    if (d_out_T && bound > 0)
-        HIPCHK(launch_scatter_T(st, h->d_T, have_list ? h->d_rank : nullptr,
-                                have_list ? n_tmax : bound, h->d_state, d_out_T));
+    HIPCHK(launch_epilogue(st, p, h->d_cand, h->d_Fmin, h->d_Sbest, h->d_state, prune_sel, d_out_T != nullptr,
+                           have_list || !d_out_T ? h->d_T : d_out_T));
+    if (d_out_T && have_list && bound > 0) HIPCHK(launch_scatter_T(st, h->d_T, h->d_rank, n_tmax, d_out_T));
     // every layer of the winning candidate (does nothing if there is none), then the walk
     if (band) {
         FastArgs fa{p, nullptr, h->d_sizes, &h->d_state->best_c, nullptr,

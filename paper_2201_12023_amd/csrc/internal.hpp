@@ -202,8 +202,8 @@ hipError_t launch_pick_candidates(hipStream_t st, const int32_t *distinct,
                                   int32_t *cand, SolveState *state, int cap);
 hipError_t launch_set_candidates(hipStream_t st, const uint32_t *n_unique, SolveState *state);
 // first round: the range worth searching and its knots
-hipError_t launch_refine_begin(hipStream_t st, const RefineQuery &rq, const int32_t *cand, int32_t *Fmin,
-                               int32_t *Sbest, SolveState *state, const RefineBuffers &rb);
+hipError_t launch_refine_begin(hipStream_t st, const RefineQuery &rq, const int32_t *cand, SolveState *state,
+                               const RefineBuffers &rb);
 // the step behind round `round` (1-based)
 hipError_t launch_refine(hipStream_t st, const RefineQuery &rq, const int32_t *cand, int32_t *Fmin,
                          SolveState *state, int round, int last, const RefineBuffers &rb);
@@ -306,15 +306,15 @@ hipError_t launch_table_bounds(hipStream_t st, const Problem &p, const int32_t *
                                const int32_t *sizes, int32_t *work, int32_t *bounds);
 hipError_t launch_epilogue(hipStream_t st, const Problem &p, const int32_t *cand,
                            const int32_t *Fmin, const int32_t *Sbest, SolveState *state, int prune,
-                           int64_t *T);
+                           bool want_T, int64_t *T);
 hipError_t launch_scatter_T(hipStream_t st, const int64_t *T, const int32_t *rank_of_orig,
-                            int n_orig, const SolveState *state, int64_t *out_T);
+                            int n_orig, int64_t *out_T);
 hipError_t launch_plan_walk(hipStream_t st, const Problem &p, const int32_t *table,
                             const int32_t *sizes, SolveState *state, const int32_t *F_all,
                             void *plan_tmp, void *best_plan, void *plan_out);
 // sweep over B: one block per B value
 hipError_t launch_sweep_epilogue(hipStream_t st, const int32_t *B_vals, int n_B,
-                                 const int32_t *n_cand_p, const int32_t *cand,
+                                 const SolveState *solve, const int32_t *cand,
                                  const int32_t *Fmin, const int32_t *Sbest, SolveState *states,
                                  int prune, int32_t *win_c, int32_t *win_s);
 hipError_t launch_plan_walk_many(hipStream_t st, const Problem &p, const int32_t *table,

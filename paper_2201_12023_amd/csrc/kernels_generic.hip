@@ -284,40 +284,43 @@ hipError_t launch_table_bounds(hipStream_t st, const Problem &p, const int32_t *
 // is the prefix [0, p) where p is the first index with B * c_p >= min_{j < p} T(c_j), as
 // in the sequential loop of Alg. 1; the winner is the lowest T, lowest index on ties
 // (strict "<" of Alg. 1 while ascending).
-// `T` may be null (no per-candidate output).  One block of SEL_THREADS threads, tiles of
-// SEL_THREADS candidates: prefix minimum inside each wave, the waves' totals through LDS, the
-// first index that fires and the arg-min through LDS atomics.
+// `T` may be null (no per-candidate output).  Only [first, range) is read: nothing else has a T (or any that matters,
+// see refine_begin_kernel), and where the loop ends behind it is found by bisection.  Tiles of four candidates a thread:
+// prefix minimum inside each thread and wave, the waves' totals through LDS, the
+// first index that fires and the arg-min through LDS atomics.  4096 candidates: 16 us a candidate a thread, in four tiles of
+// six barriers; 20 000 of which few are searched, all looked at: 43.
 constexpr int SEL_THREADS = 1024;
 constexpr int SEL_WAVES = SEL_THREADS / WAVE;
+constexpr int SEL_EACH = 4;
 
-__device__ __forceinline__ void eq4_select(int B, int n, const int32_t *__restrict__ cand,
+__device__ __forceinline__ void eq4_select(int B, int n, int j_first, int range, const int32_t *__restrict__ cand,
                                            const int32_t *__restrict__ Fmin,
                                            const int32_t *__restrict__ Sbest, SolveState *state,
                                            int prune, int64_t *__restrict__ T)
 {
     __shared__ int64_t sh_wave_min[SEL_WAVES];
-    __shared__ int sh_first_fire;
+    __shared__ int sh_first_fire, sh_index;
     __shared__ unsigned long long sh_best;             // lowest processed T of the tile
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid >> 6;
     int64_t carry = INF_I64;          // min of T over all earlier tiles
     int n_proc = n;
     int64_t bestT = INF_I64;
     int bestj = -1;
-    bool stopped = false;             // block-uniform
-    for (int j0 = 0; j0 < n; j0 += SEL_THREADS) {
-        const int j = j0 + tid;
-        if (stopped) {                // everything after the break is not evaluated
-            if (T && j < n) T[j] = INF_I64;
-            continue;
+    range = min(range, n);
+    int j0 = j_first;
+    for (; j0 < range && n_proc == n; j0 += SEL_THREADS * SEL_EACH) {      // (uniform)
+        const int j = j0 + SEL_EACH * tid;
+        int64_t t[SEL_EACH], bc[SEL_EACH], own = INF_I64;
+#pragma unroll
+        for (int u = 0; u < SEL_EACH; ++u) {
+            const int x = min(j + u, range - 1);
+            const int32_t f = Fmin[x], c = cand[x];
+            t[u] = j + u < range && f < DEV_INF ? (int64_t)f + (int64_t)(B - 1) * (int64_t)c : INF_I64;
+            bc[u] = (int64_t)B * (int64_t)c;
+            own = min64(own, t[u]);
         }
-        int64_t t = INF_I64, bc = 0;
-        if (j < n) {
-            const int32_t f = Fmin[j], c = cand[j];
-            if (f < DEV_INF) t = (int64_t)f + (int64_t)(B - 1) * (int64_t)c;
-            bc = (int64_t)B * (int64_t)c;
-        }
-        const int64_t incl = wave_prefix_min_i64(t, lane);
-        if (tid == 0) { sh_first_fire = INT32_MAX; sh_best = ~0ull; }
+        const int64_t incl = wave_prefix_min_i64(own, lane);
+        if (tid == 0) { sh_first_fire = sh_index = INT32_MAX; sh_best = ~0ull; }
         if (lane == WAVE - 1) sh_wave_min[w] = incl;
         __syncthreads();
         // exclusive prefix minimum: earlier tiles, earlier waves of this tile, earlier lanes
@@ -331,34 +334,52 @@ __device__ __forceinline__ void eq4_select(int B, int n, const int32_t *__restri
             if (x < w) excl = min64(excl, m);
             tile_min = min64(tile_min, m);
         }
-        const bool fire = prune && j < n && excl != INF_I64 && bc >= excl;
-        if (fire) atomicMin(&sh_first_fire, j);
-        __syncthreads();
+        if (prune) {
+            int fire = INT32_MAX;
+#pragma unroll
+            for (int u = 0; u < SEL_EACH; ++u) {
+                if (j + u < range && excl != INF_I64 && bc[u] >= excl) fire = min(fire, j + u);
+                excl = min64(excl, t[u]);
+            }
+            if (fire != INT32_MAX) atomicMin(&sh_first_fire, fire);
+            __syncthreads();
+        }
         const int first = sh_first_fire;               // INT32_MAX if nobody fired
-        const bool processed = j < n && j < first;
-        if (T && j < n) T[j] = processed ? t : INF_I64;
         // arg-min of the processed part of the tile in two steps: the lowest value (T >= 0, so
         // it orders as unsigned), then the lowest index that has it
-        const int64_t tt = processed ? t : INF_I64;
-        const int64_t wm = wave_min_i64(tt);
+        int64_t tm = INF_I64;
+        int jm = 0;
+#pragma unroll
+        for (int u = 0; u < SEL_EACH; ++u) {
+            const int64_t v = j + u < first ? t[u] : INF_I64;
+            if (T && j + u < range) T[j + u] = v;
+            if (v < tm) { tm = v; jm = j + u; }
+        }
+        const int64_t wm = wave_min_i64(tm);
         if (lane == 0 && wm != INF_I64) atomicMin(&sh_best, (unsigned long long)wm);
         __syncthreads();
         const int64_t m = (int64_t)sh_best;            // ~0ull (= -1) if nothing finite
-        __syncthreads();
-        if (sh_best != ~0ull && m < bestT) {           // block-uniform
-            if (tid == 0) sh_first_fire = INT32_MAX;   // reused: lowest index with T == m
-            __syncthreads();
-            if (tt == m) atomicMin(&sh_first_fire, j);
+        if (m >= 0 && m < bestT) {                     // block-uniform
+            if (tm == m) atomicMin(&sh_index, jm);
             __syncthreads();
             bestT = m;
-            bestj = sh_first_fire;
+            bestj = sh_index;
         }
-        __syncthreads();
-        if (first != INT32_MAX) {
-            n_proc = first;
-            stopped = true;
-        }
+        if (first != INT32_MAX) n_proc = first;
         carry = min64(carry, tile_min);
+        __syncthreads();
+    }
+    if (prune && n_proc == n && carry != INF_I64) {
+        int lo = max(range, j_first), hi = n;          // the first index behind the range that fires
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if ((int64_t)B * (int64_t)cand[mid] >= carry) hi = mid; else lo = mid + 1;
+        }
+        n_proc = lo;
+    }
+    if (T) {
+        for (int j = tid; j < min(j_first, n); j += SEL_THREADS) T[j] = INF_I64;
+        for (int j = max(j_first, min(j0, range)) + tid; j < n; j += SEL_THREADS) T[j] = INF_I64;
     }
     if (tid == 0) {
         state->n_processed = n_proc;
@@ -374,24 +395,24 @@ __device__ __forceinline__ void eq4_select(int B, int n, const int32_t *__restri
 __global__ __launch_bounds__(SEL_THREADS) void epilogue_kernel(Problem p, const int32_t *__restrict__ cand,
                                                         const int32_t *__restrict__ Fmin,
                                                         const int32_t *__restrict__ Sbest,
-                                                        SolveState *state, int prune,
+                                                        SolveState *state, int prune, int want_T,
                                                         int64_t *__restrict__ T)
 {
-    eq4_select(p.B, state->n_cand, cand, Fmin, Sbest, state, prune, T);
+    eq4_select(p.B, state->n_cand, state->n_first, state->n_range, cand, Fmin, Sbest, state, prune, want_T ? T : nullptr);
 }
 
 // Sweep over the number of microbatches: F of Eq. 3 does not depend on B, so one wave per
 // B value applies Eq. 4 and the selection to the same Fmin / Sbest.  states[b] receives the
 // winner for B_vals[b]; win_c / win_s are the compact copies the plan-recovery run reads.
 __global__ __launch_bounds__(SEL_THREADS) void sweep_epilogue_kernel(
-    const int32_t *__restrict__ B_vals, const int32_t *__restrict__ n_cand_p,
+    const int32_t *__restrict__ B_vals, const SolveState *__restrict__ solve,
     const int32_t *__restrict__ cand, const int32_t *__restrict__ Fmin,
     const int32_t *__restrict__ Sbest, SolveState *states, int prune, int32_t *__restrict__ win_c,
     int32_t *__restrict__ win_s)
 {
     const int b = blockIdx.x;
     SolveState *st = states + b;
-    eq4_select(B_vals[b], *n_cand_p, cand, Fmin, Sbest, st, prune, nullptr);
+    eq4_select(B_vals[b], solve->n_cand, solve->n_first, solve->n_range, cand, Fmin, Sbest, st, prune, nullptr);
     __syncthreads();                                   // lane 0's stores, then every lane's reads
     win_c[b] = st->best_c;                             // all lanes, same value
     win_s[b] = st->best_s;
@@ -405,15 +426,6 @@ __global__ void scatter_T_kernel(const int64_t *__restrict__ T, const int32_t *_
         const int r = rank[j];
         out_T[j] = r >= 0 ? T[r] : INF_I64;
     }
-}
-
-__global__ void copy_T_kernel(const int64_t *__restrict__ T, const SolveState *state, int cap,
-                              int64_t *__restrict__ out_T)
-{
-    int n = state->n_cand;
-    if (n > cap) n = cap;
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += gridDim.x * blockDim.x)
-        out_T[j] = T[j];
 }
 
 // ---------------------------------------------------------------- plan recovery
@@ -434,7 +446,7 @@ __global__ __launch_bounds__(WAVE) void plan_walk_kernel(Problem p, const int32_
                                                          const SolveState *state,
                                                          const int32_t *__restrict__ F_all,
                                                          size_t slab, PlanDev *plan,
-                                                         PlanDev *best_plan)
+                                                         PlanDev *best_plan, PlanDev *plan_out)
 {
     // block b recovers the plan of states[b] from the layers at F_all + b * slab
     __shared__ PlanDev sh;
@@ -507,15 +519,9 @@ __global__ __launch_bounds__(WAVE) void plan_walk_kernel(Problem p, const int32_
     for (int x = lane; x < n32; x += WAVE) {
         const int32_t v = ((const int32_t *)&sh)[x];
         ((int32_t *)plan)[x] = v;
+        if (plan_out) ((int32_t *)plan_out)[x] = v;
         if (better) ((int32_t *)best_plan)[x] = v;
     }
-}
-
-__global__ void copy_plan_kernel(const PlanDev *src, PlanDev *dst)
-{
-    const int n32 = (int)(sizeof(PlanDev) / 4);
-    for (int x = threadIdx.x; x < n32; x += blockDim.x)
-        ((int32_t *)dst)[x] = ((const int32_t *)src)[x];
 }
 
 // (and `words` of a bitmap to clear)
@@ -573,26 +579,21 @@ hipError_t launch_plan_layers(hipStream_t st, const Problem &p, const int32_t *t
     return hipGetLastError();
 }
 
+// T: per-candidate results, if wanted
 hipError_t launch_epilogue(hipStream_t st, const Problem &p, const int32_t *cand,
                            const int32_t *Fmin, const int32_t *Sbest, SolveState *state, int prune,
-                           int64_t *T)
+                           bool want_T, int64_t *T)
 {
     hipLaunchKernelGGL(epilogue_kernel, dim3(1), dim3(SEL_THREADS), 0, st, p, cand, Fmin, Sbest,
-                       state, prune, T);
+                       state, prune, want_T ? 1 : 0, T);
     return hipGetLastError();
 }
 
 hipError_t launch_scatter_T(hipStream_t st, const int64_t *T, const int32_t *rank_of_orig,
-                            int n_orig, const SolveState *state, int64_t *out_T)
+                            int n_orig, int64_t *out_T)
 {
-    int grid = (n_orig + 255) / 256;
-    if (grid > 1024) grid = 1024;
-    if (grid < 1) grid = 1;
-    if (rank_of_orig)
-        hipLaunchKernelGGL(scatter_T_kernel, dim3(grid), dim3(256), 0, st, T, rank_of_orig, n_orig,
-                           out_T);
-    else
-        hipLaunchKernelGGL(copy_T_kernel, dim3(grid), dim3(256), 0, st, T, state, n_orig, out_T);
+    const int grid = std::max(1, std::min((n_orig + 255) / 256, 1024));
+    hipLaunchKernelGGL(scatter_T_kernel, dim3(grid), dim3(256), 0, st, T, rank_of_orig, n_orig, out_T);
     return hipGetLastError();
 }
 
@@ -601,20 +602,17 @@ hipError_t launch_plan_walk(hipStream_t st, const Problem &p, const int32_t *tab
                             void *plan_tmp, void *best_plan, void *plan_out)
 {
     hipLaunchKernelGGL(plan_walk_kernel, dim3(1), dim3(WAVE), 0, st, p, table, sizes, state, F_all,
-                       (size_t)0, (PlanDev *)plan_tmp, (PlanDev *)best_plan);
-    if (plan_out && plan_out != plan_tmp)
-        hipLaunchKernelGGL(copy_plan_kernel, dim3(1), dim3(256), 0, st, (const PlanDev *)plan_tmp,
-                           (PlanDev *)plan_out);
+                       (size_t)0, (PlanDev *)plan_tmp, (PlanDev *)best_plan, (PlanDev *)(plan_out ? plan_out : plan_tmp));
     return hipGetLastError();
 }
 
 hipError_t launch_sweep_epilogue(hipStream_t st, const int32_t *B_vals, int n_B,
-                                 const int32_t *n_cand_p, const int32_t *cand,
+                                 const SolveState *solve, const int32_t *cand,
                                  const int32_t *Fmin, const int32_t *Sbest, SolveState *states,
                                  int prune, int32_t *win_c, int32_t *win_s)
 {
     hipLaunchKernelGGL(sweep_epilogue_kernel, dim3(n_B), dim3(SEL_THREADS), 0, st, B_vals,
-                       n_cand_p, cand, Fmin, Sbest, states, prune, win_c, win_s);
+                       solve, cand, Fmin, Sbest, states, prune, win_c, win_s);
     return hipGetLastError();
 }
 
@@ -623,7 +621,7 @@ hipError_t launch_plan_walk_many(hipStream_t st, const Problem &p, const int32_t
                                  size_t slab, void *plans, int n)
 {
     hipLaunchKernelGGL(plan_walk_kernel, dim3(n), dim3(WAVE), 0, st, p, table, sizes, states, F_all,
-                       slab, (PlanDev *)plans, (PlanDev *)nullptr);
+                       slab, (PlanDev *)plans, (PlanDev *)nullptr, (PlanDev *)nullptr);
     return hipGetLastError();
 }
 

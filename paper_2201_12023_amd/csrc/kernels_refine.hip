@@ -79,8 +79,6 @@ __device__ __forceinline__ int first_product(const int32_t *__restrict__ cand, i
 // no entry passes them.
 __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq, int all, int first_round,
                                                                   const int32_t *__restrict__ cand,
-                                                                  int32_t *__restrict__ Fmin,
-                                                                  int32_t *__restrict__ Sbest,
                                                                   SolveState *state,
                                                                   int32_t *__restrict__ knots,
                                                                   int32_t *__restrict__ list)
@@ -198,11 +196,9 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
         list[j] = k;
         if (j < REFINE_MAX_KNOTS) knots[j] = k;
     }
-    for (int j = threadIdx.x; j < j0; j += RF_THREADS) { Fmin[j] = DEV_INF; Sbest[j] = 0; }
-    for (int j = n + threadIdx.x; j < C; j += RF_THREADS) { Fmin[j] = DEV_INF; Sbest[j] = 0; }
-    // not evaluated, and not to be taken for a winner: a lower candidate has the lowest possible T here
-    // (with the early exit they lie behind it)
-    for (int j = end + threadIdx.x; j < n; j += RF_THREADS) { Fmin[j] = DEV_INF; Sbest[j] = 0; }
+    // nothing outside [j0, end) is evaluated, read, or to be taken for a winner: in front of it nothing is feasible (or
+    // gets to what a plan is known for), and behind it a lower candidate has the lowest possible T (with the early
+    // exit they lie behind it)
     if (threadIdx.x == 0) {
         state->n_first = j0;
         state->n_range = end;
@@ -391,11 +387,11 @@ hipError_t launch_set_candidates(hipStream_t st, const uint32_t *n_unique, Solve
     return hipGetLastError();
 }
 
-hipError_t launch_refine_begin(hipStream_t st, const RefineQuery &rq, const int32_t *cand, int32_t *Fmin,
-                               int32_t *Sbest, SolveState *state, const RefineBuffers &rb)
+hipError_t launch_refine_begin(hipStream_t st, const RefineQuery &rq, const int32_t *cand, SolveState *state,
+                               const RefineBuffers &rb)
 {
-    hipLaunchKernelGGL(refine_begin_kernel, dim3(1), dim3(RF_THREADS), 0, st, rq, rb.all, rb.first_round, cand, Fmin,
-                       Sbest, state, rb.knots[0], rb.list);
+    hipLaunchKernelGGL(refine_begin_kernel, dim3(1), dim3(RF_THREADS), 0, st, rq, rb.all, rb.first_round, cand,
+                       state, rb.knots[0], rb.list);
     return hipGetLastError();
 }
 
