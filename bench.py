@@ -282,7 +282,7 @@ def main():
                      "traffic": traffic, "traffic_kind": "stored rocprofv3 --pmc measurement "
                      "(profiles/) of one solve's rounds, not taken by this run" if traffic else None,
                      "traffic_measured_at_commit": commit,
-                     "kernel": "recurrence_fast_kernel", "kernel_ms_avg": head["rec_avg"]},
+                     "kernel": "recurrence_band_kernel", "kernel_ms_avg": head["rec_avg"]},
         "extra": extra,
     }
 

@@ -42,7 +42,7 @@ constexpr int BAND_ENDS = 16;
 constexpr int BAND_MAX_CELLS = 16384;        // of a layer
 constexpr int UNITS_AHEAD = 2;
 constexpr int BAND_INF_ROWS = 15;            // rows of the block of +infinity
-constexpr int BAND_WAVES = 16;               // per candidate: a compute unit's share (8: 64 layers on 8 x 8 takes 1.1 times as long)
+constexpr int BAND_WAVES = 16;               // per candidate, four per SIMD (eight and four a candidate were slower)
 constexpr int BAND_MAX_K = 248;              // (a segment's batches fit seven bits)
 
 __host__ __device__ constexpr int band_blocks(int K) { return (K + 7) / 8; }
