@@ -169,8 +169,13 @@ __global__ void band_least_kernel(const int32_t *__restrict__ table, int K, int 
 }
 
 // P(k, .) lies at k * R + RS + d (R = 2 RS + 1): RS cells of +infinity in front of d = 0, so that d - a needs no test.
-// Rows up to a multiple of 64, so that the last beginnings of a turn (below) need none either.
-__host__ __device__ constexpr int band_front_ints(int K, int RS) { return ((K + 63) / 64 * 64 + 1) * (2 * RS + 1); }
+// Rows for all beginnings of a turn (below: up to 128 of them in four groups of lanes, else up to 64), so that the last ones,
+// behind K, need none either: they read +infinity.
+__host__ __device__ constexpr int band_front_ints(int K, int RS)
+{
+    const int turn = RS == 64 ? 128 : 64;
+    return ((K + turn - 1) / turn * turn + 1) * (2 * RS + 1);
+}
 
 // P(k, .) for k = 1 .. K, one after the other (d = 0 is +infinity but for k = 0).  Lanes are G groups of device counts, each
 // with stage beginnings of its own: a turn takes two of them for every wave and group, b0 + nw (g + G y), and sixteen shapes,
@@ -184,6 +189,7 @@ __device__ __forceinline__ void band_fronts(const int32_t *__restrict__ least, c
                                             int K, int D, int S, int SP, int32_t c, int32_t *P)
 {
     constexpr int nw = BAND_WAVES, R = 2 * RS + 1, BS = 2 * G * nw;        // BS: beginnings of a turn
+    static_assert(BS <= (RS == 64 ? 128 : 64), "rows of P");
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b_lane = wid + nw * (lane / (WAVE / G)), d_lane = lane % (WAVE / G) + 1;
     struct Turn { int k, b0, q0; };
