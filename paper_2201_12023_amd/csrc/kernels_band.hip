@@ -181,8 +181,9 @@ __host__ __device__ constexpr int band_front_ints(int K, int RS)
 // with stage beginnings of its own: a turn takes two of them for every wave and group, b0 + nw (g + G y), and sixteen shapes,
 // whose t_intra come as in the recurrence, loaded two turns ahead.  Two and a half instructions a beginning and shape (half an
 // addition for the cell, an LDS read, the sum, half a three-operand minimum), four shapes at a time where a lane has a
-// cell for one of them and the filter leaves a term.  Bound by issue and by what a turn waits for: 64 layers on
-// 8 x 8 takes 115 us with four beginnings a turn, of which few are there at first, and a cell address each.
+// cell for one of them and the filter leaves a term.  Bound by issue and by what a turn waits for in
+// the one workgroup that a threshold has: 64 layers on 8 x 8 take 105 us, 48 on 32 x 8 424 (115 and 537 with four beginnings
+// a turn, of which few are there at first, and an address for each of their cells).
 // MAXIMUM: the largest stage instead of the sum.
 template <int RS, int G, bool MAXIMUM>
 __device__ __forceinline__ void band_fronts(const int32_t *__restrict__ least, const int32_t *__restrict__ sizes,

@@ -287,8 +287,8 @@ hipError_t launch_table_bounds(hipStream_t st, const Problem &p, const int32_t *
 // `T` may be null (no per-candidate output).  Only [first, range) is read: nothing else has a T (or any that matters,
 // see refine_begin_kernel), and where the loop ends behind it is found by bisection.  Tiles of four candidates a thread:
 // prefix minimum inside each thread and wave, the waves' totals through LDS, the
-// first index that fires and the arg-min through LDS atomics.  4096 candidates: 16 us a candidate a thread, in four tiles of
-// six barriers; 20 000 of which few are searched, all looked at: 43.
+// first index that fires and the arg-min through LDS atomics.  Bound by the barriers of a tile: 4096 candidates take 6 us (16 in
+// four tiles of a candidate a thread), some 20 000 of which a few hundred are searched 8 (43 with all looked at).
 constexpr int SEL_THREADS = 1024;
 constexpr int SEL_WAVES = SEL_THREADS / WAVE;
 constexpr int SEL_EACH = 4;
