@@ -370,12 +370,13 @@ __device__ __forceinline__ void eq4_select(int B, int n, int j_first, int range,
         __syncthreads();
     }
     if (prune && n_proc == n && carry != INF_I64) {
-        int lo = max(range, j_first), hi = n;          // the first index behind the range that fires
+        // the first index behind the range that fires; behind all others lie negative values (refine_begin_kernel), none of which does
+        int lo = max(range, j_first), hi = n;
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
-            if ((int64_t)B * (int64_t)cand[mid] >= carry) hi = mid; else lo = mid + 1;
+            if (cand[mid] < 0 || (int64_t)B * (int64_t)cand[mid] >= carry) hi = mid; else lo = mid + 1;
         }
-        n_proc = lo;
+        if (lo < n && cand[lo] >= 0) n_proc = lo;
     }
     if (T) {
         for (int j = tid; j < min(j_first, n); j += SEL_THREADS) T[j] = INF_I64;

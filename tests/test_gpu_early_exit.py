@@ -1,0 +1,59 @@
+"""GPU: where the early exit of Alg. 1 ends the loop, against the sequential oracle: candidates that are not values of the table,
+device lists with values that no candidate should have, on both sides of the one-block sort's longest list.
+Whole numbers: no tolerance."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2201_12023_amd import binding as B
+from paper_2201_12023_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("T_star", "t_max", "num_stages", "n_evaluated", "first_layer", "shape_idx")
+FORMS = {"own": 0, "generic": B.ALPA_DP_GENERIC}
+
+
+def _plan_is(plan, ref):
+    assert {k: plan[k] for k in KEYS} == {k: getattr(ref, k) for k in KEYS}
+
+
+def _solve_dev(h, t, flags, want_T=True):
+    import torch
+    d = torch.from_numpy(t).cuda()
+    T = torch.full((len(t),), -7, dtype=torch.int64, device="cuda")
+    plan = torch.zeros(B.PLAN_BYTES, dtype=torch.uint8, device="cuda")
+    B.alpa_dp_solve_dev(h, d, len(t), flags, T if want_T else None, plan)
+    torch.cuda.synchronize()
+    return T.cpu().numpy(), B.plan_from_bytes(plan.cpu().numpy().tobytes())
+
+
+def _sorted_as_the_library(t):
+    """Ascending distinct candidates, negative ones (sorted as unsigned) behind the others."""
+    return np.unique(t.view(np.uint32)).view(np.int32)
+
+
+# (13 layers on 2 x 4: the register/LDS kernel; on 2 x 8: the band kernel)
+@pytest.mark.parametrize("form", list(FORMS))
+@pytest.mark.parametrize("mesh", [(2, 4), (2, 8)], ids=lambda m: f"{m[0]}x{m[1]}")
+@pytest.mark.parametrize("negative", [1, 7, 300, 900])
+def test_early_exit_in_front_of_negative_values(negative, mesh, form):
+    """The loop ends among the values that are not negative, however many of the others lie behind them."""
+    w = W.random_problem(21, 13, *mesh, inf_frac=0.2, value_hi=250_000)
+    cand = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), 300)
+    t = np.concatenate([cand, -2 - 3 * np.arange(negative)]).astype(np.int32)
+    np.random.default_rng(negative).shuffle(t)
+    h = B.alpa_dp_create(w.table, w.K, w.N, w.M, 1, w.shapes)
+    try:
+        for Bv in (1, 3, 40, 100_000):
+            B.alpa_dp_set_B(h, Bv)
+            u = _sorted_as_the_library(t)
+            for prune in (True, False):
+                T_ref, p_ref = oracle.solve_parallel(w.table, w.N, w.M, Bv, w.shapes, u, prune, 8)
+                flags = FORMS[form] | (B.ALPA_DP_PRUNE if prune else 0)
+                T, plan = _solve_dev(h, t, flags)
+                assert np.array_equal(T, T_ref[np.searchsorted(u.view(np.uint32), t.view(np.uint32))])
+                _plan_is(plan, p_ref)
+                _plan_is(_solve_dev(h, t, flags, want_T=False)[1], p_ref)
+    finally:
+        B.alpa_dp_destroy(h)
