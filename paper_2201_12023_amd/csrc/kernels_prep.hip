@@ -332,7 +332,8 @@ __global__ __launch_bounds__(1024) void bitmap_write_kernel(const uint32_t *__re
 // ---------------------------------------------------------------- short lists
 //
 // A caller's list of up to LIST_SORT_MAX values in one block: sorted in LDS (bitonic), the first of each run kept, and every
-// value's place among them (rank_of_orig, if wanted).  1500 values: 16 launches of the radix sort take
+// value's place among them (rank_of_orig, if wanted).  The value -1 is no candidate and has no place (-1), as in the radix sort
+// of longer lists; it sorts behind all others, with what fills up the keys.  1500 values: 16 launches of the radix sort take
 // 55 us, and it three more for the places.
 __global__ __launch_bounds__(1024) void list_sort_kernel(const int32_t *__restrict__ tmax, int n, int N2,
                                                          int32_t *__restrict__ unique, uint32_t *__restrict__ n_unique,
@@ -362,7 +363,7 @@ __global__ __launch_bounds__(1024) void list_sort_kernel(const int32_t *__restri
     __syncthreads();
     const int per = (N2 + 1023) / 1024, from = t * per;    // (N2 is a power of two: 1, 2, 4 or 8)
     uint32_t c = 0;
-    for (int x = from; x < min(from + per, n); ++x) c += x == 0 || keys[x - 1] != keys[x];
+    for (int x = from; x < min(from + per, n); ++x) c += keys[x] != ~0u && (x == 0 || keys[x - 1] != keys[x]);
     uint32_t upto = c;
     for (int off = 1; off < 64; off <<= 1) {
         const uint32_t o = __shfl_up(upto, off, 64);
@@ -376,9 +377,9 @@ __global__ __launch_bounds__(1024) void list_sort_kernel(const int32_t *__restri
         all += wsum[y];
     }
     for (int x = from; x < min(from + per, n); ++x) {
-        const bool head = x == 0 || keys[x - 1] != keys[x];
+        const bool head = keys[x] != ~0u && (x == 0 || keys[x - 1] != keys[x]);
         if (head) unique[pos++] = (int32_t)keys[x];
-        place[x] = pos - 1;
+        place[x] = keys[x] != ~0u ? pos - 1 : ~0u;
     }
     if (t == 0) {
         *n_unique = all;

@@ -57,3 +57,27 @@ def test_early_exit_in_front_of_negative_values(negative, mesh, form):
                 _plan_is(_solve_dev(h, t, flags, want_T=False)[1], p_ref)
     finally:
         B.alpa_dp_destroy(h)
+
+
+@pytest.mark.parametrize("n", [9, 8192, 8193])
+def test_minus_one_is_no_candidate(n):
+    """The value -1 marks an entry without a candidate, in lists of every length."""
+    w = W.random_problem(22, 9, 2, 8, inf_frac=0.2, value_hi=50_000)
+    rng = np.random.default_rng(n)
+    t = rng.choice(oracle.all_candidates(w.table, w.shapes), n).astype(np.int32)
+    t[rng.permutation(n)[: n // 3]] = -1
+    u = np.unique(t[t >= 0])
+    h = B.alpa_dp_create(w.table, w.K, w.N, w.M, 5, w.shapes)
+    try:
+        for prune in (False, True):
+            T_ref, p_ref = oracle.solve_parallel(w.table, w.N, w.M, 5, w.shapes, u, prune, 8)
+            T, plan = _solve_dev(h, t, B.ALPA_DP_PRUNE if prune else 0)
+            assert np.array_equal(B.alpa_dp_candidates(h), u)
+            assert (T[t < 0] == oracle.INF64).all()
+            assert np.array_equal(T[t >= 0], T_ref[np.searchsorted(u, t[t >= 0])])
+            _plan_is(plan, p_ref)
+        T, plan = _solve_dev(h, np.full(n, -1, np.int32), 0)
+        assert (T == oracle.INF64).all() and plan["num_stages"] == 0 and plan["n_evaluated"] == 0
+        assert len(B.alpa_dp_candidates(h)) == 0
+    finally:
+        B.alpa_dp_destroy(h)
