@@ -733,7 +733,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     const int32_t *bounds = with_bounds ? h->d_bounds : h->d_no_bounds;
     // per-candidate results are wanted from every interval; a plan alone from few of them
     const RefineQuery rq{n_B > 0 ? h->d_sw_B : nullptr, p.B, std::max(n_B, 1), prune,
-                         (n_B > 0 || !d_out_T) ? 1 : 0, bounds, p.Smax,
+                         (n_B > 0 || !d_out_T) ? 1 : 0, bounds, p.Smax, prune_sel,
                          h->band_ok ? bounds + table_bounds_ints(p) : nullptr, h->max_finite};
     HIPCHK(hipEventRecord(h->ev[0], st));
     const bool bitmap = !have_list && distinct_by_bitmap(h);

@@ -193,6 +193,7 @@ struct RefineQuery {
     int plan_only;
     const int32_t *bounds;   // launch_table_bounds
     int Smax;
+    int early_exit;          // the selection uses the early exit (in a sweep too, where `prune` is not set)
     const int32_t *thr;      // BAND_TOTALS numbers of launch_band_bounds, or null
     int32_t max_finite;
 };

@@ -130,8 +130,9 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
                 if (sh_sum[t] < DEV_INF && sh_sum[t] + (B - 1) * (int64_t)sh_c[t] == U) at = min(at, sh_x[t]);
             at = wave_min_i32(at);
             // with the early exit nothing behind the first B t_max >= U is looked at; where only the plan counts, nothing that
-            // cannot get below U (nor reach it before `at`): then nothing else can set the early exit off either, as B t_max < U
-            // for every candidate in front of `at`
+            // cannot get below U (nor reach it before `at`).  What is left out must not set the early exit off either: at
+            // candidates in front of `at` it cannot, as their t_max is below that plan's largest stage and B t_max below U;
+            // but `at` itself may be far above the plan, so in front of it only what cannot get down to B t_max(at) goes
             int first = n, end = j0 + 1;
             if (U == INF_I64) {
                 first = j0;
@@ -140,16 +141,17 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
                 const int stop = rq.prune ? max(at + 1, first_product(cand, at + 1, n, B, U)) : n;
                 end = stop;
                 if (rq.plan_only) {
+                    const int64_t in_front = rq.early_exit && B * (int64_t)cand[at] > U ? B * (int64_t)cand[at] : U;
                     end = min(at + 1, n);
                     for (int t = lane; t < BAND_THRESHOLDS; t += WAVE) {
                         const int lo_t = sh_lo[t], hi_t = min(stop, t == 0 ? n : sh_lo[t - 1]);
-                        const int64_t least = rq.thr[t];
-                        if (lo_t >= hi_t || least >= DEV_INF || least + (B - 1) * (int64_t)cand[lo_t] > U) continue;
+                        const int64_t least = rq.thr[t], most = lo_t < at ? in_front : U;
+                        if (lo_t >= hi_t || least >= DEV_INF || least + (B - 1) * (int64_t)cand[lo_t] > most) continue;
                         first = min(first, lo_t);
-                        int x = lo_t, z = hi_t;        // first index that cannot get to U
+                        int x = lo_t, z = hi_t;        // first index that cannot get to `most`
                         while (x < z) {
                             const int mid = (x + z) >> 1;
-                            if (least + (B - 1) * (int64_t)cand[mid] > U) z = mid; else x = mid + 1;
+                            if (least + (B - 1) * (int64_t)cand[mid] > most) z = mid; else x = mid + 1;
                         }
                         end = max(end, x);
                     }

@@ -81,3 +81,65 @@ def test_minus_one_is_no_candidate(n):
         assert len(B.alpa_dp_candidates(h)) == 0
     finally:
         B.alpa_dp_destroy(h)
+
+
+def _one_stage_or_eight(one, each):
+    """8 layers on 1 x 16: one stage on all devices, or eight of two devices each."""
+    shapes = W.submesh_shapes(1, 16)
+    table = np.full((8, 8, 8, len(shapes)), oracle.INF32, np.int32)
+    q = [int(a * b) for a, b in shapes]
+    table[0, 0, 7, q.index(16)] = one
+    for s in range(8):
+        table[s, 7 - s, 7 - s, q.index(2)] = each
+    return table, shapes
+
+
+@pytest.mark.parametrize("form", list(FORMS))
+def test_early_exit_at_a_value_far_above_the_plan(form):
+    """t_max = 9000 admits a plan of 5000, T* 14000 with B = 2, but B t_max = 18000: the loop ends at it if a lower candidate
+    has reached that, though the lower one's T* of 17920 is above 14000."""
+    table, shapes = _one_stage_or_eight(5000, 1990)
+    h = B.alpa_dp_create(table, 8, 1, 16, 2, shapes)
+    try:
+        for t in ([2000, 9000], [2000, 8000], [2000, 8961], [2000, 8960], [1, 2000, 2100, 9000, 9500], [9000]):
+            t = np.array(t, np.int32)
+            for prune in (True, False):
+                flags = FORMS[form] | (B.ALPA_DP_PRUNE if prune else 0)
+                _, ref = oracle.solve(table, 1, 16, 2, shapes, t, prune)
+                _plan_is(B.alpa_dp_solve(h, t, flags=flags)[1], ref)
+                _plan_is(B.alpa_dp_solve(h, t, flags=flags, want_T=False)[1], ref)
+                Bs = [1, 2, 3, 50]
+                for Bv, plan in zip(Bs, B.alpa_dp_solve_sweep(h, t, Bs, flags=flags)):
+                    _plan_is(plan, oracle.solve(table, 1, 16, Bv, shapes, t, prune)[1])
+    finally:
+        B.alpa_dp_destroy(h)
+
+
+@pytest.mark.parametrize("size", [(8, 1, 16), (12, 2, 8), (10, 3, 16)], ids=lambda s: f"K{s[0]}-{s[1]}x{s[2]}")
+def test_early_exit_of_sparse_lists(size):
+    """Short lists whose values lie anywhere between and beyond the table's, and a few quantiles of it."""
+    K, N, M = size
+    tables = [W.deep_model_problem(K, K, N, M), W.many_stage_problem(K, K, N, M),
+              W.random_problem(K, K, N, M, inf_frac=0.5, value_hi=30_000)]
+    for x, w in enumerate(tables):
+        rng = np.random.default_rng(100 * K + x)
+        hi = int(oracle.all_candidates(w.table, w.shapes)[-1])
+        h = B.alpa_dp_create(w.table, K, N, M, 1, w.shapes)
+        try:
+            for trial in range(25):
+                n = int(rng.integers(2, 9))
+                t = np.unique(np.exp(rng.uniform(np.log(hi / 300), np.log(3 * hi), n)).astype(np.int32))
+                Bs = [int(v) for v in np.unique(rng.integers(1, 12, 4))]
+                for prune in (True, False):
+                    flags = B.ALPA_DP_PRUNE if prune else 0
+                    refs = [oracle.solve(w.table, N, M, Bv, w.shapes, t, prune)[1] for Bv in Bs]
+                    for Bv, ref, plan in zip(Bs, refs, B.alpa_dp_solve_sweep(h, t, Bs, flags=flags)):
+                        _plan_is(plan, ref)
+                        B.alpa_dp_set_B(h, Bv)
+                        _plan_is(B.alpa_dp_solve(h, t, flags=flags, want_T=False)[1], ref)
+                        if n > 2:
+                            q = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), n)
+                            ref = oracle.solve(w.table, N, M, Bv, w.shapes, q, prune)[1]
+                            _plan_is(B.alpa_dp_solve(h, None, n, flags, want_T=False)[1], ref)
+        finally:
+            B.alpa_dp_destroy(h)
