@@ -401,7 +401,7 @@ __global__ __launch_bounds__(1024) void list_sort_kernel(const int32_t *__restri
 
 // ---------------------------------------------------------------- candidate lists
 
-// rank_of_orig[j] = index of tmax[j] in the ascending distinct list (binary search)
+// rank_of_orig[j] = index of tmax[j] in the distinct list (binary search; it ascends as unsigned)
 __global__ void rank_lookup_kernel(const int32_t *__restrict__ tmax, int n,
                                    const int32_t *__restrict__ unique,
                                    const uint32_t *__restrict__ n_unique_p,
@@ -413,7 +413,7 @@ __global__ void rank_lookup_kernel(const int32_t *__restrict__ tmax, int n,
         int lo = 0, hi = nu;              // first index with unique[idx] >= x
         while (lo < hi) {
             int mid = (lo + hi) >> 1;
-            if (unique[mid] < x) lo = mid + 1; else hi = mid;
+            if ((uint32_t)unique[mid] < (uint32_t)x) lo = mid + 1; else hi = mid;
         }
         rank_of_orig[j] = (lo < nu && unique[lo] == x) ? lo : -1;
     }

@@ -143,3 +143,18 @@ def test_early_exit_of_sparse_lists(size):
                             _plan_is(B.alpa_dp_solve(h, None, n, flags, want_T=False)[1], ref)
         finally:
             B.alpa_dp_destroy(h)
+
+
+def test_long_list_with_negative_values():
+    """Beyond the one-block sort a value's result is found by bisection, also with most of the list negative."""
+    w = W.random_problem(23, 9, 2, 8, inf_frac=0.2, value_hi=50_000)
+    cand = oracle.all_candidates(w.table, w.shapes)[::3]
+    t = np.concatenate([cand, -2 - 2 * np.arange(9000)]).astype(np.int32)
+    np.random.default_rng(4).shuffle(t)
+    T_ref, _ = oracle.eval_candidates(w.table, w.N, w.M, 5, w.shapes, np.maximum(t, 0), threads=8)
+    T_ref[t < 0] = oracle.INF64
+    h = B.alpa_dp_create(w.table, w.K, w.N, w.M, 5, w.shapes)
+    try:
+        assert np.array_equal(_solve_dev(h, t, 0)[0], T_ref)
+    finally:
+        B.alpa_dp_destroy(h)
