@@ -76,6 +76,7 @@ struct alpa_dp {
     int32_t *d_bandrecs = nullptr, *d_bandends = nullptr, *d_bandthr = nullptr;
     bool band_ok = false;
     BandShape band{};
+    BandShapes band_shapes{};
     int32_t *d_bounds = nullptr;    // what the table says about every candidate (launch_table_bounds)
     int32_t *d_no_bounds = nullptr; // the same layout, saying nothing
     int32_t *d_bound_work = nullptr;
@@ -306,7 +307,7 @@ static int queue_table_candidates(alpa_dp *h, bool cleared = false)
 static int queue_bounds(alpa_dp *h)
 {
     if (h->band_ok)
-        HIPCHK(launch_band_bounds(h->stream, h->d_table, h->d_sizes, h->p, h->max_finite, h->d_bound_work, h->d_bandthr,
+        HIPCHK(launch_band_bounds(h->stream, h->d_table, h->band_shapes, h->p, h->max_finite, h->d_bound_work, h->d_bandthr,
                                   h->d_bounds));
     else
         HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
@@ -375,12 +376,26 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     // 2048: 252 and 215 against 298 and 190; but 72 on 2 x 4, 2048: 288 and 241 against 280 and 195).  It also takes
     // what is left up to 128 devices, the general kernel the rest.
     const bool groups_serve = K <= 128 && (D <= 4 || (D <= 8 && K <= 64));
-    h->band = band_shape(K, D, S, sizes.data());
+    // (shapes of one device count, i.e. repeated ones, are one shape to it)
+    std::vector<int32_t> band_sizes, first, next(S, -1), last;
+    for (int q = 0; q < S; ++q) {
+        const int x = (int)(std::find(band_sizes.begin(), band_sizes.end(), sizes[q]) - band_sizes.begin());
+        if (x == (int)band_sizes.size()) {
+            band_sizes.push_back(sizes[q]);
+            first.push_back(q);
+            last.push_back(q);
+        } else {
+            next[last[x]] = q;
+            last[x] = q;
+        }
+    }
+    const int SB = (int)band_sizes.size();
+    h->band = band_shape(K, D, SB, band_sizes.data());
     h->band_ok = !groups_serve && h->band.nbuf != 0;
     h->fast_ok = !h->band_ok && K <= 128 && D <= 128;
     int rc = carve(&h->arena, [&](Carver &take) {
         take(h->d_table, (size_t)K * K * K * S);
-        take(h->d_sizes, S + table_bounds_ints(h->p));             // d_no_bounds behind it
+        take(h->d_sizes, S + table_bounds_ints(h->p) + 2 * SB + S);    // behind them d_no_bounds and band_shapes
         take(h->pb.hist, SORT_RADIX * SORT_SLICES + SORT_RADIX);   // counts + totals
         take(h->d_ncount, 2);
         take(h->d_state, 1);
@@ -390,11 +405,11 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
         take(h->d_best_plan, 1);
         take(h->d_Fall, (size_t)(h->p.Smax + 1) * LS);
         take(h->d_bounds, table_bounds_ints(h->p) + (h->band_ok ? BAND_TOTALS : 0));
-        take(h->d_bound_work, h->band_ok ? band_least_ints(K, S) : table_bounds_work(h->p));
+        take(h->d_bound_work, h->band_ok ? band_least_ints(K, SB) : table_bounds_work(h->p));
         take(h->d_scratch, (size_t)gg * 2 * LS);
         if (h->band_ok) {
-            take(h->d_bandrecs, band_table_ints(K, h->p.Smax, S));
-            take(h->d_bandends, band_ends_ints(K, h->p.Smax, S));
+            take(h->d_bandrecs, band_table_ints(K, h->p.Smax, SB));
+            take(h->d_bandends, band_ends_ints(K, h->p.Smax, SB));
             take(h->d_bandthr, band_thresholds_ints(K, D));
         }
         if (h->fast_ok) {
@@ -415,11 +430,16 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     up[S + h->p.Smax + 1] = 0;                     // any t_max may have a plan, of an unknown number of stages
     up[S + h->p.Smax + 3] = DEV_INF;
     h->d_no_bounds = h->d_sizes + S;
+    const int32_t *shapes_at = h->d_sizes + up.size();
+    up.insert(up.end(), band_sizes.begin(), band_sizes.end());
+    up.insert(up.end(), first.begin(), first.end());
+    up.insert(up.end(), next.begin(), next.end());
+    h->band_shapes = BandShapes{SB, S, shapes_at, SB < S ? shapes_at + SB : nullptr, shapes_at + 2 * SB};
     HIPCHK(hipMemcpyAsync(h->d_sizes, up.data(), up.size() * 4, hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipMemsetAsync(h->d_state, 0, sizeof(SolveState), h->stream));
     HIPCHK(launch_init_best_plan(h->stream, h->d_best_plan));
     if (h->band_ok)
-        HIPCHK(launch_repack_band(h->stream, h->d_table, K, h->p.Smax, S, h->d_bandrecs, h->d_bandends));
+        HIPCHK(launch_repack_band(h->stream, h->d_table, K, h->p.Smax, h->band_shapes, h->d_bandrecs, h->d_bandends));
     if (h->fast_ok) {
         h->KP = 16 * ((K + 15) / 16);
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
@@ -558,7 +578,7 @@ extern "C" int alpa_dp_restrict_equal_layers(alpa_dp_t *h)
         if (rcb) return rcb;
     }
     if (h->band_ok)
-        HIPCHK(launch_repack_band(h->stream, h->d_table, K, h->p.Smax, S, h->d_bandrecs, h->d_bandends));
+        HIPCHK(launch_repack_band(h->stream, h->d_table, K, h->p.Smax, h->band_shapes, h->d_bandrecs, h->d_bandends));
     if (h->fast_ok) {
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
     }
@@ -728,6 +748,8 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
 
     const bool fast = h->fast_ok && !(flags & ALPA_DP_GENERIC);
     const bool band = h->band_ok && !(flags & ALPA_DP_GENERIC);
+    Problem p_band = p;
+    p_band.S = h->band_shapes.S;
     const bool with_bounds = wants_bounds(h, bound, recorded);
     const RefineBuffers rb = plan_rounds(h, bound, !fast, with_bounds);
     const int32_t *bounds = with_bounds ? h->d_bounds : h->d_no_bounds;
@@ -769,7 +791,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         // candidates of a round before the last are knots: none of them may be skipped
         const int skip = last ? prune : 0;
         if (band) {
-            FastArgs fa{p, nullptr, h->d_sizes, h->d_cand, rb.list, &h->d_state->n_list, 0, INT32_MAX,
+            FastArgs fa{p_band, nullptr, h->band_shapes.sizes, h->d_cand, rb.list, &h->d_state->n_list, 0, INT32_MAX,
                         &h->d_state->ticket, &h->d_state->wave_relax, h->d_chunkmin, skip,
                         /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cands.cap, nullptr, nullptr,
                         nullptr, bounds};
@@ -837,7 +859,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
             const int chunk = sweep_chunk(h, n_B);
             for (int b = 0, x = 0; b < n_B; b += chunk, ++x) {
                 const int n = std::min(chunk, n_B - b);
-                FastArgs fa{p, h->d_recs, h->d_sizes, h->d_sw_c + b, nullptr, h->d_sw_n + 2 * x, 0, INT32_MAX,
+                FastArgs fa{band ? p_band : p, h->d_recs, band ? h->band_shapes.sizes : h->d_sizes, h->d_sw_c + b, nullptr, h->d_sw_n + 2 * x, 0, INT32_MAX,
                             h->d_sw_n + 2 * x + 1,
                             &h->d_state->wave_relax, nullptr, 0, 0, h->d_sw_FS,
                             h->d_sw_FS + (n_B + 1), n_B, h->d_sw_Fall, h->d_sw_s + b, h->d_gmin, bounds};
@@ -868,7 +890,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     if (d_out_T && have_list && bound > 0) HIPCHK(launch_scatter_T(st, h->d_T, h->d_rank, n_tmax, d_out_T));
     // every layer of the winning candidate (does nothing if there is none), then the walk
     if (band) {
-        FastArgs fa{p, nullptr, h->d_sizes, &h->d_state->best_c, nullptr,
+        FastArgs fa{p_band, nullptr, h->band_shapes.sizes, &h->d_state->best_c, nullptr,
                     &h->d_state->plan_n, 0, INT32_MAX, &h->d_state->plan_ticket, &h->d_state->wave_relax,
                     nullptr, 0, 0, h->d_tmpFS, h->d_tmpFS + 2, 1, h->d_Fall, &h->d_state->best_s,
                     nullptr, bounds};

@@ -280,14 +280,20 @@ struct BandShape {
     int lens_at, bounds_at, lds_ints;   // in int32: where a candidate's stage lengths and its windows are kept; all of the LDS
 };
 BandShape band_shape(int K, int D, int S, const int32_t *sizes);
+// The shapes as the band kernel sees them: one per device count.  Shapes first[q], next[first[q]], .. of the table up to -1
+// have sizes[q] devices; first is null where the table has no two of a kind.
+struct BandShapes {
+    int S, S_table;
+    const int32_t *sizes, *first, *next;
+};
 size_t band_table_ints(int K, int Smax, int S);
 size_t band_ends_ints(int K, int Smax, int S);
-hipError_t launch_repack_band(hipStream_t st, const int32_t *table, int K, int Smax, int S,
+hipError_t launch_repack_band(hipStream_t st, const int32_t *table, int K, int Smax, const BandShapes &b,
                               int32_t *recs, int32_t *ends);
 // what the table says about candidates: launch_table_bounds' place for these sizes
 size_t band_least_ints(int K, int S);
 size_t band_thresholds_ints(int K, int D);
-hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const int32_t *sizes, const Problem &p, int32_t max_finite,
+hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
                               int32_t *work, int32_t *thr, int32_t *bounds);
 hipError_t launch_recurrence_band(hipStream_t st, const FastArgs &f, const BandShape &b, const int32_t *recs,
                                   const int32_t *ends, const int32_t *thr, int32_t max_finite, int mode, int grid);

@@ -75,11 +75,22 @@ __device__ __forceinline__ size_t band_cell(int P, int NHB, int q, int k, int le
            ((l & 1) * 8 + (k & 7)) * 4 + ((l >> 1) & 3);
 }
 
+// The smallest of an entry's shapes of one device count: `entry` is that of shape 0.  What a filter leaves of several shapes
+// with equal device counts has the least sum with the smallest of them, so the kernel sees one shape for each.
+__device__ __forceinline__ int32_t band_smallest(const int32_t *__restrict__ entry, const BandShapes &b, int q)
+{
+    if (!b.first) return entry[q];
+    int32_t t = INF_I32;
+    for (int x = b.first[q]; x >= 0; x = b.next[x]) t = min(t, entry[x]);
+    return t;
+}
+
 // A wave per (s, block, q): the block's units (a lane per entry and batch), and the smallest entry from each of
 // eight positions on.  Blocks and units that only fill up a tile are +infinity.
-__global__ __launch_bounds__(256) void repack_band_kernel(const int32_t *__restrict__ table, int K, int S, int n,
+__global__ __launch_bounds__(256) void repack_band_kernel(const int32_t *__restrict__ table, int K, BandShapes b, int n,
                                                           int32_t *__restrict__ recs, int32_t *__restrict__ ends)
 {
+    const int S = b.S;
     const int NHB = band_blocks(K), NG = (NHB + 3) / 4, P = band_tiles(K);
     const int lane = threadIdx.x & (WAVE - 1);
     const int n_waves = gridDim.x * (blockDim.x / WAVE);
@@ -88,7 +99,7 @@ __global__ __launch_bounds__(256) void repack_band_kernel(const int32_t *__restr
         const int g = hb >> 2;
         int32_t *out = recs + (((size_t)s * S + q) * P + band_tiles_before(NHB, g)) * BAND_TILE + (hb & 3) * 64 + lane;
         const int k = 8 * hb + ((lane >> 2) & 7), first_len = 2 * (lane & 3) + (lane >> 5);   // lane = 4 * entry + batch
-        const int32_t *row = table + ((size_t)s * K + k) * K * S + q;
+        const int32_t *row = table + ((size_t)s * K + k) * K * b.S_table;
         int32_t mn[BAND_ENDS];
 #pragma unroll
         for (int j = 0; j < BAND_ENDS; ++j) mn[j] = DEV_INF;
@@ -96,7 +107,7 @@ __global__ __launch_bounds__(256) void repack_band_kernel(const int32_t *__restr
             const int i = k + 8 * u + first_len;
             int32_t v = DEV_INF;
             if (i < K) {                               // (then k < K as well)
-                const int32_t t = row[(size_t)i * S];
+                const int32_t t = band_smallest(row + (size_t)i * b.S_table, b, q);
                 if (t != INF_I32) v = t;
             }
             out[(size_t)u * BAND_TILE] = v;
@@ -114,11 +125,11 @@ __global__ __launch_bounds__(256) void repack_band_kernel(const int32_t *__restr
     }
 }
 
-hipError_t launch_repack_band(hipStream_t st, const int32_t *table, int K, int Smax, int S,
+hipError_t launch_repack_band(hipStream_t st, const int32_t *table, int K, int Smax, const BandShapes &b,
                               int32_t *recs, int32_t *ends)
 {
-    const int n = Smax * 4 * ((band_blocks(K) + 3) / 4) * S;
-    hipLaunchKernelGGL(repack_band_kernel, dim3(std::min((n + 3) / 4, 16384)), dim3(256), 0, st, table, K, S, n,
+    const int n = Smax * 4 * ((band_blocks(K) + 3) / 4) * b.S;
+    hipLaunchKernelGGL(repack_band_kernel, dim3(std::min((n + 3) / 4, 16384)), dim3(256), 0, st, table, K, b, n,
                        recs, ends);
     return hipGetLastError();
 }
@@ -152,17 +163,20 @@ __device__ __forceinline__ void lds_barrier()
 //     dense layers, t_max at the 5 % quantile: after 4 layers, 9 with the least F of more stages and no filter).
 // And without a filter: the least largest stage (no plan below that t_max), and the lowest threshold whose least plan
 // is that without a filter (from there on F hardly changes).  least[k][i][q]: q padded to a multiple of 16 (SP).
-__global__ void band_least_kernel(const int32_t *__restrict__ table, int K, int Smax, int S, int SP,
+__global__ void band_least_kernel(const int32_t *__restrict__ table, int K, int Smax, BandShapes b, int SP,
                                   int32_t *__restrict__ least)
 {
     const int n = K * K * SP;
     for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
         const int ki = x / SP, q = x - ki * SP, k = ki / K, i = ki - k * K;
         int32_t m = DEV_INF;
-        if (q < S && i >= k) {
-            const int32_t *t = table + (size_t)ki * S + q;
+        if (q < b.S && i >= k) {
+            const int32_t *t = table + (size_t)ki * b.S_table;
+            const size_t layer = (size_t)K * K * b.S_table;
+            for (int y = b.first ? b.first[q] : q; y >= 0; y = b.first ? b.next[y] : -1) {
 #pragma unroll 8
-            for (int s = 0; s < Smax; ++s) m = min(m, t[(size_t)s * K * K * S]);
+                for (int s = 0; s < Smax; ++s) m = min(m, t[s * layer + y]);
+            }
         }
         least[x] = min(m, DEV_INF);
     }
@@ -268,11 +282,13 @@ __device__ __forceinline__ void band_fronts(const int32_t *__restrict__ least, c
 // A plan that reaches P(K, D), walked from its last stage on, with the t_intra it really has (how many stages lie
 // behind each is known now): plan[0] = their sum, plan[1] = the largest; +infinity where a stage has no entry.
 __device__ __forceinline__ void band_front_plan(const int32_t *__restrict__ least, const int32_t *__restrict__ table,
-                                                const int32_t *__restrict__ sizes, int K, int D, int S, int SP, int32_t c,
+                                                const BandShapes &bs, int K, int D, int SP, int32_t c,
                                                 const int32_t *P, int RS, int32_t *plan)
 {
     __shared__ int sh_term[2], sh_sum, sh_largest;
-    __shared__ int sh_stage[256];                  // (first layer, last, shape) of each, in the table of one number of stages
+    __shared__ int sh_stage[256];                  // 64 (first layer, last) + shape of each
+    const int S = bs.S;
+    const int32_t *const sizes = bs.sizes;
     const int R = 2 * RS + 1, tid = threadIdx.x;
     if (tid < 2) sh_term[tid] = INT32_MAX;
     if (tid == 2) sh_sum = 0;
@@ -296,7 +312,7 @@ __device__ __forceinline__ void band_front_plan(const int32_t *__restrict__ leas
         const int b = x >> 6, q = x & 63;
         if (tid == 0) {
             sh_term[~n & 1] = INT32_MAX;           // (last read a barrier ago)
-            sh_stage[n] = (b * K + k - 1) * S + q;
+            sh_stage[n] = (b * K + k - 1) * 64 + q;
         }
         lds_barrier();
         ++n;
@@ -304,7 +320,8 @@ __device__ __forceinline__ void band_front_plan(const int32_t *__restrict__ leas
         d -= sizes[q];
     }
     if (tid < n) {
-        const int32_t t = table[(size_t)tid * K * K * S + sh_stage[tid]];
+        const int ki = sh_stage[tid] >> 6;
+        const int32_t t = band_smallest(table + ((size_t)tid * K * K + ki) * bs.S_table, bs, sh_stage[tid] & 63);
         atomicMax(&sh_largest, t);
         atomicAdd(&sh_sum, t == INF_I32 ? 0 : t);
     }
@@ -391,13 +408,14 @@ __device__ __forceinline__ void band_find_windows(const int32_t *__restrict__ le
 // least largest stage behind the last.
 template <int RS, int G>
 __global__ __launch_bounds__(WAVE * BAND_WAVES) void band_thresholds_kernel(const int32_t *__restrict__ least, const int32_t *__restrict__ table,
-                                                               const int32_t *__restrict__ sizes, int K, int D, int S, int SP, int32_t max_finite,
+                                                               BandShapes bs, int K, int D, int SP, int32_t max_finite,
                                                                int32_t *__restrict__ fronts, int32_t *__restrict__ totals,
                                                                int32_t *__restrict__ plans, int32_t *__restrict__ windows)
 {
     extern __shared__ int32_t lds[];
     constexpr int R = 2 * RS + 1;
-    const int j = blockIdx.x;
+    const int j = blockIdx.x, S = bs.S;
+    const int32_t *const sizes = bs.sizes;
     if (j <= BAND_THRESHOLDS) {
         const int32_t c = j < BAND_THRESHOLDS ? band_threshold(max_finite, j) : DEV_INF - 1;
         if (j < BAND_THRESHOLDS) band_fronts<RS, G, false>(least, sizes, K, D, S, SP, c, lds);
@@ -408,7 +426,7 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void band_thresholds_kernel(cons
             const int k = x / RS, d = x - k * RS + 1;
             fronts[(size_t)j * K * RS + x] = k >= 1 && d < D ? min(lds[k * R + RS + D - d], DEV_INF) : DEV_INF;
         }
-        band_front_plan(least, table, sizes, K, D, S, SP, c, lds, RS, plans + 2 * j);
+        band_front_plan(least, table, bs, K, D, SP, c, lds, RS, plans + 2 * j);
         return;
     }
     const int w = j - BAND_THRESHOLDS - 1;
@@ -446,14 +464,14 @@ size_t band_thresholds_ints(int K, int D)
 }
 
 // work: band_least_ints; thr: band_thresholds_ints (fronts, windows); behind the bounds: BAND_TOTALS (totals, plans)
-hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const int32_t *sizes, const Problem &p, int32_t max_finite,
+hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
                               int32_t *work, int32_t *thr, int32_t *bounds)
 {
     int32_t *totals = bounds + table_bounds_ints(p), *plans = totals + BAND_THRESHOLDS + 1;
-    const int SP = (p.S + 15) / 16 * 16, RS = band_row_ints(p.D);
+    const int SP = (b.S + 15) / 16 * 16, RS = band_row_ints(p.D);
     int32_t *windows = thr + (size_t)BAND_THRESHOLDS * p.K * RS;
     hipLaunchKernelGGL(band_least_kernel, dim3(std::min((p.K * p.K * SP + 255) / 256, 16384)), dim3(256), 0, st, table, p.K,
-                       p.Smax, p.S, SP, work);
+                       p.Smax, b, SP, work);
     const size_t lds = std::max((size_t)band_front_ints(p.K, RS) * 4, (size_t)2 * p.K * (p.K | 1));
     const auto kernel = p.D <= 16 ? band_thresholds_kernel<64, 4> : p.D <= 32 ? band_thresholds_kernel<64, 2> :
                         RS == 64 ? band_thresholds_kernel<64, 1> : RS == 128 ? band_thresholds_kernel<128, 1> : band_thresholds_kernel<256, 1>;
@@ -461,7 +479,7 @@ hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const int32_
         hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kernel, dim3(2 * BAND_THRESHOLDS + 1), dim3(WAVE * BAND_WAVES), lds, st, work, table, sizes, p.K, p.D, p.S, SP,
+    hipLaunchKernelGGL(kernel, dim3(2 * BAND_THRESHOLDS + 1), dim3(WAVE * BAND_WAVES), lds, st, work, table, b, p.K, p.D, SP,
                        max_finite, thr, totals, plans, windows);
     hipLaunchKernelGGL(band_bounds_kernel, dim3(1), dim3(256), 0, st, p, max_finite, totals, bounds);
     return hipGetLastError();

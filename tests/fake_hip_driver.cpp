@@ -185,14 +185,16 @@ static void check_launches(size_t from, size_t to, const char *what)
     }
 }
 
-static alpa_dp_t *create_problem(int K, int N, int M)
+// `repeat`: fill the list up to so many shapes with the first one
+static alpa_dp_t *create_problem(int K, int N, int M, int repeat = 0)
 {
     std::vector<alpa_shape_t> shapes;
     for (int m = 1; m <= M; m *= 2) shapes.push_back({1, m});
     for (int n = 2; n <= N; ++n) shapes.push_back({n, M});
-    std::vector<int32_t> table((size_t)K * K * K * shapes.size(), 7);
+    while ((int)shapes.size() < repeat) shapes.push_back(shapes[0]);
     alpa_dp_t *h = nullptr;
-    const int rc = alpa_dp_create(&h, table.data(), K, N, M, 8, shapes.data(), (int)shapes.size());
+    static const int32_t table = 7;                // (nothing reads it)
+    const int rc = alpa_dp_create(&h, &table, K, N, M, 8, shapes.data(), (int)shapes.size());
     if (rc) { printf("create: %d %s\n", rc, alpa_dp_last_error()); exit(1); }
     CHECK(alpa_dp_set_stream(h, (void *)0x1000) == 0, "stream");   // (the null stream cannot be recorded)
     return h;
@@ -358,7 +360,7 @@ static std::string kernels_of(alpa_dp_t *h, int n)
 static void routes()
 {
     rt().n_distinct = 5000;
-    struct { int K, N, M, n; const char *has, *has_not; } cases[] = {
+    struct { int K, N, M, n; const char *has, *has_not; int repeat = 0; } cases[] = {
         // up to 8 devices: beyond two candidates per compute unit in lane groups, not with eight waves each
         {24, 1, 4, 1500, " recurrence_fast_kernel<2,1,1,false,false,false,true> ", "recurrence_fast_kernel<2,2,1,false"},
         {40, 2, 4, 2048, " recurrence_fast_kernel<3,1,1,false,false,false,true> ", "recurrence_fast_kernel<3,2,1,false"},
@@ -379,10 +381,13 @@ static void routes()
         {86, 16, 8, 300, " recurrence_band_kernel<128,0,false,false> ", "recurrence_fast"},
         {59, 32, 8, 300, " recurrence_band_kernel<256,0,false,false> ", "recurrence_generic"},
         {60, 32, 8, 300, " recurrence_generic_kernel ", "recurrence_band"},
+        // repeated shapes are one to it
+        {220, 1, 8, 300, " recurrence_band_kernel<64,0,false,false> ", "recurrence_generic", 64},
+        {205, 14, 1, 300, " recurrence_band_kernel<64,0,false,false> ", "recurrence_generic", 64},
         {124, 16, 8, 300, " recurrence_fast_kernel<8,1,2,false,false,true,false> ", "recurrence_band"},
     };
     for (auto &c : cases) {
-        alpa_dp_t *h = create_problem(c.K, c.N, c.M);
+        alpa_dp_t *h = create_problem(c.K, c.N, c.M, c.repeat);
         (void)kernels_of(h, c.n);
         const std::string k = kernels_of(h, c.n);  // with the bounds
         CHECK(k.find(c.has) != std::string::npos, "%d layers on %dx%d, %d: no%sin%s", c.K, c.N, c.M, c.n, c.has, k.c_str());

@@ -79,3 +79,30 @@ def test_band_kernel_against_the_general_kernel(size):
                 _plan_is(plans[b], B.alpa_dp_solve(h, None, 12, B.ALPA_DP_GENERIC)[1])
         finally:
             B.alpa_dp_destroy(h)
+
+
+@pytest.mark.parametrize("size", [(9, 2, 8), (24, 1, 16), (20, 17, 8), (66, 2, 4)], ids=lambda s: f"K{s[0]}-{s[1]}x{s[2]}")
+def test_repeated_shapes(size):
+    """Shapes listed up to four times, each with latencies of its own: the kernel takes the smallest of them, the plan names the one
+    that has it."""
+    K, N, M = size
+    rng = np.random.default_rng(K)
+    for x, w in enumerate((W.random_problem(K, K, N, M, inf_frac=0.5, value_hi=60), W.deep_model_problem(K, K, N, M, B=7))):
+        which = rng.permutation(np.repeat(np.arange(len(w.shapes)), rng.integers(1, 5, len(w.shapes))))
+        table = w.table[..., which].copy()
+        table[(table != oracle.INF32) & (rng.random(table.shape) < 0.3)] += 3
+        table[rng.random(table.shape) < 0.2] = oracle.INF32
+        shapes = np.ascontiguousarray(w.shapes[which])
+        cand = oracle.quantiles(oracle.all_candidates(table, shapes), 30)
+        h = B.alpa_dp_create(table, K, N, M, 5, shapes)
+        try:
+            for prune in (False, True):
+                T_ref, p_ref = oracle.solve_parallel(table, N, M, 5, shapes, cand, prune, 8)
+                flags = B.ALPA_DP_PRUNE if prune else 0
+                T, plan = B.alpa_dp_solve(h, cand, flags=flags)
+                assert np.array_equal(T, T_ref)
+                _plan_is(plan, p_ref)
+                _plan_is(B.alpa_dp_solve(h, cand, flags=flags, want_T=False)[1], p_ref)
+            _plan_is(B.alpa_dp_solve_sweep(h, cand, [5, 9])[0], oracle.solve_parallel(table, N, M, 5, shapes, cand, False, 8)[1])
+        finally:
+            B.alpa_dp_destroy(h)
