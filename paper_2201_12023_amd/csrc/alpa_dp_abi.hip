@@ -81,6 +81,7 @@ struct alpa_dp {
     int32_t *d_no_bounds = nullptr; // the same layout, saying nothing
     int32_t *d_bound_work = nullptr;
     bool have_bounds = false;       // of the present table: computed by the first solve that wants them
+    bool have_exact_bounds = false; // better ones for the band kernel, by the second one (launch_band_exact_bounds)
     PrepBuffers pb{};
     int32_t *d_distinct = nullptr;
     uint32_t *d_ncount = nullptr;   // [2]: distinct table values, distinct caller candidates
@@ -311,6 +312,14 @@ static int queue_bounds(alpa_dp *h)
                                   h->d_bounds));
     else
         HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
+    return ALPA_DP_OK;
+}
+
+// better ones, for tables that want them (launch_band_exact_bounds)
+static int queue_exact_bounds(alpa_dp *h)
+{
+    HIPCHK(launch_band_exact_bounds(h->stream, h->band_shapes, h->band, h->p, h->max_finite, h->d_bandrecs, h->d_bandends,
+                                    h->d_bound_work, h->d_bandthr, h->d_bounds));
     return ALPA_DP_OK;
 }
 
@@ -572,15 +581,16 @@ extern "C" int alpa_dp_restrict_equal_layers(alpa_dp_t *h)
         restore{prev, h->device};
     const int K = h->p.K, D = h->p.D, S = h->p.S;
     HIPCHK(launch_equal_layer_mask(h->stream, h->d_table, K, S));
-    // (a graph recorded after the first solve reads the bounds and does not compute them)
-    if (h->have_bounds) {
-        const int rcb = queue_bounds(h);
-        if (rcb) return rcb;
-    }
     if (h->band_ok)
         HIPCHK(launch_repack_band(h->stream, h->d_table, K, h->p.Smax, h->band_shapes, h->d_bandrecs, h->d_bandends));
     if (h->fast_ok) {
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
+    }
+    // (a graph recorded after the first solve reads the bounds and does not compute them)
+    if (h->have_bounds) {
+        int rcb = queue_bounds(h);
+        if (!rcb && h->have_exact_bounds) rcb = queue_exact_bounds(h);
+        if (rcb) return rcb;
     }
     // the candidate list changes with the table; the running best belonged to the old one
     int rc = queue_table_candidates(h);
@@ -702,7 +712,8 @@ static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool one_per_cu, b
     return rb;
 }
 
-// Does a solve of at most `bound` candidates use the table's bounds?  The band kernel lives on them.  For the
+// Does a solve of at most `bound` candidates use the table's bounds?  The band kernel lives on them (and gets better ones with
+// the second solve, where the table wants them: band_exact_bounds_kernel).  For the
 // others they cost the first solve that does a launch per stage count (3.3 to 6 us each), and save what is left out of the
 // recurrence, on every solve.  A small problem's first solve goes without (us before there were bounds, with them, without):
 //   12 layers on 1 x 8, all 475    105, 108,  97         48 on 1 x 2, all 2705    102, 115, 109
@@ -781,6 +792,10 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         const int rc = queue_bounds(h);
         if (rc) return rc;
         h->have_bounds = !recorded;                // (recorded, they are there only after the graph's replay)
+    } else if (h->band_ok && !h->have_exact_bounds) {
+        const int rc = queue_exact_bounds(h);
+        if (rc) return rc;
+        h->have_exact_bounds = !recorded;
     }
     HIPCHK(launch_refine_begin(st, rq, h->d_cand, h->d_state, rb));
     HIPCHK(hipEventRecord(h->ev[1], st));

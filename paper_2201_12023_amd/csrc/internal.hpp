@@ -172,8 +172,8 @@ __host__ __device__ __forceinline__ int32_t band_threshold(int32_t max_finite, i
     return (int32_t)(((int64_t)max_finite * (32 - ((j - 1) & 15)) >> 5) >> ((j - 1) >> 4)) + 1;
 }
 // behind the bounds (launch_band_bounds): a lower bound on F for each threshold and the least largest stage; then the sum and the
-// largest latency of a plan for each
-constexpr int BAND_TOTALS = 3 * BAND_THRESHOLDS + 1;
+// largest latency of a plan for each, and room for 2 BAND_THRESHOLDS + 1 more
+constexpr int BAND_TOTALS = 5 * BAND_THRESHOLDS + 2;
 
 // Rounds of evaluation (kernels_refine.hip)
 constexpr int REFINE_MAX_KNOTS = 4096;   // knots a refinement step takes in (LDS)
@@ -295,6 +295,8 @@ size_t band_least_ints(int K, int S);
 size_t band_thresholds_ints(int K, int D);
 hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
                               int32_t *work, int32_t *thr, int32_t *bounds);
+hipError_t launch_band_exact_bounds(hipStream_t st, const BandShapes &b, const BandShape &shape, const Problem &p, int32_t max_finite,
+                                    const int32_t *recs, const int32_t *ends, int32_t *work, const int32_t *thr, int32_t *bounds);
 hipError_t launch_recurrence_band(hipStream_t st, const FastArgs &f, const BandShape &b, const int32_t *recs,
                                   const int32_t *ends, const int32_t *thr, int32_t max_finite, int mode, int grid);
 

@@ -421,7 +421,10 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void band_thresholds_kernel(cons
         if (j < BAND_THRESHOLDS) band_fronts<RS, G, false>(least, sizes, K, D, S, SP, c, lds);
         else band_fronts<RS, G, true>(least, sizes, K, D, S, SP, c, lds);
         if (threadIdx.x == 0) totals[j] = min(lds[K * R + RS + D], DEV_INF);
-        if (j == BAND_THRESHOLDS) return;
+        if (j == BAND_THRESHOLDS) {
+            if (threadIdx.x == 0) plans[2 * BAND_THRESHOLDS] = 0;      // (band_bounds_kernel counts there)
+            return;
+        }
         for (int x = threadIdx.x; x < K * RS; x += blockDim.x) {
             const int k = x / RS, d = x - k * RS + 1;
             fronts[(size_t)j * K * RS + x] = k >= 1 && d < D ? min(lds[k * R + RS + D - d], DEV_INF) : DEV_INF;
@@ -436,25 +439,6 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void band_thresholds_kernel(cons
     else band_find_windows<4>(least, sizes, K, D, S, SP, c, (uint16_t *)lds, windows + 64 * w);
 }
 
-// bounds as launch_table_bounds writes them: no later layer is below the least plan without a filter; the number of
-// stages of a plan at the smallest t_max is not known.
-__global__ __launch_bounds__(256) void band_bounds_kernel(Problem p, int32_t max_finite, const int32_t *__restrict__ totals,
-                                                          int32_t *__restrict__ bounds)
-{
-    __shared__ int32_t flat;
-    if (threadIdx.x == 0) flat = DEV_INF;
-    __syncthreads();
-    for (int j = threadIdx.x; j < BAND_THRESHOLDS; j += blockDim.x)
-        if (totals[j] == totals[0]) atomicMin(&flat, band_threshold(max_finite, j));
-    __syncthreads();
-    for (int s = threadIdx.x; s <= p.Smax; s += blockDim.x) bounds[s] = totals[0];
-    if (threadIdx.x == 0) {
-        bounds[p.Smax + 1] = totals[BAND_THRESHOLDS];
-        bounds[p.Smax + 2] = -1;
-        bounds[p.Smax + 3] = flat;
-    }
-}
-
 static int band_row_ints(int D);
 
 size_t band_least_ints(int K, int S) { return (size_t)K * K * ((S + 15) / 16 * 16); }
@@ -463,51 +447,32 @@ size_t band_thresholds_ints(int K, int D)
     return (size_t)BAND_THRESHOLDS * (K * band_row_ints(D) + 64);
 }
 
-// work: band_least_ints; thr: band_thresholds_ints (fronts, windows); behind the bounds: BAND_TOTALS (totals, plans)
-hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
-                              int32_t *work, int32_t *thr, int32_t *bounds)
-{
-    int32_t *totals = bounds + table_bounds_ints(p), *plans = totals + BAND_THRESHOLDS + 1;
-    const int SP = (b.S + 15) / 16 * 16, RS = band_row_ints(p.D);
-    int32_t *windows = thr + (size_t)BAND_THRESHOLDS * p.K * RS;
-    hipLaunchKernelGGL(band_least_kernel, dim3(std::min((p.K * p.K * SP + 255) / 256, 16384)), dim3(256), 0, st, table, p.K,
-                       p.Smax, b, SP, work);
-    const size_t lds = std::max((size_t)band_front_ints(p.K, RS) * 4, (size_t)2 * p.K * (p.K | 1));
-    const auto kernel = p.D <= 16 ? band_thresholds_kernel<64, 4> : p.D <= 32 ? band_thresholds_kernel<64, 2> :
-                        RS == 64 ? band_thresholds_kernel<64, 1> : RS == 128 ? band_thresholds_kernel<128, 1> : band_thresholds_kernel<256, 1>;
-    if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(kernel, dim3(2 * BAND_THRESHOLDS + 1), dim3(WAVE * BAND_WAVES), lds, st, work, table, b, p.K, p.D, SP,
-                       max_finite, thr, totals, plans, windows);
-    hipLaunchKernelGGL(band_bounds_kernel, dim3(1), dim3(256), 0, st, p, max_finite, totals, bounds);
-    return hipGetLastError();
-}
-
 // rows U .. U + 3 of batch J of a unit (f[r]: the unit's operand row r)
-template <int U, int J>
+template <bool MAXIMUM>
+__device__ __forceinline__ int32_t band_term(int32_t t, int32_t f) { return MAXIMUM ? max(t, f) : t + f; }
+template <int U, int J, bool MAXIMUM>
 __device__ __forceinline__ void band_update(int32_t (&acc)[8], int32_t t, const int32_t (&f)[15])
 {
     // four rows at a time: eight sums in flight before their minima
-    const int32_t x0 = band_entry<U>(t) + f[U + 2 * J], y0 = band_entry<U + 8>(t) + f[U + 2 * J + 1];
-    const int32_t x1 = band_entry<U + 1>(t) + f[U + 2 * J + 1], y1 = band_entry<U + 9>(t) + f[U + 2 * J + 2];
-    const int32_t x2 = band_entry<U + 2>(t) + f[U + 2 * J + 2], y2 = band_entry<U + 10>(t) + f[U + 2 * J + 3];
-    const int32_t x3 = band_entry<U + 3>(t) + f[U + 2 * J + 3], y3 = band_entry<U + 11>(t) + f[U + 2 * J + 4];
+    constexpr auto term = band_term<MAXIMUM>;
+    const int32_t x0 = term(band_entry<U>(t), f[U + 2 * J]), y0 = term(band_entry<U + 8>(t), f[U + 2 * J + 1]);
+    const int32_t x1 = term(band_entry<U + 1>(t), f[U + 2 * J + 1]), y1 = term(band_entry<U + 9>(t), f[U + 2 * J + 2]);
+    const int32_t x2 = term(band_entry<U + 2>(t), f[U + 2 * J + 2]), y2 = term(band_entry<U + 10>(t), f[U + 2 * J + 3]);
+    const int32_t x3 = term(band_entry<U + 3>(t), f[U + 2 * J + 3]), y3 = term(band_entry<U + 11>(t), f[U + 2 * J + 4]);
     acc[U] = min(acc[U], min(x0, y0));
     acc[U + 1] = min(acc[U + 1], min(x1, y1));
     acc[U + 2] = min(acc[U + 2], min(x2, y2));
     acc[U + 3] = min(acc[U + 3], min(x3, y3));
 }
 
-template <int J>
+template <int J, bool MAXIMUM>
 __device__ __forceinline__ unsigned band_batch(int32_t (&acc)[8], int32_t t, const int32_t (&f)[15], int32_t c)
 {
     const bool pass = t <= c;
     if (__ballot(pass) == 0) return 0;
     const int32_t tv = pass ? t : DEV_INF;
-    band_update<0, J>(acc, tv, f);
-    band_update<4, J>(acc, tv, f);
+    band_update<0, J, MAXIMUM>(acc, tv, f);
+    band_update<4, J, MAXIMUM>(acc, tv, f);
     return 16;
 }
 
@@ -555,9 +520,13 @@ typedef int32_t band_v4 __attribute__((ext_vector_type(4)));
 // RS: int32 per F row (device counts of the size class).  NF: front costs that a thread keeps in registers (0: read
 // them in every layer).  DUMP: store every layer to F_all (plan recovery: entry j of the list is candidate j itself,
 // and only what the walk back from layer s_top_p[j] can reach is computed).  COUNT: tally the executed updates.
-template <int RS, int NF, bool DUMP, bool COUNT>
-__global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(BandArgs a)
+// TABLE: no candidate but the table itself, without a filter, in all its layers; F(s, 1, D) goes to a.Fmin[s - 1]
+// (TABLE_MAX: with the largest stage instead of the sum).
+enum BandMode { BAND_RUN, BAND_COUNT, BAND_DUMP, BAND_TABLE, BAND_TABLE_MAX };
+template <int RS, int NF, BandMode MODE>
+__device__ __forceinline__ void band_recurrence(const BandArgs &a)
 {
+    constexpr bool DUMP = MODE == BAND_DUMP, COUNT = MODE == BAND_COUNT, TABLE = MODE >= BAND_TABLE, MAXIMUM = MODE == BAND_TABLE_MAX;
     extern __shared__ __attribute__((aligned(16))) int32_t lds[];
     __shared__ int32_t sh_tk[1];
     __shared__ int32_t sh_skip[BAND_WAVES];
@@ -580,24 +549,24 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(Band
     const int lg_q = 32 - __builtin_clz((S - 1) | 1), per = WAVE >> lg_q, nh = (NHB + per - 1) / per, chunks = a.b.W * nh;
     const uint32_t inv_nh = 65536 / nh + 1, inv_chunks = (1u << 20) / chunks + 1;  // x / nh, x / chunks for what is divided here
     const int q_of_lane = lane & ((1 << lg_q) - 1), size_q = a.sizes[min(q_of_lane, S - 1)];
-    const int n = __builtin_amdgcn_readfirstlane(*a.n_list_p);
+    const int n = TABLE ? 1 : __builtin_amdgcn_readfirstlane(*a.n_list_p);
     if (n <= a.n_lo || n > a.n_hi) return;                                 // the other form's share (whole grid)
     unsigned long long rows_total = 0;
     // A unit of several blocks reads past the last buffer where a block has no such unit: its t_intra are
     // +infinity there, and what they are added to may be any number from 0 to +infinity (so may the work lists).
     for (int x = NO_CELL + tid; x < a.b.lens_at; x += nt) lds[x] = DEV_INF;
     __syncthreads();
-    const int32_t least_total = a.s_bound[0];                 // of any plan
+    const int32_t least_after_1 = DUMP || TABLE ? 0 : a.s_bound[1];         // of any plan of more than one stage
     const int32_t thr_lo = band_threshold(a.max_finite, min(lane, BAND_THRESHOLDS - 1));
     const int32_t thr_hi = band_threshold(a.max_finite, min(lane + WAVE, BAND_THRESHOLDS - 1));
 
     // The first candidate goes by the workgroup's number, the others are drawn.
-    for (int tk = blockIdx.x; tk < n; tk = (int)gridDim.x + draw_ticket(a.ticket, tid, sh_tk)) {
+    for (int tk = TABLE ? 0 : blockIdx.x; tk < n; tk = TABLE ? 1 : (int)gridDim.x + draw_ticket(a.ticket, tid, sh_tk)) {
         const int pos = a.descending ? n - 1 - tk : tk;
-        const int j = DUMP ? pos : __builtin_amdgcn_readfirstlane(a.list[pos]);
-        const int32_t c_given = __builtin_amdgcn_readfirstlane(a.cand[j]);
+        const int j = TABLE ? 0 : DUMP ? pos : __builtin_amdgcn_readfirstlane(a.list[pos]);
+        const int32_t c_given = TABLE ? DEV_INF : __builtin_amdgcn_readfirstlane(a.cand[j]);
         const int32_t c = min(c_given, DEV_INF - 1);   // the sentinel entries pass no candidate
-        if (a.prune) {
+        if (!DUMP && !TABLE && a.prune) {
             sh_skip[wid] = band_can_skip(a.chunk_min, j, c_given, a.p.B, lane) ? 1 : 0;
             __syncthreads();
             const int skip = __builtin_amdgcn_readfirstlane(sh_skip[0]);
@@ -673,7 +642,10 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(Band
             }
             made = s0 + ln - 1;
         };
+        // least plan of more stages than s0 + l, in lanes 32 + l
+        auto bounds_of = [&](int s0) { return DUMP || TABLE ? 0 : a.s_bound[min(s0 + (lane & 31), a.p.Smax)]; };
         const int ln2 = min(a.b.ahead, s_top - 1);
+        const int32_t bounds2 = bounds_of(2);
         // what is known of the lowest threshold that is not below the candidate (thresholds descend; the first has no filter)
         const int thr_at = max(0, min((int)(__popcll(__ballot(thr_lo >= c)) + __popcll(__ballot(lane + WAVE < BAND_THRESHOLDS && thr_hi >= c))), BAND_THRESHOLDS) - 1);
         const int32_t *w = a.thr + (size_t)BAND_THRESHOLDS * K * RS + 64 * thr_at;
@@ -681,7 +653,7 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(Band
         if (tid < 2) sh_least[tid] = DEV_INF;
         const int32_t *const fronts = a.thr + (size_t)thr_at * K * RS;
         int32_t front[NF ? NF : 1];                    // front costs of cells tid, tid + nt, ..
-        if (!DUMP) {
+        if (!DUMP && !TABLE) {
 #pragma unroll
             for (int x = 0; x < NF; ++x) front[x] = fronts[min(tid + x * nt, K * RS - 1)];
         }
@@ -703,11 +675,12 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(Band
             const int end = band_row(last + 1, RS) >> 2;
             for (int x = tid; x < end; x += by) p[x] = make_int4(DEV_INF, DEV_INF, DEV_INF, DEV_INF);
         };
-        // after layer s: does it end here?
-        auto finished = [&](int s, int F) {
+        // after layer s: does it end here?  (`least`: of any plan of more stages)
+        auto finished = [&](int s, int F, int32_t least) {
             const int32_t f1 = __builtin_amdgcn_readfirstlane(lds[F + D - 1]);     // F(s, first layer, all devices)
             if (f1 < best) { best = f1; sbest = s; }   // lowest s on ties
-            return !DUMP && least_total >= best;
+            if (TABLE && tid == 0) a.Fmin[s - 1] = min(f1, DEV_INF);
+            return !DUMP && !TABLE && least >= best;
         };
         // Can no plan that goes on from layer s be below what there is?  (A barrier; uniform.)
         auto hopeless = [&](int s, int F) {
@@ -741,7 +714,8 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(Band
         // The wave's units, in order over the layers: a layer's share goes through a ring of UNITS_AHEAD loads in
         // whole rounds, filled up with empty units.  w_A, w_B: up to 64 units of the share, a lane each.
         int w_base = 2;                                // first layer of the lists
-        int w_counts = n_units[min(lane, a.b.ahead - 1)];      // lane l: units of layer w_base + l
+        int w_counts = lane < 32 ? n_units[min(lane, a.b.ahead - 1)] : bounds2;    // lane l: units of layer w_base + l; and bounds
+        int b_base = 2;                                // layer of the first bound
         int w_A = 0, w_B = 0, w_at = 0, w_first = 0, w_end = 0;
         uint32_t w_layer = 0;                          // where the layer's records begin (in bytes)
         const uint32_t lane_16 = (lane & 15) << 4, lane_128 = (lane >> 4) << 7;
@@ -771,9 +745,9 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(Band
         };
 
         int Fp = BUF, Fn = a.b.nbuf > 2 ? 2 * BUF : 0, Fc = 0;     // buffers of layers s - 1, s and (to be) s + 1
-        bool done = s_top < 1 || finished(1, Fp);
+        bool done = s_top < 1 || finished(1, Fp, least_after_1);
         if (s_top < 2) done = true;
-        if (!DUMP && !done && best < DEV_INF) done = hopeless(1, Fp);
+        if (!DUMP && !TABLE && !done && best < DEV_INF) done = hopeless(1, Fp);
         int rounds = 0;                                // of layer s; its first units are in the ring
         if (!done) {
             rounds = enter(2);
@@ -783,12 +757,17 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(Band
         for (int s = 2; !done; ++s) {
             if (s > made) {
                 const int ln = min(a.b.ahead, s_top - s + 1);
+                int32_t bounds = w_counts;
+                if (s + ln > b_base + 32) {
+                    b_base = s;
+                    bounds = bounds_of(s);
+                }
                 build_lens(s, ln);
                 lds_barrier();
                 build_lists(s, ln);
                 lds_barrier();
                 w_base = s;
-                w_counts = n_units[min(lane, a.b.ahead - 1)];
+                w_counts = lane < 32 ? n_units[min(lane, a.b.ahead - 1)] : bounds;
                 rounds = enter(s);
 #pragma unroll
                 for (int x = 0; x < UNITS_AHEAD; ++x) load(x);
@@ -842,10 +821,10 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(Band
                             for (int r = 9; r < 15; ++r) f[r] = f1[r * RS];
                         }
                         // (one `if` behind the other: where they nest the accumulators are copied at every join)
-                        unsigned did = band_batch<0>(acc, tt.x, f, c);
-                        if ((A & 12) != 0) did += band_batch<1>(acc, tt.y, f, c);
-                        if ((A & 8) != 0) did += band_batch<2>(acc, tt.z, f, c);
-                        if ((A & 8) != 0) did += band_batch<3>(acc, tt.w, f, c);
+                        unsigned did = band_batch<0, MAXIMUM>(acc, tt.x, f, c);
+                        if ((A & 12) != 0) did += band_batch<1, MAXIMUM>(acc, tt.y, f, c);
+                        if ((A & 8) != 0) did += band_batch<2, MAXIMUM>(acc, tt.z, f, c);
+                        if ((A & 8) != 0) did += band_batch<3, MAXIMUM>(acc, tt.w, f, c);
                         if (COUNT) rows += did;
                     }
                     load(x);
@@ -858,8 +837,8 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(Band
                 if (DUMP) dump(s - 1, Fp);
             }
             lds_barrier();
-            done = finished(s, Fn) || s == s_top;
-            if (!DUMP && !done && best < DEV_INF) done = hopeless(s, Fn);
+            done = finished(s, Fn, DUMP || TABLE ? 0 : __builtin_amdgcn_readlane(w_counts, 32 + s - b_base)) || s == s_top;
+            if (!DUMP && !TABLE && !done && best < DEV_INF) done = hopeless(s, Fn);
             if (a.b.nbuf > 2) {
                 const int f = Fp;
                 Fp = Fn; Fn = Fc; Fc = f;
@@ -873,6 +852,7 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(Band
             }
         }
         if (DUMP && s_top >= 1 && wid < nw / 2) dump(s_top, Fp);
+        if (TABLE) return;
         const int slot = wid == 0 ? j : a.dummy_idx;   // wave 0 owns the result
         a.Fmin[slot] = best;                           // all lanes, same value
         a.Sbest[slot] = best >= DEV_INF ? 0 : sbest;
@@ -882,6 +862,157 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(Band
         __syncthreads();                               // LDS is reused by the next candidate
     }
     if (COUNT) atomicAdd(a.wave_relax, lane == 0 ? rows_total : 0ull);
+}
+
+template <int RS, int NF, bool DUMP, bool COUNT>
+__global__ __launch_bounds__(WAVE * BAND_WAVES) void recurrence_band_kernel(BandArgs a)
+{
+    band_recurrence<RS, NF, DUMP ? BAND_DUMP : COUNT ? BAND_COUNT : BAND_RUN>(a);
+}
+
+// the least sum of the thresholds' plans
+__device__ __forceinline__ int32_t band_best_plan(const int32_t *plans)
+{
+    int32_t best = DEV_INF;
+    for (int j = threadIdx.x & (WAVE - 1); j < BAND_THRESHOLDS; j += WAVE) best = min(best, plans[2 * j]);
+    return wave_min_i32(best);
+}
+
+// Do the thresholds say little?  Then their best plan is far above P(K, D) without a filter (latencies without any order).
+__device__ __forceinline__ bool band_bounds_poor(const int32_t *totals, int32_t best)
+{
+    return totals[0] < DEV_INF && best - totals[0] > (totals[0] >> 2);
+}
+
+// A plan of threshold j that is a real one, walked from its last stage on: how many stages lie behind each is known now, so every
+// step takes the term that is least with the t_intra it really has in front of P.  plan[0] = the sum, plan[1] = the largest; as they
+// were if it ends nowhere.
+__device__ __forceinline__ void band_real_plan(const int32_t *__restrict__ table, const BandShapes &bs, const Problem &p, int32_t c,
+                                               const int32_t *__restrict__ front, int RS, int32_t *plan)
+{
+    __shared__ unsigned long long sh_term[2];
+    const int K = p.K, tid = threadIdx.x, nt = blockDim.x;
+    if (tid < 2) sh_term[tid] = ~0ull;
+    __syncthreads();
+    int k = K, d = p.D;
+    int32_t sum = 0, largest = 0;
+    for (int n = 0; k > 0; ++n) {                  // (uniform: every thread walks the same plan)
+        unsigned long long at = ~0ull;             // sum of the term and P, first layer, shape
+        for (int b = tid >> 4; b < k; b += nt / 16)
+            for (int q = tid & 15; q < bs.S; q += 16) {
+                const int left = d - bs.sizes[q];  // P(b, left); no layer in front takes no device
+                if (left < 0) continue;
+                const int32_t f = b > 0 ? front[b * RS + p.D - left - 1] : left == 0 ? 0 : DEV_INF;
+                const int32_t t = band_smallest(table + ((size_t)n * K * K + b * K + k - 1) * bs.S_table, bs, q);
+                if (f < DEV_INF && t <= c) at = min(at, (unsigned long long)(t + f) << 32 | (unsigned)(b * 64 + q));
+            }
+        if (at != ~0ull) atomicMin(&sh_term[n & 1], at);
+        __syncthreads();
+        const unsigned long long x = sh_term[n & 1];
+        if (x == ~0ull) return;
+        const int b = (int)((uint32_t)x >> 6), q = (int)(x & 63);
+        if (tid == 0) sh_term[~n & 1] = ~0ull;     // (last read a barrier ago)
+        const int32_t t = band_smallest(table + ((size_t)n * K * K + b * K + k - 1) * bs.S_table, bs, q);
+        k = b;
+        d -= bs.sizes[q];
+        sum += t;
+        largest = max(largest, t);
+        __syncthreads();
+    }
+    if (tid == 0) {
+        plan[0] = sum;
+        plan[1] = largest;
+    }
+}
+
+// Bounds as launch_table_bounds writes them, from the thresholds: no plan of any number of stages is below P(K, D) without a filter,
+// and the number of stages of a plan at the smallest t_max is not known.  From where on F hardly changes: the lowest threshold
+// with that least sum, if the plan that reaches it is a real one (-1 for the stages).  Where it is not (a stage does not fit
+// with many behind it, stages of equal layers, latencies without any order) it is the largest stage of the best plan (-2: a
+// guess), and nowhere if that is far above.  If no threshold has a real plan, a workgroup for each looks for one, and
+// the last to end writes the bounds: 48 layers on 32 x 8 with little memory have P 41184, plans of 41412 are found, the best of all is
+// 41382 (the plan alone out of 300 candidates: 2050 us without a known plan, 606 with).
+constexpr int BAND_BOUNDS_THREADS = 512;
+__global__ __launch_bounds__(BAND_BOUNDS_THREADS) void band_bounds_kernel(Problem p, int32_t max_finite, const int32_t *__restrict__ table,
+                                                                          BandShapes bs, const int32_t *__restrict__ fronts, int RS,
+                                                                          const int32_t *__restrict__ totals, int32_t *plans,
+                                                                          int32_t *__restrict__ bounds)
+{
+    __shared__ int32_t flat, own[2];
+    __shared__ int last;
+    const int tid = threadIdx.x, j = blockIdx.x;
+    int32_t *const n_ended = plans + 2 * BAND_THRESHOLDS, *const real = n_ended + 1;
+    int32_t best = band_best_plan(plans);          // (nobody writes the plans before all have read them)
+    const bool none = totals[0] < DEV_INF && best >= DEV_INF;
+    if (!none && j > 0) return;
+    if (none) {
+        if (tid < 2) own[tid] = DEV_INF;
+        __syncthreads();
+        if (totals[j] < DEV_INF)
+            band_real_plan(table, bs, p, band_threshold(max_finite, j), fronts + (size_t)j * p.K * RS, RS, own);
+        __syncthreads();
+        if (tid == 0) {
+            __hip_atomic_store(&real[2 * j], own[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&real[2 * j + 1], own[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last = __hip_atomic_fetch_add(n_ended, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == BAND_THRESHOLDS - 1;
+        }
+        __syncthreads();
+        if (!last) return;
+        for (int x = tid; x < 2 * BAND_THRESHOLDS; x += BAND_BOUNDS_THREADS)
+            plans[x] = __hip_atomic_load(&real[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        best = band_best_plan(plans);
+    }
+    const bool reached = totals[0] >= DEV_INF || plans[0] == totals[0], poor = band_bounds_poor(totals, best);
+    if (tid == 0) flat = DEV_INF;
+    __syncthreads();
+    if (tid < BAND_THRESHOLDS) {
+        if (reached && totals[tid] == totals[0]) atomicMin(&flat, band_threshold(max_finite, tid));
+        if (!reached && !poor && plans[2 * tid] == best) atomicMin(&flat, plans[2 * tid + 1]);
+    }
+    __syncthreads();
+    for (int s = tid; s <= p.Smax; s += BAND_BOUNDS_THREADS) bounds[s] = totals[0];
+    if (tid == 0) {
+        bounds[p.Smax + 1] = totals[BAND_THRESHOLDS];
+        bounds[p.Smax + 2] = reached ? -1 : -2;
+        bounds[p.Smax + 3] = flat;
+    }
+}
+
+// Where the thresholds say little, the recurrence itself without a filter, through all its layers, in two workgroups: one for the
+// sum, one for the largest stage.  That takes 0.4 (64 layers on 8 x 8) to 2 ms (48 on 32 x 8), so it is done for a table that is
+// solved a second time.  (Random latencies, us, later solves with and without: 64 layers on 8 x 8, 4096 candidates 205 and
+// 2309; 48 on 32 x 8, 300 candidates, the plan alone 405 and 1499.)
+template <int RS>
+__global__ __launch_bounds__(WAVE * BAND_WAVES) void band_exact_bounds_kernel(BandArgs a, const int32_t *__restrict__ totals,
+                                                                             const int32_t *__restrict__ plans, int32_t *__restrict__ bounds)
+{
+    const int Smax = a.p.Smax, tid = threadIdx.x;
+    if (!band_bounds_poor(totals, band_best_plan(plans))) return;
+    if (blockIdx.x == 0) {
+        band_recurrence<RS, 0, BAND_TABLE>(a);
+        __syncthreads();
+        // bounds[s]: the least of more than s stages.  From the least of all on F does not change: no stage is larger.
+        int32_t m = DEV_INF;
+        if (tid <= Smax) {
+            for (int x = tid; x < Smax; ++x) m = min(m, a.Fmin[x]);
+            bounds[tid] = m;
+        }
+        if (tid == 0) bounds[Smax + 3] = m;
+    } else {
+        a.Fmin = a.Sbest;
+        band_recurrence<RS, 0, BAND_TABLE_MAX>(a);
+        __syncthreads();
+        if (tid == 0) {
+            int32_t g = DEV_INF, sg = 0;
+            for (int x = 0; x < Smax; ++x) {
+                const int32_t v = a.Sbest[x];
+                if (v < g) { g = v; sg = x + 1; }
+            }
+            bounds[Smax + 1] = g;
+            bounds[Smax + 2] = sg;
+        }
+    }
 }
 
 // F rows of the size class that holds D devices (0: none does)
@@ -921,6 +1052,51 @@ BandShape band_shape(int K, int D, int S, const int32_t *sizes)
         }
     }
     return b;
+}
+
+// work: band_least_ints; thr: band_thresholds_ints (fronts, windows); behind the bounds: BAND_TOTALS (totals, plans)
+hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
+                              int32_t *work, int32_t *thr, int32_t *bounds)
+{
+    int32_t *totals = bounds + table_bounds_ints(p), *plans = totals + BAND_THRESHOLDS + 1;
+    const int SP = (b.S + 15) / 16 * 16, RS = band_row_ints(p.D);
+    int32_t *windows = thr + (size_t)BAND_THRESHOLDS * p.K * RS;
+    hipLaunchKernelGGL(band_least_kernel, dim3(std::min((p.K * p.K * SP + 255) / 256, 16384)), dim3(256), 0, st, table, p.K,
+                       p.Smax, b, SP, work);
+    const size_t lds = std::max((size_t)band_front_ints(p.K, RS) * 4, (size_t)2 * p.K * (p.K | 1));
+    const auto kernel = p.D <= 16 ? band_thresholds_kernel<64, 4> : p.D <= 32 ? band_thresholds_kernel<64, 2> :
+                        RS == 64 ? band_thresholds_kernel<64, 1> : RS == 128 ? band_thresholds_kernel<128, 1> : band_thresholds_kernel<256, 1>;
+    if (lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, dim3(2 * BAND_THRESHOLDS + 1), dim3(WAVE * BAND_WAVES), lds, st, work, table, b, p.K, p.D, SP,
+                       max_finite, thr, totals, plans, windows);
+    hipLaunchKernelGGL(band_bounds_kernel, dim3(BAND_THRESHOLDS), dim3(BAND_BOUNDS_THREADS), 0, st, p, max_finite, table, b, thr, RS,
+                       totals, plans, bounds);
+    return hipGetLastError();
+}
+
+// behind launch_band_bounds of the same table, with the same arrays
+hipError_t launch_band_exact_bounds(hipStream_t st, const BandShapes &b, const BandShape &shape, const Problem &p, int32_t max_finite,
+                                    const int32_t *recs, const int32_t *ends, int32_t *work, const int32_t *thr, int32_t *bounds)
+{
+    const int32_t *totals = bounds + table_bounds_ints(p), *plans = totals + BAND_THRESHOLDS + 1;
+    const int RS = band_row_ints(p.D);
+    BandArgs a{p, shape, -1, INT32_MAX, recs, ends, b.sizes};
+    a.p.S = b.S;
+    a.Fmin = work;
+    a.Sbest = work + p.Smax;
+    a.thr = thr;
+    a.max_finite = max_finite;
+    const auto kernel = RS == 64 ? band_exact_bounds_kernel<64> : RS == 128 ? band_exact_bounds_kernel<128> : band_exact_bounds_kernel<256>;
+    const size_t lds = (size_t)shape.lds_ints * 4;
+    if (lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, dim3(2), dim3(WAVE * BAND_WAVES), lds, st, a, totals, plans, bounds);
+    return hipGetLastError();
 }
 
 template <int RS, int NF, bool DUMP, bool COUNT>

@@ -84,9 +84,11 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
                                                                   int32_t *__restrict__ list)
 {
     __shared__ int sh_end, sh_first;
-    __shared__ int32_t sh_sum[BAND_THRESHOLDS], sh_x[BAND_THRESHOLDS], sh_c[BAND_THRESHOLDS], sh_lo[BAND_THRESHOLDS];
+    constexpr int PLANS = BAND_THRESHOLDS + 2;
+    __shared__ int32_t sh_sum[PLANS], sh_x[PLANS], sh_c[PLANS], sh_lo[PLANS];
     const int C = state->n_cand;
     const int64_t t_feas = rq.bounds[rq.Smax + 1], stages = rq.bounds[rq.Smax + 2];
+    const int32_t least_of_all = rq.bounds[0], flat = rq.bounds[rq.Smax + 3];
     int lo = 0, hi = C;                                // first index with a negative value
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
@@ -106,29 +108,38 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
     __syncthreads();
     if ((rq.prune || rq.plan_only) && rq.thr && j0 < n) {
         // Plans are known (of sum s and largest stage m: T* of the first candidate c that is not below m is at
-        // most s + (B - 1) c), and for every candidate a lower bound on F.
-        for (int t = threadIdx.x; t < BAND_THRESHOLDS; t += RF_THREADS) {
-            const int32_t sum = rq.thr[BAND_THRESHOLDS + 1 + 2 * t], largest = rq.thr[BAND_THRESHOLDS + 2 + 2 * t];
-            const int32_t above = band_threshold(rq.max_finite, t + 1 < BAND_THRESHOLDS ? t + 1 : t);
+        // most s + (B - 1) c), and for every candidate a lower bound on F.  Where the bounds come from the recurrence itself, so
+        // are one of `stages` stages up to t_feas, and the least of all, whose stages are at most their sum.
+        for (int t = threadIdx.x; t < PLANS; t += RF_THREADS) {
+            const int j = min(t, BAND_THRESHOLDS - 1);
+            int32_t sum = rq.thr[BAND_THRESHOLDS + 1 + 2 * j], largest = rq.thr[BAND_THRESHOLDS + 2 + 2 * j];
+            if (t >= BAND_THRESHOLDS) {
+                const bool feas = t == BAND_THRESHOLDS;
+                sum = stages < 0 ? DEV_INF : feas ? (int32_t)(stages * t_feas) : least_of_all;
+                largest = feas ? (int32_t)t_feas : least_of_all;
+            }
+            const int32_t above = band_threshold(rq.max_finite, j + 1 < BAND_THRESHOLDS ? j + 1 : j);
             const int x = first_at_least(cand, n, largest);
             sh_sum[t] = x < n ? sum : DEV_INF;
             sh_x[t] = min(x, n - 1);
             sh_c[t] = cand[min(x, n - 1)];
             // candidates that take threshold t: from sh_lo[t] on, up to the threshold
-            sh_lo[t] = max(j0, t + 1 < BAND_THRESHOLDS ? first_at_least(cand, n, above + 1) : 0);
+            sh_lo[t] = max(j0, j + 1 < BAND_THRESHOLDS ? first_at_least(cand, n, above + 1) : 0);
         }
         __syncthreads();
         const int lane = threadIdx.x & (WAVE - 1);
         for (int b = threadIdx.x >> 6; b < rq.n_B; b += RF_WAVES) {        // a wave per B value
             const int64_t B = rq.B_vals ? rq.B_vals[b] : rq.B;
             int64_t U = INF_I64;
-            for (int t = lane; t < BAND_THRESHOLDS; t += WAVE)
+            for (int t = lane; t < PLANS; t += WAVE)
                 if (sh_sum[t] < DEV_INF) U = min64(U, sh_sum[t] + (B - 1) * (int64_t)sh_c[t]);
             U = wave_min_i64(U);
-            int at = n;                                // the lowest candidate known to reach U
-            for (int t = lane; t < BAND_THRESHOLDS; t += WAVE)
-                if (sh_sum[t] < DEV_INF && sh_sum[t] + (B - 1) * (int64_t)sh_c[t] == U) at = min(at, sh_x[t]);
-            at = wave_min_i32(at);
+            int64_t lowest = (int64_t)n << 32;         // the lowest candidate known to reach U: its number, and its value
+            for (int t = lane; t < PLANS; t += WAVE)
+                if (sh_sum[t] < DEV_INF && sh_sum[t] + (B - 1) * (int64_t)sh_c[t] == U)
+                    lowest = min64(lowest, (int64_t)sh_x[t] << 32 | sh_c[t]);
+            lowest = wave_min_i64(lowest);
+            const int at = hi32(lowest);
             // with the early exit nothing behind the first B t_max >= U is looked at; where only the plan counts, nothing that
             // cannot get below U (nor reach it before `at`).  What is left out must not set the early exit off either: at
             // candidates in front of `at` it cannot, as their t_max is below that plan's largest stage and B t_max below U;
@@ -141,11 +152,11 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
                 const int stop = rq.prune ? max(at + 1, first_product(cand, at + 1, n, B, U)) : n;
                 end = stop;
                 if (rq.plan_only) {
-                    const int64_t in_front = rq.early_exit && B * (int64_t)cand[at] > U ? B * (int64_t)cand[at] : U;
+                    const int64_t in_front = rq.early_exit ? max(B * (int64_t)lo32(lowest), U) : U;
                     end = min(at + 1, n);
                     for (int t = lane; t < BAND_THRESHOLDS; t += WAVE) {
                         const int lo_t = sh_lo[t], hi_t = min(stop, t == 0 ? n : sh_lo[t - 1]);
-                        const int64_t least = rq.thr[t], most = lo_t < at ? in_front : U;
+                        const int64_t least = max(rq.thr[t], least_of_all), most = lo_t < at ? in_front : U;
                         if (lo_t >= hi_t || least >= DEV_INF || least + (B - 1) * (int64_t)cand[lo_t] > most) continue;
                         first = min(first, lo_t);
                         int x = lo_t, z = hi_t;        // first index that cannot get to `most`
@@ -184,17 +195,18 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
         __syncthreads();
     }
     const int end = sh_end;
-    // knots: evenly up to where the table says that F hardly changes any more, and the last candidate
+    // knots: evenly up to where the table says that F hardly changes any more, and the last candidate; where that is a guess,
+    // a quarter of them evenly behind it
     lo = j0; hi = max(j0, end - 1);
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if (cand[mid] >= rq.bounds[rq.Smax + 3]) hi = mid; else lo = mid + 1;
+        if (cand[mid] >= flat) hi = mid; else lo = mid + 1;
     }
-    const int span = lo + 1 - j0, rest = lo + 1 < end ? 1 : 0;
+    const int span = lo + 1 - j0, rest = min(end - 1 - lo, stages == -1 ? 1 : first_round / 4);
     const bool whole = end - j0 <= all;
     const int m = whole ? end - j0 : min(first_round, span + rest);
     for (int j = threadIdx.x; j < m; j += RF_THREADS) {
-        const int k = whole ? j0 + j : j == m - 1 && rest ? end - 1 : j0 + even_knot(j, m - rest, span);
+        const int k = whole ? j0 + j : j < m - rest ? j0 + even_knot(j, m - rest, span) : lo + even_knot(j - (m - rest) + 1, rest + 1, end - lo);
         list[j] = k;
         if (j < REFINE_MAX_KNOTS) knots[j] = k;
     }

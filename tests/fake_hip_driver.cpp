@@ -411,9 +411,15 @@ static void routes()
         CHECK(recorded == (c.by == 1), "%d layers on %dx%d, %d: bounds in the graph: %d", c.K, c.N, c.M, c.n, recorded);
         alpa_dp_destroy(h);
         h = create_problem(c.K, c.N, c.M);
+        const bool band = kernels_of(h, c.n).find("recurrence_band") != std::string::npos;
+        alpa_dp_destroy(h);
+        h = create_problem(c.K, c.N, c.M);
         for (int restricted = 0; restricted < 2; ++restricted) {
             for (int solve = 1; solve <= 3; ++solve) {
-                const bool found = bounds_in(kernels_of(h, c.n));
+                const std::string kernels = kernels_of(h, c.n);
+                const bool found = bounds_in(kernels), exact = kernels.find("band_exact_bounds") != std::string::npos;
+                CHECK(exact == (band && solve == 2 && !restricted), "%d layers on %dx%d, %d: solve %d, exact bounds %d", c.K, c.N,
+                      c.M, c.n, solve, exact);
                 CHECK(found == (solve == c.by && !restricted), "%d layers on %dx%d, %d: solve %d, bounds %d", c.K, c.N, c.M,
                       c.n, solve, found);
             }
