@@ -172,8 +172,9 @@ __host__ __device__ __forceinline__ int32_t band_threshold(int32_t max_finite, i
     return (int32_t)(((int64_t)max_finite * (32 - ((j - 1) & 15)) >> 5) >> ((j - 1) >> 4)) + 1;
 }
 // behind the bounds (launch_band_bounds): a lower bound on F for each threshold and the least largest stage; then the sum and the
-// largest latency of a plan for each, and room for 2 BAND_THRESHOLDS + 1 more
-constexpr int BAND_TOTALS = 5 * BAND_THRESHOLDS + 2;
+// largest latency of a plan for each, room for 2 BAND_THRESHOLDS + 1 more, and what is there for the present table: 1 for these
+// numbers, 2 and 4 for the two halves of launch_band_exact_bounds
+constexpr int BAND_THERE = 5 * BAND_THRESHOLDS + 2, BAND_TOTALS = BAND_THERE + 1;
 
 // Rounds of evaluation (kernels_refine.hip)
 constexpr int REFINE_MAX_KNOTS = 4096;   // knots a refinement step takes in (LDS)
@@ -290,13 +291,14 @@ size_t band_table_ints(int K, int Smax, int S);
 size_t band_ends_ints(int K, int Smax, int S);
 hipError_t launch_repack_band(hipStream_t st, const int32_t *table, int K, int Smax, const BandShapes &b,
                               int32_t *recs, int32_t *ends);
-// what the table says about candidates: launch_table_bounds' place for these sizes
+// what the table says about candidates: launch_table_bounds' place for these sizes; `once`: nothing is done where it is there
+// (a recorded solve is replayed)
 size_t band_least_ints(int K, int S);
 size_t band_thresholds_ints(int K, int D);
 hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
-                              int32_t *work, int32_t *thr, int32_t *bounds);
+                              int32_t *work, int32_t *thr, int32_t *bounds, bool once);
 hipError_t launch_band_exact_bounds(hipStream_t st, const BandShapes &b, const BandShape &shape, const Problem &p, int32_t max_finite,
-                                    const int32_t *recs, const int32_t *ends, int32_t *work, const int32_t *thr, int32_t *bounds);
+                                    const int32_t *recs, const int32_t *ends, int32_t *work, const int32_t *thr, int32_t *bounds, bool once);
 hipError_t launch_recurrence_band(hipStream_t st, const FastArgs &f, const BandShape &b, const int32_t *recs,
                                   const int32_t *ends, const int32_t *thr, int32_t max_finite, int mode, int grid);
 

@@ -163,9 +163,11 @@ __device__ __forceinline__ void lds_barrier()
 //     dense layers, t_max at the 5 % quantile: after 4 layers, 9 with the least F of more stages and no filter).
 // And without a filter: the least largest stage (no plan below that t_max), and the lowest threshold whose least plan
 // is that without a filter (from there on F hardly changes).  least[k][i][q]: q padded to a multiple of 16 (SP).
+// there (null: not asked): see BAND_THERE.
 __global__ void band_least_kernel(const int32_t *__restrict__ table, int K, int Smax, BandShapes b, int SP,
-                                  int32_t *__restrict__ least)
+                                  const int32_t *__restrict__ there, int32_t *__restrict__ least)
 {
+    if (there && *there) return;
     const int n = K * K * SP;
     for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
         const int ki = x / SP, q = x - ki * SP, k = ki / K, i = ki - k * K;
@@ -410,8 +412,10 @@ template <int RS, int G>
 __global__ __launch_bounds__(WAVE * BAND_WAVES) void band_thresholds_kernel(const int32_t *__restrict__ least, const int32_t *__restrict__ table,
                                                                BandShapes bs, int K, int D, int SP, int32_t max_finite,
                                                                int32_t *__restrict__ fronts, int32_t *__restrict__ totals,
-                                                               int32_t *__restrict__ plans, int32_t *__restrict__ windows)
+                                                               int32_t *__restrict__ plans, int32_t *__restrict__ windows,
+                                                               const int32_t *__restrict__ there)
 {
+    if (there && *there) return;
     extern __shared__ int32_t lds[];
     constexpr int R = 2 * RS + 1;
     const int j = blockIdx.x, S = bs.S;
@@ -936,8 +940,9 @@ constexpr int BAND_BOUNDS_THREADS = 512;
 __global__ __launch_bounds__(BAND_BOUNDS_THREADS) void band_bounds_kernel(Problem p, int32_t max_finite, const int32_t *__restrict__ table,
                                                                           BandShapes bs, const int32_t *__restrict__ fronts, int RS,
                                                                           const int32_t *__restrict__ totals, int32_t *plans,
-                                                                          int32_t *__restrict__ bounds)
+                                                                          int32_t *__restrict__ bounds, int once, int32_t *there)
 {
+    if (once && *there) return;                    // (nobody writes it before all have read it, as the plans below)
     __shared__ int32_t flat, own[2];
     __shared__ int last;
     const int tid = threadIdx.x, j = blockIdx.x;
@@ -976,6 +981,7 @@ __global__ __launch_bounds__(BAND_BOUNDS_THREADS) void band_bounds_kernel(Proble
         bounds[p.Smax + 1] = totals[BAND_THRESHOLDS];
         bounds[p.Smax + 2] = reached ? -1 : -2;
         bounds[p.Smax + 3] = flat;
+        *there = 1;
     }
 }
 
@@ -985,10 +991,11 @@ __global__ __launch_bounds__(BAND_BOUNDS_THREADS) void band_bounds_kernel(Proble
 // 2309; 48 on 32 x 8, 300 candidates, the plan alone 405 and 1499.)
 template <int RS>
 __global__ __launch_bounds__(WAVE * BAND_WAVES) void band_exact_bounds_kernel(BandArgs a, const int32_t *__restrict__ totals,
-                                                                             const int32_t *__restrict__ plans, int32_t *__restrict__ bounds)
+                                                                             const int32_t *__restrict__ plans, int32_t *__restrict__ bounds,
+                                                                             int once, int32_t *there)
 {
-    const int Smax = a.p.Smax, tid = threadIdx.x;
-    if (!band_bounds_poor(totals, band_best_plan(plans))) return;
+    const int Smax = a.p.Smax, tid = threadIdx.x, half = blockIdx.x == 0 ? 2 : 4;
+    if ((once && (*there & half)) || !band_bounds_poor(totals, band_best_plan(plans))) return;
     if (blockIdx.x == 0) {
         band_recurrence<RS, 0, BAND_TABLE>(a);
         __syncthreads();
@@ -1013,6 +1020,7 @@ __global__ __launch_bounds__(WAVE * BAND_WAVES) void band_exact_bounds_kernel(Ba
             bounds[Smax + 2] = sg;
         }
     }
+    if (tid == 0) atomicOr(there, half);
 }
 
 // F rows of the size class that holds D devices (0: none does)
@@ -1056,13 +1064,14 @@ BandShape band_shape(int K, int D, int S, const int32_t *sizes)
 
 // work: band_least_ints; thr: band_thresholds_ints (fronts, windows); behind the bounds: BAND_TOTALS (totals, plans)
 hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
-                              int32_t *work, int32_t *thr, int32_t *bounds)
+                              int32_t *work, int32_t *thr, int32_t *bounds, bool once)
 {
-    int32_t *totals = bounds + table_bounds_ints(p), *plans = totals + BAND_THRESHOLDS + 1;
+    int32_t *totals = bounds + table_bounds_ints(p), *plans = totals + BAND_THRESHOLDS + 1, *there = totals + BAND_THERE;
+    const int32_t *const asked = once ? there : nullptr;
     const int SP = (b.S + 15) / 16 * 16, RS = band_row_ints(p.D);
     int32_t *windows = thr + (size_t)BAND_THRESHOLDS * p.K * RS;
     hipLaunchKernelGGL(band_least_kernel, dim3(std::min((p.K * p.K * SP + 255) / 256, 16384)), dim3(256), 0, st, table, p.K,
-                       p.Smax, b, SP, work);
+                       p.Smax, b, SP, asked, work);
     const size_t lds = std::max((size_t)band_front_ints(p.K, RS) * 4, (size_t)2 * p.K * (p.K | 1));
     const auto kernel = p.D <= 16 ? band_thresholds_kernel<64, 4> : p.D <= 32 ? band_thresholds_kernel<64, 2> :
                         RS == 64 ? band_thresholds_kernel<64, 1> : RS == 128 ? band_thresholds_kernel<128, 1> : band_thresholds_kernel<256, 1>;
@@ -1071,17 +1080,17 @@ hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const BandSh
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kernel, dim3(2 * BAND_THRESHOLDS + 1), dim3(WAVE * BAND_WAVES), lds, st, work, table, b, p.K, p.D, SP,
-                       max_finite, thr, totals, plans, windows);
+                       max_finite, thr, totals, plans, windows, asked);
     hipLaunchKernelGGL(band_bounds_kernel, dim3(BAND_THRESHOLDS), dim3(BAND_BOUNDS_THREADS), 0, st, p, max_finite, table, b, thr, RS,
-                       totals, plans, bounds);
+                       totals, plans, bounds, once, there);
     return hipGetLastError();
 }
 
-// behind launch_band_bounds of the same table, with the same arrays
+// behind launch_band_bounds of the same table, with the same arrays (`once`: see there)
 hipError_t launch_band_exact_bounds(hipStream_t st, const BandShapes &b, const BandShape &shape, const Problem &p, int32_t max_finite,
-                                    const int32_t *recs, const int32_t *ends, int32_t *work, const int32_t *thr, int32_t *bounds)
+                                    const int32_t *recs, const int32_t *ends, int32_t *work, const int32_t *thr, int32_t *bounds, bool once)
 {
-    const int32_t *totals = bounds + table_bounds_ints(p), *plans = totals + BAND_THRESHOLDS + 1;
+    int32_t *totals = bounds + table_bounds_ints(p), *plans = totals + BAND_THRESHOLDS + 1, *there = totals + BAND_THERE;
     const int RS = band_row_ints(p.D);
     BandArgs a{p, shape, -1, INT32_MAX, recs, ends, b.sizes};
     a.p.S = b.S;
@@ -1095,7 +1104,7 @@ hipError_t launch_band_exact_bounds(hipStream_t st, const BandShapes &b, const B
         hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kernel, dim3(2), dim3(WAVE * BAND_WAVES), lds, st, a, totals, plans, bounds);
+    hipLaunchKernelGGL(kernel, dim3(2), dim3(WAVE * BAND_WAVES), lds, st, a, totals, plans, bounds, once, there);
     return hipGetLastError();
 }
 

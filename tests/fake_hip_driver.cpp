@@ -395,7 +395,8 @@ static void routes()
               k.c_str());
         alpa_dp_destroy(h);
     }
-    // bounds: by the first solve, or by the second; never recorded into a small problem's graph
+    // bounds: by the first solve, or by the second; not recorded into a small problem's graph, but for the band kernel's (which replays
+    // behind the first find there)
     struct { int K, N, M, n, by; } bounds[] = {{8, 1, 4, 0, 2}, {24, 2, 8, 1000, 1}, {40, 1, 8, 512, 2}, {64, 1, 2, 300, 2},
                                                {64, 2, 8, 12, 1}, {56, 4, 8, 130, 1}, {40, 8, 8, 12, 1}, {56, 8, 8, 12, 1},
                                                {26, 12, 16, 23, 1}, {6, 16, 8, 12, 1}, {64, 8, 8, 300, 1}, {48, 8, 8, 2000, 1}, {24, 8, 8, 5000, 1},

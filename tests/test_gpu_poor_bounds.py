@@ -100,3 +100,82 @@ def test_work_for_a_plan_where_memory_is_short():
         assert alone < whole / 2
     finally:
         B.alpa_dp_destroy(h)
+
+
+@pytest.mark.parametrize("kind", ["random", "memory", "deep"])
+def test_recorded_first_solve(kind):
+    """A graph recorded before any other solve, replayed with eager solves in between, and behind the restriction to equal
+    layers (another table)."""
+    import torch
+    K, N, M, n = 20, 3, 8, 600
+    if kind == "memory":
+        table, shapes = _short_of_memory(K, N, M, 5)
+    else:
+        w = W.random_problem(K, K, N, M, inf_frac=0.3, value_hi=200_000) if kind == "random" else W.deep_model_problem(K, K, N, M)
+        table, shapes = w.table, w.shapes
+    h = B.alpa_dp_create(table, K, N, M, 9, shapes)
+    try:
+        stream = torch.cuda.Stream()
+        B.alpa_dp_set_stream(h, stream)
+        d_T = torch.zeros(n, dtype=torch.int64, device="cuda")
+        d_plan = torch.zeros(B.PLAN_BYTES, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            B.alpa_dp_solve_dev(h, None, n, 0, d_T, d_plan)
+        for equal in (False, True):
+            if equal:
+                B.alpa_dp_restrict_equal_layers(h)
+            every = oracle.all_candidates(oracle.equal_layer_table(table) if equal else table, shapes)
+            cand = oracle.quantiles(every, n) if len(every) > n else every
+            T_ref, p_ref = oracle.solve_parallel(oracle.equal_layer_table(table) if equal else table, N, M, 9, shapes, cand, False, 8)
+            for replay in range(6):
+                if replay in (2, 3, 5):
+                    T, plan = B.alpa_dp_solve(h, None, n, 0)
+                    assert np.array_equal(T, T_ref)
+                    _plan_is(plan, p_ref)
+                d_T.zero_()
+                d_plan.zero_()
+                torch.cuda.synchronize()
+                with torch.cuda.stream(stream):
+                    graph.replay()
+                torch.cuda.synchronize()
+                assert np.array_equal(d_T.cpu().numpy()[: len(cand)], T_ref)
+                _plan_is(B.plan_from_bytes(d_plan.cpu().numpy().tobytes()), p_ref)
+    finally:
+        B.alpa_dp_destroy(h)
+
+
+def test_replays_find_the_bounds_there():
+    """A replay takes as long as an eager solve that has the table's bounds (64 layers on 8 x 8: 270 us; with the thresholds
+    computed anew 375)."""
+    import torch
+    w = W.deep_model_problem(5, 64, 8, 8)
+    stream = torch.cuda.Stream()
+    d_T = torch.zeros(300, dtype=torch.int64, device="cuda")
+
+    def shortest(call):
+        times = []
+        for _ in range(30):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            with torch.cuda.stream(stream):
+                begin.record()
+                call()
+                end.record()
+            torch.cuda.synchronize()
+            times.append(begin.elapsed_time(end))
+        return min(times)
+
+    h = B.alpa_dp_create(w.table, 64, 8, 8, 8, w.shapes)
+    try:
+        B.alpa_dp_set_stream(h, stream)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            B.alpa_dp_solve_dev(h, None, 300, 0, d_T, None)
+        replay = shortest(graph.replay)
+        eager = shortest(lambda: B.alpa_dp_solve_dev(h, None, 300, 0, d_T, None))
+        print("replay", replay, "eager", eager)
+        assert replay < 1.2 * eager
+    finally:
+        B.alpa_dp_destroy(h)
