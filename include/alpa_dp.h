@@ -230,9 +230,10 @@ int alpa_dp_solve_dev(alpa_dp_t *h, const int32_t *d_tmax, int n_tmax, unsigned 
  *             B_values[b] (num_stages == 0 and T_star == ALPA_DP_INF_I64 if infeasible).
  *
  * The handle's own B and the running best of alpa_dp_best() are not touched.  Blocking.
- * On the first call (and when n_B grows) device memory for n_B sets of layers is
- * allocated: n_B * (min(K, N*M) + 1) * (K + 2) * (N*M + 1) * 4 bytes when N*M <= 64 and K <= 128, or
- * more layers as long as they fit in LDS (138 on 8 x 8, 244 on 1 x 1); one set, reused, otherwise.  Errors: EINVAL (null pointers, n_B or a B value
+ * On the first call (and when n_B grows) device memory for sets of layers is allocated, a set being
+ * (min(K, N*M) + 1) * (K + 2) * (N*M + 1) * 4 bytes: n_B sets, but not more than 1 GiB of them, fewer where
+ * memory is short, and none where the general kernel serves or the register/LDS kernel on more than 64 devices (the winners are
+ * then taken one after the other).  Errors: EINVAL (null pointers, n_B or a B value
  * out of range, and the candidate-list errors of alpa_dp_solve), ENOMEM, EHIP.
  */
 #define ALPA_DP_MAX_SWEEP 256

@@ -92,7 +92,7 @@ struct alpa_dp {
     int32_t *d_scratch = nullptr, *d_Fall = nullptr, *d_tmpFS = nullptr;
     alpa_plan_t *d_plan_tmp = nullptr, *d_best_plan = nullptr;
     // sweep over B (allocated on first use, for up to sw_cap values)
-    int sw_cap = 0;
+    int sw_cap = 0, sw_sets = 1;    // sw_sets: sets of layers in d_sw_Fall
     int32_t *d_sw_B = nullptr, *d_sw_c = nullptr, *d_sw_s = nullptr, *d_sw_FS = nullptr;
     int32_t *d_sw_n = nullptr;      // [chunk][2]: number of B values, ticket of the plan-recovery run
     SolveState *d_sw_state = nullptr;
@@ -248,30 +248,33 @@ static int ensure_candidate_arrays(alpa_dp *h, int n_list)
 // one kernel recovers the layers of all winners of a sweep (else a launch per layer, winner by winner)
 static bool plan_slabs(const alpa_dp *h) { return h->band_ok || (h->fast_ok && h->p.D <= 64); }
 
-// int32 of one winner's layers, and the winners whose layers are kept at a time (up to 1 GiB of them)
+// int32 of one winner's layers, and the winners whose layers are kept at a time: up to 1 GiB of them, as many as there is
+// memory for, and at least the one set that the handle has anyway
 static size_t slab_ints(const alpa_dp *h) { return (size_t)(h->p.Smax + 1) * (size_t)(h->p.K + 2) * (h->p.D + 1); }
-static int sweep_chunk(const alpa_dp *h, int n_B)
-{
-    return (int)std::max<size_t>(1, std::min<size_t>(n_B, (1ull << 28) / slab_ints(h)));
-}
+static int sweep_chunk(const alpa_dp *h, int n_B) { return std::min(n_B, h->sw_sets); }
 
 static int alloc_sweep_arrays(alpa_dp *h, int n_B)
 {
     const size_t n = (size_t)n_B;
     h->sw_cap = 0;
-    const int rc = carve(&h->sweep_arena, [&](Carver &take) {
-        take(h->d_sw_B, n);
-        take(h->d_sw_c, n);
-        take(h->d_sw_s, n);
-        take(h->d_sw_FS, 2 * (n + 1));
-        take(h->d_sw_n, 2 * n);
-        take(h->d_sw_state, n);
-        take(h->d_sw_plans, n);
-        // one slab of layers per B value of a chunk; the general kernel reuses d_Fall
-        if (plan_slabs(h))
-            take(h->d_sw_Fall, sweep_chunk(h, n_B) * slab_ints(h));
-    });
-    if (rc) return rc;
+    size_t sets = plan_slabs(h) ? std::max<size_t>(1, std::min<size_t>(n, (1ull << 28) / slab_ints(h))) : 1;
+    for (;; sets /= 2) {
+        const int rc = carve(&h->sweep_arena, [&](Carver &take) {
+            take(h->d_sw_B, n);
+            take(h->d_sw_c, n);
+            take(h->d_sw_s, n);
+            take(h->d_sw_FS, 2 * (n + 1));
+            take(h->d_sw_n, 2 * n);
+            take(h->d_sw_state, n);
+            take(h->d_sw_plans, n);
+            if (sets > 1) take(h->d_sw_Fall, sets * slab_ints(h));
+        });
+        if (rc == ALPA_DP_ENOMEM && sets > 1) continue;
+        if (rc) return rc;
+        break;
+    }
+    if (sets == 1) h->d_sw_Fall = h->d_Fall;
+    h->sw_sets = (int)sets;
     h->sw_cap = n_B;
     return ALPA_DP_OK;
 }
@@ -1024,12 +1027,13 @@ extern "C" int alpa_dp_solve_sweep(alpa_dp_t *h, const int32_t *tmax, int n_tmax
         rc = alloc_sweep_arrays(h, n_B);
         if (rc) return rc;
     }
-    std::vector<int32_t> head;                     // of every chunk
+    int32_t head[2 * ALPA_DP_MAX_SWEEP];           // of every chunk: B values, ticket
+    int n_head = 0;
     for (int b = 0, chunk = sweep_chunk(h, n_B); b < n_B; b += chunk) {
-        head.push_back(std::min(chunk, n_B - b));
-        head.push_back(0);
+        head[n_head++] = std::min(chunk, n_B - b);
+        head[n_head++] = 0;
     }
-    HIPCHK(hipMemcpyAsync(h->d_sw_n, head.data(), head.size() * 4, hipMemcpyHostToDevice, h->stream));
+    HIPCHK(hipMemcpyAsync(h->d_sw_n, head, (size_t)n_head * 4, hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipMemcpyAsync(h->d_sw_B, B_values, (size_t)n_B * 4, hipMemcpyHostToDevice, h->stream));
     rc = solve_dev_impl(h, d_tmax, n_tmax, flags, nullptr, nullptr, key_bits, n_B);
     if (rc) {

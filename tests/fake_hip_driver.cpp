@@ -435,6 +435,32 @@ static void routes()
     }
 }
 
+// a sweep keeps as many sets of layers as there is memory for, and needs none of its own
+static void sweep_memory()
+{
+    const int values = 256;
+    struct { int K, N, M; } cases[] = {{48, 32, 8}, {40, 8, 8}, {40, 1, 8}};
+    for (auto &c : cases) {
+        for (int failures : {0, 1, 3, 8, 40}) {
+            alpa_dp_t *h = create_problem(c.K, c.N, c.M);
+            std::vector<int32_t> B(values, 3);
+            std::vector<alpa_plan_t> plans(values);
+            const size_t before = live_bytes(), from = rt().launches.size();
+            fail_mallocs(0, failures);
+            const int rc = alpa_dp_solve_sweep(h, nullptr, 12, 0, B.data(), values, plans.data());
+            fail_mallocs(0, 0);
+            CHECK(rc == (failures <= 8 ? ALPA_DP_OK : ALPA_DP_ENOMEM), "%d layers on %dx%d, %d failures: %d", c.K, c.N, c.M, failures, rc);
+            check_launches(from, rt().launches.size(), "sweep");
+            int walks = 0;
+            for (size_t x = from; x < rt().launches.size(); ++x) walks += rt().launches[x].kernel.find("plan_walk") != std::string::npos;
+            // (half the sets at each failure; all 256 are below 1 GiB)
+            CHECK(rc != 0 || walks == 1 << failures, "%d layers on %dx%d, %d failures: %d launches", c.K, c.N, c.M, failures, walks);
+            CHECK(live_bytes() - before < 1ull << 30, "%zu bytes", live_bytes() - before);
+            alpa_dp_destroy(h);
+        }
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -444,6 +470,7 @@ int main(int argc, char **argv)
     else if (what == "long_lists") long_lists();
     else if (what == "short_memory") short_memory();
     else if (what == "routes") routes();
+    else if (what == "sweep_memory") sweep_memory();
     else { printf("unknown scenario\n"); return 1; }
     if (!bad) printf("OK\n");
     return bad ? 1 : 0;
