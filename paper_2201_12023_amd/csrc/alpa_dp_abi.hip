@@ -405,7 +405,7 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     const int SB = (int)band_sizes.size();
     h->band = band_shape(K, D, SB, band_sizes.data());
     h->band_ok = !groups_serve && h->band.nbuf != 0;
-    h->fast_ok = !h->band_ok && K <= 128 && D <= 128;
+    h->fast_ok = !h->band_ok && K <= 128 && (D <= 8 || (D > WAVE && D <= 128 && K > 16 * (FAST_WIDE_NWK - 1)));
     int rc = carve(&h->arena, [&](Carver &take) {
         take(h->d_table, (size_t)K * K * K * S);
         take(h->d_sizes, S + table_bounds_ints(h->p) + 2 * SB + S);    // behind them d_no_bounds and band_shapes
@@ -836,7 +836,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
             // small problems matters as much).  Not for lists so short that every candidate gets a compute unit
             // of its own anyway.
             int group_dp = 0;
-            if (p.D <= 32 && nc == 1 && h->tune_no_groups != 1 &&
+            if (nc == 1 && h->tune_no_groups != 1 &&
                 (bound > h->n_cu || h->tune_no_groups >= 2)) {
                 group_dp = fast_lane_group_width(p.D);
                 if (h->tune_no_groups >= 2) group_dp = std::max(group_dp, WAVE / h->tune_no_groups);

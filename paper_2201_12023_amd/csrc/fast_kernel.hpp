@@ -1,8 +1,7 @@
-// Register/LDS recurrence kernel (Eq. 3) for K <= 128 layers on N*M <= 64 devices, and on up
-// to 128 devices in a two-window form (see WIDE below).  It runs on meshes of up to 8 devices (several
-// candidates to a wave, see GROUPED) and where the band kernel's lists do not fit in LDS.  A header: the
-// instances for up to 64 and for 65-128 layers are compiled in two translation units (kernels_fast.hip,
-// kernels_fast_deep.hip).
+// Register/LDS recurrence kernel (Eq. 3) for K <= 128 layers.  It runs on meshes of up to 8 devices (4 from 65 layers on), with
+// several candidates to a wave (see GROUPED), and, in a two-window form (see WIDE), on 65..128 devices
+// where the band kernel's layers do not fit in LDS (from 89 layers on).  A header: the instances for up to 64 and
+// for 65-128 layers are compiled in two translation units (kernels_fast.hip, kernels_fast_deep.hip).
 //
 // Mapping.  One workgroup evaluates one t_max candidate at a time (persistent workgroups
 // draw candidates from a ticket counter).  Lane l of every wave owns device count
@@ -305,7 +304,7 @@ __device__ __forceinline__ bool can_skip_fast(const int64_t *chunk_min, int j, i
 // axis; NC = candidates evaluated together by one workgroup (they share every scalar load);
 // DUMP = also store every layer to F_all (plan recovery, NC = 1); COUNT = tally executed
 // half-blocks.  Fmin / Sbest have a spare slot at index dummy_idx for results nobody owns.
-// WIDE (with NC = 2): meshes of 65..128 devices.  One candidate per workgroup; the two
+// WIDE (with NC = 2, from 81 layers on): meshes of 65..128 devices.  One candidate per workgroup; the two
 // accumulator sets and the two LDS regions that otherwise belong to two candidates hold the
 // device counts 1..64 and 65..128 of the one candidate ("windows" 0 and 1).
 // GROUPED (with NC = 1): meshes of up to 32 devices, 64 / DP candidates per workgroup (see
@@ -986,18 +985,24 @@ static hipError_t launch_one(hipStream_t st, const FastArgs &a, int grid)
 template <int NWK>
 static hipError_t launch_nwk(hipStream_t st, const FastArgs &a, int mode, int nc, int grid)
 {
+    if (a.p.D > WAVE) {                            // (the band kernel takes shallower models on these meshes)
+        if constexpr (NWK >= FAST_WIDE_NWK) {
+            switch (mode) {
+            case FAST_MODE_FEW: return launch_one<NWK, plan_wi(NWK), 2, false, false, true>(st, a, grid);
+            case FAST_MODE_COUNT: return launch_one<NWK, 1, 2, false, true, true>(st, a, grid);
+            case FAST_MODE_BATCH: return launch_one<NWK, 1, 2, false, false, true>(st, a, grid);
+            }
+        }
+        return hipErrorInvalidValue;
+    }
     switch (mode) {
     case FAST_MODE_PLAN: return launch_one<NWK, plan_wi(NWK), 1, true, false>(st, a, grid);
-    case FAST_MODE_FEW:
-        if (a.p.D > WAVE) return launch_one<NWK, plan_wi(NWK), 2, false, false, true>(st, a, grid);
-        return launch_one<NWK, plan_wi(NWK), 1, false, false>(st, a, grid);
+    case FAST_MODE_FEW: return launch_one<NWK, plan_wi(NWK), 1, false, false>(st, a, grid);
     case FAST_MODE_COUNT:
-        if (a.p.D > WAVE) return launch_one<NWK, 1, 2, false, true, true>(st, a, grid);
         if (a.grouped) return launch_one<NWK, 1, 1, false, true, false, true>(st, a, grid);
         return nc == 2 ? launch_one<NWK, 1, 2, false, true>(st, a, grid)
                        : launch_one<NWK, 1, 1, false, true>(st, a, grid);
     default:
-        if (a.p.D > WAVE) return launch_one<NWK, 1, 2, false, false, true>(st, a, grid);
         if (a.grouped) return launch_one<NWK, 1, 1, false, false, false, true>(st, a, grid);
         return nc == 2 ? launch_one<NWK, 1, 2, false, false>(st, a, grid)
                        : launch_one<NWK, 1, 1, false, false>(st, a, grid);

@@ -255,17 +255,19 @@ struct FastArgs {
     const int32_t *s_top_p;
     const int32_t *group_min;   // early-stop table (launch_repack_fast)
     const int32_t *s_bound;     // [Smax + 1]: the least unfiltered F of more than s stages (batch modes)
-    // batch modes, at most 32 devices, one-candidate form: 0, or the width DP of the lane groups
+    // batch modes, one-candidate form: 0, or the width DP of the lane groups
     // (a power of two, D <= DP <= 32): 64 / DP candidates per workgroup
     int grouped = 0;
 };
-// narrowest lane group that holds a mesh of D <= 32 devices
+// narrowest lane group that holds a mesh of D devices
 inline int fast_lane_group_width(int D)
 {
     int dp = 1;
     while (dp < D) dp <<= 1;
     return dp;
 }
+// more than 64 devices: from this many waves along the first layers on (81 layers)
+constexpr int FAST_WIDE_NWK = 6;
 enum { FAST_MODE_BATCH = 0, FAST_MODE_COUNT = 1, FAST_MODE_PLAN = 2, FAST_MODE_FEW = 3 };
 hipError_t launch_recurrence_fast(hipStream_t st, const FastArgs &a, int mode, int nc, int grid);
 int fast_kernel_blocks_per_cu(int K, int nc);
