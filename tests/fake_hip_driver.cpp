@@ -185,13 +185,14 @@ static void check_launches(size_t from, size_t to, const char *what)
     }
 }
 
-// `repeat`: fill the list up to so many shapes with the first one
+// `repeat`: fill the list up to so many shapes with the first one; negative: only so many shapes
 static alpa_dp_t *create_problem(int K, int N, int M, int repeat = 0)
 {
     std::vector<alpa_shape_t> shapes;
     for (int m = 1; m <= M; m *= 2) shapes.push_back({1, m});
     for (int n = 2; n <= N; ++n) shapes.push_back({n, M});
     while ((int)shapes.size() < repeat) shapes.push_back(shapes[0]);
+    if (repeat < 0) shapes.resize(-repeat);
     alpa_dp_t *h = nullptr;
     static const int32_t table = 7;                // (nothing reads it)
     const int rc = alpa_dp_create(&h, &table, K, N, M, 8, shapes.data(), (int)shapes.size());
@@ -385,6 +386,11 @@ static void routes()
         {220, 1, 8, 300, " recurrence_band_kernel<64,0,false,false> ", "recurrence_generic", 64},
         {205, 14, 1, 300, " recurrence_band_kernel<64,0,false,false> ", "recurrence_generic", 64},
         {124, 16, 8, 300, " recurrence_fast_kernel<8,1,2,false,false,true,false> ", "recurrence_band"},
+        {96, 110, 1, 300, " recurrence_fast_kernel<6,1,2,false,false,true,false> ", "recurrence_band", -64},
+        {96, 110, 1, 7, " recurrence_fast_kernel<6,2,2,false,false,true,false> ", "recurrence_band", -64},
+        {110, 49, 2, 300, " recurrence_fast_kernel<7,1,2,false,false,true,false> ", "recurrence_band"},
+        {112, 63, 2, 7, " recurrence_fast_kernel<7,2,2,false,false,true,false> ", "recurrence_band"},
+        {128, 28, 4, 300, " recurrence_fast_kernel<8,1,2,false,false,true,false> ", "recurrence_band"},
     };
     for (auto &c : cases) {
         alpa_dp_t *h = create_problem(c.K, c.N, c.M, c.repeat);
@@ -393,6 +399,21 @@ static void routes()
         CHECK(k.find(c.has) != std::string::npos, "%d layers on %dx%d, %d: no%sin%s", c.K, c.N, c.M, c.n, c.has, k.c_str());
         CHECK(k.find(c.has_not) == std::string::npos, "%d layers on %dx%d, %d: %s in%s", c.K, c.N, c.M, c.n, c.has_not,
               k.c_str());
+        alpa_dp_destroy(h);
+    }
+    // forms that the tuning call asks for, on the meshes of the register/LDS kernel
+    struct { int K, N, M, n, key, value; const char *has; } tuned[] = {
+        {64, 2, 4, 300, ALPA_DP_TUNE_LANE_GROUPS, 2, " recurrence_fast_kernel<4,1,1,false,false,false,true> "},
+        {17, 5, 1, 300, ALPA_DP_TUNE_LANE_GROUPS, 64, " recurrence_fast_kernel<2,1,1,false,false,false,true> "},
+        {128, 3, 1, 600, ALPA_DP_TUNE_LANE_GROUPS, 1, " recurrence_fast_kernel<8,1,1,false,false,false,false> "},
+        {48, 5, 1, 301, ALPA_DP_TUNE_CANDIDATES_PER_WG, 2, " recurrence_fast_kernel<3,1,2,false,false,false,false> "},
+        {128, 1, 4, 301, ALPA_DP_TUNE_CANDIDATES_PER_WG, 2, " recurrence_fast_kernel<8,1,2,false,false,false,false> "},
+    };
+    for (auto &c : tuned) {
+        alpa_dp_t *h = create_problem(c.K, c.N, c.M);
+        CHECK(alpa_dp_set_tuning(h, c.key, c.value) == 0, "tuning");
+        const std::string k = kernels_of(h, c.n);
+        CHECK(k.find(c.has) != std::string::npos, "%d layers on %dx%d, %d, key %d: no%sin%s", c.K, c.N, c.M, c.n, c.key, c.has, k.c_str());
         alpa_dp_destroy(h);
     }
     // bounds: by the first solve, or by the second; not recorded into a small problem's graph, but for the band kernel's (which replays

@@ -56,7 +56,7 @@ RANDOM_CASES = [
     (0, 1, 1, 1), (1, 2, 1, 2), (2, 3, 2, 2), (3, 5, 1, 4), (4, 6, 2, 4), (5, 7, 3, 2),
     (6, 9, 3, 4), (7, 12, 2, 8), (8, 17, 4, 4), (9, 16, 1, 8), (10, 33, 2, 2), (11, 20, 5, 4),
     (12, 10, 8, 8), (13, 40, 3, 8), (14, 64, 1, 2), (15, 13, 7, 8),
-    # more shapes than the register/LDS kernel's early-stop table covers (18, then the maximum 64)
+    # many shapes (18, then the maximum 64)
     (16, 30, 16, 4), (17, 20, 64, 1), (18, 64, 5, 8), (19, 57, 8, 8),
 ]
 
@@ -291,18 +291,21 @@ def test_create_checks_the_range_of_the_table_on_the_device():
     assert create_rc(allinf)[0] == 0
 
 
-LANE_GROUP_CASES = [  # seed, K, N, M: every group width 1, 2, 4, 8, 16, 32 and meshes that do
-    # not fill their group (3, 6, 10, 12, 24 devices)
+LANE_GROUP_CASES = [  # seed, K, N, M: every group width 1, 2, 4, 8 (two groups: 32) and meshes that do
+    # not fill their group (3, 5, 6, 7 devices), up to 64 layers and, on up to 4 devices, 128
     (700, 9, 1, 1), (701, 20, 1, 2), (702, 14, 3, 1), (703, 33, 1, 4), (704, 25, 3, 2),
-    (705, 48, 1, 8), (706, 17, 5, 2), (707, 30, 3, 4), (708, 64, 2, 8), (709, 40, 3, 8),
-    (710, 22, 1, 32), (711, 64, 4, 8), (712, 100, 2, 16), (713, 70, 1, 4), (714, 5, 2, 16),
+    (705, 48, 1, 8), (713, 70, 1, 4), (715, 17, 5, 1), (716, 30, 7, 1), (717, 64, 2, 4), (718, 40, 6, 1),
+    (719, 64, 8, 1), (720, 5, 4, 2), (721, 100, 2, 2), (722, 128, 3, 1), (723, 97, 1, 1),
+    # the band kernel's meshes, on which the key has no effect
+    (706, 17, 5, 2), (707, 30, 3, 4), (708, 64, 2, 8), (709, 40, 3, 8),
+    (710, 22, 1, 32), (711, 64, 4, 8), (712, 100, 2, 16), (714, 5, 2, 16),
 ]
 
 
 @pytest.mark.parametrize("prune", [False, True])
 @pytest.mark.parametrize("case", LANE_GROUP_CASES, ids=lambda c: f"s{c[0]}-K{c[1]}-{c[2]}x{c[3]}")
 def test_small_meshes_in_lane_groups(case, prune):
-    """On meshes of up to 32 devices the register/LDS kernel cuts the wave into groups of lanes
+    """On meshes of up to 8 devices the register/LDS kernel cuts the wave into groups of lanes
     with a candidate each (64, 32, ... 2 candidates per workgroup).  Unstructured tables with a
     narrow value range (neighbouring candidates then differ in few entries: the lane-by-lane
     filter) and formula tables; every candidate, quantiles, and an unsorted caller list with
@@ -430,8 +433,7 @@ def test_full_size_workloads_against_stored_oracle_results(idx):
 
 @pytest.mark.parametrize("kernel", list(KERNELS))
 def test_deep_model_on_a_mesh_larger_than_64_devices(kernel):
-    """N*M = 80 and K = 66: a workgroup per candidate (layers recovered by the general kernel), and the general
-    kernel on request."""
+    """N*M = 80 and K = 66: the band kernel, and the general kernel on request."""
     w = W.random_problem(77, 66, 10, 8, inf_frac=0.3, value_hi=900)
     allc = oracle.all_candidates(w.table, w.shapes)
     cand = oracle.quantiles(allc, 8)
@@ -483,12 +485,14 @@ def test_valu_peak_probe_and_readme_example():
         B.alpa_dp_destroy(h)
 
 
-@pytest.mark.parametrize("case", [c for c in RANDOM_CASES if c[1] <= 64 and c[2] * c[3] <= 64],
+@pytest.mark.parametrize("case", [c for c in RANDOM_CASES if c[1] <= 64 and c[2] * c[3] <= 64] +
+                         [(40, 9, 1, 1), (41, 16, 1, 2), (42, 17, 3, 1), (43, 33, 1, 4), (44, 48, 5, 1), (45, 64, 3, 2),
+                          (46, 40, 7, 1), (47, 64, 2, 4), (48, 31, 1, 8), (49, 70, 2, 2), (50, 128, 1, 4)],
                          ids=lambda c: f"s{c[0]}-K{c[1]}-{c[2]}x{c[3]}")
 def test_random_tables_two_candidates_per_workgroup(case):
     """The register/LDS kernel takes two candidates per workgroup (and packs them into one
-    pass where it can) only for long candidate lists; the tuning call forces that form
-    here, on unstructured tables where most half-blocks need the entry-wise filter, odd
+    pass where it can) where the tuning call asks for it, on up to 8 devices (the other meshes are the band
+    kernel's), on unstructured tables where most half-blocks need the entry-wise filter, odd
     candidate counts included."""
     seed, K, N, M = case
     w = W.random_problem(500 + seed, K, N, M, inf_frac=0.25, value_hi=[6, 80, 7000][seed % 3])
@@ -557,7 +561,7 @@ def test_create_and_destroy_give_the_memory_back():
     assert free0 - free1 < 64 << 20                # no growth with the number of handles
 
 
-WIDE_CASES = [  # seed, K, N, M: 65..128 devices, K <= 64: the two-window form of the fast kernel
+WIDE_CASES = [  # seed, K, N, M: 65..128 devices, K <= 64: the band kernel with two windows of device counts
     (60, 40, 10, 8), (61, 64, 16, 8), (62, 33, 9, 8), (63, 20, 3, 32), (64, 57, 2, 64),
     (65, 12, 33, 2), (66, 64, 13, 8), (67, 5, 4, 32),
 ]
@@ -588,8 +592,8 @@ def test_meshes_of_65_to_128_devices(case, kernel):
             B.alpa_dp_destroy(h)
 
 
-DEEP_CASES = [  # seed, K, N, M: 65..128 layers (all but the one-device case by a workgroup per candidate), the last
-    # four on 65..128 devices (stage counts up to 128; from 92 layers on two windows of the register/LDS kernel)
+DEEP_CASES = [  # seed, K, N, M: 65..128 layers (all but the one-device case and the last by the band kernel), the last
+    # four on 65..128 devices (stage counts up to 128; 128 layers on 16 x 8: two windows of the register/LDS kernel)
     (70, 65, 4, 8), (71, 80, 8, 8), (72, 96, 2, 8), (73, 128, 8, 8), (74, 100, 1, 8),
     (75, 113, 4, 16), (76, 128, 3, 4), (77, 81, 1, 1),
     (78, 70, 9, 8), (79, 100, 16, 8), (80, 128, 2, 64), (81, 128, 16, 8),
@@ -648,9 +652,9 @@ def test_plans_of_many_stages(case, kernel):
                          ids=lambda c: f"s{c[0]}-K{c[1]}-{c[2]}x{c[3]}-nc{c[4]}")
 def test_deep_formula_tables(case):
     """Structured tables (monotone in the stage span, memory-bound infeasibility) are where the early stops
-    take effect: those of the kernel with a workgroup per candidate, and, on the smallest meshes and with
-    many shapes, the column loops and the packed two-candidate passes of the register/LDS kernel (nc: candidates
-    per workgroup, which only that kernel knows)."""
+    take effect: those of the band kernel, and, on the smallest meshes, the column loops and the packed two-candidate
+    passes of the register/LDS kernel (nc: candidates per workgroup, which only that kernel knows; 99 layers
+    on 64 x 1 are the band kernel's)."""
     seed, K, N, M, nc = case
     w = W.deep_model_problem(seed, K, N, M)
     cand_ref = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), 121 if N < 64 else 9)
@@ -674,8 +678,8 @@ def test_deep_formula_tables(case):
 ], ids=lambda c: f"s{c[0]}-K{c[1]}-max{c[4]}")
 def test_candidate_list_by_bitmap_and_by_sort(case, force_sort):
     """The ascending distinct finite table values (the candidates when no list is given) come
-    from a presence bitmap when the largest value is below 2^19 and from a radix sort
-    otherwise; both against the oracle's list, with zeros, the extreme values present, and the
+    from a presence bitmap (in LDS when the largest value is below 2^19, in memory while it has no more words than the
+    table entries) and from a radix sort otherwise; all against the oracle's list, with zeros, the extreme values present, and the
     tuning call that forces the sort."""
     seed, K, N, M, hi = case
     w = W.random_problem(seed, K, N, M, inf_frac=0.3, value_hi=hi)

@@ -110,20 +110,20 @@ def test_bound_on_late_layers(size):
             B.alpa_dp_destroy(h)
 
 
-# the sizes of the kernel with a workgroup per candidate: 65 layers and more (beyond 128: the third scale of its row ends),
-# 129-256 devices; one, odd and even numbers of half-blocks of 8 layers, device counts at the edges of 16, 32, 64 and
-# their multiples, many shapes; the largest layer counts that fit in LDS
+# sizes of the kernel with a workgroup per candidate: 65 layers and more, 129-256 devices; one, odd and even numbers of blocks
+# of 8 layers, device counts at the edges of 16, 32, 64 and their multiples, many shapes; deep models (244 layers on 1 x 1
+# and 97 on 1 x 4 are the general and the register/LDS kernel's)
 ROW_CASES = [(65, 3, 2), (72, 1, 16), (73, 3, 8), (96, 4, 8), (121, 5, 4), (128, 8, 8), (97, 1, 4), (88, 60, 1),
              (66, 10, 8), (86, 16, 8),
              (1, 17, 8), (8, 24, 8), (9, 32, 8), (17, 12, 16), (23, 60, 4), (40, 31, 8), (48, 16, 16), (54, 16, 16),
-             (129, 1, 2), (244, 1, 1), (191, 1, 4), (240, 2, 8), (195, 4, 8), (130, 8, 8), (138, 8, 8)]
+             (129, 1, 2), (244, 1, 1), (191, 1, 4), (240, 2, 8), (195, 4, 8), (130, 8, 8), (138, 8, 8), (99, 64, 1), (120, 32, 2)]
 
 
 @pytest.mark.parametrize("size", ROW_CASES, ids=lambda s: f"K{s[0]}-{s[1]}x{s[2]}")
 @pytest.mark.parametrize("inf_frac", [0.0, 0.6])
 def test_workgroup_per_candidate_sizes(size, inf_frac):
     K, N, M = size
-    if K > 128 and N * M > 16 and inf_frac:
+    if inf_frac and (K > 128 and N * M > 16 or K * N * M > 6300 and M <= 2):
         pytest.skip("one share of infinite entries for the sizes that take the oracle longest")
     w = W.random_problem(K + 7 * N, K, N, M, inf_frac=inf_frac, value_hi=9000)
     cand = oracle.quantiles(oracle.all_candidates(w.table, w.shapes), 12)
@@ -145,10 +145,9 @@ def test_workgroup_per_candidate_sizes(size, inf_frac):
         B.alpa_dp_destroy(h)
 
 
-# sizes of 65-128 layers that stay with the register/LDS kernel: the smallest meshes, and up to 64 devices with so many
-# shapes that the other kernel's rows do not fit in LDS; lists in the share of each of its forms (sixteen and eight
-# waves per candidate, four; lane groups)
-DEEP_CASES = [(65, 1, 1), (65, 1, 2), (128, 1, 1), (72, 1, 2), (81, 3, 1), (96, 1, 4), (112, 2, 1), (128, 1, 2), (99, 64, 1), (120, 32, 2)]
+# sizes of 65-128 layers that stay with the register/LDS kernel: the smallest meshes; lists in the share of each of its forms
+# (sixteen and eight waves per candidate, four; lane groups)
+DEEP_CASES = [(65, 1, 1), (65, 1, 2), (128, 1, 1), (72, 1, 2), (81, 3, 1), (96, 1, 4), (112, 2, 1), (128, 1, 2), (97, 4, 1), (128, 2, 2)]
 
 
 @pytest.mark.parametrize("size", DEEP_CASES, ids=lambda s: f"K{s[0]}-{s[1]}x{s[2]}")
@@ -175,6 +174,40 @@ def test_deep_models_in_the_register_kernel(size):
         for Bv, plan in zip([1, 40], B.alpa_dp_solve_sweep(h, few, [1, 40])):
             _, p_ref = oracle.solve_parallel(w.table, N, M, Bv, w.shapes, few, False, 8)
             _same_plan(plan, p_ref)
+    finally:
+        B.alpa_dp_destroy(h)
+
+
+# 65-128 devices with so many layers and shapes that the band kernel does not fit: the register/LDS kernel's two-window form, for each
+# number of waves along the layers (6, 7, 8)
+WINDOW_CASES = [(96, 110, 1), (110, 49, 2), (112, 63, 2), (128, 28, 4)]
+
+
+@pytest.mark.parametrize("size", WINDOW_CASES, ids=lambda s: f"K{s[0]}-{s[1]}x{s[2]}")
+def test_two_windows_of_the_register_kernel(size):
+    K, N, M = size
+    shapes = W.submesh_shapes(N, M)[:64]
+    rng = np.random.default_rng(K)
+    k, i = np.arange(K)[:, None], np.arange(K)[None, :]
+    # stages that take longer the longer they are and the fewer devices they have, with noise; many have no entry
+    a = (shapes[:, 0] * shapes[:, 1])[None, None, :]
+    t = (900 * (i - k + 1))[:, :, None] // a + 30 * a + rng.integers(0, 200, (K, K, len(shapes)))
+    t = np.where(((i >= k) & (rng.random((K, K)) < 0.8))[:, :, None], t, oracle.INF32).astype(np.int32)
+    table = np.broadcast_to(t, (K, *t.shape)).copy()
+    table[K // 2:, :, :, ::3] = oracle.INF32
+    few = oracle.quantiles(np.unique(t[t != oracle.INF32]).astype(np.int32), 7)
+    many = np.concatenate([few, few[-1] + 1 + np.arange(300)]).astype(np.int32)
+    h = B.alpa_dp_create(table, K, N, M, 20, shapes)
+    try:
+        for prune in (0, B.ALPA_DP_PRUNE):
+            T_gen, p_gen = B.alpa_dp_solve(h, few, flags=prune | B.ALPA_DP_GENERIC)
+            assert p_gen["num_stages"] > 0
+            for extra in (0, B.ALPA_DP_COUNT_WORK):
+                T, plan = B.alpa_dp_solve(h, few, flags=prune | extra)        # sixteen waves a candidate
+                assert np.array_equal(T, T_gen) and plan == p_gen
+                T, plan = B.alpa_dp_solve(h, many, flags=prune | extra)       # eight
+                assert np.array_equal(T[:7], T_gen) and plan["T_star"] == p_gen["T_star"]
+                assert plan["first_layer"] == p_gen["first_layer"] and plan["shape_idx"] == p_gen["shape_idx"]
     finally:
         B.alpa_dp_destroy(h)
 
