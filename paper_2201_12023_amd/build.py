@@ -29,10 +29,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 # instances is checked after every build instead of being found out on the GPU.
 _BATCH_INSTANCE = re.compile(r"recurrence_fast_kernelILi[1-4]ELi1ELi1ELb0ELb0ELb0ELb0E")
 # The band kernel has a compute unit to itself (its layers fill the LDS): sixteen waves, four per SIMD, in all its
-# instances.
-_BAND_INSTANCE = re.compile(r"recurrence_band_kernelI")
-# A further tuned one, until it has a line of its own: eight waves per SIMD.  (The general kernel has no such budget.)
-_OTHER_INSTANCE = re.compile(r"recurrence_(?!fast_|generic_)\w*kernelI")
+# instances, and where it computes a table's bounds.
+_BAND_INSTANCE = re.compile(r"(recurrence_band|band_exact_bounds)_kernelI")
 
 
 def parse_resource_remarks(text: str) -> dict:
@@ -65,9 +63,6 @@ def check_resources(kernels: dict) -> list:
         elif _BAND_INSTANCE.search(name):
             if r.get("occupancy", 0) < 4 or r.get("scratch", 0) != 0 or r.get("agprs", 0) != 0:
                 bad.append(f"{name}: {r} (band kernel: 4 waves/SIMD and no spills expected)")
-        elif _OTHER_INSTANCE.search(name):
-            if r.get("occupancy", 0) < 8 or r.get("scratch", 0) != 0 or r.get("agprs", 0) != 0:
-                bad.append(f"{name}: {r} (recurrence kernel: 8 waves/SIMD and no spills expected)")
         elif "recurrence_fast_kernel" in name and r.get("scratch", 0) != 0:
             bad.append(f"{name}: {r} (scratch memory in the recurrence kernel)")
         # The kernel's warm-up loads land in a vector register that must stay where it is while

@@ -1,9 +1,12 @@
 """The build step's register-budget check (host logic only: the remark text is made up here)."""
+import pytest
+
 from paper_2201_12023_amd import build as B
 
 BATCH = "_ZN4alpa22recurrence_fast_kernelILi4ELi1ELi1ELb0ELb0ELb0ELb0EEEvNS_7ProblemEPKi"
 PLAN = "_ZN4alpa22recurrence_fast_kernelILi4ELi4ELi1ELb1ELb0ELb0ELb0EEEvNS_7ProblemEPKi"
-ROW = "_ZN4alpa21recurrence_row_kernelILi129ELb0ELb0EEEvNS_7RowArgsE"
+BAND = "_ZN4alpa22recurrence_band_kernelILi64ELi8ELb0ELb0EEEvNS_8BandArgsE"
+BAND_BOUNDS = "_ZN4alpa24band_exact_bounds_kernelILi64EEEvNS_8BandArgsEPKiS3_PiiS4_"
 OTHER = "_ZN4alpa15epilogue_kernelENS_7ProblemEPKi"
 
 
@@ -36,10 +39,11 @@ def test_batch_instance_must_keep_eight_waves_and_no_scratch():
     assert len(B.check_resources(B.parse_resource_remarks(remarks(PLAN, 72, 0, 7, agprs=4)))) == 1
 
 
-def test_row_kernel_must_keep_eight_waves_and_no_spills():
-    check = lambda *r: len(B.check_resources(B.parse_resource_remarks(remarks(ROW, *r))))
-    assert check(57, 0, 8) == 0
-    assert check(68, 0, 7) == check(64, 24, 8) == check(64, 0, 8, 4) == 1
+@pytest.mark.parametrize("name", [BAND, BAND_BOUNDS])
+def test_band_kernel_must_keep_four_waves_and_no_spills(name):
+    check = lambda *r: len(B.check_resources(B.parse_resource_remarks(remarks(name, *r))))
+    assert check(128, 0, 4) == 0
+    assert check(136, 0, 3) == check(128, 8, 4) == check(128, 0, 4, 4) == 1
 
 
 ASM_HEAD = "\t.text\n_ZN4alpa22recurrence_fast_kernelILi4ELi1ELi1ELb0ELb0ELb0ELb0EEEvNS_7ProblemE: ; @x\n"
