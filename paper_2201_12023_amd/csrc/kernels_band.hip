@@ -647,7 +647,12 @@ __device__ __forceinline__ void band_recurrence(const BandArgs &a)
             made = s0 + ln - 1;
         };
         // least plan of more stages than s0 + l, in lanes 32 + l
-        auto bounds_of = [&](int s0) { return DUMP || TABLE ? 0 : a.s_bound[min(s0 + (lane & 31), a.p.Smax)]; };
+        constexpr bool BOUNDED = !DUMP && !TABLE;
+        auto bounds_of = [&](int s0) { return BOUNDED ? a.s_bound[min(s0 + (lane & 31), a.p.Smax)] : 0; };
+        auto counts_of = [&](int32_t bounds) {
+            const int n = n_units[min(lane, a.b.ahead - 1)];
+            return BOUNDED && lane >= 32 ? bounds : n;
+        };
         const int ln2 = min(a.b.ahead, s_top - 1);
         const int32_t bounds2 = bounds_of(2);
         // what is known of the lowest threshold that is not below the candidate (thresholds descend; the first has no filter)
@@ -718,7 +723,7 @@ __device__ __forceinline__ void band_recurrence(const BandArgs &a)
         // The wave's units, in order over the layers: a layer's share goes through a ring of UNITS_AHEAD loads in
         // whole rounds, filled up with empty units.  w_A, w_B: up to 64 units of the share, a lane each.
         int w_base = 2;                                // first layer of the lists
-        int w_counts = lane < 32 ? n_units[min(lane, a.b.ahead - 1)] : bounds2;    // lane l: units of layer w_base + l; and bounds
+        int w_counts = counts_of(bounds2);             // lane l: units of layer w_base + l; and bounds
         int b_base = 2;                                // layer of the first bound
         int w_A = 0, w_B = 0, w_at = 0, w_first = 0, w_end = 0;
         uint32_t w_layer = 0;                          // where the layer's records begin (in bytes)
@@ -762,7 +767,7 @@ __device__ __forceinline__ void band_recurrence(const BandArgs &a)
             if (s > made) {
                 const int ln = min(a.b.ahead, s_top - s + 1);
                 int32_t bounds = w_counts;
-                if (s + ln > b_base + 32) {
+                if (BOUNDED && s + ln > b_base + 32) {
                     b_base = s;
                     bounds = bounds_of(s);
                 }
@@ -771,7 +776,7 @@ __device__ __forceinline__ void band_recurrence(const BandArgs &a)
                 build_lists(s, ln);
                 lds_barrier();
                 w_base = s;
-                w_counts = lane < 32 ? n_units[min(lane, a.b.ahead - 1)] : bounds;
+                w_counts = counts_of(bounds);
                 rounds = enter(s);
 #pragma unroll
                 for (int x = 0; x < UNITS_AHEAD; ++x) load(x);
