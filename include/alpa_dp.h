@@ -150,17 +150,17 @@ int alpa_dp_set_B(alpa_dp_t *h, int B);
  * Tuning of the launch shape; cites no passage of the paper because no result depends on it
  * (the parity tests run every setting against the same oracle values).  value 0 restores the
  * library's own choice.  All keys but DISTINCT_BY_SORT are about the register/LDS kernel and without
- * effect where another one serves: 129 devices or more, and from 65 layers on all but up to 128
- * layers on 1 or 2 devices, 96 on 3 or 4, and sizes whose layers do not fit in LDS (more than 138 layers
- * on 8 x 8, 86 on 16 x 8).  Errors: EINVAL (null handle, unknown key, value out of range).
+ * effect where another one serves: it serves up to 8 devices with up to 64 layers and up to 4 with up to 128, and, up to 128
+ * layers, those meshes of 65 to 128 devices on which the band kernel's layers do not fit in LDS (from 124 layers on
+ * 16 x 8, 110 on 49 x 2).  Errors: EINVAL (null handle, unknown key, value out of range).
  */
 #define ALPA_DP_TUNE_CANDIDATES_PER_WG 1  /* 1 or 2 t_max candidates per workgroup of the
                                              register/LDS kernel (own choice: 1, with more waves
                                              for short lists)                                   */
 #define ALPA_DP_TUNE_DISTINCT_BY_SORT  2  /* 1: distinct table values by the radix sort also where
-                                             the presence bitmap applies                        */
+                                             a presence bitmap applies                          */
 #define ALPA_DP_TUNE_WG_PER_CU         3  /* upper bound on resident workgroups per compute unit */
-#define ALPA_DP_TUNE_LANE_GROUPS        5  /* meshes of up to 32 devices: 1 = do not cut the wave
+#define ALPA_DP_TUNE_LANE_GROUPS        5  /* meshes of up to 8 devices: 1 = do not cut the wave
                                              into lane groups with a candidate each; 2, 4, .. 64
                                              = that many groups (at most 64 / devices rounded up
                                              to a power of two)                                 */
@@ -204,7 +204,8 @@ int alpa_dp_solve(alpa_dp_t *h, const int32_t *tmax, int n_tmax, unsigned flags,
  * d_tmax (or NULL), d_out_T (or NULL) and d_out_plan (or NULL) are device pointers
  * with the sizes given for alpa_dp_solve; they must stay valid until the stream has
  * run the work.  Candidates are not range-checked (values outside [0, INT32_MAX) give
- * T* = ALPA_DP_INF_I64 or unfiltered results for that candidate, never a fault).
+ * T* = ALPA_DP_INF_I64 or unfiltered results for that candidate, never a fault; negative ones come last among the candidates,
+ * and -1 is none).
  * A list longer than any before it may allocate; the call waits only if device memory is too short for that.
  *
  * It may be recorded into a HIP graph on the handle's stream.  The graph solves the handle's table as it is

@@ -387,7 +387,7 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     // solve more than it saves there, so that one stays on up to 4 devices (us, first solve and later ones: 128 layers on 1 x 4,
     // 1000 candidates: 241 and 212 against 321 and 199) and on up to 8 with up to 64 layers (64 on 1 x 8,
     // 2048: 252 and 215 against 298 and 190; but 72 on 2 x 4, 2048: 288 and 241 against 280 and 195).  It also takes
-    // what is left up to 128 devices, the general kernel the rest.
+    // what is left of 65 to 128 devices (two windows: from 89 layers on), the general kernel the rest.
     const bool groups_serve = K <= 128 && (D <= 4 || (D <= 8 && K <= 64));
     // (shapes of one device count, i.e. repeated ones, are one shape to it)
     std::vector<int32_t> band_sizes, first, next(S, -1), last;

@@ -28,9 +28,9 @@
 //
 // What bounds a round is the slowest candidate's chain of layers (list, shares, units, barrier: 5 to 8 thousand clocks a
 // layer at 64 layers on 8 x 8), so what helps is fewer batches and fewer layers.  A whole solve, t_intra by last layer and a
-// bound on the sum alone against this (us): 64 layers on 8 x 8, T* of 4096 candidates 912 and 470; the plan alone out of
-// every distinct value 804 and 340; 128 layers, 1024 candidates 2290 and 1032; 64 layers on 16 x 8, 1024: 1124 and 424;
-// 48 on 32 x 8, 64 candidates 1165 and 585.
+// bound on the sum alone against this (us): 64 layers on 8 x 8, T* of 4096 candidates 1022 and 419; the plan alone out of
+// every distinct value 754 and 195; 128 layers, 1024 candidates 2267 and 1059; 64 layers on 16 x 8, 1024: 1060 and 386;
+// 48 on 32 x 8, 64 candidates 1186 and 569.
 #include "internal.hpp"
 
 #include <type_traits>

@@ -111,8 +111,8 @@ def test_bound_on_late_layers(size):
 
 
 # sizes of the kernel with a workgroup per candidate: 65 layers and more, 129-256 devices; one, odd and even numbers of blocks
-# of 8 layers, device counts at the edges of 16, 32, 64 and their multiples, many shapes; deep models (244 layers on 1 x 1
-# and 97 on 1 x 4 are the general and the register/LDS kernel's)
+# of 8 layers, device counts at the edges of 16, 32, 64 and their multiples, many shapes; deep models (97 layers
+# on 1 x 4 are the register/LDS kernel's)
 ROW_CASES = [(65, 3, 2), (72, 1, 16), (73, 3, 8), (96, 4, 8), (121, 5, 4), (128, 8, 8), (97, 1, 4), (88, 60, 1),
              (66, 10, 8), (86, 16, 8),
              (1, 17, 8), (8, 24, 8), (9, 32, 8), (17, 12, 16), (23, 60, 4), (40, 31, 8), (48, 16, 16), (54, 16, 16),
