@@ -450,11 +450,9 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     h->band_shapes = BandShapes{SB, S, shapes_at, SB < S ? shapes_at + SB : nullptr, shapes_at + 2 * SB};
     HIPCHK(hipMemcpyAsync(h->d_sizes, up.data(), up.size() * 4, hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipMemsetAsync(h->d_state, 0, sizeof(SolveState), h->stream));
-    if (h->band_ok)
-        HIPCHK(hipMemsetAsync(h->d_bounds + table_bounds_ints(h->p) + BAND_THERE, 0, 4, h->stream));
     HIPCHK(launch_init_best_plan(h->stream, h->d_best_plan));
     if (h->band_ok)
-        HIPCHK(launch_repack_band(h->stream, h->d_table, K, h->p.Smax, h->band_shapes, h->d_bandrecs, h->d_bandends));
+        HIPCHK(launch_repack_band(h->stream, h->d_table, h->p, h->band_shapes, h->d_bandrecs, h->d_bandends, h->d_bounds));
     if (h->fast_ok) {
         h->KP = 16 * ((K + 15) / 16);
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
@@ -588,12 +586,10 @@ extern "C" int alpa_dp_restrict_equal_layers(alpa_dp_t *h)
     const int K = h->p.K, D = h->p.D, S = h->p.S;
     HIPCHK(launch_equal_layer_mask(h->stream, h->d_table, K, S));
     if (h->band_ok)
-        HIPCHK(launch_repack_band(h->stream, h->d_table, K, h->p.Smax, h->band_shapes, h->d_bandrecs, h->d_bandends));
+        HIPCHK(launch_repack_band(h->stream, h->d_table, h->p, h->band_shapes, h->d_bandrecs, h->d_bandends, h->d_bounds));
     if (h->fast_ok) {
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
     }
-    if (h->band_ok)
-        HIPCHK(hipMemsetAsync(h->d_bounds + table_bounds_ints(h->p) + BAND_THERE, 0, 4, h->stream));
     // (a graph recorded after the first solve reads the bounds and does not compute them)
     if (h->have_bounds) {
         int rcb = queue_bounds(h, false);

@@ -291,8 +291,8 @@ struct BandShapes {
 };
 size_t band_table_ints(int K, int Smax, int S);
 size_t band_ends_ints(int K, int Smax, int S);
-hipError_t launch_repack_band(hipStream_t st, const int32_t *table, int K, int Smax, const BandShapes &b,
-                              int32_t *recs, int32_t *ends);
+hipError_t launch_repack_band(hipStream_t st, const int32_t *table, const Problem &p, const BandShapes &b,
+                              int32_t *recs, int32_t *ends, int32_t *bounds);
 // what the table says about candidates: launch_table_bounds' place for these sizes; `once`: nothing is done where it is there
 // (a recorded solve is replayed)
 size_t band_least_ints(int K, int S);

@@ -86,10 +86,11 @@ __device__ __forceinline__ int32_t band_smallest(const int32_t *__restrict__ ent
 }
 
 // A wave per (s, block, q): the block's units (a lane per entry and batch), and the smallest entry from each of
-// eight positions on.  Blocks and units that only fill up a tile are +infinity.
+// eight positions on.  Blocks and units that only fill up a tile are +infinity.  there: see BAND_THERE.
 __global__ __launch_bounds__(256) void repack_band_kernel(const int32_t *__restrict__ table, int K, BandShapes b, int n,
-                                                          int32_t *__restrict__ recs, int32_t *__restrict__ ends)
+                                                          int32_t *__restrict__ recs, int32_t *__restrict__ ends, int32_t *there)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *there = 0;       // (another table)
     const int S = b.S;
     const int NHB = band_blocks(K), NG = (NHB + 3) / 4, P = band_tiles(K);
     const int lane = threadIdx.x & (WAVE - 1);
@@ -125,12 +126,13 @@ __global__ __launch_bounds__(256) void repack_band_kernel(const int32_t *__restr
     }
 }
 
-hipError_t launch_repack_band(hipStream_t st, const int32_t *table, int K, int Smax, const BandShapes &b,
-                              int32_t *recs, int32_t *ends)
+hipError_t launch_repack_band(hipStream_t st, const int32_t *table, const Problem &p, const BandShapes &b,
+                              int32_t *recs, int32_t *ends, int32_t *bounds)
 {
+    const int K = p.K, Smax = p.Smax;
     const int n = Smax * 4 * ((band_blocks(K) + 3) / 4) * b.S;
     hipLaunchKernelGGL(repack_band_kernel, dim3(std::min((n + 3) / 4, 16384)), dim3(256), 0, st, table, K, b, n,
-                       recs, ends);
+                       recs, ends, bounds + table_bounds_ints(p) + BAND_THERE);
     return hipGetLastError();
 }
 
