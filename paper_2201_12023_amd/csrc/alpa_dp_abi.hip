@@ -73,8 +73,13 @@ struct alpa_dp {
     GrowingArena keys, cands;
     bool recorded = false;          // a solve has been recorded into a graph
     int32_t *d_table = nullptr, *d_sizes = nullptr, *d_recs = nullptr, *d_gmin = nullptr;
-    int32_t *d_bandrecs = nullptr, *d_bandends = nullptr, *d_bandthr = nullptr;
+    int32_t *d_bandrecs = nullptr, *d_bandends = nullptr, *d_bandthr = nullptr, *d_backs = nullptr;
+    int32_t *d_front = nullptr, *d_graph = nullptr;
     bool band_ok = false;
+    bool sparse_ok = false;         // there is room for candidates to go by graphs (kernels_sparse.hip)
+    bool ordered = false;           // and the table's latencies do not fall with the number of stages
+    uint16_t *d_kept = nullptr;     // plans of those that are settled
+    int32_t *d_kept_from = nullptr;
     BandShape band{};
     BandShapes band_shapes{};
     int32_t *d_bounds = nullptr;    // what the table says about every candidate (launch_table_bounds)
@@ -86,7 +91,7 @@ struct alpa_dp {
     int32_t *d_distinct = nullptr;
     uint32_t *d_ncount = nullptr;   // [2]: distinct table values, distinct caller candidates
     int32_t *d_cand = nullptr, *d_rank = nullptr, *d_tmax_stage = nullptr;
-    int32_t *d_Fmin = nullptr, *d_Sbest = nullptr, *d_knots = nullptr, *d_list = nullptr;
+    int32_t *d_Fmin = nullptr, *d_Sbest = nullptr, *d_knots = nullptr, *d_list = nullptr, *d_todo = nullptr, *d_slot = nullptr;
     int64_t *d_T = nullptr, *d_outT_stage = nullptr, *d_chunkmin = nullptr;
     SolveState *d_state = nullptr;
     int32_t *d_scratch = nullptr, *d_Fall = nullptr, *d_tmpFS = nullptr;
@@ -148,6 +153,8 @@ static void candidate_layout(alpa_dp *h, size_t c, Carver &take)
 {
     take(h->d_cand, c);
     take(h->d_list, c);
+    take(h->d_todo, h->sparse_ok ? c : 0);
+    take(h->d_slot, h->sparse_ok ? c : 0);
     take(h->d_rank, c);
     take(h->d_tmax_stage, c);
     take(h->d_Fmin, c + 1);                        // + one spare slot (see FastArgs)
@@ -312,7 +319,8 @@ static int queue_table_candidates(alpa_dp *h, bool cleared = false)
 static int queue_bounds(alpa_dp *h, bool recorded)
 {
     if (h->band_ok)
-        HIPCHK(launch_band_bounds(h->stream, h->d_table, h->band_shapes, h->p, h->max_finite, h->d_bound_work, h->d_bandthr,
+        HIPCHK(launch_band_bounds(h->stream, h->d_table, h->band_shapes, h->p, h->max_finite,
+                                  BandWork{h->d_bound_work, h->d_front, h->d_bandthr, h->d_backs, h->d_graph},
                                   h->d_bounds, recorded));
     else
         HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
@@ -405,6 +413,7 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     const int SB = (int)band_sizes.size();
     h->band = band_shape(K, D, SB, band_sizes.data());
     h->band_ok = !groups_serve && h->band.nbuf != 0;
+    h->sparse_ok = h->band_ok && SB == S;          // (of shapes with equal device counts the graph would not know the lowest)
     h->fast_ok = !h->band_ok && K <= 128 && (D <= 8 || (D > WAVE && D <= 128 && K > 16 * (FAST_WIDE_NWK - 1)));
     int rc = carve(&h->arena, [&](Carver &take) {
         take(h->d_table, (size_t)K * K * K * S);
@@ -418,12 +427,19 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
         take(h->d_best_plan, 1);
         take(h->d_Fall, (size_t)(h->p.Smax + 1) * LS);
         take(h->d_bounds, table_bounds_ints(h->p) + (h->band_ok ? BAND_TOTALS : 0));
-        take(h->d_bound_work, h->band_ok ? band_least_ints(K, SB) : table_bounds_work(h->p));
+        take(h->d_bound_work, h->band_ok ? front_least_ints(K, SB) : table_bounds_work(h->p));
         take(h->d_scratch, (size_t)gg * 2 * LS);
         if (h->band_ok) {
             take(h->d_bandrecs, band_table_ints(K, h->p.Smax, SB));
             take(h->d_bandends, band_ends_ints(K, h->p.Smax, SB));
             take(h->d_bandthr, band_thresholds_ints(K, D));
+            take(h->d_backs, band_thresholds_ints(K, D));
+            take(h->d_front, front_table_ints(K, SB));
+            if (h->sparse_ok) {
+                take(h->d_graph, graph_table_ints(K));
+                take(h->d_kept, (size_t)SPARSE_PLANS * K);
+                take(h->d_kept_from, SPARSE_PLANS);
+            }
         }
         if (h->fast_ok) {
             take(h->d_recs, fast_table_ints(K, S));
@@ -452,7 +468,7 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     HIPCHK(hipMemsetAsync(h->d_state, 0, sizeof(SolveState), h->stream));
     HIPCHK(launch_init_best_plan(h->stream, h->d_best_plan));
     if (h->band_ok)
-        HIPCHK(launch_repack_band(h->stream, h->d_table, h->p, h->band_shapes, h->d_bandrecs, h->d_bandends, h->d_bounds));
+        HIPCHK(launch_repack_band(h->stream, h->d_table, h->p, h->band_shapes, h->d_bandrecs, h->d_bandends, h->d_bounds, !h->ordered));
     if (h->fast_ok) {
         h->KP = 16 * ((K + 15) / 16);
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
@@ -509,15 +525,16 @@ extern "C" int alpa_dp_create(alpa_dp_t **out, const int32_t *cost_table, int K,
     return create_handle(out, K, N, M, B, sizes, [&](alpa_dp *h) -> int {
         // the range check of the used part of the table (no negative latency; largest finite
         // entry for the overflow proof) is a reduction on the device copy
-        int32_t *d_range = h->d_tmpFS;             // (free until the first solve)
+        int32_t *d_range = h->d_tmpFS;             // (three; free until the first solve)
         HIPCHK(hipMemcpyAsync(h->d_table, cost_table, (size_t)K * K * K * S * 4,
                               hipMemcpyHostToDevice, h->stream));
-        HIPCHK(launch_table_range(h->stream, h->d_table, K, S, d_range));
-        int32_t range[2] = {0, -1};
+        HIPCHK(launch_table_range(h->stream, h->d_table, K, S, h->p.Smax, d_range));
+        int32_t range[3] = {0, -1, 1};
         HIPCHK(hipMemcpyAsync(range, d_range, sizeof(range), hipMemcpyDeviceToHost, h->stream));
         HIPCHK(hipStreamSynchronize(h->stream));
         if (range[0] < 0) return fail(ALPA_DP_EINVAL, "negative latency in cost_table");
         h->max_finite = range[1];
+        h->ordered = range[2] == 0;
         return ALPA_DP_OK;
     });
 }
@@ -567,6 +584,7 @@ extern "C" int alpa_dp_create_from_profiles(alpa_dp_t **out, const int32_t *t_l,
             HIPCHK(hipMemcpyAsync(&mx, d_max, 4, hipMemcpyDeviceToHost, h->stream));
             HIPCHK(hipStreamSynchronize(h->stream));
             h->max_finite = mx;
+            h->ordered = true;                     // (what fits with more stages fits with fewer)
             return ALPA_DP_OK;
         };
         const int rc2 = body();
@@ -585,8 +603,9 @@ extern "C" int alpa_dp_restrict_equal_layers(alpa_dp_t *h)
         restore{prev, h->device};
     const int K = h->p.K, D = h->p.D, S = h->p.S;
     HIPCHK(launch_equal_layer_mask(h->stream, h->d_table, K, S));
+    h->ordered = false;
     if (h->band_ok)
-        HIPCHK(launch_repack_band(h->stream, h->d_table, h->p, h->band_shapes, h->d_bandrecs, h->d_bandends, h->d_bounds));
+        HIPCHK(launch_repack_band(h->stream, h->d_table, h->p, h->band_shapes, h->d_bandrecs, h->d_bandends, h->d_bounds, !h->ordered));
     if (h->fast_ok) {
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
     }
@@ -703,16 +722,16 @@ static int candidate_bound(const alpa_dp *h, bool have_list, int n_tmax)
 // (the band kernel) the work counts from fewer on (us in one round and in two: 64 layers on 16 x 8, 1024
 // candidates: 2235 and 1367; 48 on 8 x 8, 2048: 716 and 337; but 24 on 2 x 8, 1500: 175 and 177).
 // Without the bounds the problem is small and one round takes everything.
-static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool one_per_cu, bool with_bounds)
+static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool one_per_cu, bool with_bounds, bool sparse)
 {
     RefineBuffers rb{};
     rb.knots[0] = h->d_knots;
     rb.knots[1] = h->d_knots + REFINE_MAX_KNOTS;
     rb.list = h->d_list;
-    rb.all = !with_bounds ? INT32_MAX : one_per_cu ? 512 : 2048;
-    rb.first_round = 256;                          // a candidate per compute unit
+    rb.all = !with_bounds ? INT32_MAX : sparse ? 4096 : one_per_cu ? 512 : 2048;
+    rb.first_round = sparse ? 2048 : 256;          // a candidate per compute unit, or eight
     rb.budget = 512;
-    rb.rounds = bound <= rb.all ? 1 : bound <= 8192 ? 2 : 3;
+    rb.rounds = bound <= rb.all ? 1 : sparse || bound <= 8192 ? 2 : 3;
     return rb;
 }
 
@@ -763,10 +782,13 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
 
     const bool fast = h->fast_ok && !(flags & ALPA_DP_GENERIC);
     const bool band = h->band_ok && !(flags & ALPA_DP_GENERIC);
+    const bool sparse = band && h->sparse_ok && h->ordered;
+    const SparseOut sparse_out{h->d_todo, &h->d_state->n_todo, h->d_slot, &h->d_state->n_slots, h->d_kept, h->d_kept_from};
+    const KeptPlans kept{sparse ? h->d_slot : nullptr, h->d_kept, h->d_kept_from, sparse ? graph_stages(h->d_graph, p.K) : nullptr};
     Problem p_band = p;
     p_band.S = h->band_shapes.S;
     const bool with_bounds = wants_bounds(h, bound, recorded);
-    const RefineBuffers rb = plan_rounds(h, bound, !fast, with_bounds);
+    const RefineBuffers rb = plan_rounds(h, bound, !fast, with_bounds, sparse);
     const int32_t *bounds = with_bounds ? h->d_bounds : h->d_no_bounds;
     // per-candidate results are wanted from every interval; a plan alone from few of them
     const RefineQuery rq{n_B > 0 ? h->d_sw_B : nullptr, p.B, std::max(n_B, 1), prune,
@@ -815,6 +837,13 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                         &h->d_state->ticket, &h->d_state->wave_relax, h->d_chunkmin, skip,
                         /*descending=*/prune ? 0 : 1, h->d_Fmin, h->d_Sbest, h->cands.cap, nullptr, nullptr,
                         nullptr, bounds};
+            if (sparse) {                          // what is not settled there is left to the recurrence
+                HIPCHK(launch_sparse_eval(st, fa, h->d_table, h->d_graph, h->max_finite, sparse_out, (flags & ALPA_DP_COUNT_WORK) != 0,
+                                          bound, h->n_cu));
+                fa.list = h->d_todo;
+                fa.n_list_p = &h->d_state->n_todo;
+                fa.ticket = &h->d_state->todo_ticket;
+            }
             HIPCHK(launch_recurrence_band(st, fa, h->band, h->d_bandrecs, h->d_bandends, h->d_bandthr, h->max_finite,
                                           (flags & ALPA_DP_COUNT_WORK) ? FAST_MODE_COUNT : FAST_MODE_BATCH,
                                           std::max(1, std::min(bound, h->n_cu))));
@@ -874,7 +903,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     HIPCHK(hipEventRecord(h->ev[2], st));
     if (n_B > 0) {
         HIPCHK(launch_sweep_epilogue(st, h->d_sw_B, n_B, h->d_state, h->d_cand, h->d_Fmin,
-                                     h->d_Sbest, h->d_sw_state, prune_sel, h->d_sw_c, h->d_sw_s));
+                                     h->d_Sbest, h->d_sw_state, prune_sel, h->d_sw_c, h->d_sw_s, p, kept, h->d_sw_plans));
         if (plan_slabs(h) && !(flags & ALPA_DP_GENERIC)) {
             const int chunk = sweep_chunk(h, n_B);
             for (int b = 0, x = 0; b < n_B; b += chunk, ++x) {
@@ -906,7 +935,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         return ALPA_DP_OK;
     }
     HIPCHK(launch_epilogue(st, p, h->d_cand, h->d_Fmin, h->d_Sbest, h->d_state, prune_sel, d_out_T != nullptr,
-                           have_list || !d_out_T ? h->d_T : d_out_T));
+                           have_list || !d_out_T ? h->d_T : d_out_T, kept, h->d_plan_tmp, h->d_best_plan, d_out_plan));
     if (d_out_T && have_list && bound > 0) HIPCHK(launch_scatter_T(st, h->d_T, h->d_rank, n_tmax, d_out_T));
     // every layer of the winning candidate (does nothing if there is none), then the walk
     if (band) {

@@ -33,6 +33,10 @@ struct SolveState {
     int32_t n_range;
     int32_t n_list;          // candidates to evaluate in the present round
     int32_t n_knots;         // candidates evaluated so far
+    int32_t n_todo;          // of the present round, those that the graphs do not settle
+    int32_t todo_ticket;
+    int32_t n_slots;         // plans kept for the selection (kernels_sparse.hip)
+    int32_t plan_done;       // the selection has written the plan
 };
 
 struct Problem {
@@ -135,6 +139,14 @@ __device__ __forceinline__ void publish_min(int64_t *p, int64_t v, int tid)
     if (t == 0) atomicMin((long long *)p, (long long)v);
 }
 
+// Barrier for what the waves exchange through LDS: loads from global memory stay in flight across it.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // ---- host-side launchers (callers validate sizes first; none of these synchronises)
 
 constexpr int SORT_SLICES = 1024;        // one-wave slices of the radix sort
@@ -173,8 +185,8 @@ __host__ __device__ __forceinline__ int32_t band_threshold(int32_t max_finite, i
 }
 // behind the bounds (launch_band_bounds): a lower bound on F for each threshold and the least largest stage; then the sum and the
 // largest latency of a plan for each, room for 2 BAND_THRESHOLDS + 1 more, and what is there for the present table: 1 for these
-// numbers, 2 and 4 for the two halves of launch_band_exact_bounds
-constexpr int BAND_THERE = 5 * BAND_THRESHOLDS + 2, BAND_TOTALS = BAND_THERE + 1;
+// numbers, 2 and 4 for the two halves of launch_band_exact_bounds; and whether latencies fall with the number of stages
+constexpr int BAND_THERE = 5 * BAND_THRESHOLDS + 2, BAND_FALLS = BAND_THERE + 1, BAND_TOTALS = BAND_FALLS + 1;
 
 // Rounds of evaluation (kernels_refine.hip)
 constexpr int REFINE_MAX_KNOTS = 4096;   // knots a refinement step takes in (LDS)
@@ -218,8 +230,9 @@ hipError_t launch_build_table(hipStream_t st, const int32_t *t_l, const int64_t 
                               const int64_t *mem_act, int K, int S, int O, int64_t mem_device,
                               int32_t *table, int32_t *max_finite);
 
-// out[0] = smallest, out[1] = largest finite entry (-1 if none) of the used part of a table
-hipError_t launch_table_range(hipStream_t st, const int32_t *table, int K, int S, int32_t *out);
+// out[0] = smallest, out[1] = largest finite entry (-1 if none) of the used part of a table, out[2] = 1 if one is below that of fewer
+// stages (of up to Smax)
+hipError_t launch_table_range(hipStream_t st, const int32_t *table, int K, int S, int Smax, int32_t *out);
 
 hipError_t launch_valu_peak(hipStream_t st, int grid, int iters, int32_t *sink);
 hipError_t launch_equal_layer_mask(hipStream_t st, int32_t *table, int K, int S);
@@ -289,20 +302,67 @@ struct BandShapes {
     int S, S_table;
     const int32_t *sizes, *first, *next;
 };
+// The smallest of an entry's shapes of one device count: `entry` is that of shape 0.  What a filter leaves of several shapes
+// with equal device counts has the least sum with the smallest of them, so the kernel sees one shape for each.
+__device__ __forceinline__ int32_t band_smallest(const int32_t *__restrict__ entry, const BandShapes &b, int q)
+{
+    if (!b.first) return entry[q];
+    int32_t t = INF_I32;
+    for (int x = b.first[q]; x >= 0; x = b.next[x]) t = min(t, entry[x]);
+    return t;
+}
+
 size_t band_table_ints(int K, int Smax, int S);
 size_t band_ends_ints(int K, int Smax, int S);
 hipError_t launch_repack_band(hipStream_t st, const int32_t *table, const Problem &p, const BandShapes &b,
-                              int32_t *recs, int32_t *ends, int32_t *bounds);
+                              int32_t *recs, int32_t *ends, int32_t *bounds, bool falls);
 // what the table says about candidates: launch_table_bounds' place for these sizes; `once`: nothing is done where it is there
 // (a recorded solve is replayed)
-size_t band_least_ints(int K, int S);
 size_t band_thresholds_ints(int K, int D);
+struct BandWork {
+    int32_t *least, *front;  // front_least_ints, front_table_ints
+    int32_t *thr, *backs;    // band_thresholds_ints each (no windows in the second)
+    int32_t *graph;          // graph_table_ints; null where candidates do not go by graphs
+};
 hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
-                              int32_t *work, int32_t *thr, int32_t *bounds, bool once);
+                              const BandWork &w, int32_t *bounds, bool once);
 hipError_t launch_band_exact_bounds(hipStream_t st, const BandShapes &b, const BandShape &shape, const Problem &p, int32_t max_finite,
                                     const int32_t *recs, const int32_t *ends, int32_t *work, const int32_t *thr, int32_t *bounds, bool once);
 hipError_t launch_recurrence_band(hipStream_t st, const FastArgs &f, const BandShape &b, const int32_t *recs,
                                   const int32_t *ends, const int32_t *thr, int32_t max_finite, int mode, int grid);
+
+// front costs (kernels_front.hip)
+struct FrontTable {
+    const int32_t *units, *unit_min, *least;
+    const uint8_t *run;
+    const int32_t *sizes;
+    int NG;
+};
+size_t front_least_ints(int K, int S);
+size_t front_table_ints(int K, int S);
+size_t front_lds_bytes(int K, int D, int S);
+FrontTable front_table(const int32_t *least, const int32_t *front, int K, int S, const int32_t *sizes, bool back);
+hipError_t launch_front_thresholds(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
+                                   int32_t *work, int32_t *front, int32_t *fronts, int32_t *backs, int32_t *totals,
+                                   int32_t *plans, int32_t *windows, int32_t *graph_used, const int32_t *asked);
+
+// candidates by the stages that can be in their best plans (kernels_sparse.hip)
+constexpr int SPARSE_PLANS = 4096;       // plans that are kept for the selection, K uint16 each
+struct SparseOut {
+    int32_t *todo, *n_todo;  // candidates that are left to the recurrence
+    int32_t *slot, *n_slots; // each candidate's plan (-1: not kept)
+    uint16_t *plans;         // its stages in the graph that it is from
+    int32_t *plan_from;      // where that begins
+};
+size_t graph_table_ints(int K);
+int32_t *graph_used(int32_t *graph, int K);
+const int4 *graph_stages(int32_t *graph, int K);
+hipError_t launch_sparse_graph(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
+                               const int32_t *work, const int32_t *front, const int32_t *fronts, const int32_t *backs,
+                               const int32_t *totals, const int32_t *plans, const int32_t *falls, int32_t *graph, const int32_t *asked);
+// f: the recurrence's arguments (those of them that count); most: upper bound of the list's length
+hipError_t launch_sparse_eval(hipStream_t st, const FastArgs &f, const int32_t *table, int32_t *graph, int32_t max_finite, const SparseOut &o, bool count,
+                              int most, int n_cu);
 
 // plan recovery of one candidate, a launch per layer (general sizes)
 hipError_t launch_plan_layers(hipStream_t st, const Problem &p, const int32_t *table,
@@ -317,9 +377,16 @@ inline size_t table_bounds_work(const Problem &p)
 }
 hipError_t launch_table_bounds(hipStream_t st, const Problem &p, const int32_t *table,
                                const int32_t *sizes, int32_t *work, int32_t *bounds);
+// plans of the candidates that the graphs have settled (slot null: of none)
+struct KeptPlans {
+    const int32_t *slot;
+    const uint16_t *plans;
+    const int32_t *from;
+    const int4 *stages;      // of all graphs (kernels_sparse.hip)
+};
 hipError_t launch_epilogue(hipStream_t st, const Problem &p, const int32_t *cand,
                            const int32_t *Fmin, const int32_t *Sbest, SolveState *state, int prune,
-                           bool want_T, int64_t *T);
+                           bool want_T, int64_t *T, const KeptPlans &kept, void *plan_tmp, void *best_plan, void *plan_out);
 hipError_t launch_scatter_T(hipStream_t st, const int64_t *T, const int32_t *rank_of_orig,
                             int n_orig, int64_t *out_T);
 hipError_t launch_plan_walk(hipStream_t st, const Problem &p, const int32_t *table,
@@ -329,7 +396,7 @@ hipError_t launch_plan_walk(hipStream_t st, const Problem &p, const int32_t *tab
 hipError_t launch_sweep_epilogue(hipStream_t st, const int32_t *B_vals, int n_B,
                                  const SolveState *solve, const int32_t *cand,
                                  const int32_t *Fmin, const int32_t *Sbest, SolveState *states,
-                                 int prune, int32_t *win_c, int32_t *win_s);
+                                 int prune, int32_t *win_c, int32_t *win_s, const Problem &p, const KeptPlans &kept, void *plans);
 hipError_t launch_plan_walk_many(hipStream_t st, const Problem &p, const int32_t *table,
                                  const int32_t *sizes, SolveState *states, const int32_t *F_all,
                                  size_t slab, void *plans, int n);

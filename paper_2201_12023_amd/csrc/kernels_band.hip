@@ -75,22 +75,12 @@ __device__ __forceinline__ size_t band_cell(int P, int NHB, int q, int k, int le
            ((l & 1) * 8 + (k & 7)) * 4 + ((l >> 1) & 3);
 }
 
-// The smallest of an entry's shapes of one device count: `entry` is that of shape 0.  What a filter leaves of several shapes
-// with equal device counts has the least sum with the smallest of them, so the kernel sees one shape for each.
-__device__ __forceinline__ int32_t band_smallest(const int32_t *__restrict__ entry, const BandShapes &b, int q)
-{
-    if (!b.first) return entry[q];
-    int32_t t = INF_I32;
-    for (int x = b.first[q]; x >= 0; x = b.next[x]) t = min(t, entry[x]);
-    return t;
-}
-
 // A wave per (s, block, q): the block's units (a lane per entry and batch), and the smallest entry from each of
 // eight positions on.  Blocks and units that only fill up a tile are +infinity.  there: see BAND_THERE.
 __global__ __launch_bounds__(256) void repack_band_kernel(const int32_t *__restrict__ table, int K, BandShapes b, int n,
-                                                          int32_t *__restrict__ recs, int32_t *__restrict__ ends, int32_t *there)
+                                                          int32_t *__restrict__ recs, int32_t *__restrict__ ends, int32_t *there, int falls)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *there = 0;       // (another table)
+    if (blockIdx.x == 0 && threadIdx.x < 2) there[threadIdx.x] = threadIdx.x ? falls : 0;      // (another table; BAND_FALLS)
     const int S = b.S;
     const int NHB = band_blocks(K), NG = (NHB + 3) / 4, P = band_tiles(K);
     const int lane = threadIdx.x & (WAVE - 1);
@@ -127,12 +117,12 @@ __global__ __launch_bounds__(256) void repack_band_kernel(const int32_t *__restr
 }
 
 hipError_t launch_repack_band(hipStream_t st, const int32_t *table, const Problem &p, const BandShapes &b,
-                              int32_t *recs, int32_t *ends, int32_t *bounds)
+                              int32_t *recs, int32_t *ends, int32_t *bounds, bool falls)
 {
     const int K = p.K, Smax = p.Smax;
     const int n = Smax * 4 * ((band_blocks(K) + 3) / 4) * b.S;
     hipLaunchKernelGGL(repack_band_kernel, dim3(std::min((n + 3) / 4, 16384)), dim3(256), 0, st, table, K, b, n,
-                       recs, ends, bounds + table_bounds_ints(p) + BAND_THERE);
+                       recs, ends, bounds + table_bounds_ints(p) + BAND_THERE, falls ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -143,311 +133,8 @@ __device__ __forceinline__ int32_t band_entry(int32_t t)
     return __builtin_amdgcn_update_dpp(0, t, 0x150 + N, 0xf, 0xf, true);
 }
 
-// Barrier for what the waves exchange through LDS: loads from global memory stay in flight across it.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// ---- what a table says about candidates (once per table)
-//
-// For BAND_THRESHOLDS values of t_max, from the largest latency down: a candidate takes what is known of the next
-// threshold that is not below it, whose filter leaves every term of its own.
-//   * Windows.  A plan has a stage of the layers k .. on d devices behind it only if the layers from k on need no
-//     more than d under the filter and those in front of k leave as many.  With t_max at the low end, where most
-//     layers are run, few device counts are left: 1 to 16 a block of eight layers where the smallest
-//     t_max with a plan takes all of 64 devices.
-//   * Front costs.  P(k, d): the least sum of stages that cover the k layers in front on d devices, with the least
-//     t_intra over the number of stages behind them.  F(s, k, d) + P(k, D - d) bounds every plan that goes on from
-//     there, so a candidate is finished once no cell of layer s gets below what it has (64 layers on 8 x 8 of
-//     dense layers, t_max at the 5 % quantile: after 4 layers, 9 with the least F of more stages and no filter).
-// And without a filter: the least largest stage (no plan below that t_max), and the lowest threshold whose least plan
-// is that without a filter (from there on F hardly changes).  least[k][i][q]: q padded to a multiple of 16 (SP).
-// there (null: not asked): see BAND_THERE.
-__global__ void band_least_kernel(const int32_t *__restrict__ table, int K, int Smax, BandShapes b, int SP,
-                                  const int32_t *__restrict__ there, int32_t *__restrict__ least)
-{
-    if (there && *there) return;
-    const int n = K * K * SP;
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
-        const int ki = x / SP, q = x - ki * SP, k = ki / K, i = ki - k * K;
-        int32_t m = DEV_INF;
-        if (q < b.S && i >= k) {
-            const int32_t *t = table + (size_t)ki * b.S_table;
-            const size_t layer = (size_t)K * K * b.S_table;
-            for (int y = b.first ? b.first[q] : q; y >= 0; y = b.first ? b.next[y] : -1) {
-#pragma unroll 8
-                for (int s = 0; s < Smax; ++s) m = min(m, t[s * layer + y]);
-            }
-        }
-        least[x] = min(m, DEV_INF);
-    }
-}
-
-// P(k, .) lies at k * R + RS + d (R = 2 RS + 1): RS cells of +infinity in front of d = 0, so that d - a needs no test.
-// Rows for all beginnings of a turn (below: up to 128 of them in four groups of lanes, else up to 64), so that the last ones,
-// behind K, need none either: they read +infinity.
-__host__ __device__ constexpr int band_front_ints(int K, int RS)
-{
-    const int turn = RS == 64 ? 128 : 64;
-    return ((K + turn - 1) / turn * turn + 1) * (2 * RS + 1);
-}
-
-// P(k, .) for k = 1 .. K, one after the other (d = 0 is +infinity but for k = 0).  Lanes are G groups of device counts, each
-// with stage beginnings of its own: a turn takes two of them for every wave and group, b0 + nw (g + G y), and sixteen shapes,
-// whose t_intra come as in the recurrence, loaded two turns ahead.  Two and a half instructions a beginning and shape (half an
-// addition for the cell, an LDS read, the sum, half a three-operand minimum), four shapes at a time where a lane has a
-// cell for one of them and the filter leaves a term.  Bound by issue and by what a turn waits for in
-// the one workgroup that a threshold has: 64 layers on 8 x 8 take 105 us, 48 on 32 x 8 424 (115 and 537 with four beginnings
-// a turn, of which few are there at first, and an address for each of their cells).
-// MAXIMUM: the largest stage instead of the sum.
-template <int RS, int G, bool MAXIMUM>
-__device__ __forceinline__ void band_fronts(const int32_t *__restrict__ least, const int32_t *__restrict__ sizes,
-                                            int K, int D, int S, int SP, int32_t c, int32_t *P)
-{
-    constexpr int nw = BAND_WAVES, R = 2 * RS + 1, BS = 2 * G * nw;        // BS: beginnings of a turn
-    static_assert(BS <= (RS == 64 ? 128 : 64), "rows of P");
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int b_lane = wid + nw * (lane / (WAVE / G)), d_lane = lane % (WAVE / G) + 1;
-    struct Turn { int k, b0, q0; };
-    auto behind = [&](Turn t) {
-        if (t.b0 + BS < t.k) return Turn{t.k, t.b0 + BS, t.q0};
-        if (t.q0 + 16 < S) return Turn{t.k, 0, t.q0 + 16};
-        return Turn{t.k + 1, 0, 0};
-    };
-    struct Load { int32_t t[2], size; };
-    auto load = [&](Turn n, Load &l) {
-        const int k = min(n.k, K);
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-            l.t[y] = least[(uint32_t)((min(n.b0 + b_lane + y * (G * nw), k - 1) * K + k - 1) * SP + n.q0 + (lane & 15))];
-        l.size = sizes[min(n.q0 + (lane & 15), S - 1)];
-    };
-    Turn now{1, 0, 0}, next = behind(now);
-    Load l0, l1;
-    load(now, l0);
-    load(next, l1);
-    const int all = band_front_ints(K, RS);
-    for (int x = tid; x < all; x += nw * WAVE) P[x] = x == RS ? 0 : DEV_INF;
-    lds_barrier();
-    auto turn = [&](Load &l) {                     // `now`, then loads for two turns on
-        const int k = now.k, size = l.size, b = now.b0 + b_lane;
-        const int32_t t0 = l.t[0] <= c && b < k ? l.t[0] : DEV_INF;
-        const int32_t t1 = l.t[1] <= c && b + G * nw < k ? l.t[1] : DEV_INF;
-        const uint64_t lanes = __ballot(min(t0, t1) < DEV_INF);
-        unsigned some = (unsigned)(lanes | lanes >> 32);
-        some = (some | some >> 16) & 0xffff;       // shapes with a term
-        const Turn then = behind(next);
-        load(then, l);
-        for (int d0 = 0; d0 < D && some != 0; d0 += WAVE / G) {
-            const unsigned has = some & (unsigned)__ballot(size <= d0 + WAVE / G);
-            if (has == 0) continue;
-            int32_t acc = DEV_INF;
-            const int32_t *p = P + b * R + RS + d0 + d_lane;
-            auto shapes = [&](auto Q_T) {
-                constexpr int Q = decltype(Q_T)::value;
-                if ((has >> Q & 15) == 0) return;
-                int32_t f0[4], f1[4];
-                auto read = [&](auto X_T) {
-                    constexpr int X = decltype(X_T)::value;
-                    const int32_t *cell = p - __builtin_amdgcn_update_dpp(0, size, 0x150 + Q + X, 0xf, 0xf, true);
-                    f0[X] = cell[0];
-                    f1[X] = cell[G * nw * R];
-                };
-                auto term = [&](auto X_T) {
-                    constexpr int X = decltype(X_T)::value;
-                    const int32_t u0 = band_entry<Q + X>(t0), u1 = band_entry<Q + X>(t1);
-                    acc = min(acc, MAXIMUM ? min(max(u0, f0[X]), max(u1, f1[X])) : min(u0 + f0[X], u1 + f1[X]));
-                };
-                read(std::integral_constant<int, 0>{}); read(std::integral_constant<int, 1>{});
-                read(std::integral_constant<int, 2>{}); read(std::integral_constant<int, 3>{});
-                term(std::integral_constant<int, 0>{}); term(std::integral_constant<int, 1>{});
-                term(std::integral_constant<int, 2>{}); term(std::integral_constant<int, 3>{});
-            };
-            shapes(std::integral_constant<int, 0>{});
-            shapes(std::integral_constant<int, 4>{});
-            shapes(std::integral_constant<int, 8>{});
-            shapes(std::integral_constant<int, 12>{});
-            if (d0 + d_lane <= D) atomicMin(&P[k * R + RS + d0 + d_lane], acc);
-        }
-        if (next.k != k) lds_barrier();
-        now = next;
-        next = then;
-    };
-    while (now.k <= K) {
-        turn(l0);
-        if (now.k > K) break;
-        turn(l1);
-    }
-}
-
-// A plan that reaches P(K, D), walked from its last stage on, with the t_intra it really has (how many stages lie
-// behind each is known now): plan[0] = their sum, plan[1] = the largest; +infinity where a stage has no entry.
-__device__ __forceinline__ void band_front_plan(const int32_t *__restrict__ least, const int32_t *__restrict__ table,
-                                                const BandShapes &bs, int K, int D, int SP, int32_t c,
-                                                const int32_t *P, int RS, int32_t *plan)
-{
-    __shared__ int sh_term[2], sh_sum, sh_largest;
-    __shared__ int sh_stage[256];                  // 64 (first layer, last) + shape of each
-    const int S = bs.S;
-    const int32_t *const sizes = bs.sizes;
-    const int R = 2 * RS + 1, tid = threadIdx.x;
-    if (tid < 2) sh_term[tid] = INT32_MAX;
-    if (tid == 2) sh_sum = 0;
-    if (tid == 3) sh_largest = 0;
-    lds_barrier();
-    int k = K, d = D, n = 0;
-    bool found = P[K * R + RS + D] < DEV_INF;
-    while (found && k > 0) {                       // (uniform: every thread walks the same plan)
-        const int32_t want = P[k * R + RS + d];
-        int at = INT32_MAX;
-        for (int b = tid >> 4; b < k; b += BAND_WAVES * WAVE / 16)
-            for (int q = tid & 15; q < S; q += 16) {
-                const int32_t t = least[(uint32_t)((b * K + k - 1) * SP + q)];
-                if (t <= c && t + P[b * R + RS + d - sizes[q]] == want) at = min(at, b * 64 + q);
-            }
-        if (at != INT32_MAX) atomicMin(&sh_term[n & 1], at);
-        lds_barrier();
-        const int x = __builtin_amdgcn_readfirstlane(sh_term[n & 1]);
-        found = x != INT32_MAX;                    // (there is a term)
-        if (!found) break;
-        const int b = x >> 6, q = x & 63;
-        if (tid == 0) {
-            sh_term[~n & 1] = INT32_MAX;           // (last read a barrier ago)
-            sh_stage[n] = (b * K + k - 1) * 64 + q;
-        }
-        lds_barrier();
-        ++n;
-        k = b;
-        d -= sizes[q];
-    }
-    if (tid < n) {
-        const int ki = sh_stage[tid] >> 6;
-        const int32_t t = band_smallest(table + ((size_t)tid * K * K + ki) * bs.S_table, bs, sh_stage[tid] & 63);
-        atomicMax(&sh_largest, t);
-        atomicAdd(&sh_sum, t == INF_I32 ? 0 : t);
-    }
-    lds_barrier();
-    if (tid == 0) {
-        const bool whole = found && sh_largest != INF_I32;
-        plan[0] = whole ? sh_sum : DEV_INF;
-        plan[1] = whole ? sh_largest : DEV_INF;
-    }
-}
-
-// Windows of one threshold.  `need`: fewest devices of each stage; then wave 0 goes through the layers from the front
-// and wave 1 from the back.  NX: layers / 64, at least.
-template <int NX>
-__device__ __forceinline__ void band_find_windows(const int32_t *__restrict__ least, const int32_t *__restrict__ sizes,
-                                                  int K, int D, int S, int SP, int32_t c, uint16_t *need, int32_t *windows)
-{
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int KS = K | 1;                          // (odd: a column is read as fast as a row)
-    for (int x = tid; x < K * K; x += blockDim.x) {
-        const int4 *row = (const int4 *)(least + (size_t)x * SP);
-        int m = 1 << 14;
-        for (int q = 0; q < S; q += 4) {
-            const int4 t = row[q >> 2];
-            if (t.x <= c) m = min(m, sizes[q]);
-            if (t.y <= c) m = min(m, sizes[min(q + 1, S - 1)]);
-            if (t.z <= c) m = min(m, sizes[min(q + 2, S - 1)]);
-            if (t.w <= c) m = min(m, sizes[min(q + 3, S - 1)]);
-        }
-        need[(x / K) * KS + x % K] = (uint16_t)m;  // (the stage of layers x / K .. x % K)
-    }
-    __syncthreads();
-    if (wid >= 2) return;
-    const bool front = wid == 0;
-    int v[NX];                                     // front: fewest devices of layers 0 .. k - 1, k = 64 x + lane; back: of k .. K - 1
-#pragma unroll
-    for (int x = 0; x < NX; ++x) v[x] = front && x == 0 && lane == 0 ? 0 : 1 << 20;
-    int far = 0;
-    constexpr int Y = 8;                           // rows read ahead
-    for (int y0 = 0; y0 < K; y0 += Y) {
-        int m[Y][NX];
-#pragma unroll
-        for (int y = 0; y < Y; ++y) {
-            const int i = front ? min(y0 + y, K - 1) : max(K - 1 - y0 - y, 0);     // stages that begin (end) with layer i
-#pragma unroll
-            for (int x = 0; x < NX; ++x) {
-                const int k = WAVE * x + lane - (front ? 1 : 0), at = max(0, min(k, K - 1));
-                const int n = need[front ? i * KS + at : at * KS + i];
-                m[y][x] = k < 0 ? 1 << 20 : n;
-            }
-        }
-#pragma unroll
-        for (int y = 0; y < Y; ++y) {
-            if (y0 + y >= K) break;
-            const int i = front ? y0 + y : K - 1 - y0 - y;
-            if (front) {
-#pragma unroll
-                for (int x = 0; x < NX; ++x)
-                    if (x == 0 || i >= WAVE * x) far = __builtin_amdgcn_readlane(v[x], i & 63);
-            }
-#pragma unroll
-            for (int x = 0; x < NX; ++x) v[x] = min(v[x], far + m[y][x]);
-            if (!front) {
-#pragma unroll
-                for (int x = 0; x < NX; ++x)
-                    if (x == 0 || i >= WAVE * x) far = __builtin_amdgcn_readlane(v[x], i & 63);
-            }
-        }
-    }
-#pragma unroll
-    for (int x = 0; x < NX; ++x) {
-        int m = WAVE * x + lane < K ? v[x] : 1 << 20;      // the least of the block's eight
-        m = min(m, dpp_mov<0xB1>(m));
-        m = min(m, dpp_mov<0x4E>(m));
-        m = min(m, dpp_mov<0x141>(m));
-        const int b = 8 * x + (lane >> 3);
-        if ((lane & 7) == 0 && b < 32) windows[(front ? 32 : 0) + b] = front ? max(0, D - m) : min(m, D + 1);
-    }
-    for (int b = 8 * NX + lane; b < 32; b += WAVE) windows[(front ? 32 : 0) + b] = front ? 0 : D + 1;
-}
-
-// Blocks [0, BAND_THRESHOLDS): front costs, then the least largest stage, then windows.
-// fronts[j][k][RS]: P(k, D - d) at d - 1 (+infinity where no layer or no device is in front); totals[j]: P(K, D), and the
-// least largest stage behind the last.
-template <int RS, int G>
-__global__ __launch_bounds__(WAVE * BAND_WAVES) void band_thresholds_kernel(const int32_t *__restrict__ least, const int32_t *__restrict__ table,
-                                                               BandShapes bs, int K, int D, int SP, int32_t max_finite,
-                                                               int32_t *__restrict__ fronts, int32_t *__restrict__ totals,
-                                                               int32_t *__restrict__ plans, int32_t *__restrict__ windows,
-                                                               const int32_t *__restrict__ there)
-{
-    if (there && *there) return;
-    extern __shared__ int32_t lds[];
-    constexpr int R = 2 * RS + 1;
-    const int j = blockIdx.x, S = bs.S;
-    const int32_t *const sizes = bs.sizes;
-    if (j <= BAND_THRESHOLDS) {
-        const int32_t c = j < BAND_THRESHOLDS ? band_threshold(max_finite, j) : DEV_INF - 1;
-        if (j < BAND_THRESHOLDS) band_fronts<RS, G, false>(least, sizes, K, D, S, SP, c, lds);
-        else band_fronts<RS, G, true>(least, sizes, K, D, S, SP, c, lds);
-        if (threadIdx.x == 0) totals[j] = min(lds[K * R + RS + D], DEV_INF);
-        if (j == BAND_THRESHOLDS) {
-            if (threadIdx.x == 0) plans[2 * BAND_THRESHOLDS] = 0;      // (band_bounds_kernel counts there)
-            return;
-        }
-        for (int x = threadIdx.x; x < K * RS; x += blockDim.x) {
-            const int k = x / RS, d = x - k * RS + 1;
-            fronts[(size_t)j * K * RS + x] = k >= 1 && d < D ? min(lds[k * R + RS + D - d], DEV_INF) : DEV_INF;
-        }
-        band_front_plan(least, table, bs, K, D, SP, c, lds, RS, plans + 2 * j);
-        return;
-    }
-    const int w = j - BAND_THRESHOLDS - 1;
-    const int32_t c = band_threshold(max_finite, w);
-    if (K <= 64) band_find_windows<1>(least, sizes, K, D, S, SP, c, (uint16_t *)lds, windows + 64 * w);
-    else if (K <= 128) band_find_windows<2>(least, sizes, K, D, S, SP, c, (uint16_t *)lds, windows + 64 * w);
-    else band_find_windows<4>(least, sizes, K, D, S, SP, c, (uint16_t *)lds, windows + 64 * w);
-}
-
 static int band_row_ints(int D);
 
-size_t band_least_ints(int K, int S) { return (size_t)K * K * ((S + 15) / 16 * 16); }
 size_t band_thresholds_ints(int K, int D)
 {
     return (size_t)BAND_THRESHOLDS * (K * band_row_ints(D) + 64);
@@ -583,6 +270,7 @@ __device__ __forceinline__ void band_recurrence(const BandArgs &a)
                 continue;
             }
         }
+        if (DUMP && a.s_top_p[j] < 1) continue;        // (uniform: there is no plan, or it is known)
         // Plan recovery walks back from F(s*, first layer 1, all devices): only layers up to s* are needed,
         // and of layer s only first layers (0-based) s* - s <= k <= K - s
         const int s_top = DUMP ? min(a.p.Smax, __builtin_amdgcn_readfirstlane(a.s_top_p[j])) : a.p.Smax;
@@ -1069,25 +757,19 @@ BandShape band_shape(int K, int D, int S, const int32_t *sizes)
     return b;
 }
 
-// work: band_least_ints; thr: band_thresholds_ints (fronts, windows); behind the bounds: BAND_TOTALS (totals, plans)
+// behind the bounds: BAND_TOTALS (totals, plans)
 hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
-                              int32_t *work, int32_t *thr, int32_t *bounds, bool once)
+                              const BandWork &w, int32_t *bounds, bool once)
 {
     int32_t *totals = bounds + table_bounds_ints(p), *plans = totals + BAND_THRESHOLDS + 1, *there = totals + BAND_THERE;
     const int32_t *const asked = once ? there : nullptr;
-    const int SP = (b.S + 15) / 16 * 16, RS = band_row_ints(p.D);
-    int32_t *windows = thr + (size_t)BAND_THRESHOLDS * p.K * RS;
-    hipLaunchKernelGGL(band_least_kernel, dim3(std::min((p.K * p.K * SP + 255) / 256, 16384)), dim3(256), 0, st, table, p.K,
-                       p.Smax, b, SP, asked, work);
-    const size_t lds = std::max((size_t)band_front_ints(p.K, RS) * 4, (size_t)2 * p.K * (p.K | 1));
-    const auto kernel = p.D <= 16 ? band_thresholds_kernel<64, 4> : p.D <= 32 ? band_thresholds_kernel<64, 2> :
-                        RS == 64 ? band_thresholds_kernel<64, 1> : RS == 128 ? band_thresholds_kernel<128, 1> : band_thresholds_kernel<256, 1>;
-    if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(kernel, dim3(2 * BAND_THRESHOLDS + 1), dim3(WAVE * BAND_WAVES), lds, st, work, table, b, p.K, p.D, SP,
-                       max_finite, thr, totals, plans, windows, asked);
+    const int RS = band_row_ints(p.D);
+    int32_t *const thr = w.thr;
+    hipError_t e = launch_front_thresholds(st, table, b, p, max_finite, w.least, w.front, thr, w.backs, totals, plans,
+                                           thr + (size_t)BAND_THRESHOLDS * p.K * RS, w.graph ? graph_used(w.graph, p.K) : nullptr, asked);
+    if (e == hipSuccess && w.graph)
+        e = launch_sparse_graph(st, table, b, p, max_finite, w.least, w.front, thr, w.backs, totals, plans, totals + BAND_FALLS, w.graph, asked);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(band_bounds_kernel, dim3(BAND_THRESHOLDS), dim3(BAND_BOUNDS_THREADS), 0, st, p, max_finite, table, b, thr, RS,
                        totals, plans, bounds, once, there);
     return hipGetLastError();

@@ -393,13 +393,69 @@ __device__ __forceinline__ void eq4_select(int B, int n, int j_first, int range,
     }
 }
 
+struct PlanDev {                       // same layout as alpa_plan_t (2072 bytes)
+    int64_t T_star;
+    int32_t t_max, num_stages, n_evaluated;
+    int32_t first_layer[256 + 1];
+    int32_t shape_idx[256];
+};
+static_assert(sizeof(PlanDev) == 2072, "PlanDev layout");
+
+// running best over all solves of a handle (not kept by sweeps: best_plan is null): lower T*, then lower t_max
+__device__ __forceinline__ bool better_plan(const PlanDev *best_plan, int64_t T, int32_t c)
+{
+    return best_plan && (T < best_plan->T_star || (T == best_plan->T_star && c < best_plan->t_max));
+}
+
+// Writes the winner's plan where it is kept, or that there is none (one block, behind eq4_select).  Else nothing: the plan is
+// recovered from the winner's layers.
+__device__ __forceinline__ void kept_plan(SolveState *state, const KeptPlans &kept, int K, PlanDev *plan, PlanDev *best_plan,
+                                          PlanDev *plan_out)
+{
+    __shared__ PlanDev sh;
+    __shared__ int sh_better;
+    const int tid = threadIdx.x, j = state->best_idx, s = state->best_s;
+    const int slot = j >= 0 && kept.slot ? kept.slot[j] : -1;
+    if (j >= 0 && slot < 0) {                      // (uniform)
+        if (tid == 0) state->plan_done = 0;
+        return;
+    }
+    constexpr int n32 = (int)(sizeof(PlanDev) / 4);
+    for (int x = tid; x < n32; x += SEL_THREADS) ((int32_t *)&sh)[x] = 0;
+    __syncthreads();
+    if (tid == 0) {
+        sh.T_star = j >= 0 ? state->best_T : INF_I64;
+        sh.t_max = j >= 0 ? state->best_c : 0;
+        sh.num_stages = j >= 0 ? s : 0;
+        sh.n_evaluated = state->n_processed;
+        sh_better = j >= 0 && better_plan(best_plan, state->best_T, state->best_c);
+        state->plan_done = 1;
+        state->plan_n = 0;
+    }
+    if (j >= 0 && tid < s) {                       // (s <= 256)
+        const int v = kept.stages[kept.from[slot] + kept.plans[(size_t)slot * K + tid]].w;
+        sh.first_layer[tid + 1] = (v >> 14 & 255) + 1;     // (the last one is K)
+        sh.shape_idx[tid] = v >> 8 & 63;
+    }
+    __syncthreads();
+    for (int x = tid; x < n32; x += SEL_THREADS) {
+        const int32_t v = ((const int32_t *)&sh)[x];
+        ((int32_t *)plan)[x] = v;
+        if (plan_out) ((int32_t *)plan_out)[x] = v;
+        if (sh_better) ((int32_t *)best_plan)[x] = v;
+    }
+}
+
 __global__ __launch_bounds__(SEL_THREADS) void epilogue_kernel(Problem p, const int32_t *__restrict__ cand,
                                                         const int32_t *__restrict__ Fmin,
                                                         const int32_t *__restrict__ Sbest,
                                                         SolveState *state, int prune, int want_T,
-                                                        int64_t *__restrict__ T)
+                                                        int64_t *__restrict__ T, KeptPlans kept, PlanDev *plan,
+                                                        PlanDev *best_plan, PlanDev *plan_out)
 {
     eq4_select(p.B, state->n_cand, state->n_first, state->n_range, cand, Fmin, Sbest, state, prune, want_T ? T : nullptr);
+    __syncthreads();                                   // thread 0's stores, then every thread's reads
+    kept_plan(state, kept, p.K, plan, best_plan, plan_out);
 }
 
 // Sweep over the number of microbatches: F of Eq. 3 does not depend on B, so one wave per
@@ -409,14 +465,17 @@ __global__ __launch_bounds__(SEL_THREADS) void sweep_epilogue_kernel(
     const int32_t *__restrict__ B_vals, const SolveState *__restrict__ solve,
     const int32_t *__restrict__ cand, const int32_t *__restrict__ Fmin,
     const int32_t *__restrict__ Sbest, SolveState *states, int prune, int32_t *__restrict__ win_c,
-    int32_t *__restrict__ win_s)
+    int32_t *__restrict__ win_s, int K, KeptPlans kept, PlanDev *plans)
 {
     const int b = blockIdx.x;
     SolveState *st = states + b;
     eq4_select(B_vals[b], solve->n_cand, solve->n_first, solve->n_range, cand, Fmin, Sbest, st, prune, nullptr);
     __syncthreads();                                   // lane 0's stores, then every lane's reads
     win_c[b] = st->best_c;                             // all lanes, same value
-    win_s[b] = st->best_s;
+    const int32_t s = st->best_s;
+    kept_plan(st, kept, K, plans + b, nullptr, nullptr);
+    __syncthreads();
+    win_s[b] = st->plan_done ? 0 : s;                  // (0: no layers to recover)
 }
 
 // out_T in the caller's order: out_T[j] = T[rank_of_orig[j]]
@@ -430,14 +489,6 @@ __global__ void scatter_T_kernel(const int64_t *__restrict__ T, const int32_t *_
 }
 
 // ---------------------------------------------------------------- plan recovery
-
-struct PlanDev {                       // same layout as alpa_plan_t (2072 bytes)
-    int64_t T_star;
-    int32_t t_max, num_stages, n_evaluated;
-    int32_t first_layer[256 + 1];
-    int32_t shape_idx[256];
-};
-static_assert(sizeof(PlanDev) == 2072, "PlanDev layout");
 
 // One wave walks from (s*, first layer, all devices): at every step the (last layer, shape)
 // terms are scanned in tie-break order, 64 at a time, and the first one that reproduces the
@@ -455,6 +506,7 @@ __global__ __launch_bounds__(WAVE) void plan_walk_kernel(Problem p, const int32_
     const int K = p.K, D = p.D, S = p.S;
     const int LS = (K + 2) * (D + 1);
     state += blockIdx.x;
+    if (state->plan_done) return;
     F_all += blockIdx.x * slab;
     plan += blockIdx.x;
     const bool feasible = state->best_idx >= 0;
@@ -510,11 +562,7 @@ __global__ __launch_bounds__(WAVE) void plan_walk_kernel(Problem p, const int32_
         sh.n_evaluated = state->n_processed;
     }
     __syncthreads();
-    // running best over all solves of the handle (not kept by sweeps: best_plan is null):
-    // lower T*, then lower t_max
-    const int64_t bT = best_plan ? best_plan->T_star : INF_I64;
-    const int32_t bc = best_plan ? best_plan->t_max : 0;
-    const bool better = best_plan && good && (T_new < bT || (T_new == bT && c < bc));
+    const bool better = good && better_plan(best_plan, T_new, c);
     const int n32 = (int)(sizeof(PlanDev) / 4);
     __syncthreads();
     for (int x = lane; x < n32; x += WAVE) {
@@ -539,6 +587,8 @@ __global__ void init_state_kernel(SolveState *state, int64_t *chunk_min, int n_c
         state->wave_relax = 0ull;
         state->plan_n = 0;
         state->plan_ticket = 0;
+        state->n_slots = 0;
+        state->plan_done = 0;
     }
     for (int x = t; x < n_chunks; x += gridDim.x * blockDim.x) chunk_min[x] = INF_I64;
     for (int x = t; x < words; x += gridDim.x * blockDim.x) clear[x] = 0;
@@ -583,10 +633,11 @@ hipError_t launch_plan_layers(hipStream_t st, const Problem &p, const int32_t *t
 // T: per-candidate results, if wanted
 hipError_t launch_epilogue(hipStream_t st, const Problem &p, const int32_t *cand,
                            const int32_t *Fmin, const int32_t *Sbest, SolveState *state, int prune,
-                           bool want_T, int64_t *T)
+                           bool want_T, int64_t *T, const KeptPlans &kept, void *plan_tmp, void *best_plan, void *plan_out)
 {
     hipLaunchKernelGGL(epilogue_kernel, dim3(1), dim3(SEL_THREADS), 0, st, p, cand, Fmin, Sbest,
-                       state, prune, want_T ? 1 : 0, T);
+                       state, prune, want_T ? 1 : 0, T, kept, (PlanDev *)plan_tmp, (PlanDev *)best_plan,
+                       (PlanDev *)(plan_out ? plan_out : plan_tmp));
     return hipGetLastError();
 }
 
@@ -610,10 +661,10 @@ hipError_t launch_plan_walk(hipStream_t st, const Problem &p, const int32_t *tab
 hipError_t launch_sweep_epilogue(hipStream_t st, const int32_t *B_vals, int n_B,
                                  const SolveState *solve, const int32_t *cand,
                                  const int32_t *Fmin, const int32_t *Sbest, SolveState *states,
-                                 int prune, int32_t *win_c, int32_t *win_s)
+                                 int prune, int32_t *win_c, int32_t *win_s, const Problem &p, const KeptPlans &kept, void *plans)
 {
     hipLaunchKernelGGL(sweep_epilogue_kernel, dim3(n_B), dim3(SEL_THREADS), 0, st, B_vals,
-                       solve, cand, Fmin, Sbest, states, prune, win_c, win_s);
+                       solve, cand, Fmin, Sbest, states, prune, win_c, win_s, p.K, kept, (PlanDev *)plans);
     return hipGetLastError();
 }
 

@@ -218,6 +218,8 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
         state->n_range = end;
         state->n_list = m;
         state->n_knots = min(m, REFINE_MAX_KNOTS);
+        state->n_todo = 0;
+        state->todo_ticket = 0;
     }
 }
 
@@ -382,6 +384,8 @@ __global__ __launch_bounds__(RF_THREADS) void refine_kernel(
         state->n_list = list_base;
         state->n_knots = last ? m : m + list_base;
         state->ticket = 0;
+        state->n_todo = 0;
+        state->todo_ticket = 0;
     }
 }
 

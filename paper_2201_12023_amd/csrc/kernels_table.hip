@@ -108,14 +108,17 @@ __global__ void set_i32_kernel(int32_t *p, int32_t v)
 // out[0] = smallest entry (a negative one is an argument error), out[1] = largest finite entry
 // (-1 if none; for the overflow proof and the sort's key width).  HBM-bound: 4 bytes per entry.
 __global__ __launch_bounds__(256) void table_range_kernel(const int32_t *__restrict__ table, int K,
-                                                          int S, int32_t *__restrict__ out)
+                                                          int S, int Smax, int32_t *__restrict__ out)
 {
     // one block per (s, first layer k): its used entries, last layers k..K-1, are contiguous
     const int k = blockIdx.x % K;
     const int32_t *row = table + (size_t)blockIdx.x * K * S;
     int32_t mn = INF_I32, mx = -1;
+    const bool more = (int)blockIdx.x / K + 1 < Smax;
+    bool falls = false;
     for (int x = k * S + threadIdx.x; x < K * S; x += blockDim.x) {
         const int32_t t = row[x];
+        falls |= more && row[(size_t)K * K * S + x] < t;
         mn = min(mn, t);
         if (t != INF_I32) mx = max(mx, t);
     }
@@ -125,13 +128,15 @@ __global__ __launch_bounds__(256) void table_range_kernel(const int32_t *__restr
         atomicMin(&out[0], mn);
         atomicMax(&out[1], mx);
     }
+    if (__ballot(falls) && (threadIdx.x & (WAVE - 1)) == 0) out[2] = 1;
 }
 
-hipError_t launch_table_range(hipStream_t st, const int32_t *table, int K, int S, int32_t *out)
+hipError_t launch_table_range(hipStream_t st, const int32_t *table, int K, int S, int Smax, int32_t *out)
 {
     hipLaunchKernelGGL(set_i32_kernel, dim3(1), dim3(WAVE), 0, st, out + 0, INF_I32);
     hipLaunchKernelGGL(set_i32_kernel, dim3(1), dim3(WAVE), 0, st, out + 1, -1);
-    hipLaunchKernelGGL(table_range_kernel, dim3(K * K), dim3(256), 0, st, table, K, S, out);
+    hipLaunchKernelGGL(set_i32_kernel, dim3(1), dim3(WAVE), 0, st, out + 2, 0);
+    hipLaunchKernelGGL(table_range_kernel, dim3(K * K), dim3(256), 0, st, table, K, S, Smax, out);
     return hipGetLastError();
 }
 
