@@ -12,48 +12,115 @@
 // bytes: 240 of 790 us at 3002 operators; the band takes 20.)
 //
 // The recurrence over r is one launch for up to ROWS_PER_LAUNCH values of r (cluster_rows_kernel): a workgroup
-// owns a tile of consecutive n, with 16 lanes per n that share its candidates, whose C values stay in registers; row
+// owns a tile of consecutive n, with 8 lanes per n that share its candidates, whose C values stay in registers; row
 // r - 1 of its own tile is in LDS, and the rows of the tiles in front come through memory.
 #include "internal.hpp"
+
+#include <type_traits>
 
 namespace alpa {
 
 constexpr int CL_THREADS = 1024;
-constexpr int CL_LANES = 16;           // lanes per prefix length n
-constexpr int CL_TILE = CL_THREADS / CL_LANES;     // prefix lengths per workgroup
-constexpr int CL_KEEP = 8;             // candidates per lane whose C and squared FLOP are kept in registers
+constexpr int CL_ROW_THREADS = 512;    // of a workgroup that computes rows
+constexpr int CL_LANES = 8;            // lanes per prefix length n
+constexpr int CL_TILE = (CL_ROW_THREADS - WAVE) / CL_LANES;    // prefix lengths per workgroup (a wave fetches what is in front)
+constexpr int CL_KEEP = 16;            // candidates per lane whose C and squared FLOP are kept in registers
 constexpr int ROWS_PER_LAUNCH = 128;
 constexpr int64_t NOT_YET = -1;        // no value of a row is negative
+
+// Argument checks for device-resident inputs (what alpa_cluster_layers does on the host):
+// ctl[0] = 0, ALPA_DP_EINVAL (-1: negative figure, bad edge) or ALPA_DP_EOVERFLOW (-2: total FLOP
+// >= 2^31, total * L >= 2^42, edge sizes adding up to >= 2^62); ctl[1] = the FLOP bound per
+// layer, floor((10^6 + delta_ppm) * total / (L * 10^6)).  One block.
+// (ends with a barrier; whether they are refused, and the bound)
+struct ClusterInputs {
+    const int32_t *src, *dst;
+    const int64_t *nbytes;
+    int E, L, delta_ppm;
+};
+__device__ __forceinline__ bool cluster_check(const int32_t *__restrict__ flop, int K, const ClusterInputs &in, int64_t *__restrict__ ctl,
+                                              int64_t &cap)
+{
+    const int32_t *__restrict__ const src = in.src, *__restrict__ const dst = in.dst;
+    const int64_t *__restrict__ const nbytes = in.nbytes;
+    const int E = in.E, L = in.L;
+    __shared__ int64_t sh_ctl[2];
+    __shared__ unsigned long long sh_flop[CL_THREADS / WAVE], sh_bytes[CL_THREADS / WAVE];
+    __shared__ int sh_bad, sh_over;
+    const int t = threadIdx.x;
+    if (t == 0) { sh_bad = 0; sh_over = 0; }
+    __syncthreads();
+    constexpr unsigned long long LIM = 1ull << 62;
+    unsigned long long f = 0, b = 0;
+    int bad = 0, over = 0;
+    for (int k = t; k < K; k += CL_THREADS) {
+        const int32_t v = flop[k];
+        if (v < 0) bad = 1; else f += (unsigned long long)v;        // < 2^31 * 4 per thread
+    }
+    for (int e = t; e < E; e += CL_THREADS) {
+        const int u = src[e], v = dst[e];
+        const int64_t n = nbytes[e];
+        if (u < 0 || v >= K || u >= v || n < 0) { bad = 1; continue; }
+        if ((unsigned long long)n >= LIM) over = 1;
+        b = min(LIM, b + min(LIM, (unsigned long long)n));         // saturating: stays <= 2^62
+    }
+    if (bad) atomicOr(&sh_bad, 1);
+    if (over) atomicOr(&sh_over, 1);
+    // the byte total saturates at every sum (1024 partial ones of up to 2^62 would wrap an unsigned 64-bit add)
+    for (int off = 32; off >= 1; off >>= 1) {
+        f += __shfl_xor(f, off, WAVE);
+        b = min(LIM, b + __shfl_xor(b, off, WAVE));
+    }
+    if ((t & (WAVE - 1)) == 0) { sh_flop[t / WAVE] = f; sh_bytes[t / WAVE] = b; }
+    __syncthreads();
+    if (t == 0) {
+        unsigned long long total = 0, bytes = 0;
+        for (int w = 0; w < CL_THREADS / WAVE; ++w) {
+            total += sh_flop[w];
+            bytes = min(LIM, bytes + sh_bytes[w]);
+        }
+        int64_t status = 0;
+        if (sh_bad) status = -1;
+        else if (total >= (1ull << 31) || total * (unsigned long long)L >= (1ull << 42) ||
+                 sh_over || bytes >= LIM) status = -2;
+        ctl[0] = sh_ctl[0] = status;
+        ctl[1] = sh_ctl[1] = status ? 0
+                        : (int64_t)(((1000000ull + (unsigned long long)in.delta_ppm) * total) /
+                                    ((unsigned long long)L * 1000000ull));
+    }
+    __syncthreads();
+    cap = sh_ctl[1];
+    return sh_ctl[0] != 0;
+}
 
 // pf[x] = FLOP of operators 0..x-1 (int64); win[n] = number of feasible first operators of a layer that ends
 // with the n-th (1-based); meta[0] = the largest of them (at least 1), meta[1] = work counter, meta[2] = a wait
 // has run out.  One block.
 __global__ __launch_bounds__(CL_THREADS) void cluster_prefix_kernel(
-    const int32_t *__restrict__ flop, int K, int64_t cap, const int64_t *__restrict__ ctl,
+    const int32_t *__restrict__ flop, int K, int64_t cap, ClusterInputs in, int64_t *__restrict__ ctl,
     int64_t *__restrict__ pf, int32_t *__restrict__ win, int64_t *__restrict__ tot, int32_t *__restrict__ meta)
 {
     extern __shared__ int64_t sh[];                  // [K + 1] prefix sums
-    __shared__ int64_t part[CL_THREADS];
+    __shared__ int64_t part[CL_THREADS / WAVE];
     __shared__ int sh_max;
-    // Bound computed on the device (cluster_check_kernel).  Inputs that it has refused have no feasible first
+    // Device-resident inputs (ctl) are checked here.  Those that are refused have no feasible first
     // operator anywhere: with a negative figure a row value could be any number, NOT_YET among them.
-    const bool refused = ctl && ctl[0] != 0;
-    if (ctl) cap = ctl[1];
+    const bool refused = ctl && cluster_check(flop, K, in, ctl, cap);
     const int t = threadIdx.x;
     const int per = (K + CL_THREADS - 1) / CL_THREADS;
     const int lo = min(K, t * per), hi = min(K, lo + per);
     int64_t s = 0;
     for (int x = lo; x < hi; ++x) s += flop[x];
-    part[t] = s;
+    int64_t upto = s;                                // of the wave's lanes up to this one
+    for (int off = 1; off < WAVE; off <<= 1) {
+        const int64_t o = __shfl_up(upto, off, WAVE);
+        if ((t & (WAVE - 1)) >= off) upto += o;
+    }
+    if ((t & (WAVE - 1)) == WAVE - 1) part[t / WAVE] = upto;
     if (t == 0) { sh_max = 1; sh[0] = 0; }
     __syncthreads();
-    for (int off = 1; off < CL_THREADS; off <<= 1) {
-        const int64_t o = (t >= off) ? part[t - off] : 0;
-        __syncthreads();
-        part[t] += o;
-        __syncthreads();
-    }
-    int64_t run = part[t] - s;
+    int64_t run = upto - s;
+    for (int w = 0; w < t / WAVE; ++w) run += part[w];
     for (int x = lo; x < hi; ++x) {
         run += flop[x];
         sh[x + 1] = run;
@@ -79,12 +146,17 @@ __global__ __launch_bounds__(CL_THREADS) void cluster_prefix_kernel(
     if (t == 0) { meta[0] = sh_max; meta[1] = 0; meta[2] = 0; }
 }
 
-__global__ void cluster_zero_band_kernel(int64_t *__restrict__ band, int K, const int32_t *__restrict__ meta)
+// The band, empty, and the rows of the first launch: row 0 is the empty prefix alone, the others are not there yet
+__global__ void cluster_clear_kernel(int64_t *__restrict__ band, int64_t *__restrict__ G, int64_t *__restrict__ V, int K, int rows,
+                                     const int32_t *__restrict__ meta)
 {
-    const long long n = (long long)meta[0] * K;
-    for (long long x = blockIdx.x * (long long)blockDim.x + threadIdx.x; x < n;
-         x += (long long)gridDim.x * blockDim.x)
-        band[x] = 0;
+    const long long n = (long long)meta[0] * K, m = (long long)(rows + 1) * (K + 1);
+    const long long stride = (long long)gridDim.x * blockDim.x, x0 = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+    for (long long x = x0; x < n; x += stride) band[x] = 0;
+    for (long long x = x0; x < m; x += stride) {
+        G[x] = x == 0 ? 0 : x <= K ? INF_I64 : NOT_YET;
+        V[x] = x <= K ? 0 : NOT_YET;
+    }
 }
 
 // band[v - u][v] += bytes(u -> v) inside the band; tot[v] += bytes of every edge into v
@@ -147,7 +219,7 @@ __global__ __launch_bounds__(64) void cluster_band_sum_kernel(int64_t *__restric
     for (; j < width; ++j) { run += p[j * step]; p[j * step] = run; }
 }
 
-// Rows of one launch: row 0 is the row in front (the empty prefix alone for the first launch, else the
+// Rows of a launch that is not the first: row 0 is the row in front (the empty prefix alone for the first of the exact run, else the
 // last row of the launch before), the others are not there yet.  EXACT rows hold W in V.
 __global__ void cluster_begin_rows_kernel(int64_t *__restrict__ G, int64_t *__restrict__ V, int K, int rows,
                                           int first, int exact, int last_row, int32_t *__restrict__ meta)
@@ -170,208 +242,200 @@ __global__ void cluster_begin_rows_kernel(int64_t *__restrict__ G, int64_t *__re
     if (blockIdx.x == 0 && threadIdx.x == 0) meta[1] = 0;
 }
 
-struct Lex {                    // (G, V, i): smaller is better, component by component
-    int64_t g, v;
-    int i;
-};
-__device__ __forceinline__ bool lex_less(const Lex &a, const Lex &b)
+// (g, v): smaller is better, component by component.  No branches: a row is a chain of these.
+struct Lex { uint64_t g, v; };
+__device__ __forceinline__ bool lex_not_above(const Lex &a, const Lex &b)
 {
-    return a.g < b.g || (a.g == b.g && (a.v < b.v || (a.v == b.v && a.i < b.i)));
+    return (a.g < b.g) | ((a.g == b.g) & (a.v <= b.v));
 }
-template <int CTRL>
+template <int CTRL, bool EXACT>
 __device__ __forceinline__ void lex_step(Lex &a)
 {
-    const Lex o{dpp_mov64<CTRL>(a.g), dpp_mov64<CTRL>(a.v), dpp_mov<CTRL>(a.i)};
-    if (lex_less(o, a)) a = o;
+    const Lex o{(uint64_t)dpp_mov64<CTRL>((int64_t)a.g), EXACT ? 0 : (uint64_t)dpp_mov64<CTRL>((int64_t)a.v)};
+    const bool take = EXACT ? o.g < a.g : lex_not_above(o, a);
+    a.g = take ? o.g : a.g;
+    if (!EXACT) a.v = take ? o.v : a.v;
 }
 
-// The value at p once it is there.  Every wait of a call that has the work memory to itself ends by itself (see
-// cluster_rows_kernel); what another call overwrites may never come, so after max_spins looks, or once some
-// wait has run out (*lost), the caller goes on without it and the call reports it.  (A clock in the place of
-// the count is 2 % of the whole call.)
-__device__ __forceinline__ int64_t await(const int64_t *p, int32_t *lost, unsigned max_spins)
+__device__ __forceinline__ int64_t row_value(const int64_t *p)
 {
-    int64_t v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The value at p once it is there (v: what was there at the first look).  Every wait of a call that has the work memory to itself
+// ends by itself (see cluster_rows_kernel); what another call overwrites may never come, so after max_spins further looks, or once
+// some wait has run out (*lost), the caller goes on without it and the call reports it.  (A clock in the place of
+// the count is 2 % of the whole call.)
+__device__ __forceinline__ int64_t await(int64_t v, const int64_t *p, int32_t *lost, unsigned max_spins)
+{
     for (unsigned spin = 0; v == NOT_YET; ++spin) {
         if (spin >= max_spins ||
             (spin % 64 == 63 && __hip_atomic_load(lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
             __hip_atomic_store(lost, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return INF_I64;
         }
-        __builtin_amdgcn_s_sleep(1);
-        v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        v = row_value(p);
     }
     return v;
 }
 
-// Rows 1..rows of this launch, 64 prefix lengths to a workgroup.  Bound by the way of a value from one
-// workgroup to the next (2.5 us a row at 3002 operators; a launch per row took 5.8).  512 prefix lengths to
-// a workgroup, two lanes each, need no such way up to 512 operators, but take 3 us a row to compute.
+// Rows 1..rows of this launch, 56 prefix lengths to a workgroup: seven waves compute a row while the last one fetches
+// what the tiles in front have of it, for the next row, so a row takes what its computation takes (0.6 us) and the way of a value
+// from one workgroup to the next (1.8 us) is paid once a tile instead of once a row.  3002 operators, 96
+// layers: 185 us (where every wave fetched for itself before it computed: 243); 386 operators, 32 layers: 37 us.  By 120 prefix
+// lengths to a workgroup 202 and 44 us, by 24 220 and 53, with 16 lanes each on 60 198 and 53; asking for two rows at a time
+// 206 and 45: a value that is asked for too early is asked for twice.
 // A tile reads rows of tiles in front of it only, and tiles are handed out in order, so the workgroup
 // that a wait is for has always started and waits itself only for tiles further in front: every
 // wait ends.  A value is its own signal (NOT_YET until it is there), so no fence is needed.
 // EXACT (the variance tie-break over whole clusterings): with G* = G(K, L) in *gstar_p,
 //   W(n, r) = min over the feasible i with C(i, n) <= G* of W(i-1, r-1) + FLOP(o_i..o_n)^2, lowest i on ties.
+// room: prefix lengths in front and own that LDS has room for
 template <bool EXACT>
-__global__ __launch_bounds__(CL_THREADS) void cluster_rows_kernel(
+__global__ __launch_bounds__(CL_ROW_THREADS) void cluster_rows_kernel(
     const int64_t *__restrict__ band, const int64_t *__restrict__ pf, const int32_t *__restrict__ win, int K,
     int rows, int64_t *G, int64_t *V, int32_t *__restrict__ arg, int32_t *meta,
-    const int64_t *__restrict__ gstar_p, unsigned max_spins)
+    const int64_t *__restrict__ gstar_p, unsigned max_spins, int room)
 {
-    constexpr int T = CL_TILE, GL = CL_LANES, KEEP = CL_KEEP;
+    constexpr int T = CL_TILE, GL = CL_LANES, KEEP = CL_KEEP, ASK = 4;
     extern __shared__ int64_t sh[];
     __shared__ int sh_tile;
     if (threadIdx.x == 0) sh_tile = atomicAdd(&meta[1], 1);
     __syncthreads();
     const int n0 = sh_tile * T;                      // the tile: prefix lengths n0 + 1 .. n0 + T
     if (n0 >= K) return;
-    const int g = threadIdx.x % GL, nl = threadIdx.x / GL;
+    const int g = threadIdx.x % GL, nl = threadIdx.x / GL, lane = threadIdx.x & (WAVE - 1);
+    const bool fetches = threadIdx.x >= CL_ROW_THREADS - WAVE;
     const int n = n0 + 1 + nl;
     const int base = max(0, n0 - meta[0] + 1);       // first prefix length that the tile reads
     const int halo = n0 + 1 - base;                  // base .. n0 come from tiles in front
-    const int size = halo + T;
-    int64_t *sG = sh, *sV = sh + size, *sP = sh + 2 * size;
     const size_t ld = (size_t)K + 1;
-    for (int x = threadIdx.x; x < size; x += CL_THREADS) {
+    // two rows: what is read is the one in front, [halo + T] values of V and of G
+    constexpr int ENTRY = EXACT ? 1 : 2;             // V, G
+    int64_t *now = sh, *next = sh + ENTRY * room;
+    for (int x = threadIdx.x; x < halo + T; x += CL_ROW_THREADS) {
         const int m = min(base + x, K);
-        sP[x] = pf[m];
-        if (!EXACT) sG[x] = G[m];
-        sV[x] = V[m];
+        now[ENTRY * x] = V[m];
+        if (!EXACT) now[ENTRY * x + 1] = G[m];
     }
     // (no further back than the tile reads, whatever another call may have left in `win`)
-    const int width = n <= K ? min(win[n], n - base) : 0;
+    const int width = n <= K && !fetches ? min(win[n], n - base) : 0;
     const int64_t pn = pf[min(n, K)];
     const int64_t gstar = EXACT ? *gstar_p : 0;
-    __syncthreads();
     // FLOP(o_i..o_n)^2, i = n - j (a layer's FLOP fits 31 bits)
     auto squared = [&](int j) {
-        const uint32_t f = (uint32_t)(pn - sP[n - 1 - j - base]);
+        const uint32_t f = (uint32_t)(pn - pf[n - 1 - j]);
         return (int64_t)((uint64_t)f * f);
     };
-    int64_t keep_c[KEEP], keep_f[KEEP];
+    // candidate j = g + u * 8; what is none has an infinite cost (in the exact run FLOP^2, and what costs more than G* is none)
+    uint64_t keep_c[KEEP], keep_f[KEEP];
+    int keep_x[KEEP], terms = 0;                     // terms: how many u the wave has
 #pragma unroll
     for (int u = 0; u < KEEP; ++u) {
         const int j = g + u * GL;
-        keep_c[u] = j < width ? band[(size_t)j * K + n - 1] : 0;
-        keep_f[u] = j < width ? squared(j) : 0;
+        const int64_t c = j < width ? band[(size_t)j * K + n - 1] : INF_I64;
+        const bool none = j >= width || (EXACT && (gstar == INF_I64 || c > gstar));
+        keep_c[u] = c;
+        keep_f[u] = !none ? (uint64_t)squared(j) : EXACT ? (uint64_t)INF_I64 : 0;
+        keep_x[u] = ENTRY * max(n - 1 - j - base, 0);                // prefix length i - 1, i = n - j
+        terms += __ballot(j < width) != 0;
+    }
+    __syncthreads();
+    if (fetches) {
+        for (int r = 1; r <= rows; ++r) {            // row r of the tiles in front, for row r + 1 (the last row's for nobody)
+            for (int x0 = 0; r < rows && x0 < halo; x0 += ASK * WAVE) {
+                int64_t v[ASK], w[ASK];
+#pragma unroll
+                for (int u = 0; u < ASK; ++u) {
+                    if (x0 + u * WAVE >= halo) continue;
+                    const size_t at = r * ld + base + min(x0 + u * WAVE + lane, halo - 1);
+                    v[u] = row_value(&V[at]);
+                    if (!EXACT) w[u] = row_value(&G[at]);
+                }
+#pragma unroll
+                for (int u = 0; u < ASK; ++u) {
+                    const int x = x0 + u * WAVE + lane, m = base + x;
+                    if (x >= halo) continue;
+                    // G(0, r) of a positive number of layers is infinite; nobody owns it
+                    if (!EXACT) next[ENTRY * x + 1] = m == 0 ? INF_I64 : await(w[u], &G[r * ld + m], &meta[2], max_spins);
+                    next[ENTRY * x] = m == 0 ? (EXACT ? INF_I64 : 0) : await(v[u], &V[r * ld + m], &meta[2], max_spins);
+                }
+            }
+            lds_barrier();
+            int64_t *const t = now;
+            now = next;
+            next = t;
+        }
+        return;
     }
     for (int r = 1; r <= rows; ++r) {
-        if (r > 1)
-            for (int x = threadIdx.x; x < halo; x += CL_THREADS) {
-                const int m = base + x;
-                // G(0, r) of a positive number of layers is infinite; nobody owns it
-                if (!EXACT) sG[x] = m == 0 ? INF_I64 : await(&G[(r - 1) * ld + m], &meta[2], max_spins);
-                sV[x] = m == 0 ? (EXACT ? INF_I64 : 0) : await(&V[(r - 1) * ld + m], &meta[2], max_spins);
-            }
-        __syncthreads();
-        Lex best{INF_I64, 0, 0};
-        auto term = [&](int j, int64_t c, int64_t ff) {
-            const int x = n - 1 - j - base;          // prefix length i - 1, i = n - j
-            Lex cur;
-            if (EXACT) {
-                const int64_t wp = sV[x];
-                if (gstar == INF_I64 || wp == INF_I64 || c > gstar) return;
-                cur = Lex{wp + ff, 0, n - j};
-            } else {
-                const int64_t gp = sG[x];
-                if (gp == INF_I64) return;
-                cur = Lex{gp > c ? gp : c, sV[x] + ff, n - j};
-            }
-            if (lex_less(cur, best)) best = cur;
+        // (EXACT: W in g.  Sums of an infinite W and a square stay below 2^64)
+        Lex best{(uint64_t)INF_I64, 0};
+        int at = 0;                                  // its j + 1; of equals the largest
+        auto better = [&](const Lex &cur, int j) {
+            const bool take = EXACT ? cur.g <= best.g : lex_not_above(cur, best);
+            best.g = take ? cur.g : best.g;
+            if (!EXACT) best.v = take ? cur.v : best.v;
+            at = take ? j + 1 : at;
         };
+        auto larger = [](uint64_t a, uint64_t b) { return a > b ? a : b; };
+        auto kept = [&](auto count) {
+            constexpr int N = decltype(count)::value;
+            uint64_t v[N], gp[N];
 #pragma unroll
-        for (int u = 0; u < KEEP; ++u) {
-            const int j = g + u * GL;
-            if (j < width) term(j, keep_c[u], keep_f[u]);
+            for (int u = 0; u < N; ++u) {
+                v[u] = now[keep_x[u]];
+                if (!EXACT) gp[u] = now[keep_x[u] + 1];
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+                better(EXACT ? Lex{v[u] + keep_f[u], 0} : Lex{larger(gp[u], keep_c[u]), v[u] + keep_f[u]}, g + u * GL);
+        };
+        if (terms <= 4) kept(std::integral_constant<int, 4>());
+        else if (terms <= 8) kept(std::integral_constant<int, 8>());
+        else kept(std::integral_constant<int, KEEP>());
+        for (int j = g + KEEP * GL; j < width; j += GL) {
+            const int x = ENTRY * (n - 1 - j - base);
+            const uint64_t c = band[(size_t)j * K + n - 1], ff = squared(j);
+            if (EXACT) {
+                if (gstar != INF_I64 && c <= (uint64_t)gstar) better(Lex{now[x] + ff, 0}, j);
+            } else {
+                better(Lex{larger(now[x + 1], c), now[x] + ff}, j);
+            }
         }
-        for (int j = g + KEEP * GL; j < width; j += GL)
-            term(j, band[(size_t)j * K + n - 1], squared(j));
-        lex_step<0xB1>(best);                        // the n's 16 lanes: neighbours, pairs, quads, halves of a row
-        lex_step<0x4E>(best);
-        lex_step<0x141>(best);
-        lex_step<0x140>(best);
-        if (best.g == INF_I64) { best.v = 0; best.i = 0; }
-        __syncthreads();                             // the row in front has been read
+        const Lex own = best;
+        lex_step<0xB1, EXACT>(best);             // the n's 8 lanes: neighbours, pairs, quads
+        lex_step<0x4E, EXACT>(best);
+        lex_step<0x141, EXACT>(best);
+        at = (own.g == best.g) & (EXACT | (own.v == best.v)) ? at : 0;
+        at = max(at, dpp_mov<0xB1>(at));
+        at = max(at, dpp_mov<0x4E>(at));
+        at = max(at, dpp_mov<0x141>(at));
         if (g == 0 && n <= K) {
-            const int64_t v = EXACT ? best.g : best.v;
-            if (!EXACT) sG[halo + nl] = best.g;
-            sV[halo + nl] = v;
-            if (!EXACT) __hip_atomic_store(&G[r * ld + n], best.g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&V[r * ld + n], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            arg[(r - 1) * ld + n] = best.i;
+            const bool none = best.g >= (uint64_t)INF_I64;
+            const int64_t G_n = none ? INF_I64 : (int64_t)best.g, V_n = EXACT ? G_n : none ? 0 : (int64_t)best.v;
+            if (!EXACT) __hip_atomic_store(&G[r * ld + n], G_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&V[r * ld + n], V_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!EXACT) next[ENTRY * (halo + nl) + 1] = G_n;
+            next[ENTRY * (halo + nl)] = V_n;
+            arg[(r - 1) * ld + n] = none ? 0 : n - at + 1;
         }
-        if (r > 0 && threadIdx.x == 0 && n0 == 0) {  // G(0, r), for the row that the next launch starts from
+        if (threadIdx.x == 0 && n0 == 0) {       // G(0, r), for the row that the next launch starts from
             if (!EXACT) G[r * ld] = INF_I64;
             V[r * ld] = EXACT ? INF_I64 : 0;
             arg[(r - 1) * ld] = 0;
         }
+        lds_barrier();
+        int64_t *const t = now;
+        now = next;
+        next = t;
     }
 }
 
 // *keep = G(K, L) of the first run (the second one does not write the G rows)
 __global__ void cluster_keep_kernel(const int64_t *__restrict__ G, int64_t *__restrict__ keep) { *keep = *G; }
 
-// Argument checks for device-resident inputs (what alpa_cluster_layers does on the host):
-// ctl[0] = 0, ALPA_DP_EINVAL (-1: negative figure, bad edge) or ALPA_DP_EOVERFLOW (-2: total FLOP
-// >= 2^31, total * L >= 2^42, edge sizes adding up to >= 2^62); ctl[1] = the FLOP bound per
-// layer, floor((10^6 + delta_ppm) * total / (L * 10^6)).  One block.
-__global__ __launch_bounds__(1024) void cluster_check_kernel(
-    const int32_t *__restrict__ flop, int K, const int32_t *__restrict__ src,
-    const int32_t *__restrict__ dst, const int64_t *__restrict__ nbytes, int E, int L,
-    int delta_ppm, int64_t *__restrict__ ctl)
-{
-    __shared__ unsigned long long sh_flop, sh_bytes;
-    __shared__ int sh_bad, sh_over;
-    const int t = threadIdx.x;
-    if (t == 0) { sh_flop = 0; sh_bytes = 0; sh_bad = 0; sh_over = 0; }
-    __syncthreads();
-    constexpr unsigned long long LIM = 1ull << 62;
-    unsigned long long f = 0, b = 0;
-    int bad = 0, over = 0;
-    for (int k = t; k < K; k += 1024) {
-        const int32_t v = flop[k];
-        if (v < 0) bad = 1; else f += (unsigned long long)v;        // < 2^31 * 4 per thread
-    }
-    for (int e = t; e < E; e += 1024) {
-        const int u = src[e], v = dst[e];
-        const int64_t n = nbytes[e];
-        if (u < 0 || v >= K || u >= v || n < 0) { bad = 1; continue; }
-        if ((unsigned long long)n >= LIM) over = 1;
-        b = min(LIM, b + min(LIM, (unsigned long long)n));         // saturating: stays <= 2^62
-    }
-    atomicAdd(&sh_flop, f);
-    if (bad) atomicOr(&sh_bad, 1);
-    if (over) atomicOr(&sh_over, 1);
-    __syncthreads();
-    // the byte total, saturating, one thread after the other (1024 partial sums <= 2^62 each
-    // would wrap an unsigned 64-bit add)
-    for (int turn = 0; turn < 1024; turn += WAVE) {
-        if (t >= turn && t < turn + WAVE) {
-            unsigned long long x = b;
-            for (int off = 32; off >= 1; off >>= 1) {
-                const unsigned long long o =
-                    (unsigned long long)i64_from(__shfl_xor(lo32((int64_t)x), off, 64),
-                                                 __shfl_xor(hi32((int64_t)x), off, 64));
-                x = min(LIM, x + o);
-            }
-            if ((t & (WAVE - 1)) == 0) sh_bytes = min(LIM, sh_bytes + x);
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        const unsigned long long total = sh_flop;
-        int64_t status = 0;
-        if (sh_bad) status = -1;
-        else if (total >= (1ull << 31) || total * (unsigned long long)L >= (1ull << 42) ||
-                 sh_over || sh_bytes >= LIM) status = -2;
-        ctl[0] = status;
-        ctl[1] = status ? 0
-                        : (int64_t)(((1000000ull + (unsigned long long)delta_ppm) * total) /
-                                    ((unsigned long long)L * 1000000ull));
-    }
-}
-
-// out[0] = G(K, L), out[1] = V(K, L); first_op[0..L] by walking arg back (one thread).  out[2] = 0, or ctl[0], the
+// out[0] = G(K, L), out[1] = V(K, L); first_op[0..L] by walking arg back (one wave).  out[2] = 0, or ctl[0], the
 // status of the argument checks (device-resident inputs), or -4 (ALPA_DP_EHIP) if a wait has run out; "no
 // clustering" is reported if that is not 0.
 __global__ void cluster_walk_kernel(const int64_t *__restrict__ G, const int64_t *__restrict__ V,
@@ -380,22 +444,54 @@ __global__ void cluster_walk_kernel(const int64_t *__restrict__ G, const int64_t
                                     int64_t *__restrict__ out, int32_t *__restrict__ first_op)
 {
     // G: G(K, L); V: the sum of squares that goes with it (exact mode: W(K, L))
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    const int lane = threadIdx.x;
     const int64_t status = ctl && ctl[0] != 0 ? ctl[0] : meta[2] != 0 ? -4 : 0;
-    out[2] = status;
     const int64_t g = status != 0 ? INF_I64 : *G;
-    out[0] = g;
-    out[1] = g == INF_I64 ? 0 : *V;
+    if (lane == 0) {
+        out[2] = status;
+        out[0] = g;
+        out[1] = g == INF_I64 ? 0 : *V;
+    }
     if (g == INF_I64) {
-        for (int r = 0; r <= L; ++r) first_op[r] = -1;
+        for (int r = lane; r <= L; r += WAVE) first_op[r] = -1;
         return;
     }
-    int n = K;
-    first_op[L] = K;
-    for (int r = L; r >= 1; --r) {
-        const int i = arg[(size_t)(r - 1) * (K + 1) + n];
-        n = min(max(i - 1, 0), K);                   // (i is in 1..n unless another call wrote here)
-        first_op[r - 1] = n;
+    int n = K, r = L;
+    if (lane == 0) first_op[L] = K;
+    // A layer has at most `width` operators: where they fit a wave, what any of the next three rows can be asked for is
+    // loaded along with the present one (a load a row in turn: 23 us for 96 rows)
+    const int width = meta[0];
+    const size_t ld = (size_t)K + 1;
+    while (r >= 1) {
+        // lane l: row r - 1 at n; row r - 2 at n - 1 - l; row r - 3 at n - 2 - l and 64 before; row r - 4 at n - 3 - l ..
+        auto at = [&](int row, int x) { return arg[(size_t)max(row, 0) * ld + min(max(x, 0), K)]; };
+        const bool ahead = width <= WAVE;
+        const int a = at(r - 1, n);
+        int b = 0, c[2] = {}, d[3] = {};
+        if (ahead) {
+            b = at(r - 2, n - 1 - lane);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) c[u] = at(r - 3, n - 2 - lane - u * WAVE);
+#pragma unroll
+            for (int u = 0; u < 3; ++u) d[u] = at(r - 4, n - 3 - lane - u * WAVE);
+        }
+        const int from = n;
+        auto step = [&](int i) {                     // (i is in 1..n unless another call wrote here)
+            n = min(max(i - 1, 0), K);
+            --r;
+            if (lane == 0) first_op[r] = n;
+        };
+        auto pick = [&](const int *v, int count, int x) {      // of lane x & 63 of v[x / 64]
+            x = min(max(x, 0), count * WAVE - 1);
+            int i = 0;
+            for (int u = 0; u < count; ++u) i = x / WAVE == u ? __builtin_amdgcn_readlane(v[u], x % WAVE) : i;
+            return i;
+        };
+        step(__builtin_amdgcn_readfirstlane(a));
+        if (!ahead) continue;
+        if (r >= 1) step(pick(&b, 1, from - 1 - n));
+        if (r >= 1) step(pick(c, 2, from - 2 - n));
+        if (r >= 1) step(pick(d, 3, from - 3 - n));
     }
 }
 
@@ -404,14 +500,15 @@ static hipError_t launch_rows(hipStream_t st, const ClusterWork &w, int K, int r
                               unsigned max_spins)
 {
     constexpr int T = CL_TILE;
-    const size_t lds = (size_t)3 * (std::min(width, K) + T + 1) * sizeof(int64_t);
+    const int room = std::min(width, K) + T + 1;
+    const size_t lds = (size_t)(EXACT ? 2 : 4) * room * sizeof(int64_t);   // (133 KB at most)
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)cluster_rows_kernel<EXACT>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((cluster_rows_kernel<EXACT>), dim3((K + T - 1) / T), dim3(CL_THREADS), lds, st, w.band,
-                       w.pf, w.win, K, rows, w.G, w.V, arg, w.meta, w.keep, max_spins);
+    hipLaunchKernelGGL((cluster_rows_kernel<EXACT>), dim3((K + T - 1) / T), dim3(CL_ROW_THREADS), lds, st, w.band,
+                       w.pf, w.win, K, rows, w.G, w.V, arg, w.meta, w.keep, max_spins, room);
     return hipGetLastError();
 }
 
@@ -423,8 +520,9 @@ static hipError_t launch_run(hipStream_t st, const ClusterWork &w, int K, int L,
     int done = 0, last = 0;
     while (done < L) {
         const int rows = std::min(ROWS_PER_LAUNCH, L - done);
-        hipLaunchKernelGGL(cluster_begin_rows_kernel, dim3((K + 64) / 64), dim3(64), 0, st, w.G, w.V, K, rows,
-                           done == 0 ? 1 : 0, EXACT ? 1 : 0, last, w.meta);
+        if (EXACT || done > 0)
+            hipLaunchKernelGGL(cluster_begin_rows_kernel, dim3((K + 64) / 64), dim3(64), 0, st, w.G, w.V, K, rows,
+                               done == 0 ? 1 : 0, EXACT ? 1 : 0, last, w.meta);
         const hipError_t e = launch_rows<EXACT>(st, w, K, rows, width, arg + done * ld, max_spins);
         if (e != hipSuccess) return e;
         done += rows;
@@ -439,14 +537,12 @@ hipError_t launch_cluster(hipStream_t st, const int32_t *flop, const int32_t *sr
                           int32_t *first_op, int64_t *ctl, int delta_ppm, int exact,
                           unsigned max_spins)
 {
-    if (ctl)
-        hipLaunchKernelGGL(cluster_check_kernel, dim3(1), dim3(1024), 0, st, flop, K, src, dst,
-                           nbytes, E, L, delta_ppm, ctl);
     hipLaunchKernelGGL(cluster_prefix_kernel, dim3(1), dim3(CL_THREADS), ((size_t)K + 1) * 8, st, flop, K, cap,
-                       (const int64_t *)ctl, w.pf, w.win, w.tot, w.meta);
-    const long long cells = (long long)width * K;
-    hipLaunchKernelGGL(cluster_zero_band_kernel, dim3((unsigned)std::min<long long>((cells + 1023) / 1024, 1024)),
-                       dim3(256), 0, st, w.band, K, w.meta);
+                       ClusterInputs{src, dst, nbytes, E, L, delta_ppm}, ctl, w.pf, w.win, w.tot, w.meta);
+    const int rows = std::min(L, ROWS_PER_LAUNCH);
+    const long long cells = std::max((long long)width * K, (rows + 1ll) * (K + 1));
+    hipLaunchKernelGGL(cluster_clear_kernel, dim3((unsigned)std::min<long long>((cells + 1023) / 1024, 1024)),
+                       dim3(256), 0, st, w.band, w.G, w.V, K, rows, w.meta);
     if (E > 0)
         hipLaunchKernelGGL(cluster_edges_kernel, dim3((E + 255) / 256), dim3(256), 0, st, src, dst,
                            nbytes, E, K, w.band, w.tot, w.meta);

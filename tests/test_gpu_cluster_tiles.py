@@ -17,11 +17,16 @@ CASES = [(1, 1, 0, 1, 0, 9), (2, 63, 200, 5, 500000, 9), (3, 64, 200, 64, 10**9,
          (11, 640, 4000, 2, 0, 1), (12, 900, 6000, 4, 10**9, 9), (13, 520, 0, 7, 500000, 0), (14, 600, 900, 300, 0, 50)]
 
 
+# one tile of 56 prefix lengths and the next, a window of one candidate a lane and more, as many as a wave walks at a time and more
+EDGES = [(15, 55, 200, 4, 500000, 9), (16, 56, 200, 5, 500000, 9), (17, 57, 200, 6, 500000, 9), (18, 112, 500, 2, 10**6, 3),
+         (19, 113, 500, 14, 500000, 9), (20, 256, 900, 2, 0, 1), (21, 257, 900, 4, 10**6, 1), (22, 300, 900, 1, 0, 9)]
+
+
 def _edges(seed, K, E, hi):
     return W.random_op_graph(seed, K, E, flop_hi=hi)
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: f"K{c[1]}-L{c[3]}")
+@pytest.mark.parametrize("case", CASES + EDGES, ids=lambda c: f"K{c[1]}-L{c[3]}")
 @pytest.mark.parametrize("rule", ["cell", "exact", "static"])
 def test_tiles_and_windows(case, rule):
     import torch
