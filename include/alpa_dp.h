@@ -251,8 +251,8 @@ int alpa_dp_candidates(alpa_dp_t *h, int32_t *out, int cap, int *out_n);
  * execution latency T*" that Alg. 1 outputs).  Blocking. */
 int alpa_dp_best(alpa_dp_t *h, alpa_plan_t *out_plan);
 
-/* Device time of the phases of the last solve, from HIP events recorded on the
- * handle's stream: candidate preparation (sort / dedup / quantiles), the recurrence
+/* Device time of the phases of the last solve, by the device's clock as the handle's
+ * stream reaches them: candidate preparation (sort / dedup / quantiles), the recurrence
  * kernel of Eq. 3, and Eq. 4 + best selection + plan recovery.  Blocking.  Any
  * pointer may be NULL. */
 int alpa_dp_last_timing(alpa_dp_t *h, float *ms_candidates, float *ms_recurrence,

@@ -103,7 +103,7 @@ struct alpa_dp {
     SolveState *d_sw_state = nullptr;
     int32_t *d_sw_Fall = nullptr;
     alpa_plan_t *d_sw_plans = nullptr;
-    hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
+    int clock_khz = 100000;         // of the clock that kernels read
     bool any_solve = false, timed = false;
     bool have_best = false;         // d_best_plan holds the best of a solve made with the current
                                     // table and B (sweeps do not touch it)
@@ -347,7 +347,6 @@ extern "C" void alpa_dp_destroy(alpa_dp_t *h)
     (void)hipFree(h->arena); (void)hipFree(h->sweep_arena); (void)hipFree(h->distinct_arena);
     h->keys.release();
     h->cands.release();
-    for (auto &e : h->ev) if (e) (void)hipEventDestroy(e);
     (void)hipSetDevice(prev);
     delete h;
 }
@@ -383,7 +382,7 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     const int K = h->p.K, S = h->p.S, D = h->p.D;
     HIPCHK(hipGetDevice(&h->device));
     HIPCHK(hipDeviceGetAttribute(&h->n_cu, hipDeviceAttributeMultiprocessorCount, h->device));
-    for (auto &e : h->ev) HIPCHK(hipEventCreate(&e));
+    HIPCHK(hipDeviceGetAttribute(&h->clock_khz, hipDeviceAttributeWallClockRate, h->device));
     const size_t LS = (size_t)(K + 2) * (D + 1);
     // general kernel: two F layers per resident workgroup, at most 256 MiB in total
     int gg = h->n_cu * 4;
@@ -794,7 +793,6 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     const RefineQuery rq{n_B > 0 ? h->d_sw_B : nullptr, p.B, std::max(n_B, 1), prune,
                          (n_B > 0 || !d_out_T) ? 1 : 0, bounds, p.Smax, prune_sel,
                          h->band_ok ? bounds + table_bounds_ints(p) : nullptr, h->max_finite};
-    HIPCHK(hipEventRecord(h->ev[0], st));
     const bool bitmap = !have_list && distinct_by_bitmap(h);
     HIPCHK(launch_init_state(st, h->d_state, h->d_chunkmin, bound / PRUNE_CHUNK + 1, (uint32_t *)h->pb.keys[1],
                              bitmap ? h->max_finite / 32 + 1 : 0));
@@ -825,7 +823,6 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         h->have_exact_bounds = !recorded;
     }
     HIPCHK(launch_refine_begin(st, rq, h->d_cand, h->d_state, rb));
-    HIPCHK(hipEventRecord(h->ev[1], st));
     for (int round = 1; bound > 0 && round <= rb.rounds; ++round) {
         const bool last = round == rb.rounds;
         if (round > 1)
@@ -900,7 +897,6 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                                              h->d_scratch, 2, bounds, grid));
         }
     }
-    HIPCHK(hipEventRecord(h->ev[2], st));
     if (n_B > 0) {
         HIPCHK(launch_sweep_epilogue(st, h->d_sw_B, n_B, h->d_state, h->d_cand, h->d_Fmin,
                                      h->d_Sbest, h->d_sw_state, prune_sel, h->d_sw_c, h->d_sw_s, p, kept, h->d_sw_plans));
@@ -917,7 +913,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                                                   FAST_MODE_PLAN, std::min(n, h->n_cu)));
                 else
                     HIPCHK(launch_recurrence_fast(st, fa, FAST_MODE_PLAN, 1, std::min(n, h->n_cu)));
-                HIPCHK(launch_plan_walk_many(st, p, h->d_table, h->d_sizes, h->d_sw_state + b,
+                HIPCHK(launch_plan_walk_many(st, p, h->d_table, h->d_sizes, h->d_state, h->d_sw_state + b,
                                              h->d_sw_Fall, slab_ints(h), h->d_sw_plans + b, n));
             }
         } else {
@@ -925,11 +921,10 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                 SolveState *sb = h->d_sw_state + b;
                 HIPCHK(launch_plan_layers(st, p, h->d_table, h->d_sizes, h->d_sw_c + b,
                                           &sb->plan_n, h->d_sw_s + b, h->d_Fall));
-                HIPCHK(launch_plan_walk_many(st, p, h->d_table, h->d_sizes, sb, h->d_Fall, 0,
+                HIPCHK(launch_plan_walk_many(st, p, h->d_table, h->d_sizes, h->d_state, sb, h->d_Fall, 0,
                                              h->d_sw_plans + b, 1));
             }
         }
-        HIPCHK(hipEventRecord(h->ev[3], st));
         h->any_solve = true;
         h->timed = true;
         return ALPA_DP_OK;
@@ -956,7 +951,6 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     }
     HIPCHK(launch_plan_walk(st, p, h->d_table, h->d_sizes, h->d_state, h->d_Fall, h->d_plan_tmp,
                             h->d_best_plan, d_out_plan));
-    HIPCHK(hipEventRecord(h->ev[3], st));
     h->any_solve = true;
     h->have_best = true;
     h->timed = true;
@@ -1118,14 +1112,13 @@ extern "C" int alpa_dp_last_timing(alpa_dp_t *h, float *ms_candidates, float *ms
 {
     if (!h) return fail(ALPA_DP_EINVAL, "handle is null");
     if (!h->timed) return fail(ALPA_DP_EINVAL, "no solve has been made on this handle");
-    HIPCHK(hipEventSynchronize(h->ev[3]));
-    float a = 0, b = 0, c = 0;
-    HIPCHK(hipEventElapsedTime(&a, h->ev[0], h->ev[1]));
-    HIPCHK(hipEventElapsedTime(&b, h->ev[1], h->ev[2]));
-    HIPCHK(hipEventElapsedTime(&c, h->ev[2], h->ev[3]));
-    if (ms_candidates) *ms_candidates = a;
-    if (ms_recurrence) *ms_recurrence = b;
-    if (ms_epilogue) *ms_epilogue = c;
+    SolveState s;
+    HIPCHK(hipMemcpyAsync(&s, h->d_state, sizeof(s), hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
+    auto ms = [&](int x) { return (float)((double)(s.clock[x + 1] - s.clock[x]) / h->clock_khz); };
+    if (ms_candidates) *ms_candidates = ms(0);
+    if (ms_recurrence) *ms_recurrence = ms(1);
+    if (ms_epilogue) *ms_epilogue = ms(2);
     return ALPA_DP_OK;
 }
 

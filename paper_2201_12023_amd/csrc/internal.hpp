@@ -37,6 +37,7 @@ struct SolveState {
     int32_t todo_ticket;
     int32_t n_slots;         // plans kept for the selection (kernels_sparse.hip)
     int32_t plan_done;       // the selection has written the plan
+    int64_t clock[4];        // the device's clock before the candidates, behind them, before the selection and at the end
 };
 
 struct Problem {
@@ -394,11 +395,11 @@ hipError_t launch_plan_walk(hipStream_t st, const Problem &p, const int32_t *tab
                             void *plan_tmp, void *best_plan, void *plan_out);
 // sweep over B: one block per B value
 hipError_t launch_sweep_epilogue(hipStream_t st, const int32_t *B_vals, int n_B,
-                                 const SolveState *solve, const int32_t *cand,
+                                 SolveState *solve, const int32_t *cand,
                                  const int32_t *Fmin, const int32_t *Sbest, SolveState *states,
                                  int prune, int32_t *win_c, int32_t *win_s, const Problem &p, const KeptPlans &kept, void *plans);
 hipError_t launch_plan_walk_many(hipStream_t st, const Problem &p, const int32_t *table,
-                                 const int32_t *sizes, SolveState *states, const int32_t *F_all,
+                                 const int32_t *sizes, SolveState *solve, SolveState *states, const int32_t *F_all,
                                  size_t slab, void *plans, int n);
 hipError_t launch_init_state(hipStream_t st, SolveState *state, int64_t *chunk_min, int n_chunks, uint32_t *clear, int words);
 hipError_t launch_init_best_plan(hipStream_t st, void *best_plan);

@@ -453,6 +453,7 @@ __global__ __launch_bounds__(SEL_THREADS) void epilogue_kernel(Problem p, const 
                                                         int64_t *__restrict__ T, KeptPlans kept, PlanDev *plan,
                                                         PlanDev *best_plan, PlanDev *plan_out)
 {
+    if (threadIdx.x == 0) state->clock[2] = wall_clock64();
     eq4_select(p.B, state->n_cand, state->n_first, state->n_range, cand, Fmin, Sbest, state, prune, want_T ? T : nullptr);
     __syncthreads();                                   // thread 0's stores, then every thread's reads
     kept_plan(state, kept, p.K, plan, best_plan, plan_out);
@@ -462,13 +463,14 @@ __global__ __launch_bounds__(SEL_THREADS) void epilogue_kernel(Problem p, const 
 // B value applies Eq. 4 and the selection to the same Fmin / Sbest.  states[b] receives the
 // winner for B_vals[b]; win_c / win_s are the compact copies the plan-recovery run reads.
 __global__ __launch_bounds__(SEL_THREADS) void sweep_epilogue_kernel(
-    const int32_t *__restrict__ B_vals, const SolveState *__restrict__ solve,
+    const int32_t *__restrict__ B_vals, SolveState *solve,
     const int32_t *__restrict__ cand, const int32_t *__restrict__ Fmin,
     const int32_t *__restrict__ Sbest, SolveState *states, int prune, int32_t *__restrict__ win_c,
     int32_t *__restrict__ win_s, int K, KeptPlans kept, PlanDev *plans)
 {
     const int b = blockIdx.x;
     SolveState *st = states + b;
+    if (b == 0 && threadIdx.x == 0) solve->clock[2] = wall_clock64();
     eq4_select(B_vals[b], solve->n_cand, solve->n_first, solve->n_range, cand, Fmin, Sbest, st, prune, nullptr);
     __syncthreads();                                   // lane 0's stores, then every lane's reads
     win_c[b] = st->best_c;                             // all lanes, same value
@@ -495,7 +497,7 @@ __global__ void scatter_T_kernel(const int64_t *__restrict__ T, const int32_t *_
 // stored F is taken (ballot + find-first-set = the wave-level arg-min with a fixed order).
 __global__ __launch_bounds__(WAVE) void plan_walk_kernel(Problem p, const int32_t *__restrict__ table,
                                                          const int32_t *__restrict__ sizes,
-                                                         const SolveState *state,
+                                                         SolveState *solve, const SolveState *state,
                                                          const int32_t *__restrict__ F_all,
                                                          size_t slab, PlanDev *plan,
                                                          PlanDev *best_plan, PlanDev *plan_out)
@@ -506,6 +508,7 @@ __global__ __launch_bounds__(WAVE) void plan_walk_kernel(Problem p, const int32_
     const int K = p.K, D = p.D, S = p.S;
     const int LS = (K + 2) * (D + 1);
     state += blockIdx.x;
+    if (blockIdx.x == 0 && lane == 0) solve->clock[3] = wall_clock64();    // (again behind a plan that has to be walked)
     if (state->plan_done) return;
     F_all += blockIdx.x * slab;
     plan += blockIdx.x;
@@ -571,6 +574,7 @@ __global__ __launch_bounds__(WAVE) void plan_walk_kernel(Problem p, const int32_
         if (plan_out) ((int32_t *)plan_out)[x] = v;
         if (better) ((int32_t *)best_plan)[x] = v;
     }
+    if (blockIdx.x == 0 && lane == 0) solve->clock[3] = wall_clock64();
 }
 
 // (and `words` of a bitmap to clear)
@@ -578,6 +582,7 @@ __global__ void init_state_kernel(SolveState *state, int64_t *chunk_min, int n_c
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t == 0) {
+        state->clock[0] = wall_clock64();
         state->ticket = 0;
         state->n_processed = 0;
         state->best_idx = -1;
@@ -653,13 +658,13 @@ hipError_t launch_plan_walk(hipStream_t st, const Problem &p, const int32_t *tab
                             const int32_t *sizes, SolveState *state, const int32_t *F_all,
                             void *plan_tmp, void *best_plan, void *plan_out)
 {
-    hipLaunchKernelGGL(plan_walk_kernel, dim3(1), dim3(WAVE), 0, st, p, table, sizes, state, F_all,
+    hipLaunchKernelGGL(plan_walk_kernel, dim3(1), dim3(WAVE), 0, st, p, table, sizes, state, state, F_all,
                        (size_t)0, (PlanDev *)plan_tmp, (PlanDev *)best_plan, (PlanDev *)(plan_out ? plan_out : plan_tmp));
     return hipGetLastError();
 }
 
 hipError_t launch_sweep_epilogue(hipStream_t st, const int32_t *B_vals, int n_B,
-                                 const SolveState *solve, const int32_t *cand,
+                                 SolveState *solve, const int32_t *cand,
                                  const int32_t *Fmin, const int32_t *Sbest, SolveState *states,
                                  int prune, int32_t *win_c, int32_t *win_s, const Problem &p, const KeptPlans &kept, void *plans)
 {
@@ -669,10 +674,10 @@ hipError_t launch_sweep_epilogue(hipStream_t st, const int32_t *B_vals, int n_B,
 }
 
 hipError_t launch_plan_walk_many(hipStream_t st, const Problem &p, const int32_t *table,
-                                 const int32_t *sizes, SolveState *states, const int32_t *F_all,
+                                 const int32_t *sizes, SolveState *solve, SolveState *states, const int32_t *F_all,
                                  size_t slab, void *plans, int n)
 {
-    hipLaunchKernelGGL(plan_walk_kernel, dim3(n), dim3(WAVE), 0, st, p, table, sizes, states, F_all,
+    hipLaunchKernelGGL(plan_walk_kernel, dim3(n), dim3(WAVE), 0, st, p, table, sizes, solve, states, F_all,
                        slab, (PlanDev *)plans, (PlanDev *)nullptr, (PlanDev *)nullptr);
     return hipGetLastError();
 }

@@ -218,6 +218,7 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
         state->n_range = end;
         state->n_list = m;
         state->n_knots = min(m, REFINE_MAX_KNOTS);
+        state->clock[1] = wall_clock64();
         state->n_todo = 0;
         state->todo_ticket = 0;
     }
