@@ -360,7 +360,7 @@ int32_t *graph_used(int32_t *graph, int K);
 const int4 *graph_stages(int32_t *graph, int K);
 hipError_t launch_sparse_graph(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
                                const int32_t *work, const int32_t *front, const int32_t *fronts, const int32_t *backs,
-                               const int32_t *totals, const int32_t *plans, const int32_t *falls, int32_t *graph, const int32_t *asked);
+                               const int32_t *totals, int32_t *plans, const int32_t *falls, int32_t *graph, int32_t *bounds, int32_t *there, bool once);
 // f: the recurrence's arguments (those of them that count); most: upper bound of the list's length
 hipError_t launch_sparse_eval(hipStream_t st, const FastArgs &f, const int32_t *table, int32_t *graph, int32_t max_finite, const SparseOut &o, bool count,
                               int most, int n_cu);

@@ -192,7 +192,7 @@ __global__ __launch_bounds__(WAVE * FRONT_WAVES) void band_thresholds_kernel(Fro
         front_costs<W, FRONT_WAVES, NH, true>(ft, K, D, S, DEV_INF - 1, l);
         if (threadIdx.x == 0) {
             totals[BAND_THRESHOLDS] = l.P[K * R + 1 + D];
-            plans[2 * BAND_THRESHOLDS] = 0;        // (band_bounds_kernel counts there)
+            plans[2 * BAND_THRESHOLDS] = 0;        // (band_bounds counts there)
             if (graph_used) *graph_used = 0;       // (sparse_graph_kernel counts there)
         }
         return;

@@ -19,6 +19,7 @@
 // On ties: of the plans with the least sum, min_s F of Eq. 3 takes the fewest stages, and the walk from the first stage on
 // the lowest last layer, then the lowest shape.  A cell on such a plan has the fewest stages of all ways of its sum (else the plan
 // would have fewer), so the order of (sum, stages, last layer, shape) in each cell's own minimum is that of the walk.
+#include "bounds.hpp"
 #include "front.hpp"
 
 namespace alpa {
@@ -29,7 +30,7 @@ constexpr int GRAPH_CHUNKS = 512;              // of up to 64 stages that begin 
 constexpr int GRAPH_THREADS = WAVE * FRONT_WAVES;
 constexpr int GRAPH_SEARCH = 4096;             // stages of a graph in which the least t_max with a plan is looked for
 constexpr int GRAPH_LAYERS = 512;              // stages of a graph on which Eq. 3 is run
-constexpr int GRAPH_LDS = 64 * 1024;           // of the workgroup that makes a graph, at least
+constexpr int GRAPH_LDS = 128 * 1024;          // of the workgroup that makes a graph, if its list of stages takes so much
 
 // room for the stages of all graphs (64 layers: 49 000; what does not find room goes to the recurrence)
 static int graph_room(int K) { return std::min(std::max(12 * K * K, 8192), 3 << 16); }
@@ -90,23 +91,25 @@ __device__ __forceinline__ int graph_scan(int v, int *sh, int &total)
     return base + x - v;
 }
 
-// The graph of each interval, a workgroup each.  Bound by the loads of each cell's stages (least latencies), four in flight a wave.
+// The graph of interval j.  Bound by the loads of each cell's stages (least latencies), four in flight a wave, so a cell is looked
+// at once, up to the last layer that the filter lets its stages reach, and what is found is listed in LDS; only a graph of more
+// stages than the list holds is looked at again (every cell twice and to the last layer: 64 layers on 8 x 8 156 us, now 78; on
+// 16 x 8 209 and 86; 128 layers 308 and 174; 48 layers on 32 x 8 520 and 210).
 template <int W>
-__global__ __launch_bounds__(GRAPH_THREADS) void sparse_graph_kernel(FrontTable ft, const int32_t *__restrict__ table, BandShapes bs, int K,
-                                                                     int D, int32_t max_finite, const int32_t *__restrict__ fronts,
-                                                                     const int32_t *__restrict__ backs, const int32_t *__restrict__ totals,
-                                                                     const int32_t *__restrict__ plans, const int32_t *__restrict__ falls,
-                                                                     GraphTable g, const int32_t *__restrict__ there)
+__device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const int32_t *__restrict__ table, const BandShapes &bs, int K, int D,
+                                             int32_t max_finite, const int32_t *__restrict__ fronts, const int32_t *__restrict__ backs,
+                                             const int32_t *__restrict__ totals, const int32_t *plans, const int32_t *__restrict__ falls,
+                                             const GraphTable &g, int list_room)
 {
-    if (there && *there) return;
     extern __shared__ __attribute__((aligned(16))) int32_t lds[];
     __shared__ int sh_scan[FRONT_WAVES], sh_first;
     __shared__ int32_t sh_U, sh_plan[2];
     __shared__ uint16_t sh_cell[GRAPH_CELLS];      // cells in order: position in a [K][RS] array
     __shared__ int sh_at[GRAPH_CELLS + 1];         // where their stages start
-    __shared__ int sh_size[64];
+    __shared__ int sh_size[64], sh_listed;
+    __shared__ int16_t sh_reach[256];              // the last layer that a stage which begins with k reaches in the interval
     constexpr int RS = WAVE * W;
-    const int j = blockIdx.x, tid = threadIdx.x, lane = tid & (WAVE - 1), wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int S = bs.S, SP = front_padded(S), N = K * RS;
     const int32_t single = front_single(table, bs, K, D), c = min(band_threshold(max_finite, j), single);
     const int32_t low = j + 1 < BAND_THRESHOLDS ? band_threshold(max_finite, j + 1) : 0, feasible = totals[BAND_THRESHOLDS];
@@ -126,6 +129,9 @@ __global__ __launch_bounds__(GRAPH_THREADS) void sparse_graph_kernel(FrontTable 
     const int32_t *const P = fronts + (size_t)j * N;
     int32_t *const Q = lds;                        // [K][RS]
     uint16_t *const id = (uint16_t *)(lds + N);    // [K][RS]
+    // the stages as they are found: cell << 14 | number among all of its layers and shapes, and the place among the cell's
+    uint32_t *const listed = (uint32_t *)(lds + N + N / 2);
+    uint16_t *const listed_at = (uint16_t *)(listed + list_room);
     const int per = (N + GRAPH_THREADS - 1) / GRAPH_THREADS;
     auto place = [&](int y) { return (K - 1 - y / RS) * RS + y % RS; };
     // (in front of the first layer there is one cell, all devices: P(0, 0) = 0)
@@ -133,9 +139,25 @@ __global__ __launch_bounds__(GRAPH_THREADS) void sparse_graph_kernel(FrontTable 
     const int inv = (1 << 20) / S + 1;             // x / S for x < 2^14 (S <= 64)
     int n_cells, n_stages, at;
     int32_t U = sh_U;
-    // the stages of a cell, in order: found(lanes that have one, last layer, shape, latency, place of the cell behind)
+    for (int k = wid; k < K; k += FRONT_WAVES) {
+        const int n = (K - k) * SP;
+        const int32_t *const row = ft.least + (uint32_t)((k * K + k) * SP);
+        int reach = -1;
+        for (int y0 = 0; y0 < n; y0 += 4 * WAVE) {
+            int32_t t[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[u] = row[min(y0 + u * WAVE + lane, n - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint64_t lanes = __ballot(t[u] <= c);
+                if (lanes) reach = min(y0 + u * WAVE + 63 - __clzll((long long)lanes), n - 1);
+            }
+        }
+        if (lane == 0) sh_reach[k] = (int16_t)(reach < 0 ? -1 : k + reach / SP);
+    }
+    // the stages of a cell, in order: found(lanes that have one, whether this one has, its number)
     auto stages = [&](int cell, auto found) {
-        const int x0 = sh_cell[cell], k = x0 / RS, d = x0 % RS + 1, n = (K - k) * S;
+        const int x0 = sh_cell[cell], k = x0 / RS, d = x0 % RS + 1, n = (sh_reach[k] + 1 - k) * S;
         const int32_t room = U - front_of(x0);     // for the stage and what is behind it
         const int32_t *const row = ft.least + (uint32_t)((k * K + k) * SP);
         for (int y0 = 0; y0 < n; y0 += 4 * WAVE) {
@@ -155,12 +177,13 @@ __global__ __launch_bounds__(GRAPH_THREADS) void sparse_graph_kernel(FrontTable 
                 bool ok = y0 + u * WAVE + lane < n && t[u] <= c && (end ? left == 0 : left > 0);
                 const int32_t f = ok && !end ? Q[behind] : 0;
                 ok = ok && f < DEV_INF && t[u] + f <= room;
-                found(__ballot(ok), ok, i[u], q[u], t[u], behind);
+                found(__ballot(ok), ok, y0 + u * WAVE + lane);
             }
         }
     };
     for (int turn = 0;; ++turn) {
         for (int x = tid; x < N; x += GRAPH_THREADS) Q[x] = backs[(size_t)j * N + x];
+        if (tid == 0) sh_listed = 0;
         __syncthreads();
         int mine = 0;
         for (int y = tid * per; y < min(tid * per + per, N); ++y) {
@@ -184,7 +207,17 @@ __global__ __launch_bounds__(GRAPH_THREADS) void sparse_graph_kernel(FrontTable 
             // how many stages each has: a wave per cell
             for (int cell = 1 + wid; cell < n_cells; cell += FRONT_WAVES) {
                 int n = 0;
-                stages(cell, [&](uint64_t lanes, bool, int, int, int32_t, int) { n += __popcll(lanes); });
+                stages(cell, [&](uint64_t lanes, bool ok, int y) {
+                    if (lanes == 0) return;
+                    int to = 0;
+                    if (lane == 0) to = atomicAdd(&sh_listed, __popcll(lanes));
+                    const int before = __popcll(lanes & ((1ull << lane) - 1)), e = __builtin_amdgcn_readfirstlane(to) + before;
+                    if (ok && e < list_room) {
+                        listed[e] = (uint32_t)cell << 14 | (uint32_t)y;
+                        listed_at[e] = (uint16_t)(n + before);
+                    }
+                    n += __popcll(lanes);
+                });
                 if (lane == 0) sh_at[cell] = n < 1 << 13 ? n : GRAPH_STAGES + 1;     // (a label has 13 bits for its number)
             }
             __syncthreads();
@@ -221,19 +254,23 @@ __global__ __launch_bounds__(GRAPH_THREADS) void sparse_graph_kernel(FrontTable 
     __syncthreads();
     const int first = sh_first;
     if (first + n_stages > g.room) return none();
-    for (int cell = 1 + wid; cell < n_cells; cell += FRONT_WAVES) {
-        const int k = sh_cell[cell] / RS;
-        int to = 0;
-        stages(cell, [&](uint64_t lanes, bool ok, int i, int q, int32_t t, int behind) {
-            if (ok) {
-                const int local = to + __popcll(lanes & ((1ull << lane) - 1)), to_cell = i == K - 1 ? 0 : id[behind];
-                const int run = ft.run[(uint32_t)((k * K + i) * SP + q)];
-                g.stages[first + sh_at[cell] + local] = make_int4(t, 8 * cell | 8 * to_cell << 16, (1 << 24) + (local << 11 | to_cell),
-                                                                  k << 22 | i << 14 | q << 8 | run);
-            }
-            to += __popcll(lanes);
-        });
-    }
+    auto write = [&](int cell, int local, int y) {
+        const int x0 = sh_cell[cell], k = x0 / RS, d = x0 % RS + 1, l = (int)(((int64_t)y * inv) >> 20), i = k + l, q = y - l * S;
+        const uint32_t at = (uint32_t)((k * K + i) * SP + q);
+        const int to_cell = i == K - 1 ? 0 : id[(i + 1) * RS + d - sh_size[q] - 1];
+        g.stages[first + sh_at[cell] + local] = make_int4(ft.least[at], 8 * cell | 8 * to_cell << 16, (1 << 24) + (local << 11 | to_cell),
+                                                          k << 22 | i << 14 | q << 8 | ft.run[at]);
+    };
+    if (n_stages <= list_room)
+        for (int e = tid; e < n_stages; e += GRAPH_THREADS) write((int)(listed[e] >> 14), listed_at[e], (int)(listed[e] & 0x3fff));
+    else
+        for (int cell = 1 + wid; cell < n_cells; cell += FRONT_WAVES) {
+            int to = 0;
+            stages(cell, [&](uint64_t lanes, bool ok, int y) {
+                if (ok) write(cell, to + __popcll(lanes & ((1ull << lane) - 1)), y);
+                to += __popcll(lanes);
+            });
+        }
     for (int x = tid; x < n_cells; x += GRAPH_THREADS) g.cells[j * GRAPH_CELLS + x] = sh_at[x];
     // chunks: a thread per first layer, r = K - 1 - k
     auto row_start = [&](int r) {                  // where the stages that begin with layer K - 1 - r start
@@ -255,7 +292,7 @@ __global__ __launch_bounds__(GRAPH_THREADS) void sparse_graph_kernel(FrontTable 
     int32_t from_c = 0;
     if (U == INT32_MAX && n_stages <= GRAPH_SEARCH) {
         __syncthreads();                               // (the graph is there, and Q no longer needed)
-        const int tries = min(FRONT_WAVES, GRAPH_LDS / 4 / n_cells);
+        const int tries = min(FRONT_WAVES, (K * RS * 6 + list_room * 6) / 4 / n_cells);
         int32_t *const fewest = lds + wid * n_cells;
         const int4 *const all = g.stages + first;
         int32_t lo = max(low + 1, feasible), hi = c + 1;       // the answer is in [lo, hi], hi: none in the interval
@@ -266,15 +303,28 @@ __global__ __launch_bounds__(GRAPH_THREADS) void sparse_graph_kernel(FrontTable 
             if (wid < tries && x < hi) {
                 for (int y = lane; y < n_cells; y += WAVE) fewest[y] = y == 0 ? 0 : 1 << 20;
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-                for (int ch = 0; ch < n_chunks; ++ch) {
-                    const int e = __builtin_amdgcn_readfirstlane(chunks[ch]), count = __builtin_amdgcn_readfirstlane(chunks[ch + 1]) - e;
-                    const int4 v = all[e + min(lane, count - 1)];
-                    const int s = *(const int32_t *)((const char *)fewest + ((uint32_t)v.y >> 17)) + 1;
-                    int32_t t = v.x;
-                    if (s > (v.w & 255))
-                        t = s <= min(K, D) ? table[(((size_t)(s - 1) * K + (v.w >> 22)) * K + (v.w >> 14 & 255)) * S + (v.w >> 8 & 63)] : INF_I32;
-                    if (lane < count && t <= x) atomicMin((int32_t *)((char *)fewest + ((v.y & 0xffff) >> 1)), s);
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+                int4 w[4];                         // of chunks, as they are asked for
+                int count[4];
+                auto load = [&](int ch, int u) {
+                    const int e = __builtin_amdgcn_readfirstlane(chunks[min(ch, n_chunks)]);
+                    count[u] = __builtin_amdgcn_readfirstlane(chunks[min(ch + 1, n_chunks)]) - e;
+                    w[u] = all[e + lane];          // (there is room behind the last)
+                };
+#pragma unroll
+                for (int u = 0; u < 4; ++u) load(u, u);
+                for (int ch = 0; ch < n_chunks; ch += 4) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int4 v = w[u];
+                        const bool in = lane < count[u];
+                        load(ch + u + 4, u);
+                        const int s = in ? *(const int32_t *)((const char *)fewest + ((uint32_t)v.y >> 17)) + 1 : 1 << 20;
+                        int32_t t = v.x;
+                        if (s > (v.w & 255))
+                            t = s <= min(K, D) ? table[(((size_t)(s - 1) * K + (v.w >> 22)) * K + (v.w >> 14 & 255)) * S + (v.w >> 8 & 63)] : INF_I32;
+                        if (t <= x) atomicMin((int32_t *)((char *)fewest + ((v.y & 0xffff) >> 1)), s);
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+                    }
                 }
                 if (lane == 0 && fewest[n_cells - 1] < 1 << 20) atomicMin(&sh_first, x);
             }
@@ -290,6 +340,22 @@ __global__ __launch_bounds__(GRAPH_THREADS) void sparse_graph_kernel(FrontTable 
         from_c = lo;
     }
     if (tid == 0) g.heads[j] = GraphHead{first, n_stages, n_cells, n_chunks, from_c, {0, 0, 0}};
+}
+
+// A workgroup for each interval, and beside them one for each threshold that may have to look for a plan: see band_bounds.
+template <int W>
+__global__ __launch_bounds__(GRAPH_THREADS) void sparse_graph_kernel(FrontTable ft, const int32_t *__restrict__ table, BandShapes bs, Problem p,
+                                                                     int32_t max_finite, const int32_t *__restrict__ fronts,
+                                                                     const int32_t *__restrict__ backs, const int32_t *__restrict__ totals,
+                                                                     int32_t *plans, const int32_t *__restrict__ falls, GraphTable g, int list_room,
+                                                                     int32_t *__restrict__ bounds, int once, int32_t *there)
+{
+    if (once && *there) return;
+    const bool looks = blockIdx.x >= BAND_THRESHOLDS;
+    const int j = blockIdx.x - (looks ? BAND_THRESHOLDS : 0);
+    if (!looks) sparse_graph<W>(j, ft, table, bs, p.K, p.D, max_finite, fronts, backs, totals, plans, falls, g, list_room);
+    __syncthreads();
+    band_bounds(p, max_finite, table, bs, fronts, WAVE * W, totals, plans, bounds, there, j, looks);
 }
 
 struct SparseArgs {
@@ -460,17 +526,19 @@ const int4 *graph_stages(int32_t *graph, int K) { return graph_table(graph, K).s
 
 hipError_t launch_sparse_graph(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
                                const int32_t *work, const int32_t *front, const int32_t *fronts, const int32_t *backs,
-                               const int32_t *totals, const int32_t *plans, const int32_t *falls, int32_t *graph, const int32_t *asked)
+                               const int32_t *totals, int32_t *plans, const int32_t *falls, int32_t *graph, int32_t *bounds, int32_t *there, bool once)
 {
     const int K = p.K, D = p.D, RS = D <= 64 ? 64 : D <= 128 ? 128 : 256;
-    const size_t lds = std::max(std::max(front_lds_bytes(K, D, b.S), (size_t)K * RS * 6), (size_t)GRAPH_LDS);
+    const size_t cells = (size_t)K * RS * 6;       // (a multiple of 16)
+    const size_t lds = std::max({front_lds_bytes(K, D, b.S), cells, std::min(cells + 6 * GRAPH_STAGES, (size_t)GRAPH_LDS)});
+    const int list_room = (int)std::min((lds - cells) / 6, (size_t)GRAPH_STAGES);
     const auto kernel = D > 128 ? sparse_graph_kernel<4> : D > 64 ? sparse_graph_kernel<2> : sparse_graph_kernel<1>;
     if (lds > 48 * 1024) {
         const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kernel, dim3(BAND_THRESHOLDS), dim3(GRAPH_THREADS), lds, st, front_table(work, front, K, b.S, b.sizes, false),
-                       table, b, K, D, max_finite, fronts, backs, totals, plans, falls, graph_table(graph, K), asked);
+    hipLaunchKernelGGL(kernel, dim3(2 * BAND_THRESHOLDS), dim3(GRAPH_THREADS), lds, st, front_table(work, front, K, b.S, b.sizes, false),
+                       table, b, p, max_finite, fronts, backs, totals, plans, falls, graph_table(graph, K), list_room, bounds, once ? 1 : 0, there);
     return hipGetLastError();
 }
 
