@@ -74,7 +74,7 @@ struct alpa_dp {
     bool recorded = false;          // a solve has been recorded into a graph
     int32_t *d_table = nullptr, *d_sizes = nullptr, *d_recs = nullptr, *d_gmin = nullptr;
     int32_t *d_bandrecs = nullptr, *d_bandends = nullptr, *d_bandthr = nullptr, *d_backs = nullptr;
-    int32_t *d_front = nullptr, *d_graph = nullptr;
+    int32_t *d_least = nullptr, *d_front = nullptr, *d_graph = nullptr;
     bool band_ok = false;
     bool sparse_ok = false;         // there is room for candidates to go by graphs (kernels_sparse.hip)
     bool ordered = false;           // and the table's latencies do not fall with the number of stages
@@ -314,13 +314,20 @@ static int queue_table_candidates(alpa_dp *h, bool cleared = false)
     return ALPA_DP_OK;
 }
 
+// the table as the band kernel and what it takes beforehand read it
+static hipError_t launch_band_table(alpa_dp *h)
+{
+    const hipError_t e = launch_repack_band(h->stream, h->d_table, h->p, h->band_shapes, h->d_bandrecs, h->d_bandends, h->d_bounds, !h->ordered);
+    return e != hipSuccess ? e : launch_front_table(h->stream, h->d_table, h->band_shapes, h->p, h->d_least, h->d_front);
+}
+
 // what the table says about every candidate -> d_bounds; `recorded`: a graph's replays behind the first find the band
 // kernel's bounds there, and only look (27 us at 24 layers on 2 x 8, 105 at 64 on 8 x 8, 420 at 48 on 32 x 8 each otherwise)
 static int queue_bounds(alpa_dp *h, bool recorded)
 {
     if (h->band_ok)
         HIPCHK(launch_band_bounds(h->stream, h->d_table, h->band_shapes, h->p, h->max_finite,
-                                  BandWork{h->d_bound_work, h->d_front, h->d_bandthr, h->d_backs, h->d_graph},
+                                  BandWork{h->d_least, h->d_front, h->d_bandthr, h->d_backs, h->d_graph},
                                   h->d_bounds, recorded));
     else
         HIPCHK(launch_table_bounds(h->stream, h->p, h->d_table, h->d_sizes, h->d_bound_work, h->d_bounds));
@@ -426,13 +433,14 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
         take(h->d_best_plan, 1);
         take(h->d_Fall, (size_t)(h->p.Smax + 1) * LS);
         take(h->d_bounds, table_bounds_ints(h->p) + (h->band_ok ? BAND_TOTALS : 0));
-        take(h->d_bound_work, h->band_ok ? front_least_ints(K, SB) : table_bounds_work(h->p));
+        take(h->d_bound_work, h->band_ok ? 2 * (size_t)h->p.Smax : table_bounds_work(h->p));
         take(h->d_scratch, (size_t)gg * 2 * LS);
         if (h->band_ok) {
             take(h->d_bandrecs, band_table_ints(K, h->p.Smax, SB));
             take(h->d_bandends, band_ends_ints(K, h->p.Smax, SB));
             take(h->d_bandthr, band_thresholds_ints(K, D));
             take(h->d_backs, band_thresholds_ints(K, D));
+            take(h->d_least, front_least_ints(K, SB));
             take(h->d_front, front_table_ints(K, SB));
             if (h->sparse_ok) {
                 take(h->d_graph, graph_table_ints(K));
@@ -466,8 +474,7 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
     HIPCHK(hipMemcpyAsync(h->d_sizes, up.data(), up.size() * 4, hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipMemsetAsync(h->d_state, 0, sizeof(SolveState), h->stream));
     HIPCHK(launch_init_best_plan(h->stream, h->d_best_plan));
-    if (h->band_ok)
-        HIPCHK(launch_repack_band(h->stream, h->d_table, h->p, h->band_shapes, h->d_bandrecs, h->d_bandends, h->d_bounds, !h->ordered));
+    if (h->band_ok) HIPCHK(launch_band_table(h));
     if (h->fast_ok) {
         h->KP = 16 * ((K + 15) / 16);
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
@@ -603,8 +610,7 @@ extern "C" int alpa_dp_restrict_equal_layers(alpa_dp_t *h)
     const int K = h->p.K, D = h->p.D, S = h->p.S;
     HIPCHK(launch_equal_layer_mask(h->stream, h->d_table, K, S));
     h->ordered = false;
-    if (h->band_ok)
-        HIPCHK(launch_repack_band(h->stream, h->d_table, h->p, h->band_shapes, h->d_bandrecs, h->d_bandends, h->d_bounds, !h->ordered));
+    if (h->band_ok) HIPCHK(launch_band_table(h));
     if (h->fast_ok) {
         HIPCHK(launch_repack_fast(h->stream, h->d_table, K, D, S, h->KP, h->d_recs, h->d_gmin));
     }

@@ -66,10 +66,10 @@ __device__ __forceinline__ void band_real_plan(const int32_t *__restrict__ table
 // guess), and nowhere if that is far above.  If no threshold has a real plan, a workgroup for each looks for one, and
 // the last to end writes the bounds: 48 layers on 32 x 8 with little memory have P 41184, plans of 41412 are found, the best of all is
 // 41382 (the plan alone out of 300 candidates: 2050 us without a known plan, 606 with). (The thresholds' plans
-// stay as they are until every workgroup has ended, as does `there`.)  `looks`: the workgroup looks for a plan of threshold j.
+// stay as they are until every workgroup has ended, as does `there`.)
 __device__ __forceinline__ void band_bounds(const Problem &p, int32_t max_finite, const int32_t *__restrict__ table, const BandShapes &bs,
                                             const int32_t *__restrict__ fronts, int RS, const int32_t *__restrict__ totals, int32_t *plans,
-                                            int32_t *__restrict__ bounds, int32_t *there, int j, bool looks)
+                                            int32_t *__restrict__ bounds, int32_t *there, int j)
 {
     __shared__ int32_t flat, own[2];
     __shared__ int last;
@@ -77,7 +77,7 @@ __device__ __forceinline__ void band_bounds(const Problem &p, int32_t max_finite
     int32_t *const n_ended = plans + 2 * BAND_THRESHOLDS, *const real = n_ended + 1;
     int32_t best = band_best_plan(plans);
     const bool none = totals[0] < DEV_INF && best >= DEV_INF;
-    if (none && looks) {
+    if (none) {
         if (tid < 2) own[tid] = DEV_INF;
         __syncthreads();
         if (totals[j] < DEV_INF)
@@ -85,7 +85,7 @@ __device__ __forceinline__ void band_bounds(const Problem &p, int32_t max_finite
     }
     __syncthreads();
     if (tid == 0) {
-        if (none && looks) {
+        if (none) {
             __hip_atomic_store(&real[2 * j], own[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(&real[2 * j + 1], own[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }

@@ -321,7 +321,7 @@ hipError_t launch_repack_band(hipStream_t st, const int32_t *table, const Proble
 // (a recorded solve is replayed)
 size_t band_thresholds_ints(int K, int D);
 struct BandWork {
-    int32_t *least, *front;  // front_least_ints, front_table_ints
+    const int32_t *least, *front;  // front_least_ints, front_table_ints, of launch_front_table
     int32_t *thr, *backs;    // band_thresholds_ints each (no windows in the second)
     int32_t *graph;          // graph_table_ints; null where candidates do not go by graphs
 };
@@ -343,8 +343,9 @@ size_t front_least_ints(int K, int S);
 size_t front_table_ints(int K, int S);
 size_t front_lds_bytes(int K, int D, int S);
 FrontTable front_table(const int32_t *least, const int32_t *front, int K, int S, const int32_t *sizes, bool back);
+hipError_t launch_front_table(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t *work, int32_t *front);
 hipError_t launch_front_thresholds(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
-                                   int32_t *work, int32_t *front, int32_t *fronts, int32_t *backs, int32_t *totals,
+                                   const int32_t *work, const int32_t *front, int32_t *fronts, int32_t *backs, int32_t *totals,
                                    int32_t *plans, int32_t *windows, int32_t *graph_used, const int32_t *asked);
 
 // candidates by the stages that can be in their best plans (kernels_sparse.hip)

@@ -577,7 +577,7 @@ __global__ __launch_bounds__(BAND_BOUNDS_THREADS) void band_bounds_kernel(Proble
                                                                           int32_t *__restrict__ bounds, int once, int32_t *there)
 {
     if (once && *there) return;
-    band_bounds(p, max_finite, table, bs, fronts, RS, totals, plans, bounds, there, blockIdx.x, true);
+    band_bounds(p, max_finite, table, bs, fronts, RS, totals, plans, bounds, there, blockIdx.x);
 }
 
 // Where the thresholds say little, the recurrence itself without a filter, through all its layers, in two workgroups: one for the

@@ -22,12 +22,11 @@ FrontTable front_table(const int32_t *least, const int32_t *front, int K, int S,
 }
 
 // least[b][i][q] and run[b][i][q] (q padded to front_padded): the least latency over the numbers of stages behind, and with how
-// many, itself included, the stage has it from one on.  there (null: not asked): see BAND_THERE.
+// many, itself included, the stage has it from one on.
 __global__ __launch_bounds__(256) void front_least_kernel(const int32_t *__restrict__ table, int K, int Smax, BandShapes bs, int SP,
-                                                          const int32_t *__restrict__ there, int32_t *__restrict__ least,
+                                                          int32_t *__restrict__ least,
                                                           uint8_t *__restrict__ run)
 {
-    if (there && *there) return;
     const int n = K * K * SP;
     for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < n; x += gridDim.x * blockDim.x) {
         const int ki = x / SP, q = x - ki * SP, k = ki / K, i = ki - k * K;
@@ -54,9 +53,8 @@ __global__ __launch_bounds__(256) void front_least_kernel(const int32_t *__restr
 
 // The units from `least`, a wave each; blockIdx.y: those of P, those of Q (the layers in reverse order)
 __global__ __launch_bounds__(256) void front_units_kernel(const int32_t *__restrict__ least, int K, int S, int SP,
-                                                          const int32_t *__restrict__ there, int32_t *__restrict__ units)
+                                                          int32_t *__restrict__ units)
 {
-    if (there && *there) return;
     const int lane = threadIdx.x & (WAVE - 1), NG = front_groups(S), n = front_units(K, S);
     const bool back = blockIdx.y == 1;
     units += back ? (size_t)n * 65 : 0;
@@ -209,17 +207,26 @@ size_t front_lds_bytes(int K, int D, int S)
     return (size_t)front_lds(nullptr, K, D, front_groups(S), D <= 64 ? 1 : D <= 128 ? 2 : 4).ints * 4;
 }
 
-// work: front_least_ints; front: front_table_ints
+// What front costs are found from, laid out when the table is (a recorded solve launches only what depends on the bounds not being
+// there).  work: front_least_ints; front: front_table_ints
+hipError_t launch_front_table(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t *work, int32_t *front)
+{
+    const int K = p.K, SP = front_padded(b.S);
+    const FrontTable ft = front_table(work, front, K, b.S, b.sizes, false);
+    hipLaunchKernelGGL(front_least_kernel, dim3(std::min((K * K * SP + 255) / 256, 16384)), dim3(256), 0, st, table, K, p.Smax, b, SP,
+                       work, (uint8_t *)ft.run);
+    hipLaunchKernelGGL(front_units_kernel, dim3(std::min((front_units(K, b.S) + 3) / 4, 8192), 2), dim3(256), 0, st, work, K, b.S, SP,
+                       (int32_t *)ft.units);
+    return hipGetLastError();
+}
+
+// behind launch_front_table of the same table
 hipError_t launch_front_thresholds(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
-                                   int32_t *work, int32_t *front, int32_t *fronts, int32_t *backs, int32_t *totals,
+                                   const int32_t *work, const int32_t *front, int32_t *fronts, int32_t *backs, int32_t *totals,
                                    int32_t *plans, int32_t *windows, int32_t *graph_used, const int32_t *asked)
 {
-    const int K = p.K, D = p.D, SP = front_padded(b.S);
+    const int K = p.K, D = p.D;
     const FrontTable ft = front_table(work, front, K, b.S, b.sizes, false), ft_back = front_table(work, front, K, b.S, b.sizes, true);
-    hipLaunchKernelGGL(front_least_kernel, dim3(std::min((K * K * SP + 255) / 256, 16384)), dim3(256), 0, st, table, K, p.Smax, b, SP,
-                       asked, work, (uint8_t *)ft.run);
-    hipLaunchKernelGGL(front_units_kernel, dim3(std::min((front_units(K, b.S) + 3) / 4, 8192), 2), dim3(256), 0, st, work, K, b.S, SP,
-                       asked, (int32_t *)ft.units);
     const size_t lds = std::max(front_lds_bytes(K, D, b.S), (size_t)2 * K * (K | 1));
     const auto kernel = D > 128 ? band_thresholds_kernel<4, 0> : D > 64 ? band_thresholds_kernel<2, 0> : b.S > 16 ? band_thresholds_kernel<1, 0> :
                         b.S > 12 ? band_thresholds_kernel<1, 4> : b.S > 8 ? band_thresholds_kernel<1, 3> : band_thresholds_kernel<1, 2>;

@@ -91,10 +91,11 @@ __device__ __forceinline__ int graph_scan(int v, int *sh, int &total)
     return base + x - v;
 }
 
-// The graph of interval j.  Bound by the loads of each cell's stages (least latencies), four in flight a wave, so a cell is looked
-// at once, up to the last layer that the filter lets its stages reach, and what is found is listed in LDS; only a graph of more
-// stages than the list holds is looked at again (every cell twice and to the last layer: 64 layers on 8 x 8 156 us, now 78; on
-// 16 x 8 209 and 86; 128 layers 308 and 174; 48 layers on 32 x 8 520 and 210).
+// The graph of interval j.  Bound by what is looked at of each cell's stages, so that is done once, up to the last layer that the
+// filter lets a stage reach, by as many neighbouring cells to a wave as to any other, with the latencies of their first layer in
+// registers; what is found is listed in LDS, and only a graph of more stages than the list holds is looked at again.  (64 layers on
+// 8 x 8: every cell twice and to the last layer 156 us, listed 78, latencies kept 73; on 16 x 8 209, 86 and 72; 128 layers 308, 174 and
+// 127; 48 layers on 32 x 8, with front costs of its own for the lowest interval, 520, 210 and 191.)
 template <int W>
 __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const int32_t *__restrict__ table, const BandShapes &bs, int K, int D,
                                              int32_t max_finite, const int32_t *__restrict__ fronts, const int32_t *__restrict__ backs,
@@ -106,13 +107,15 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
     __shared__ int32_t sh_U, sh_plan[2];
     __shared__ uint16_t sh_cell[GRAPH_CELLS];      // cells in order: position in a [K][RS] array
     __shared__ int sh_at[GRAPH_CELLS + 1];         // where their stages start
+    __shared__ int32_t sh_room[GRAPH_CELLS];       // for a stage and what is behind it
     __shared__ int sh_size[64], sh_listed;
     __shared__ int16_t sh_reach[256];              // the last layer that a stage which begins with k reaches in the interval
     constexpr int RS = WAVE * W;
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int lane = threadIdx.x & (WAVE - 1);
+    const int tid = threadIdx.x, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int S = bs.S, SP = front_padded(S), N = K * RS;
-    const int32_t single = front_single(table, bs, K, D), c = min(band_threshold(max_finite, j), single);
-    const int32_t low = j + 1 < BAND_THRESHOLDS ? band_threshold(max_finite, j + 1) : 0, feasible = totals[BAND_THRESHOLDS];
+    const int32_t single = __builtin_amdgcn_readfirstlane(front_single(table, bs, K, D)), c = min(band_threshold(max_finite, j), single);
+    const int32_t low = j + 1 < BAND_THRESHOLDS ? band_threshold(max_finite, j + 1) : 0, feasible = __builtin_amdgcn_readfirstlane(totals[BAND_THRESHOLDS]);
     auto none = [&]() {
         if (tid == 0) g.heads[j] = GraphHead{0, -1, 0, 0, 0, {0, 0, 0}};
     };
@@ -138,7 +141,7 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
     auto front_of = [&](int x) { return x >= RS ? P[x] : x == D - 1 ? 0 : DEV_INF; };
     const int inv = (1 << 20) / S + 1;             // x / S for x < 2^14 (S <= 64)
     int n_cells, n_stages, at;
-    int32_t U = sh_U;
+    int32_t U = __builtin_amdgcn_readfirstlane(sh_U);
     for (int k = wid; k < K; k += FRONT_WAVES) {
         const int n = (K - k) * SP;
         const int32_t *const row = ft.least + (uint32_t)((k * K + k) * SP);
@@ -155,59 +158,67 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
         }
         if (lane == 0) sh_reach[k] = (int16_t)(reach < 0 ? -1 : k + reach / SP);
     }
-    // the stages of a cell, in order: found(lanes that have one, whether this one has, its number)
-    auto stages = [&](int cell, auto found) {
+    // the stages of a cell, in order: found(lanes that have one, whether this one has, its number).  Neighbouring cells mostly begin
+    // with the same layer, whose latencies stay in registers
+    struct Row { int32_t t[4]; int at[4], have = -1; };      // at: last layer << 16 | devices
+    auto stages = [&](Row &r, int cell, auto found) {
         const int x0 = sh_cell[cell], k = x0 / RS, d = x0 % RS + 1, n = (sh_reach[k] + 1 - k) * S;
-        const int32_t room = U - front_of(x0);     // for the stage and what is behind it
+        const int32_t room = sh_room[cell];
         const int32_t *const row = ft.least + (uint32_t)((k * K + k) * SP);
         for (int y0 = 0; y0 < n; y0 += 4 * WAVE) {
-            int32_t t[4];
-            int i[4], q[4];
+            if (r.have != (k << 16 | y0)) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int y = min(y0 + u * WAVE + lane, n - 1), l = (int)(((int64_t)y * inv) >> 20);
-                i[u] = k + l;
-                q[u] = y - l * S;
-                t[u] = row[(uint32_t)(l * SP + q[u])];
+                for (int u = 0; u < 4; ++u) {
+                    const int y = min(y0 + u * WAVE + lane, n - 1), l = (int)(((int64_t)y * inv) >> 20);
+                    const int q = y - l * S;
+                    r.t[u] = y0 + u * WAVE + lane < n ? row[(uint32_t)(l * SP + q)] : INF_I32;
+                    r.at[u] = (k + l) << 16 | sh_size[q];
+                }
+                r.have = k << 16 | y0;
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int left = d - sh_size[q[u]], behind = (i[u] + 1) * RS + left - 1;
-                const bool end = i[u] == K - 1;
-                bool ok = y0 + u * WAVE + lane < n && t[u] <= c && (end ? left == 0 : left > 0);
+                if (y0 + u * WAVE >= n) continue;  // (uniform)
+                const int i = r.at[u] >> 16, left = d - (r.at[u] & 0xffff), behind = (i + 1) * RS + left - 1;
+                const bool end = i == K - 1;
+                bool ok = r.t[u] <= c && (end ? left == 0 : left > 0);
                 const int32_t f = ok && !end ? Q[behind] : 0;
-                ok = ok && f < DEV_INF && t[u] + f <= room;
+                ok = ok && f < DEV_INF && r.t[u] + f <= room;
                 found(__ballot(ok), ok, y0 + u * WAVE + lane);
             }
         }
     };
     for (int turn = 0;; ++turn) {
-        for (int x = tid; x < N; x += GRAPH_THREADS) Q[x] = backs[(size_t)j * N + x];
-        if (tid == 0) sh_listed = 0;
+        // (opaque: what is computed of it would be kept in registers through the front costs below)
+        int me = tid;
+        asm volatile("" : "+v"(me));
+        lane = me & (WAVE - 1);
+        for (int x = me; x < N; x += GRAPH_THREADS) {
+            const int32_t p = front_of(x), q = backs[(size_t)j * N + x];
+            Q[x] = p < DEV_INF && q < DEV_INF && p + q <= U ? q : DEV_INF;
+        }
+        if (me == 0) sh_listed = 0;
         __syncthreads();
         int mine = 0;
-        for (int y = tid * per; y < min(tid * per + per, N); ++y) {
-            const int x = place(y);
-            const int32_t p = front_of(x), q = Q[x];
-            mine += p < DEV_INF && q < DEV_INF && p + q <= U;
-        }
+        for (int y = me * per; y < min(me * per + per, N); ++y) mine += Q[place(y)] < DEV_INF;
         at = 1 + graph_scan(mine, sh_scan, n_cells);
         ++n_cells;
         n_stages = GRAPH_STAGES + 1;
         if (n_cells <= GRAPH_CELLS) {              // (uniform)
-            for (int y = tid * per; y < min(tid * per + per, N); ++y) {
+            for (int y = me * per; y < min(me * per + per, N); ++y) {
                 const int x = place(y);
-                const int32_t p = front_of(x), q = Q[x];
-                if (p < DEV_INF && q < DEV_INF && p + q <= U) {
+                if (Q[x] < DEV_INF) {
                     sh_cell[at] = (uint16_t)x;
+                    sh_room[at] = U - front_of(x);
                     id[x] = (uint16_t)at++;
                 }
             }
             __syncthreads();
-            // how many stages each has: a wave per cell
-            for (int cell = 1 + wid; cell < n_cells; cell += FRONT_WAVES) {
+            // how many stages each has: as many cells for every wave
+            Row row;
+            for (int cell = 1 + (n_cells - 1) * wid / FRONT_WAVES; cell < 1 + (n_cells - 1) * (wid + 1) / FRONT_WAVES; ++cell) {
                 int n = 0;
-                stages(cell, [&](uint64_t lanes, bool ok, int y) {
+                stages(row, cell, [&](uint64_t lanes, bool ok, int y) {
                     if (lanes == 0) return;
                     int to = 0;
                     if (lane == 0) to = atomicAdd(&sh_listed, __popcll(lanes));
@@ -225,7 +236,7 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
             int own[EACH], sum = 0;
 #pragma unroll
             for (int u = 0; u < EACH; ++u) {
-                const int x = tid * EACH + u;
+                const int x = me * EACH + u;
                 own[u] = x >= 1 && x < n_cells ? sh_at[x] : 0;
                 sum += own[u];
             }
@@ -233,11 +244,11 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
             __syncthreads();
 #pragma unroll
             for (int u = 0; u < EACH; ++u) {
-                const int x = tid * EACH + u;
+                const int x = me * EACH + u;
                 if (x < n_cells) sh_at[x] = at;
                 at += own[u];
             }
-            if (tid == 0) sh_at[n_cells] = n_stages;               // (n_cells <= GRAPH_CELLS)
+            if (me == 0) sh_at[n_cells] = n_stages;               // (n_cells <= GRAPH_CELLS)
         }
         __syncthreads();
         if (n_stages <= GRAPH_STAGES) break;
@@ -248,7 +259,7 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
         front_plan(ft, table, bs, K, D, min(feasible, single), l.P, sh_plan);
         __syncthreads();
         if (sh_plan[1] > feasible || sh_plan[0] >= U) return none();
-        U = sh_plan[0];
+        U = __builtin_amdgcn_readfirstlane(sh_plan[0]);
     }
     if (tid == 0) sh_first = atomicAdd(g.used, n_stages);
     __syncthreads();
@@ -263,10 +274,11 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
     };
     if (n_stages <= list_room)
         for (int e = tid; e < n_stages; e += GRAPH_THREADS) write((int)(listed[e] >> 14), listed_at[e], (int)(listed[e] & 0x3fff));
-    else
-        for (int cell = 1 + wid; cell < n_cells; cell += FRONT_WAVES) {
+    Row row;
+    if (n_stages > list_room)
+        for (int cell = 1 + (n_cells - 1) * wid / FRONT_WAVES; cell < 1 + (n_cells - 1) * (wid + 1) / FRONT_WAVES; ++cell) {
             int to = 0;
-            stages(cell, [&](uint64_t lanes, bool ok, int y) {
+            stages(row, cell, [&](uint64_t lanes, bool ok, int y) {
                 if (ok) write(cell, to + __popcll(lanes & ((1ull << lane) - 1)), y);
                 to += __popcll(lanes);
             });
@@ -342,7 +354,7 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
     if (tid == 0) g.heads[j] = GraphHead{first, n_stages, n_cells, n_chunks, from_c, {0, 0, 0}};
 }
 
-// A workgroup for each interval, and beside them one for each threshold that may have to look for a plan: see band_bounds.
+// A workgroup for each interval; see band_bounds.
 template <int W>
 __global__ __launch_bounds__(GRAPH_THREADS) void sparse_graph_kernel(FrontTable ft, const int32_t *__restrict__ table, BandShapes bs, Problem p,
                                                                      int32_t max_finite, const int32_t *__restrict__ fronts,
@@ -351,11 +363,9 @@ __global__ __launch_bounds__(GRAPH_THREADS) void sparse_graph_kernel(FrontTable 
                                                                      int32_t *__restrict__ bounds, int once, int32_t *there)
 {
     if (once && *there) return;
-    const bool looks = blockIdx.x >= BAND_THRESHOLDS;
-    const int j = blockIdx.x - (looks ? BAND_THRESHOLDS : 0);
-    if (!looks) sparse_graph<W>(j, ft, table, bs, p.K, p.D, max_finite, fronts, backs, totals, plans, falls, g, list_room);
+    sparse_graph<W>(blockIdx.x, ft, table, bs, p.K, p.D, max_finite, fronts, backs, totals, plans, falls, g, list_room);
     __syncthreads();
-    band_bounds(p, max_finite, table, bs, fronts, WAVE * W, totals, plans, bounds, there, j, looks);
+    band_bounds(p, max_finite, table, bs, fronts, WAVE * W, totals, plans, bounds, there, blockIdx.x);
 }
 
 struct SparseArgs {
@@ -537,7 +547,7 @@ hipError_t launch_sparse_graph(hipStream_t st, const int32_t *table, const BandS
         const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kernel, dim3(2 * BAND_THRESHOLDS), dim3(GRAPH_THREADS), lds, st, front_table(work, front, K, b.S, b.sizes, false),
+    hipLaunchKernelGGL(kernel, dim3(BAND_THRESHOLDS), dim3(GRAPH_THREADS), lds, st, front_table(work, front, K, b.S, b.sizes, false),
                        table, b, p, max_finite, fronts, backs, totals, plans, falls, graph_table(graph, K), list_room, bounds, once ? 1 : 0, there);
     return hipGetLastError();
 }
