@@ -802,6 +802,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     const bool bitmap = !have_list && distinct_by_bitmap(h);
     HIPCHK(launch_init_state(st, h->d_state, h->d_chunkmin, bound / PRUNE_CHUNK + 1, (uint32_t *)h->pb.keys[1],
                              bitmap ? h->max_finite / 32 + 1 : 0));
+    PickQuery pick{};
     if (have_list && n_tmax <= LIST_SORT_MAX) {
         HIPCHK(launch_list_sort(st, d_tmax, n_tmax, h->d_cand, h->d_ncount + 1, h->d_state, d_out_T ? h->d_rank : nullptr));
     } else if (have_list) {
@@ -815,8 +816,8 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     } else {
         int rc = queue_table_candidates(h, bitmap);
         if (rc) return rc;
-        HIPCHK(launch_pick_candidates(st, h->d_distinct, h->d_ncount + 0, n_tmax, bound, h->d_cand,
-                                      h->d_state, h->cands.cap));
+        pick = PickQuery{h->d_distinct, h->d_ncount + 0, n_tmax, h->cands.cap};
+        HIPCHK(launch_pick_candidates(st, pick, bound, h->d_cand, h->d_state));
     }
     if (with_bounds && !h->have_bounds) {
         int rc = queue_bounds(h, recorded);
@@ -828,7 +829,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
         if (rc) return rc;
         h->have_exact_bounds = !recorded;
     }
-    HIPCHK(launch_refine_begin(st, rq, h->d_cand, h->d_state, rb));
+    HIPCHK(launch_refine_begin(st, rq, pick, h->d_cand, h->d_state, rb));
     for (int round = 1; bound > 0 && round <= rb.rounds; ++round) {
         const bool last = round == rb.rounds;
         if (round > 1)

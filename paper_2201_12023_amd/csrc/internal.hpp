@@ -212,12 +212,16 @@ struct RefineQuery {
     int32_t max_finite;
 };
 // `bound`: the host's upper bound of the number of candidates
-hipError_t launch_pick_candidates(hipStream_t st, const int32_t *distinct,
-                                  const uint32_t *n_distinct, int n_quantiles, int bound,
-                                  int32_t *cand, SolveState *state, int cap);
+// candidates from the table's distinct values (distinct null: they are there)
+struct PickQuery {
+    const int32_t *distinct;
+    const uint32_t *n_distinct;
+    int n_quantiles, cap;
+};
+hipError_t launch_pick_candidates(hipStream_t st, PickQuery &pick, int bound, int32_t *cand, SolveState *state);
 hipError_t launch_set_candidates(hipStream_t st, const uint32_t *n_unique, SolveState *state);
 // first round: the range worth searching and its knots
-hipError_t launch_refine_begin(hipStream_t st, const RefineQuery &rq, const int32_t *cand, SolveState *state,
+hipError_t launch_refine_begin(hipStream_t st, const RefineQuery &rq, const PickQuery &pick, int32_t *cand, SolveState *state,
                                const RefineBuffers &rb);
 // the step behind round `round` (1-based)
 hipError_t launch_refine(hipStream_t st, const RefineQuery &rq, const int32_t *cand, int32_t *Fmin,

@@ -25,20 +25,25 @@ __device__ __forceinline__ int even_knot(int g, int m, int n)
     return m <= 1 ? 0 : (int)(((long long)g * (n - 1)) / (m - 1));
 }
 
-__global__ void pick_candidates_kernel(const int32_t *__restrict__ distinct,
-                                       const uint32_t *__restrict__ n_distinct_p, int n_quantiles,
-                                       int32_t *__restrict__ cand, SolveState *state, int cap)
+// The candidates from the table's distinct values: all of them, or evenly spaced ones.  (by threads x of n)
+__device__ __forceinline__ int pick_candidates(const PickQuery &pick, int32_t *cand, SolveState *state, int x, int n)
 {
-    const int n = (int)*n_distinct_p;
-    int C = (n_quantiles == 0 || n <= n_quantiles) ? n : n_quantiles;
-    if (C > cap) C = cap;
-    const bool all = (C == n);
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < C; j += gridDim.x * blockDim.x)
-        cand[j] = all ? distinct[j] : distinct[((long long)j * (n - 1)) / (n_quantiles - 1)];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const int m = (int)*pick.n_distinct;
+    int C = (pick.n_quantiles == 0 || m <= pick.n_quantiles) ? m : pick.n_quantiles;
+    if (C > pick.cap) C = pick.cap;
+    const bool all = (C == m);
+    for (int j = x; j < C; j += n)
+        cand[j] = all ? pick.distinct[j] : pick.distinct[((long long)j * (m - 1)) / (pick.n_quantiles - 1)];
+    if (x == 0) {
         state->n_cand = C;
-        state->n_distinct = n;
+        state->n_distinct = m;
     }
+    return C;
+}
+
+__global__ void pick_candidates_kernel(PickQuery pick, int32_t *cand, SolveState *state)
+{
+    pick_candidates(pick, cand, state, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
 __global__ void set_candidates_kernel(const uint32_t *__restrict__ n_unique_p, SolveState *state)
@@ -78,7 +83,7 @@ __device__ __forceinline__ int first_product(const int32_t *__restrict__ cand, i
 // The list is sorted as unsigned, so values below zero (only a device-side list can hold them) come last;
 // no entry passes them.
 __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq, int all, int first_round,
-                                                                  const int32_t *__restrict__ cand,
+                                                                  PickQuery pick, int32_t *cand,
                                                                   SolveState *state,
                                                                   int32_t *__restrict__ knots,
                                                                   int32_t *__restrict__ list)
@@ -86,7 +91,13 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
     __shared__ int sh_end, sh_first;
     constexpr int PLANS = BAND_THRESHOLDS + 2;
     __shared__ int32_t sh_sum[PLANS], sh_x[PLANS], sh_c[PLANS], sh_lo[PLANS];
-    const int C = state->n_cand;
+    int C;
+    if (pick.distinct) {
+        C = pick_candidates(pick, cand, state, threadIdx.x, RF_THREADS);
+        __syncthreads();
+    } else {
+        C = state->n_cand;
+    }
     const int64_t t_feas = rq.bounds[rq.Smax + 1], stages = rq.bounds[rq.Smax + 2];
     const int32_t least_of_all = rq.bounds[0], flat = rq.bounds[rq.Smax + 3];
     int lo = 0, hi = C;                                // first index with a negative value
@@ -390,13 +401,16 @@ __global__ __launch_bounds__(RF_THREADS) void refine_kernel(
     }
 }
 
-hipError_t launch_pick_candidates(hipStream_t st, const int32_t *distinct,
-                                  const uint32_t *n_distinct, int n_quantiles, int bound,
-                                  int32_t *cand, SolveState *state, int cap)
+// Up to PICK_HERE candidates are picked by the block that begins the first round (a launch of its own is 4 us of the stream's time; eight
+// turns of the block's threads are 3).
+constexpr int PICK_HERE = 8192;
+
+hipError_t launch_pick_candidates(hipStream_t st, PickQuery &pick, int bound, int32_t *cand, SolveState *state)
 {
+    if (bound <= PICK_HERE) return hipSuccess;
     const int grid = std::max(1, std::min((bound + 255) / 256, 1024));
-    hipLaunchKernelGGL(pick_candidates_kernel, dim3(grid), dim3(256), 0, st, distinct, n_distinct,
-                       n_quantiles, cand, state, cap);
+    hipLaunchKernelGGL(pick_candidates_kernel, dim3(grid), dim3(256), 0, st, pick, cand, state);
+    pick.distinct = nullptr;
     return hipGetLastError();
 }
 
@@ -406,10 +420,10 @@ hipError_t launch_set_candidates(hipStream_t st, const uint32_t *n_unique, Solve
     return hipGetLastError();
 }
 
-hipError_t launch_refine_begin(hipStream_t st, const RefineQuery &rq, const int32_t *cand, SolveState *state,
+hipError_t launch_refine_begin(hipStream_t st, const RefineQuery &rq, const PickQuery &pick, int32_t *cand, SolveState *state,
                                const RefineBuffers &rb)
 {
-    hipLaunchKernelGGL(refine_begin_kernel, dim3(1), dim3(RF_THREADS), 0, st, rq, rb.all, rb.first_round, cand,
+    hipLaunchKernelGGL(refine_begin_kernel, dim3(1), dim3(RF_THREADS), 0, st, rq, rb.all, rb.first_round, pick, cand,
                        state, rb.knots[0], rb.list);
     return hipGetLastError();
 }
