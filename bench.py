@@ -8,12 +8,11 @@ Eq. 3 for every candidate, Eq. 4 + best selection, and plan recovery; all on the
 
 Prints ONE JSON line.  ``value`` = index-reachable cell-updates (n_struct per candidate x
 candidates) per second on workload 4.  It counts the updates that Eq. 3 states for the whole
-candidate list, every candidate of which gets its exact T*; the library runs the recurrence only
-for the candidates that settle the others (equal neighbours on the staircase of F over t_max,
-bounds from the table), so ``value`` is a rate of the problem solved and not of instructions.  What
+candidate list, every candidate of which gets its exact T*; the library takes each
+through the few stages that can be in its best plan (the dense recurrence only where those are too many), so ``value`` is a rate of the problem solved and not of instructions.  What
 was executed is in ``executed_lane_relaxations_over_n_struct`` and, as a fraction of the int32 vector
 peak, in ``roofline`` (``frac_kind`` "executed": an add and a minimum per lane of every update run,
-idle lanes included).  ``extra.workloads`` has one row per workload 1-5 (same
+idle lanes included; 64 stages of a candidate's pass are one update of a wave).  ``extra.workloads`` has one row per workload 1-5 (same
 path, each workload's own candidate mode and pruning flag): wall-clock mean and HIP-event
 median of the step, the recurrence rounds' own time, that fraction, cell-updates/s, candidates/s,
 and whether the results equal the stored oracle results.
@@ -128,7 +127,7 @@ def main():
         ms_per_step = dt / args.steps * 1e3
 
         # per-step device time: HIP events on the stream the library launches on, and the
-        # library's own events around the recurrence launch; one query per step
+        # library's own clock around the recurrence launches; one query per step
         rec_ms, cand_ms, epi_ms, step_ms = [], [], [], []
         for _ in range(event_steps):
             e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -282,7 +281,7 @@ def main():
                      "traffic": traffic, "traffic_kind": "stored rocprofv3 --pmc measurement "
                      "(profiles/) of one solve's rounds, not taken by this run" if traffic else None,
                      "traffic_measured_at_commit": commit,
-                     "kernel": "recurrence_band_kernel", "kernel_ms_avg": head["rec_avg"]},
+                     "kernel": "sparse_eval_kernel, recurrence_band_kernel", "kernel_ms_avg": head["rec_avg"]},
         "extra": extra,
     }
 

@@ -322,7 +322,7 @@ static hipError_t launch_band_table(alpa_dp *h)
 }
 
 // what the table says about every candidate -> d_bounds; `recorded`: a graph's replays behind the first find the band
-// kernel's bounds there, and only look (27 us at 24 layers on 2 x 8, 105 at 64 on 8 x 8, 420 at 48 on 32 x 8 each otherwise)
+// kernel's bounds there, and only look (46 us at 24 layers on 2 x 8, 165 at 64 on 8 x 8, 550 at 48 on 32 x 8 each otherwise)
 static int queue_bounds(alpa_dp *h, bool recorded)
 {
     if (h->band_ok)
@@ -726,6 +726,8 @@ static int candidate_bound(const alpa_dp *h, bool have_list, int n_tmax)
 // candidates as for 2048 (64 layers on 1 x 8 in lane groups).  Where every candidate keeps a compute unit busy by itself
 // (the band kernel) the work counts from fewer on (us in one round and in two: 64 layers on 16 x 8, 1024
 // candidates: 2235 and 1367; 48 on 8 x 8, 2048: 716 and 337; but 24 on 2 x 8, 1500: 175 and 177).
+// Where a candidate is a wave's pass over a graph, 3072 run at a time and 4096 take little longer than 256 (64 layers on 8 x 8: 66 and
+// 28 us, two rounds about 72; 47 on 7 x 8 110 for 4096, 55 for 2048), beyond that half of them are knots.
 // Without the bounds the problem is small and one round takes everything.
 static RefineBuffers plan_rounds(const alpa_dp *h, int bound, bool one_per_cu, bool with_bounds, bool sparse)
 {
