@@ -21,11 +21,11 @@
 // would have fewer), so the order of (sum, stages, last layer, shape) in each cell's own minimum is that of the walk.
 #include "bounds.hpp"
 #include "front.hpp"
+#include "graph_label.hpp"
 
 namespace alpa {
 
-constexpr int GRAPH_CELLS = 1536;              // of one graph, the end included
-constexpr int GRAPH_STAGES = 1 << 14;
+constexpr int GRAPH_STAGES = 1 << 14;          // of one graph
 constexpr int GRAPH_CHUNKS = 512;              // of up to 64 stages that begin with one layer (at most 248 + 16384 / 64)
 constexpr int GRAPH_THREADS = WAVE * FRONT_WAVES;
 constexpr int GRAPH_SEARCH = 4096;             // stages of a graph in which the least t_max with a plan is looked for
@@ -269,7 +269,7 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
         const int x0 = sh_cell[cell], k = x0 / RS, d = x0 % RS + 1, l = (int)(((int64_t)y * inv) >> 20), i = k + l, q = y - l * S;
         const uint32_t at = (uint32_t)((k * K + i) * SP + q);
         const int to_cell = i == K - 1 ? 0 : id[(i + 1) * RS + d - sh_size[q] - 1];
-        g.stages[first + sh_at[cell] + local] = make_int4(ft.least[at], 8 * cell | 8 * to_cell << 16, (1 << 24) + (local << 11 | to_cell),
+        g.stages[first + sh_at[cell] + local] = make_int4(ft.least[at], graph_label_bytes(cell, to_cell), (1 << 24) + (local << 11 | to_cell),
                                                           k << 22 | i << 14 | q << 8 | ft.run[at]);
     };
     if (n_stages <= list_room)
@@ -435,10 +435,10 @@ __global__ __launch_bounds__(SPARSE_WAVES * WAVE) void sparse_eval_kernel(Sparse
 #pragma unroll
                 for (int y = 0; y < AHEAD; ++y) {
                     const int4 v = w[y];
-                    const bool in = lane < count[y] && v.x <= c;
+                    const bool in = lane < count[y];
                     load(x + y + AHEAD, y);
-                    const uint2 b = *(const uint2 *)(Lb + ((uint32_t)v.y >> 16));      // (of lanes behind the chunk: some label)
-                    const bool ok = in && b.y != ~0u, as_is = b.x >> 24 < (uint32_t)(v.w & 255);
+                    const uint2 b = *(const uint2 *)(Lb + graph_label_behind(v.y, in));
+                    const bool ok = in && v.x <= c && b.y != ~0u, as_is = b.x >> 24 < (uint32_t)(v.w & 255);
                     left_out |= ok && !as_is;
                     if (ok && (as_is || !real)) {
                         const unsigned long long own = (unsigned long long)(b.y + (uint32_t)v.x) << 32 | ((b.x & 0xff000000u) + (uint32_t)v.z);
