@@ -800,7 +800,8 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     // per-candidate results are wanted from every interval; a plan alone from few of them
     const RefineQuery rq{n_B > 0 ? h->d_sw_B : nullptr, p.B, std::max(n_B, 1), prune,
                          (n_B > 0 || !d_out_T) ? 1 : 0, bounds, p.Smax, prune_sel,
-                         h->band_ok ? bounds + table_bounds_ints(p) : nullptr, h->max_finite};
+                         h->band_ok ? bounds + table_bounds_ints(p) : nullptr, h->max_finite,
+                         sparse && rb.rounds > 1 ? graph_heads(h->d_graph, p.K) : nullptr};
     const bool bitmap = !have_list && distinct_by_bitmap(h);
     HIPCHK(launch_init_state(st, h->d_state, h->d_chunkmin, bound / PRUNE_CHUNK + 1, (uint32_t *)h->pb.keys[1],
                              bitmap ? h->max_finite / 32 + 1 : 0));
@@ -849,6 +850,13 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                 fa.list = h->d_todo;
                 fa.n_list_p = &h->d_state->n_todo;
                 fa.ticket = &h->d_state->todo_ticket;
+                fa.whole = rb.list;
+                fa.n_whole_p = &h->d_state->n_list;
+                fa.rest = h->d_todo;               // (not read in a launch that lists what is left itself)
+                fa.thin = h->d_state->thin;
+                fa.leave_out = last && rq.plan_only;
+                fa.B_vals = rq.B_vals;
+                fa.n_B = rq.n_B;
             }
             HIPCHK(launch_recurrence_band(st, fa, h->band, h->d_bandrecs, h->d_bandends, h->d_bandthr, h->max_finite,
                                           (flags & ALPA_DP_COUNT_WORK) ? FAST_MODE_COUNT : FAST_MODE_BATCH,

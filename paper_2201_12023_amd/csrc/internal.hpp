@@ -13,6 +13,10 @@ constexpr int32_t DEV_INF = (1 << 30) - 1;
 constexpr int64_t INF_I64 = INT64_MAX;
 constexpr int32_t INF_I32 = INT32_MAX;
 
+// What Fmin holds besides sums and DEV_INF (no plan): not there yet; not evaluated, as the early exit comes before; not
+// evaluated, as a lower candidate has no higher T.
+constexpr int32_t F_NOT_YET = -1, F_SKIPPED = DEV_INF + 1, F_LEFT_OUT = DEV_INF + 2;
+
 constexpr int WAVE = 64;
 constexpr int PRUNE_CHUNK = 64;          // candidates per published running-minimum slot
 
@@ -35,6 +39,7 @@ struct SolveState {
     int32_t n_knots;         // candidates evaluated so far
     int32_t n_todo;          // of the present round, those that the graphs do not settle
     int32_t todo_ticket;
+    int32_t thin[4];         // see recurrence_band_kernel
     int32_t n_slots;         // plans kept for the selection (kernels_sparse.hip)
     int32_t plan_done;       // the selection has written the plan
     int64_t clock[4];        // the device's clock before the candidates, behind them, before the selection and at the end
@@ -210,6 +215,7 @@ struct RefineQuery {
     int early_exit;          // the selection uses the early exit (in a sweep too, where `prune` is not set)
     const int32_t *thr;      // BAND_TOTALS numbers of launch_band_bounds, or null
     int32_t max_finite;
+    const struct GraphHead *heads;   // of the table's graphs, where fewer knots do if many candidates have none (or null)
 };
 // `bound`: the host's upper bound of the number of candidates
 // candidates from the table's distinct values (distinct null: they are there)
@@ -276,6 +282,13 @@ struct FastArgs {
     // batch modes, one-candidate form: 0, or the width DP of the lane groups
     // (a power of two, D <= DP <= 32): 64 / DP candidates per workgroup
     int grouped = 0;
+    // band kernel: the list that `list` is what is left of, ascending (null: none), and, where a candidate that a lower one beats for
+    // every B value need not be evaluated, those values (n_B of them, or null: p.B)
+    const int32_t *whole = nullptr, *n_whole_p = nullptr;
+    int32_t *rest = nullptr, *thin = nullptr;      // room for as many as `list` has; SolveState::thin
+    bool leave_out = false;
+    const int32_t *B_vals = nullptr;
+    int n_B = 0;
 };
 // narrowest lane group that holds a mesh of D devices
 inline int fast_lane_group_width(int D)
@@ -294,6 +307,7 @@ hipError_t launch_recurrence_fast_deep(hipStream_t st, const FastArgs &a, int mo
 int fast_kernel_blocks_per_cu_deep(int K, int nc);
 
 // a workgroup per candidate, t_intra in bands by row broadcast (kernels_band.hip)
+constexpr int BAND_THIN_FROM = 512;            // more left than that: knots first, from the whole list (up to two a compute unit run at once)
 struct BandShape {
     int nbuf;                // F buffers in LDS; 0: the problem does not fit
     int W;                   // windows of 64 device counts
@@ -353,6 +367,8 @@ hipError_t launch_front_thresholds(hipStream_t st, const int32_t *table, const B
                                    int32_t *plans, int32_t *windows, int32_t *graph_used, const int32_t *asked);
 
 // candidates by the stages that can be in their best plans (kernels_sparse.hip)
+struct GraphHead { int first, n_stages, n_cells, n_chunks, from, pad[3]; };      // see kernels_sparse.hip; n_stages < 0: no graph
+const GraphHead *graph_heads(int32_t *graph, int K);
 constexpr int SPARSE_PLANS = 4096;       // plans that are kept for the selection, K uint16 each
 struct SparseOut {
     int32_t *todo, *n_todo;  // candidates that are left to the recurrence

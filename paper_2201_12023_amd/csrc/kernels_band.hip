@@ -206,7 +206,138 @@ struct BandArgs {
     const int32_t *s_top_p, *s_bound;
     const int32_t *thr;      // launch_band_bounds
     int32_t max_finite;
+    const int32_t *whole, *n_whole_p;      // see FastArgs
+    int32_t *rest, *thin;
+    int leave_out;
+    const int32_t *B_vals;
+    int n_B;
 };
+
+// Lists of which much is left (of a list that graphs were to settle it may be all: rounds are planned for graphs then): knots first,
+// and then what lies between two that differ, in the same launch (us, later calls, with all of it evaluated and so: 48 layers on 32 x 8, 4096
+// candidates 20 160 and 2430; random latencies in order, 24 on 2 x 8, 4096: 287 and 211; 40 on 32 x 8: 1700 and 340).
+constexpr int BAND_THIN_KNOTS = 256;
+constexpr int BAND_BETWEEN = INT32_MAX - 1;            // (in the place of a candidate) all knots are there
+// the launch's: knots that are there, is the rest listed, how many that is, its tickets
+enum { THIN_DONE, THIN_READY, THIN_REST, THIN_TICKET };
+struct BandThin {
+    int n, even, behind, span;                         // entries (0: no such list); knots over the first `span` of them, and behind
+    int min_B;
+    int pending, rests;                                // a knot is being evaluated; the rest's turn
+    int count, leave_out;
+    const int32_t *whole, *cand;                       // (arguments would take scalar registers)
+    int32_t *Fmin, *rest, *thin, *ticket;
+};
+
+__device__ __forceinline__ int band_knot(const BandThin &t, int g)
+{
+    const bool front = g < t.even;
+    const int at = front ? g : g - t.even + 1, m = front ? t.even : t.behind + 1, n = front ? t.span : t.n - t.span + 1;
+    return (front ? 0 : t.span - 1) + (m <= 1 ? 0 : (int)((int64_t)at * (n - 1) / (m - 1)));
+}
+
+// One wave.  Knots lie evenly up to where F hardly changes (as those of refine_begin_kernel); most: at most so many
+__device__ __forceinline__ void band_thin_begin(const BandArgs &a, int n_left, int most, BandThin *sh)
+{
+    const int lane = threadIdx.x & (WAVE - 1), n = a.whole && n_left > BAND_THIN_FROM ? *a.n_whole_p : 0;
+    if (n == 0) {
+        if (lane == 0) sh->n = 0;
+        return;
+    }
+    const int32_t stages = a.s_bound[a.p.Smax + 2], flat = a.s_bound[a.p.Smax + 3];
+    int lo = 0, hi = n - 1;                            // the first entry not below `flat`
+    while (lo < hi) {
+        const int step = (hi - lo + WAVE - 1) / WAVE, x = lo + step * (lane + 1) - 1;
+        const uint64_t valid = __ballot(x < hi), above = __ballot(x < hi && a.cand[a.whole[min(x, hi)]] >= flat);
+        if (above) {
+            const int l = __ffsll((unsigned long long)above) - 1;
+            hi = lo + step * (l + 1) - 1;
+            lo += step * l;
+        } else {
+            lo += step * __popcll(valid);
+        }
+    }
+    int min_B = a.B_vals ? INT32_MAX : a.p.B;
+    for (int x = lane; a.B_vals && x < a.n_B; x += WAVE) min_B = min(min_B, a.B_vals[x]);
+    min_B = wave_min_i32(min_B);
+    most = min(most, BAND_THIN_KNOTS);
+    const int behind = min(n - 1 - lo, stages == -1 ? 1 : most / 4);
+    if (lane == 0) *sh = BandThin{n, min(most - behind, lo + 1), behind, lo + 1, min_B, 0, 0, 0, a.leave_out, a.whole, a.cand, a.Fmin, a.rest, a.thin, a.ticket};
+}
+
+// The complement of the next candidate to evaluate, BAND_BETWEEN for the workgroup whose knot is the last to be there, or INT32_MAX
+// (one thread).  All tickets are drawn, so the knots that a wait is for are with workgroups that run and do not wait: every wait ends.
+__device__ __forceinline__ int band_thin(BandThin *sh)
+{
+    const int knots = sh->even + sh->behind;
+    auto there = [&] { return __hip_atomic_fetch_add(&sh->thin[THIN_DONE], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == knots - 1; };
+    if (!sh->rests) {
+        if (sh->pending) {
+            sh->pending = 0;
+            if (there()) return BAND_BETWEEN;
+        }
+        for (int g; (g = atomicAdd(sh->ticket, 1)) < knots;) {
+            const int j = sh->whole[band_knot(*sh, g)];
+            if (sh->Fmin[j] == F_NOT_YET) {              // (else a graph has settled it)
+                sh->pending = 1;
+                return ~j;
+            }
+            if (there()) return BAND_BETWEEN;
+        }
+        while (__hip_atomic_load(&sh->thin[THIN_READY], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == 0) __builtin_amdgcn_s_sleep(8);
+        sh->rests = 1;
+    }
+    const int x = atomicAdd(&sh->thin[THIN_TICKET], 1);
+    return x < __hip_atomic_load(&sh->thin[THIN_REST], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+               ? ~__hip_atomic_load(&sh->rest[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : INT32_MAX;
+}
+
+// All knots are there: entries between two equal ones get their value, those that cannot get below T at the knot in front for any B (where
+// only plans count) and those behind the end of Alg. 1's loop none, and the rest is listed.  knot: room for 2 BAND_THIN_KNOTS.
+__device__ __forceinline__ void band_between(BandThin *sh, int32_t *knot)
+{
+    constexpr int nt = BAND_WAVES * WAVE;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                      // (what is computed of it would be kept in registers through the candidates)
+    const int lane = tid & (WAVE - 1), n = sh->n, knots = sh->even + sh->behind;
+    int32_t *const F = knot + knots;
+    for (int g = tid; g < knots; g += nt) {
+        const int x = band_knot(*sh, g);
+        knot[g] = x;
+        F[g] = __hip_atomic_load(&sh->Fmin[sh->whole[x]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    for (int x0 = 0; x0 < n; x0 += nt) {
+        const int x = x0 + tid, j = sh->whole[min(x, n - 1)];
+        bool evaluate = false;
+        if (x < n - 1 && sh->Fmin[j] == F_NOT_YET) {
+            int lo = 0, hi = knots - 1;                // knot[lo] <= x < knot[hi]
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (knot[mid] <= x) lo = mid; else hi = mid;
+            }
+            const int32_t fl = F[lo], fr = F[hi];
+            int32_t own = F_NOT_YET;
+            if (fl == F_SKIPPED || fl == fr) own = fl;
+            else if (sh->leave_out && fl < DEV_INF && fr < DEV_INF &&
+                     (int64_t)fr - fl + (sh->min_B - 1) * ((int64_t)sh->cand[j] - sh->cand[sh->whole[knot[lo]]]) >= 0) own = F_LEFT_OUT;
+            evaluate = own == F_NOT_YET && knot[lo] != x;
+            if (own != F_NOT_YET) sh->Fmin[j] = own;
+        }
+        const uint64_t lanes = __ballot(evaluate);
+        int at = 0;
+        if (lanes && lane == 0) at = atomicAdd(&sh->count, __popcll(lanes));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(lanes & ((1ull << lane) - 1));
+        if (evaluate) __hip_atomic_store(&sh->rest[at], j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __syncthreads();
+    if (tid == 0) {
+        __hip_atomic_store(&sh->thin[THIN_REST], sh->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&sh->thin[THIN_READY], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();                                   // (F's place is the next candidate's)
+}
 
 typedef int32_t band_v4 __attribute__((ext_vector_type(4)));
 
@@ -253,10 +384,30 @@ __device__ __forceinline__ void band_recurrence(const BandArgs &a)
     const int32_t thr_lo = band_threshold(a.max_finite, min(lane, BAND_THRESHOLDS - 1));
     const int32_t thr_hi = band_threshold(a.max_finite, min(lane + WAVE, BAND_THRESHOLDS - 1));
 
-    // The first candidate goes by the workgroup's number, the others are drawn.
-    for (int tk = TABLE ? 0 : blockIdx.x; tk < n; tk = TABLE ? 1 : (int)gridDim.x + draw_ticket(a.ticket, tid, sh_tk)) {
+    // The first candidate goes by the workgroup's number, the others are drawn; of a list of which much is left all are, and given by
+    // their complement (what that takes is in LDS: there is no register to spare)
+    constexpr bool THINS = !DUMP && !TABLE;
+    __shared__ BandThin sh_thin;
+    if (THINS) {
+        if (wid == 0) band_thin_begin(a, n, NO_CELL / 2, &sh_thin);
+        __syncthreads();
+    }
+    auto next = [&](bool first) {
+        while (THINS && __builtin_amdgcn_readfirstlane(sh_thin.n) != 0) {
+            int t = tid;
+            asm volatile("" : "+v"(t));                // (see draw_ticket)
+            if (t == 0) *sh_tk = band_thin(&sh_thin);
+            __syncthreads();
+            const int x = __builtin_amdgcn_readfirstlane(*sh_tk);
+            __syncthreads();
+            if (x != BAND_BETWEEN) return x;
+            band_between(&sh_thin, lds);
+        }
+        return TABLE ? (first ? 0 : 1) : first ? (int)blockIdx.x : (int)gridDim.x + draw_ticket(a.ticket, tid, sh_tk);
+    };
+    for (int tk, turn = 0; (tk = next(turn == 0)) < n; ++turn) {
         const int pos = a.descending ? n - 1 - tk : tk;
-        const int j = TABLE ? 0 : DUMP ? pos : __builtin_amdgcn_readfirstlane(a.list[pos]);
+        const int j = TABLE ? 0 : DUMP ? pos : tk < 0 ? ~tk : __builtin_amdgcn_readfirstlane(a.list[pos]);
         const int32_t c_given = TABLE ? DEV_INF : __builtin_amdgcn_readfirstlane(a.cand[j]);
         const int32_t c = min(c_given, DEV_INF - 1);   // the sentinel entries pass no candidate
         if (!DUMP && !TABLE && a.prune) {
@@ -265,7 +416,7 @@ __device__ __forceinline__ void band_recurrence(const BandArgs &a)
             const int skip = __builtin_amdgcn_readfirstlane(sh_skip[0]);
             __syncthreads();
             if (skip) {
-                a.Fmin[j] = DEV_INF;                   // all threads, same value
+                a.Fmin[j] = F_SKIPPED;                 // all threads, same value
                 a.Sbest[j] = -1;
                 continue;
             }
@@ -386,8 +537,14 @@ __device__ __forceinline__ void band_recurrence(const BandArgs &a)
             int32_t m = DEV_INF;
             auto cell = [&](int e, int32_t f) { m = min(m, lds[F + e + e / (8 * RS) * 16] + f); };
             if (NF) {
+                // (eight registers: for layers of more than four cells a thread; the first four are at constant distances, which takes no
+                // registers for where they are)
+                static_assert(nt % (8 * RS) == 0 || 8 * RS % nt == 0);
 #pragma unroll
-                for (int x = 0; x < NF; ++x) cell(min(tid + x * nt, K * RS - 1), front[x]);
+                for (int x = 0; x < NF; ++x) {
+                    if (NF == 8 && x < 4) m = min(m, lds[F + tid + (nt > 8 * RS ? tid / (8 * RS) * 16 : 0) + x * nt + x * nt / (8 * RS) * 16] + front[x]);
+                    else cell(min(tid + x * nt, K * RS - 1), front[x]);
+                }
             } else {
                 for (int x = 0; x < K * RS; x += 4 * nt) {
                     int32_t f[4];
@@ -729,7 +886,8 @@ hipError_t launch_recurrence_band(hipStream_t st, const FastArgs &f, const BandS
                                   const int32_t *ends, const int32_t *thr, int32_t max_finite, int mode, int grid)
 {
     BandArgs a{f.p, b, f.n_lo, f.n_hi, recs, ends, f.sizes, f.cand, f.list, f.n_list_p, f.ticket, f.wave_relax,
-               f.chunk_min, f.prune, f.descending, f.Fmin, f.Sbest, f.dummy_idx, f.F_all, f.s_top_p, f.s_bound, thr, max_finite};
+               f.chunk_min, f.prune, f.descending, f.Fmin, f.Sbest, f.dummy_idx, f.F_all, f.s_top_p, f.s_bound, thr, max_finite,
+               f.whole, f.n_whole_p, f.rest, f.thin, f.leave_out ? 1 : 0, f.B_vals, f.n_B};
     switch (band_row_ints(f.p.D)) {
     case 64: return launch_band_mode<64>(st, a, mode, grid);
     case 128: return launch_band_mode<128>(st, a, mode, grid);

@@ -213,6 +213,22 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
         const int mid = (lo + hi) >> 1;
         if (cand[mid] >= flat) hi = mid; else lo = mid + 1;
     }
+    if (rq.heads && end - j0 > all) {
+        // Candidates without a graph cost a workgroup each: where they are many, as many knots as without graphs
+        __shared__ int sh_bare;
+        __syncthreads();
+        if (threadIdx.x == 0) sh_bare = 0;
+        __syncthreads();
+        for (int t = threadIdx.x; t < BAND_THRESHOLDS; t += RF_THREADS)
+            if (rq.heads[t].n_stages < 0) {
+                const int from = t + 1 < BAND_THRESHOLDS ? first_at_least(cand, n, band_threshold(rq.max_finite, t + 1) + 1) : 0;
+                const int to = t == 0 ? n : first_at_least(cand, n, band_threshold(rq.max_finite, t) + 1);
+                const int bare = min(to, end) - max(from, j0);
+                if (bare > 0) atomicAdd(&sh_bare, bare);
+            }
+        __syncthreads();
+        if (sh_bare > 512) first_round = min(first_round, 256);
+    }
     const int span = lo + 1 - j0, rest = min(end - 1 - lo, stages == -1 ? 1 : first_round / 4);
     const bool whole = end - j0 <= all;
     const int m = whole ? end - j0 : min(first_round, span + rest);
@@ -232,6 +248,7 @@ __global__ __launch_bounds__(RF_THREADS) void refine_begin_kernel(RefineQuery rq
         state->clock[1] = wall_clock64();
         state->n_todo = 0;
         state->todo_ticket = 0;
+        for (int x = 0; x < 4; ++x) state->thin[x] = 0;
     }
 }
 
@@ -398,6 +415,7 @@ __global__ __launch_bounds__(RF_THREADS) void refine_kernel(
         state->ticket = 0;
         state->n_todo = 0;
         state->todo_ticket = 0;
+        for (int x = 0; x < 4; ++x) state->thin[x] = 0;
     }
 }
 

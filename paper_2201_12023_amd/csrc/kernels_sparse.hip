@@ -38,8 +38,7 @@ static int graph_room(int K) { return std::min(std::max(12 * K * K, 8192), 3 << 
 // graphs[j] of the candidates up to threshold j; stages by cell (falling first layer, rising devices), then rising last layer and
 // shape, in chunks that begin with one layer.  A stage: least latency; byte of its cell's label | byte of that of the cell behind
 // << 16; what it adds to the lower half of a label; first layer << 22 | last layer << 14 | shape << 8 | run
-// from: candidates below that have no plan at all; n_stages < 0: no graph
-struct GraphHead { int first, n_stages, n_cells, n_chunks, from, pad[3]; };
+// GraphHead::from: candidates below that have no plan at all
 struct GraphTable {
     GraphHead *heads;
     int32_t *chunks;         // [BAND_THRESHOLDS][GRAPH_CHUNKS] where each starts, and their end
@@ -66,6 +65,7 @@ static GraphTable graph_table(int32_t *base, int K)
     return g;
 }
 int32_t *graph_used(int32_t *graph, int K) { return graph_table(graph, K).used; }
+const GraphHead *graph_heads(int32_t *graph, int K) { return graph_table(graph, K).heads; }
 
 // Exclusive prefix sum over the block, and the total.
 __device__ __forceinline__ int graph_scan(int v, int *sh, int &total)
@@ -522,7 +522,7 @@ __global__ __launch_bounds__(SPARSE_WAVES * WAVE) void sparse_eval_kernel(Sparse
             }
         }
         if (lane == 0) {
-            a.Fmin[j] = settled ? F : DEV_INF;
+            a.Fmin[j] = settled ? F : F_NOT_YET;
             a.Sbest[j] = settled ? s : 0;
             a.o.slot[j] = settled ? slot : -1;
             if (!settled) a.o.todo[atomicAdd(a.o.n_todo, 1)] = j;

@@ -84,3 +84,43 @@ def test_more_candidates_than_kept_plans(n):
             _plan_is(plans[b], ref)
     finally:
         B.alpa_dp_destroy(h)
+
+
+# ordered tables on which hardly an interval has a graph: the recurrence does not run for more of their candidates than it does for
+# the same table with one entry that falls, which no graphs are made for
+@pytest.mark.parametrize("size", [(24, 2, 8), (40, 16, 8), (30, 32, 8)], ids=lambda s: f"K{s[0]}-{s[1]}x{s[2]}")
+@pytest.mark.parametrize("n", [513, 4096, 9000])
+def test_candidates_without_graphs(size, n):
+    K, N, M = size
+    shapes = W.submesh_shapes(N, M)
+    table = np.sort(W.random_problem(1, K, N, M, inf_frac=0.2, value_hi=100_000).table, axis=0)
+    fell = table.copy()
+    at = np.argwhere(fell[1] != oracle.INF32)[-1]                            # (a long stage with one behind it)
+    fell[(1, *at)] = fell[(0, *at)] - 1
+    work = []
+    for t in (table, fell):
+        h = B.alpa_dp_create(t, K, N, M, 7, shapes)
+        try:
+            B.alpa_dp_solve(h, None, n)                                      # (the table's bounds, and better ones with the second)
+            B.alpa_dp_solve(h, None, n)
+            T, plan = B.alpa_dp_solve(h, None, n, B.ALPA_DP_COUNT_WORK)
+            work.append(B.alpa_dp_last_counters(h)["wave_relaxations"])
+            T_ref, ref = B.alpa_dp_solve(h, None, n, B.ALPA_DP_GENERIC)
+            assert np.array_equal(T, T_ref)
+            _plan_is(plan, ref)
+            _plan_is(B.alpa_dp_solve(h, None, n, want_T=False)[1], ref)
+            T_ref, ref = B.alpa_dp_solve(h, None, n, B.ALPA_DP_GENERIC | B.ALPA_DP_PRUNE)
+            T, plan = B.alpa_dp_solve(h, None, n, B.ALPA_DP_PRUNE)
+            assert np.array_equal(T, T_ref)
+            _plan_is(plan, ref)
+            _plan_is(B.alpa_dp_solve(h, None, n, B.ALPA_DP_PRUNE, want_T=False)[1], ref)
+            for flags in (0, B.ALPA_DP_PRUNE):
+                for plan, Bv in zip(B.alpa_dp_solve_sweep(h, None, [1, 7, 300], n, flags), (1, 7, 300)):
+                    B.alpa_dp_set_B(h, Bv)
+                    _plan_is(plan, B.alpa_dp_solve(h, None, n, flags | B.ALPA_DP_GENERIC)[1])
+            B.alpa_dp_set_B(h, 7)
+        finally:
+            B.alpa_dp_destroy(h)
+    # (knots lie evenly over all candidates, settled or not)
+    print(size, n, work)
+    assert work[0] <= 1.5 * work[1] + 100, work
