@@ -443,7 +443,7 @@ static int create_on_device(alpa_dp *h, const std::vector<int32_t> &sizes, FillT
             take(h->d_least, front_least_ints(K, SB));
             take(h->d_front, front_table_ints(K, SB));
             if (h->sparse_ok) {
-                take(h->d_graph, graph_table_ints(K));
+                take(h->d_graph, graph_table_ints(K, D));
                 take(h->d_kept, (size_t)SPARSE_PLANS * K);
                 take(h->d_kept_from, SPARSE_PLANS);
             }
@@ -790,8 +790,8 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     const bool fast = h->fast_ok && !(flags & ALPA_DP_GENERIC);
     const bool band = h->band_ok && !(flags & ALPA_DP_GENERIC);
     const bool sparse = band && h->sparse_ok && h->ordered;
-    const SparseOut sparse_out{h->d_todo, &h->d_state->n_todo, h->d_slot, &h->d_state->n_slots, h->d_kept, h->d_kept_from};
-    const KeptPlans kept{sparse ? h->d_slot : nullptr, h->d_kept, h->d_kept_from, sparse ? graph_stages(h->d_graph, p.K) : nullptr};
+    const SparseOut sparse_out{h->d_todo, &h->d_state->n_todo, h->d_slot, &h->d_state->n_slots, h->d_kept, h->d_kept_from, h->d_state->routes};
+    const KeptPlans kept{sparse ? h->d_slot : nullptr, h->d_kept, h->d_kept_from, sparse ? graph_stages(h->d_graph, p.K, p.D) : nullptr};
     Problem p_band = p;
     p_band.S = h->band_shapes.S;
     const bool with_bounds = wants_bounds(h, bound, recorded);
@@ -801,7 +801,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
     const RefineQuery rq{n_B > 0 ? h->d_sw_B : nullptr, p.B, std::max(n_B, 1), prune,
                          (n_B > 0 || !d_out_T) ? 1 : 0, bounds, p.Smax, prune_sel,
                          h->band_ok ? bounds + table_bounds_ints(p) : nullptr, h->max_finite,
-                         sparse && rb.rounds > 1 ? graph_heads(h->d_graph, p.K) : nullptr};
+                         sparse && rb.rounds > 1 ? graph_heads(h->d_graph, p.K, p.D) : nullptr};
     const bool bitmap = !have_list && distinct_by_bitmap(h);
     HIPCHK(launch_init_state(st, h->d_state, h->d_chunkmin, bound / PRUNE_CHUNK + 1, (uint32_t *)h->pb.keys[1],
                              bitmap ? h->max_finite / 32 + 1 : 0));
@@ -1136,6 +1136,21 @@ extern "C" int alpa_dp_last_timing(alpa_dp_t *h, float *ms_candidates, float *ms
     if (ms_candidates) *ms_candidates = ms(0);
     if (ms_recurrence) *ms_recurrence = ms(1);
     if (ms_epilogue) *ms_epilogue = ms(2);
+    return ALPA_DP_OK;
+}
+
+// For the tests that name a route (not in the public header): the graph of each interval of thresholds, eight int32 each as GraphHead has
+// them, and how the candidates of the last solve with ALPA_DP_COUNT_WORK were settled (SparseRoute).  EINVAL where there are no graphs.
+extern "C" int alpa_dp_routes_(alpa_dp_t *h, int32_t *heads, int32_t *routes)
+{
+    static_assert(sizeof(GraphHead) == 32, "eight int32");
+    if (!h || !heads || !routes) return fail(ALPA_DP_EINVAL, "null argument");
+    if (!h->sparse_ok || !h->have_bounds) return fail(ALPA_DP_EINVAL, "no graphs on this handle");
+    SolveState s;
+    HIPCHK(hipMemcpyAsync(heads, graph_heads(h->d_graph, h->p.K, h->p.D), BAND_THRESHOLDS * sizeof(GraphHead), hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(hipMemcpyAsync(&s, h->d_state, sizeof(s), hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
+    std::copy(s.routes, s.routes + 5, routes);
     return ALPA_DP_OK;
 }
 

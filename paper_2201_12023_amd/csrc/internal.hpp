@@ -42,6 +42,7 @@ struct SolveState {
     int32_t thin[4];         // see recurrence_band_kernel
     int32_t n_slots;         // plans kept for the selection (kernels_sparse.hip)
     int32_t plan_done;       // the selection has written the plan
+    int32_t routes[5];       // instrumented runs: see SparseRoute
     int64_t clock[4];        // the device's clock before the candidates, behind them, before the selection and at the end
 };
 
@@ -367,18 +368,21 @@ hipError_t launch_front_thresholds(hipStream_t st, const int32_t *table, const B
                                    int32_t *plans, int32_t *windows, int32_t *graph_used, const int32_t *asked);
 
 // candidates by the stages that can be in their best plans (kernels_sparse.hip)
-struct GraphHead { int first, n_stages, n_cells, n_chunks, from, pad[3]; };      // see kernels_sparse.hip; n_stages < 0: no graph
-const GraphHead *graph_heads(int32_t *graph, int K);
+struct GraphHead { int first, n_stages, n_cells, n_chunks, from, twice, pad[2]; };      // see kernels_sparse.hip; n_stages < 0: no graph
+const GraphHead *graph_heads(int32_t *graph, int K, int D);
 constexpr int SPARSE_PLANS = 4096;       // plans that are kept for the selection, K uint16 each
+// how sparse_eval_kernel has settled a candidate
+enum SparseRoute { ROUTE_BELOW, ROUTE_PASS, ROUTE_SECOND_PASS, ROUTE_LAYERS, ROUTE_LEFT };
 struct SparseOut {
     int32_t *todo, *n_todo;  // candidates that are left to the recurrence
     int32_t *slot, *n_slots; // each candidate's plan (-1: not kept)
     uint16_t *plans;         // its stages in the graph that it is from
     int32_t *plan_from;      // where that begins
+    int32_t *routes;
 };
-size_t graph_table_ints(int K);
-int32_t *graph_used(int32_t *graph, int K);
-const int4 *graph_stages(int32_t *graph, int K);
+size_t graph_table_ints(int K, int D);
+int32_t *graph_used(int32_t *graph, int K, int D);
+const int4 *graph_stages(int32_t *graph, int K, int D);
 hipError_t launch_sparse_graph(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
                                const int32_t *work, const int32_t *front, const int32_t *fronts, const int32_t *backs,
                                const int32_t *totals, int32_t *plans, const int32_t *falls, int32_t *graph, int32_t *bounds, int32_t *there, bool once);

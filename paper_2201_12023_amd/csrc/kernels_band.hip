@@ -287,9 +287,9 @@ __device__ __forceinline__ int band_thin(BandThin *sh)
         while (__hip_atomic_load(&sh->thin[THIN_READY], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == 0) __builtin_amdgcn_s_sleep(8);
         sh->rests = 1;
     }
-    const int x = atomicAdd(&sh->thin[THIN_TICKET], 1);
-    return x < __hip_atomic_load(&sh->thin[THIN_REST], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-               ? ~__hip_atomic_load(&sh->rest[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : INT32_MAX;
+    const int x = atomicAdd(&sh->thin[THIN_TICKET], 1), n = __hip_atomic_load(&sh->thin[THIN_REST], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (x >= n) return INT32_MAX;
+    return ~__hip_atomic_load(&sh->rest[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // All knots are there: entries between two equal ones get their value, those that cannot get below T at the knot in front for any B (where
@@ -823,7 +823,7 @@ hipError_t launch_band_bounds(hipStream_t st, const int32_t *table, const BandSh
     const int RS = band_row_ints(p.D);
     int32_t *const thr = w.thr;
     hipError_t e = launch_front_thresholds(st, table, b, p, max_finite, w.least, w.front, thr, w.backs, totals, plans,
-                                           thr + (size_t)BAND_THRESHOLDS * p.K * RS, w.graph ? graph_used(w.graph, p.K) : nullptr, asked);
+                                           thr + (size_t)BAND_THRESHOLDS * p.K * RS, w.graph ? graph_used(w.graph, p.K, p.D) : nullptr, asked);
     if (e == hipSuccess && w.graph)
         return launch_sparse_graph(st, table, b, p, max_finite, w.least, w.front, thr, w.backs, totals, plans, totals + BAND_FALLS, w.graph,
                                    bounds, there, once);

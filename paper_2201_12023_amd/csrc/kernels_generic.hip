@@ -594,6 +594,7 @@ __global__ void init_state_kernel(SolveState *state, int64_t *chunk_min, int n_c
         state->plan_ticket = 0;
         state->n_slots = 0;
         state->plan_done = 0;
+        for (int x = 0; x < 5; ++x) state->routes[x] = 0;
     }
     for (int x = t; x < n_chunks; x += gridDim.x * blockDim.x) chunk_min[x] = INF_I64;
     for (int x = t; x < words; x += gridDim.x * blockDim.x) clear[x] = 0;

@@ -32,13 +32,16 @@ constexpr int GRAPH_SEARCH = 4096;             // stages of a graph in which the
 constexpr int GRAPH_LAYERS = 512;              // stages of a graph on which Eq. 3 is run
 constexpr int GRAPH_LDS = 128 * 1024;          // of the workgroup that makes a graph, if its list of stages takes so much
 
-// room for the stages of all graphs (64 layers: 49 000; what does not find room goes to the recurrence)
-static int graph_room(int K) { return std::min(std::max(12 * K * K, 8192), 3 << 16); }
+// Room for the stages of all graphs (what does not find room goes to the recurrence; which graphs find it where it is short depends on
+// the order in which workgroups get there).  Graphs lie on up to K D cells: models of 24 to 200 layers on 2 x 8 to 32 x 8 take 56 to 81 000
+// stages, 48 layers on 32 x 8 74 000 (with room for 28 000, 16 candidates 329 us, now 125), 100 on 12 x 8 81 000.  More room at few layers is only
+// for latencies without structure, where the recurrence is the faster way (24 layers on 2 x 8, a list of 4096 256 us, 285 with all graphs).
+static int graph_room(int K, int D) { return std::min(std::max({12 * K * K, 8 * K * D, 8192}), 3 << 16); }
 
 // graphs[j] of the candidates up to threshold j; stages by cell (falling first layer, rising devices), then rising last layer and
 // shape, in chunks that begin with one layer.  A stage: least latency; byte of its cell's label | byte of that of the cell behind
 // << 16; what it adds to the lower half of a label; first layer << 22 | last layer << 14 | shape << 8 | run
-// GraphHead::from: candidates below that have no plan at all
+// GraphHead::from: candidates below that have no plan at all; twice: more stages than the list held, so its cells were looked at again
 struct GraphTable {
     GraphHead *heads;
     int32_t *chunks;         // [BAND_THRESHOLDS][GRAPH_CHUNKS] where each starts, and their end
@@ -48,15 +51,15 @@ struct GraphTable {
     int room;
 };
 
-size_t graph_table_ints(int K)
+size_t graph_table_ints(int K, int D)
 {
-    return (size_t)BAND_THRESHOLDS * (8 + GRAPH_CHUNKS + GRAPH_CELLS) + 4 * (size_t)(graph_room(K) + WAVE) + 4;
+    return (size_t)BAND_THRESHOLDS * (8 + GRAPH_CHUNKS + GRAPH_CELLS) + 4 * (size_t)(graph_room(K, D) + WAVE) + 4;
 }
 
-static GraphTable graph_table(int32_t *base, int K)
+static GraphTable graph_table(int32_t *base, int K, int D)
 {
     GraphTable g;
-    g.room = graph_room(K);
+    g.room = graph_room(K, D);
     g.heads = (GraphHead *)base;
     g.stages = (int4 *)(base + 8 * BAND_THRESHOLDS);
     g.chunks = (int32_t *)(g.stages + g.room + WAVE);      // (a wave reads up to 64 stages behind its own)
@@ -64,8 +67,8 @@ static GraphTable graph_table(int32_t *base, int K)
     g.used = g.cells + BAND_THRESHOLDS * GRAPH_CELLS;
     return g;
 }
-int32_t *graph_used(int32_t *graph, int K) { return graph_table(graph, K).used; }
-const GraphHead *graph_heads(int32_t *graph, int K) { return graph_table(graph, K).heads; }
+int32_t *graph_used(int32_t *graph, int K, int D) { return graph_table(graph, K, D).used; }
+const GraphHead *graph_heads(int32_t *graph, int K, int D) { return graph_table(graph, K, D).heads; }
 
 // Exclusive prefix sum over the block, and the total.
 __device__ __forceinline__ int graph_scan(int v, int *sh, int &total)
@@ -117,7 +120,7 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
     const int32_t single = __builtin_amdgcn_readfirstlane(front_single(table, bs, K, D)), c = min(band_threshold(max_finite, j), single);
     const int32_t low = j + 1 < BAND_THRESHOLDS ? band_threshold(max_finite, j + 1) : 0, feasible = __builtin_amdgcn_readfirstlane(totals[BAND_THRESHOLDS]);
     auto none = [&]() {
-        if (tid == 0) g.heads[j] = GraphHead{0, -1, 0, 0, 0, {0, 0, 0}};
+        if (tid == 0) g.heads[j] = GraphHead{0, -1};
     };
     if (*falls || totals[j] >= DEV_INF) return none();
     if (tid == 0) {
@@ -261,10 +264,16 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
         if (sh_plan[1] > feasible || sh_plan[0] >= U) return none();
         U = __builtin_amdgcn_readfirstlane(sh_plan[0]);
     }
-    if (tid == 0) sh_first = atomicAdd(g.used, n_stages);
+    if (tid == 0) {                                // (what does not fit gives it back)
+        sh_first = atomicAdd(g.used, n_stages);
+        if (sh_first + n_stages > g.room) {
+            atomicSub(g.used, n_stages);
+            sh_first = -1;
+        }
+    }
     __syncthreads();
     const int first = sh_first;
-    if (first + n_stages > g.room) return none();
+    if (first < 0) return none();
     auto write = [&](int cell, int local, int y) {
         const int x0 = sh_cell[cell], k = x0 / RS, d = x0 % RS + 1, l = (int)(((int64_t)y * inv) >> 20), i = k + l, q = y - l * S;
         const uint32_t at = (uint32_t)((k * K + i) * SP + q);
@@ -351,7 +360,7 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
         }
         from_c = lo;
     }
-    if (tid == 0) g.heads[j] = GraphHead{first, n_stages, n_cells, n_chunks, from_c, {0, 0, 0}};
+    if (tid == 0) g.heads[j] = GraphHead{first, n_stages, n_cells, n_chunks, from_c, n_stages > list_room};
 }
 
 // A workgroup for each interval; see band_bounds.
@@ -456,9 +465,10 @@ __global__ __launch_bounds__(SPARSE_WAVES * WAVE) void sparse_eval_kernel(Sparse
         };
         bool settled = false;
         int32_t F = DEV_INF;
-        int s = 0, slot = -1;
+        int s = 0, slot = -1, route = ROUTE_PASS;
         if (n_stages >= 0 && c < __builtin_amdgcn_readfirstlane(h.from)) {
             settled = true;
+            route = ROUTE_BELOW;
         } else if (n_stages >= 0) {
             pass(true);
             const unsigned long long root = label(n_cells - 1);
@@ -487,6 +497,7 @@ __global__ __launch_bounds__(SPARSE_WAVES * WAVE) void sparse_eval_kernel(Sparse
             if (__ballot(left_out) != 0) {
                 pass(false);
                 settled = label(n_cells - 1) >> 32 == root >> 32;
+                route = ROUTE_SECOND_PASS;
             }
             if (!settled && n_stages <= GRAPH_LAYERS) {
                 // Eq. 3 on the graph: layers of sums, by the number of stages
@@ -519,8 +530,10 @@ __global__ __launch_bounds__(SPARSE_WAVES * WAVE) void sparse_eval_kernel(Sparse
                 }
                 slot = -1;
                 settled = true;
+                route = ROUTE_LAYERS;
             }
         }
+        if (COUNT && lane == 0) atomicAdd(&a.o.routes[settled ? route : ROUTE_LEFT], 1);
         if (lane == 0) {
             a.Fmin[j] = settled ? F : F_NOT_YET;
             a.Sbest[j] = settled ? s : 0;
@@ -534,7 +547,7 @@ __global__ __launch_bounds__(SPARSE_WAVES * WAVE) void sparse_eval_kernel(Sparse
 }
 
 // the stages of the graphs, for the selection's plans
-const int4 *graph_stages(int32_t *graph, int K) { return graph_table(graph, K).stages; }
+const int4 *graph_stages(int32_t *graph, int K, int D) { return graph_table(graph, K, D).stages; }
 
 hipError_t launch_sparse_graph(hipStream_t st, const int32_t *table, const BandShapes &b, const Problem &p, int32_t max_finite,
                                const int32_t *work, const int32_t *front, const int32_t *fronts, const int32_t *backs,
@@ -550,14 +563,14 @@ hipError_t launch_sparse_graph(hipStream_t st, const int32_t *table, const BandS
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kernel, dim3(BAND_THRESHOLDS), dim3(GRAPH_THREADS), lds, st, front_table(work, front, K, b.S, b.sizes, false),
-                       table, b, p, max_finite, fronts, backs, totals, plans, falls, graph_table(graph, K), list_room, bounds, once ? 1 : 0, there);
+                       table, b, p, max_finite, fronts, backs, totals, plans, falls, graph_table(graph, K, D), list_room, bounds, once ? 1 : 0, there);
     return hipGetLastError();
 }
 
 hipError_t launch_sparse_eval(hipStream_t st, const FastArgs &f, const int32_t *table, int32_t *graph, int32_t max_finite, const SparseOut &o, bool count,
                               int most, int n_cu)
 {
-    SparseArgs a{f.p, table, graph_table(graph, f.p.K), max_finite, f.cand, f.list, f.n_list_p, f.Fmin, f.Sbest, o, f.chunk_min,
+    SparseArgs a{f.p, table, graph_table(graph, f.p.K, f.p.D), max_finite, f.cand, f.list, f.n_list_p, f.Fmin, f.Sbest, o, f.chunk_min,
                  f.prune, f.descending, f.wave_relax};
     const auto kernel = count ? sparse_eval_kernel<true> : sparse_eval_kernel<false>;
     const int grid = std::max(1, std::min((most + SPARSE_WAVES - 1) / SPARSE_WAVES, 3 * n_cu));     // (three fit a compute unit's LDS)

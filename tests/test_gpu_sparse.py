@@ -2,6 +2,8 @@
 number of stages behind), against the CPU oracle or, where that takes too long, the general kernel: at the edges of eight layers and
 of the devices' size classes, with stages that are least only at first, memory that ends early, many ties, more candidates than kept
 plans, intervals whose stages are too many, and tables in which one entry falls.  Whole numbers: no tolerance."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -15,6 +17,17 @@ KEYS = ("T_star", "t_max", "num_stages", "n_evaluated", "first_layer", "shape_id
 # layers, mesh; whether the oracle is quick enough
 SIZES = [(1, 2, 1, True), (8, 2, 8, True), (9, 9, 1, True), (17, 4, 8, True), (16, 1, 64, True), (24, 33, 1, True), (20, 17, 8, False),
          (33, 2, 64, False), (31, 2, 128, False), (48, 1, 128, False)]
+
+
+BELOW, PASS, SECOND_PASS, LAYERS, LEFT = range(5)      # how a candidate was settled
+
+
+def _routes(h):
+    """The graphs of the intervals, (first, stages, cells, chunks, from, twice, ..) each, stages < 0: none; and how many candidates of the
+    last solve with the counting flag were settled in each way."""
+    heads, routes = np.zeros((120, 8), np.int32), np.zeros(5, np.int32)
+    B._check(B.load().alpa_dp_routes_(h, ctypes.c_void_p(heads.ctypes.data), ctypes.c_void_p(routes.ctypes.data)))
+    return heads, routes
 
 
 def _plan_is(plan, ref):
@@ -124,3 +137,62 @@ def test_candidates_without_graphs(size, n):
     # (knots lie evenly over all candidates, settled or not)
     print(size, n, work)
     assert work[0] <= 1.5 * work[1] + 100, work
+
+
+# graphs of 12 900 stages in all, few layers on many devices: they find room, and the same ones each time
+def test_graphs_find_room():
+    K, N, M = 20, 24, 8
+    w = W.many_stage_problem(3, K, N, M)
+    sizes = []
+    for _ in range(3):
+        h = B.alpa_dp_create(w.table, K, N, M, 64, w.shapes)
+        try:
+            B.alpa_dp_solve(h, None, 1000, B.ALPA_DP_COUNT_WORK)
+            heads, routes = _routes(h)
+        finally:
+            B.alpa_dp_destroy(h)
+        assert routes[LEFT] == 0
+        sizes.append(heads[:, 1])
+    assert sizes[0][sizes[0] > 0].sum() > max(12 * K * K, 8192)
+    assert np.array_equal(sizes[0], sizes[1]) and np.array_equal(sizes[0], sizes[2])
+
+
+# each way of settling candidates is taken by tables made for it, with the general kernel's results
+WAYS = {BELOW: "deep", PASS: "deep", SECOND_PASS: "deep", LAYERS: "ordered", LEFT: "deep"}
+
+
+@pytest.mark.parametrize("way", WAYS, ids=["below", "pass", "second-pass", "layers", "left"])
+def test_ways_of_settling(way):
+    if WAYS[way] == "deep":
+        K, N, M = (32, 16, 8)
+        table = W.deep_model_problem(7, K, N, M).table
+    else:
+        K, N, M = (20, 8, 8)
+        table = np.sort(W.random_problem(1, K, N, M, inf_frac=0.2, value_hi=100_000).table, axis=0)
+    h = B.alpa_dp_create(table, K, N, M, 40, W.submesh_shapes(N, M))
+    try:
+        T, plan = B.alpa_dp_solve(h, None, 2000, B.ALPA_DP_COUNT_WORK)
+        heads, routes = _routes(h)
+        assert routes[way] > 0 and routes.sum() <= 2000
+        assert way != BELOW or (heads[:, 4] > 0).any()
+        T_ref, ref = B.alpa_dp_solve(h, None, 2000, B.ALPA_DP_GENERIC)
+        assert np.array_equal(T, T_ref)
+        _plan_is(plan, ref)
+    finally:
+        B.alpa_dp_destroy(h)
+
+
+# graphs of more stages than the list in LDS holds: the cells are looked at again to write them
+def test_graph_larger_than_the_list():
+    K, N, M = 100, 16, 8
+    w = W.deep_model_problem(3, K, N, M)
+    h = B.alpa_dp_create(w.table, K, N, M, 40, w.shapes)
+    try:
+        T, plan = B.alpa_dp_solve(h, None, 300)
+        heads, _ = _routes(h)
+        assert heads[:, 5].any()
+        T_ref, ref = B.alpa_dp_solve(h, None, 300, B.ALPA_DP_GENERIC)
+        assert np.array_equal(T, T_ref)
+        _plan_is(plan, ref)
+    finally:
+        B.alpa_dp_destroy(h)
