@@ -224,7 +224,7 @@ struct BandThin {
     int n, even, behind, span;                         // entries (0: no such list); knots over the first `span` of them, and behind
     int min_B;
     int pending, rests;                                // a knot is being evaluated; the rest's turn
-    int count, leave_out;
+    int count, leave_out, descending;
     const int32_t *whole, *cand;                       // (arguments would take scalar registers)
     int32_t *Fmin, *rest, *thin, *ticket;
 };
@@ -262,7 +262,7 @@ __device__ __forceinline__ void band_thin_begin(const BandArgs &a, int n_left, i
     min_B = wave_min_i32(min_B);
     most = min(most, BAND_THIN_KNOTS);
     const int behind = min(n - 1 - lo, stages == -1 ? 1 : most / 4);
-    if (lane == 0) *sh = BandThin{n, min(most - behind, lo + 1), behind, lo + 1, min_B, 0, 0, 0, a.leave_out, a.whole, a.cand, a.Fmin, a.rest, a.thin, a.ticket};
+    if (lane == 0) *sh = BandThin{n, min(most - behind, lo + 1), behind, lo + 1, min_B, 0, 0, 0, a.leave_out, a.descending, a.whole, a.cand, a.Fmin, a.rest, a.thin, a.ticket};
 }
 
 // The complement of the next candidate to evaluate, BAND_BETWEEN for the workgroup whose knot is the last to be there, or INT32_MAX
@@ -277,7 +277,7 @@ __device__ __forceinline__ int band_thin(BandThin *sh)
             if (there()) return BAND_BETWEEN;
         }
         for (int g; (g = atomicAdd(sh->ticket, 1)) < knots;) {
-            const int j = sh->whole[band_knot(*sh, g)];
+            const int j = sh->whole[band_knot(*sh, sh->descending ? knots - 1 - g : g)];
             if (sh->Fmin[j] == F_NOT_YET) {              // (else a graph has settled it)
                 sh->pending = 1;
                 return ~j;
@@ -289,7 +289,7 @@ __device__ __forceinline__ int band_thin(BandThin *sh)
     }
     const int x = atomicAdd(&sh->thin[THIN_TICKET], 1), n = __hip_atomic_load(&sh->thin[THIN_REST], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (x >= n) return INT32_MAX;
-    return ~__hip_atomic_load(&sh->rest[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return ~__hip_atomic_load(&sh->rest[sh->descending ? n - 1 - x : x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // All knots are there: entries between two equal ones get their value, those that cannot get below T at the knot in front for any B (where

@@ -399,6 +399,7 @@ template <bool COUNT>
 __global__ __launch_bounds__(SPARSE_WAVES * WAVE) void sparse_eval_kernel(SparseArgs a)
 {
     __shared__ unsigned long long labels[SPARSE_WAVES][GRAPH_CELLS];
+    __shared__ int sh_left[SPARSE_WAVES], sh_at;
     const int lane = threadIdx.x & (WAVE - 1), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     unsigned long long *const L = labels[wid];
     char *const Lb = (char *)L;
@@ -406,6 +407,12 @@ __global__ __launch_bounds__(SPARSE_WAVES * WAVE) void sparse_eval_kernel(Sparse
     const int32_t thr_lo = band_threshold(a.max_finite, min(lane, BAND_THRESHOLDS - 1));
     const int32_t thr_hi = band_threshold(a.max_finite, min(lane + WAVE, BAND_THRESHOLDS - 1));
     unsigned long long relaxed = 0;
+    // candidates that are left to the recurrence, a lane each, listed by the workgroup (4096 additions to one word take 45 us)
+    int left = 0, left_j = 0;
+    auto list_left = [&](int at) {
+        if (lane < left) a.o.todo[at + lane] = left_j;
+        left = 0;
+    };
     auto fence = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); };    // (LDS takes a wave's accesses in order)
     for (int tk = blockIdx.x * SPARSE_WAVES + wid; tk < n; tk += gridDim.x * SPARSE_WAVES) {
         const int j = __builtin_amdgcn_readfirstlane(a.list[a.descending ? n - 1 - tk : tk]);
@@ -538,11 +545,28 @@ __global__ __launch_bounds__(SPARSE_WAVES * WAVE) void sparse_eval_kernel(Sparse
             a.Fmin[j] = settled ? F : F_NOT_YET;
             a.Sbest[j] = settled ? s : 0;
             a.o.slot[j] = settled ? slot : -1;
-            if (!settled) a.o.todo[atomicAdd(a.o.n_todo, 1)] = j;
             if (settled && a.prune && F < DEV_INF)
                 atomicMin((long long *)&a.chunk_min[j / PRUNE_CHUNK], (long long)F + (long long)(a.p.B - 1) * c_given);
         }
+        if (!settled) {
+            left_j = lane == left ? j : left_j;
+            if (++left == WAVE) {
+                int at = 0;
+                if (lane == 0) at = atomicAdd(a.o.n_todo, left);
+                list_left(__builtin_amdgcn_readfirstlane(at));
+            }
+        }
     }
+    if (lane == 0) sh_left[wid] = left;
+    __syncthreads();
+    int before = 0, all = 0;
+    for (int w = 0; w < SPARSE_WAVES; ++w) {
+        before += w < wid ? sh_left[w] : 0;
+        all += sh_left[w];
+    }
+    if (threadIdx.x == 0 && all > 0) sh_at = atomicAdd(a.o.n_todo, all);
+    __syncthreads();
+    list_left(sh_at + before);
     if (COUNT) atomicAdd(a.wave_relax, lane == 0 ? relaxed : 0ull);
 }
 
