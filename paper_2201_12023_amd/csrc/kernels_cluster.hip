@@ -12,7 +12,7 @@
 // bytes: 240 of 790 us at 3002 operators; the band takes 20.)
 //
 // The recurrence over r is one launch for up to ROWS_PER_LAUNCH values of r (cluster_rows_kernel): a workgroup
-// owns a tile of consecutive n, with 8 lanes per n that share its candidates, whose C values stay in registers; row
+// owns a tile of consecutive n, with 8 or 16 lanes per n that share its candidates, whose C values stay in registers; row
 // r - 1 of its own tile is in LDS, and the rows of the tiles in front come through memory.
 #include "internal.hpp"
 
@@ -21,10 +21,12 @@
 namespace alpa {
 
 constexpr int CL_THREADS = 1024;
-constexpr int CL_ROW_THREADS = 512;    // of a workgroup that computes rows
-constexpr int CL_LANES = 8;            // lanes per prefix length n
-constexpr int CL_TILE = (CL_ROW_THREADS - WAVE) / CL_LANES;    // prefix lengths per workgroup (a wave fetches what is in front)
-constexpr int CL_KEEP = 16;            // candidates per lane whose C and squared FLOP are kept in registers
+// A workgroup that computes rows: LANES to a prefix length n, FETCH waves that fetch what is in front, TILE prefix lengths, and KEEP
+// candidates per lane whose C and squared FLOP are kept in registers.
+template <int L, int N_THREADS, int F>
+struct RowForm {
+    static constexpr int LANES = L, THREADS = N_THREADS, FETCH = F, TILE = (N_THREADS - F * WAVE) / L, KEEP = 16;
+};
 constexpr int ROWS_PER_LAUNCH = 128;
 constexpr int64_t NOT_YET = -1;        // no value of a row is negative
 
@@ -279,7 +281,7 @@ __device__ __forceinline__ int64_t await(int64_t v, const int64_t *p, int32_t *l
     return v;
 }
 
-// Rows 1..rows of this launch, 56 prefix lengths to a workgroup: seven waves compute a row while the last one fetches
+// Rows 1..rows of this launch, 56 prefix lengths to a workgroup (24 with wide windows, see launch_cluster): seven waves compute a row while the last one fetches
 // what the tiles in front have of it, for the next row, so a row takes what its computation takes (0.6 us) and the way of a value
 // from one workgroup to the next (1.8 us) is paid once a tile instead of once a row.  3002 operators, 96
 // layers: 185 us (where every wave fetched for itself before it computed: 243); 386 operators, 32 layers: 37 us.  By 120 prefix
@@ -291,13 +293,13 @@ __device__ __forceinline__ int64_t await(int64_t v, const int64_t *p, int32_t *l
 // EXACT (the variance tie-break over whole clusterings): with G* = G(K, L) in *gstar_p,
 //   W(n, r) = min over the feasible i with C(i, n) <= G* of W(i-1, r-1) + FLOP(o_i..o_n)^2, lowest i on ties.
 // room: prefix lengths in front and own that LDS has room for
-template <bool EXACT>
-__global__ __launch_bounds__(CL_ROW_THREADS) void cluster_rows_kernel(
+template <bool EXACT, class FORM>
+__global__ __launch_bounds__(FORM::THREADS) void cluster_rows_kernel(
     const int64_t *__restrict__ band, const int64_t *__restrict__ pf, const int32_t *__restrict__ win, int K,
     int rows, int64_t *G, int64_t *V, int32_t *__restrict__ arg, int32_t *meta,
     const int64_t *__restrict__ gstar_p, unsigned max_spins, int room)
 {
-    constexpr int T = CL_TILE, GL = CL_LANES, KEEP = CL_KEEP, ASK = 4;
+    constexpr int T = FORM::TILE, GL = FORM::LANES, KEEP = FORM::KEEP, NT = FORM::THREADS, NF = FORM::FETCH, ASK = 4;
     extern __shared__ int64_t sh[];
     __shared__ int sh_tile;
     if (threadIdx.x == 0) sh_tile = atomicAdd(&meta[1], 1);
@@ -305,7 +307,7 @@ __global__ __launch_bounds__(CL_ROW_THREADS) void cluster_rows_kernel(
     const int n0 = sh_tile * T;                      // the tile: prefix lengths n0 + 1 .. n0 + T
     if (n0 >= K) return;
     const int g = threadIdx.x % GL, nl = threadIdx.x / GL, lane = threadIdx.x & (WAVE - 1);
-    const bool fetches = threadIdx.x >= CL_ROW_THREADS - WAVE;
+    const bool fetches = threadIdx.x >= NT - NF * WAVE;
     const int n = n0 + 1 + nl;
     const int base = max(0, n0 - meta[0] + 1);       // first prefix length that the tile reads
     const int halo = n0 + 1 - base;                  // base .. n0 come from tiles in front
@@ -313,7 +315,7 @@ __global__ __launch_bounds__(CL_ROW_THREADS) void cluster_rows_kernel(
     // two rows: what is read is the one in front, [halo + T] values of V and of G
     constexpr int ENTRY = EXACT ? 1 : 2;             // V, G
     int64_t *now = sh, *next = sh + ENTRY * room;
-    for (int x = threadIdx.x; x < halo + T; x += CL_ROW_THREADS) {
+    for (int x = threadIdx.x; x < halo + T; x += NT) {
         const int m = min(base + x, K);
         now[ENTRY * x] = V[m];
         if (!EXACT) now[ENTRY * x + 1] = G[m];
@@ -343,7 +345,7 @@ __global__ __launch_bounds__(CL_ROW_THREADS) void cluster_rows_kernel(
     __syncthreads();
     if (fetches) {
         for (int r = 1; r <= rows; ++r) {            // row r of the tiles in front, for row r + 1 (the last row's for nobody)
-            for (int x0 = 0; r < rows && x0 < halo; x0 += ASK * WAVE) {
+            for (int x0 = ((int)threadIdx.x - (NT - NF * WAVE)) / WAVE * ASK * WAVE; r < rows && x0 < halo; x0 += NF * ASK * WAVE) {
                 int64_t v[ASK], w[ASK];
 #pragma unroll
                 for (int u = 0; u < ASK; ++u) {
@@ -404,13 +406,15 @@ __global__ __launch_bounds__(CL_ROW_THREADS) void cluster_rows_kernel(
             }
         }
         const Lex own = best;
-        lex_step<0xB1, EXACT>(best);             // the n's 8 lanes: neighbours, pairs, quads
+        lex_step<0xB1, EXACT>(best);             // the n's lanes: neighbours, pairs, quads, halves of a row of 16
         lex_step<0x4E, EXACT>(best);
         lex_step<0x141, EXACT>(best);
+        if (GL == 16) lex_step<0x140, EXACT>(best);
         at = (own.g == best.g) & (EXACT | (own.v == best.v)) ? at : 0;
         at = max(at, dpp_mov<0xB1>(at));
         at = max(at, dpp_mov<0x4E>(at));
         at = max(at, dpp_mov<0x141>(at));
+        if (GL == 16) at = max(at, dpp_mov<0x140>(at));
         if (g == 0 && n <= K) {
             const bool none = best.g >= (uint64_t)INF_I64;
             const int64_t G_n = none ? INF_I64 : (int64_t)best.g, V_n = EXACT ? G_n : none ? 0 : (int64_t)best.v;
@@ -495,25 +499,33 @@ __global__ void cluster_walk_kernel(const int64_t *__restrict__ G, const int64_t
     }
 }
 
-template <bool EXACT>
-static hipError_t launch_rows(hipStream_t st, const ClusterWork &w, int K, int rows, int width, int32_t *arg,
-                              unsigned max_spins)
+template <bool EXACT, class FORM>
+static hipError_t launch_rows_as(hipStream_t st, const ClusterWork &w, int K, int rows, int width, int32_t *arg,
+                                 unsigned max_spins)
 {
-    constexpr int T = CL_TILE;
+    constexpr int T = FORM::TILE;
+    const auto kernel = cluster_rows_kernel<EXACT, FORM>;
     const int room = std::min(width, K) + T + 1;
     const size_t lds = (size_t)(EXACT ? 2 : 4) * room * sizeof(int64_t);   // (133 KB at most)
     if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)cluster_rows_kernel<EXACT>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((cluster_rows_kernel<EXACT>), dim3((K + T - 1) / T), dim3(CL_ROW_THREADS), lds, st, w.band,
+    hipLaunchKernelGGL(kernel, dim3((K + T - 1) / T), dim3(FORM::THREADS), lds, st, w.band,
                        w.pf, w.win, K, rows, w.G, w.V, arg, w.meta, w.keep, max_spins, room);
     return hipGetLastError();
 }
 
 template <bool EXACT>
-static hipError_t launch_run(hipStream_t st, const ClusterWork &w, int K, int L, int width, int32_t *arg,
+static hipError_t launch_rows(hipStream_t st, const ClusterWork &w, int K, int rows, int width, bool wide, int32_t *arg,
+                              unsigned max_spins)
+{
+    if (wide) return launch_rows_as<EXACT, RowForm<16, 512, 2>>(st, w, K, rows, width, arg, max_spins);
+    return launch_rows_as<EXACT, RowForm<8, 512, 1>>(st, w, K, rows, width, arg, max_spins);
+}
+
+template <bool EXACT>
+static hipError_t launch_run(hipStream_t st, const ClusterWork &w, int K, int L, int width, bool wide, int32_t *arg,
                              unsigned max_spins)
 {
     const size_t ld = (size_t)K + 1;
@@ -523,7 +535,7 @@ static hipError_t launch_run(hipStream_t st, const ClusterWork &w, int K, int L,
         if (EXACT || done > 0)
             hipLaunchKernelGGL(cluster_begin_rows_kernel, dim3((K + 64) / 64), dim3(64), 0, st, w.G, w.V, K, rows,
                                done == 0 ? 1 : 0, EXACT ? 1 : 0, last, w.meta);
-        const hipError_t e = launch_rows<EXACT>(st, w, K, rows, width, arg + done * ld, max_spins);
+        const hipError_t e = launch_rows<EXACT>(st, w, K, rows, width, wide, arg + done * ld, max_spins);
         if (e != hipSuccess) return e;
         done += rows;
         last = rows;
@@ -548,13 +560,19 @@ hipError_t launch_cluster(hipStream_t st, const int32_t *flop, const int32_t *sr
                            nbytes, E, K, w.band, w.tot, w.meta);
     hipLaunchKernelGGL(cluster_band_in_kernel, dim3((K + 63) / 64), dim3(64), 0, st, w.band, w.tot, K, w.meta);
     hipLaunchKernelGGL(cluster_band_sum_kernel, dim3((K + 63) / 64), dim3(64), 0, st, w.band, K, w.meta);
-    hipError_t e = launch_run<false>(st, w, K, L, width, w.arg, max_spins);
+    // Windows of more than 128 operators: what eight lanes do not keep in registers they read from memory in every row.  Sixteen lanes and
+    // two waves that fetch (device time, us, cell by cell and exact, 8 lanes / 16: 3590 operators, windows of 100
+    // 273 and 403 / 285 and 416; 130 276 and 411 / 270 and 399; 200 300 and 499 / 215 and 315; 600 321 and 509 / 238 and 354; 1200 479 and 776 /
+    // 328 and 477; 962 operators, 200 113 and 168 / 90 and 124).  Where the width is not known (ctl) it is the narrow form: at most 512 operators, windows of 25
+    // 77 / 87, of 200 84 / 73.
+    const bool wide = !ctl && width > 128;
+    hipError_t e = launch_run<false>(st, w, K, L, width, wide, w.arg, max_spins);
     if (e != hipSuccess) return e;
     const size_t ld = (size_t)K + 1;
     const size_t end = (size_t)((L - 1) % ROWS_PER_LAUNCH + 1) * ld + K;   // (K, L) in the last launch's rows
     if (exact) {
         hipLaunchKernelGGL(cluster_keep_kernel, dim3(1), dim3(1), 0, st, w.G + end, w.keep);
-        e = launch_run<true>(st, w, K, L, width, w.arg, max_spins);
+        e = launch_run<true>(st, w, K, L, width, wide, w.arg, max_spins);
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(cluster_walk_kernel, dim3(1), dim3(WAVE), 0, st, exact ? w.keep : w.G + end, w.V + end,

@@ -21,12 +21,16 @@ CASES = [(1, 1, 0, 1, 0, 9), (2, 63, 200, 5, 500000, 9), (3, 64, 200, 64, 10**9,
 EDGES = [(15, 55, 200, 4, 500000, 9), (16, 56, 200, 5, 500000, 9), (17, 57, 200, 6, 500000, 9), (18, 112, 500, 2, 10**6, 3),
          (19, 113, 500, 14, 500000, 9), (20, 256, 900, 2, 0, 1), (21, 257, 900, 4, 10**6, 1), (22, 300, 900, 1, 0, 9)]
 
+# windows around 128 operators, from where on sixteen lanes share a prefix length (tiles of 24), and of more than those keep (256)
+WIDE = [(23, 300, 900, 4, 700000, 1), (24, 400, 1500, 5, 600000, 9), (25, 400, 1500, 5, 650000, 9), (26, 512, 3000, 3, 0, 9),
+        (27, 777, 4000, 3, 200000, 5), (28, 1200, 6000, 4, 10**6, 9), (29, 1200, 300, 9, 0, 1), (30, 1200, 5000, 9, 20000, 1)]
+
 
 def _edges(seed, K, E, hi):
     return W.random_op_graph(seed, K, E, flop_hi=hi)
 
 
-@pytest.mark.parametrize("case", CASES + EDGES, ids=lambda c: f"K{c[1]}-L{c[3]}")
+@pytest.mark.parametrize("case", CASES + EDGES + WIDE, ids=lambda c: f"K{c[1]}-L{c[3]}")
 @pytest.mark.parametrize("rule", ["cell", "exact", "static"])
 def test_tiles_and_windows(case, rule):
     import torch
