@@ -254,7 +254,8 @@ int alpa_dp_best(alpa_dp_t *h, alpa_plan_t *out_plan);
 /* Device time of the phases of the last solve, by the device's clock as the handle's
  * stream reaches them: candidate preparation (sort / dedup / quantiles), the recurrence
  * kernel of Eq. 3, and Eq. 4 + best selection + plan recovery.  Blocking.  Any
- * pointer may be NULL. */
+ * pointer may be NULL.  Errors: EINVAL (no solve was made), EHIP (also where the last solve was recorded into
+ * a graph). */
 int alpa_dp_last_timing(alpa_dp_t *h, float *ms_candidates, float *ms_recurrence,
                         float *ms_epilogue);
 

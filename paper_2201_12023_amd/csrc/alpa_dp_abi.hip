@@ -104,7 +104,8 @@ struct alpa_dp {
     int32_t *d_sw_Fall = nullptr;
     alpa_plan_t *d_sw_plans = nullptr;
     int clock_khz = 100000;         // of the clock that kernels read
-    bool any_solve = false, timed = false;
+    bool any_solve = false;
+    enum { NOT_TIMED, TIMED, RECORDED } timed = NOT_TIMED;   // the last solve's times are in d_state (a recorded one's are a replay's)
     bool have_best = false;         // d_best_plan holds the best of a solve made with the current
                                     // table and B (sweeps do not touch it)
     // tuning (alpa_dp_set_tuning); 0 = the library's own choice
@@ -943,7 +944,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
             }
         }
         h->any_solve = true;
-        h->timed = true;
+        h->timed = recorded ? alpa_dp::RECORDED : alpa_dp::TIMED;
         return ALPA_DP_OK;
     }
     HIPCHK(launch_epilogue(st, p, h->d_cand, h->d_Fmin, h->d_Sbest, h->d_state, prune_sel, d_out_T != nullptr,
@@ -970,7 +971,7 @@ static int solve_dev_impl(alpa_dp *h, const int32_t *d_tmax, int n_tmax, unsigne
                             h->d_best_plan, d_out_plan));
     h->any_solve = true;
     h->have_best = true;
-    h->timed = true;
+    h->timed = recorded ? alpa_dp::RECORDED : alpa_dp::TIMED;
     return ALPA_DP_OK;
 }
 
@@ -1128,7 +1129,8 @@ extern "C" int alpa_dp_last_timing(alpa_dp_t *h, float *ms_candidates, float *ms
                                    float *ms_epilogue)
 {
     if (!h) return fail(ALPA_DP_EINVAL, "handle is null");
-    if (!h->timed) return fail(ALPA_DP_EINVAL, "no solve has been made on this handle");
+    if (h->timed == alpa_dp::NOT_TIMED) return fail(ALPA_DP_EINVAL, "no solve has been made on this handle");
+    if (h->timed == alpa_dp::RECORDED) return fail(ALPA_DP_EHIP, "the last solve was recorded into a graph");
     SolveState s;
     HIPCHK(hipMemcpyAsync(&s, h->d_state, sizeof(s), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));

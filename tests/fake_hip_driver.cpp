@@ -325,6 +325,26 @@ static void long_lists()
     }
 }
 
+// times are those of a solve that has run: none are there behind one that was only recorded
+static void timing()
+{
+    alpa_dp_t *h = create();
+    alpa_plan_t plan;
+    float a, b, c;
+    CHECK(alpa_dp_last_timing(h, &a, &b, &c) == ALPA_DP_EINVAL, "times of no solve");
+    const int32_t Bs[] = {1, 3};
+    alpa_plan_t plans[2];
+    for (int eager = 0; eager < 3; ++eager) {
+        rt().capturing = true;
+        CHECK(alpa_dp_solve_dev(h, nullptr, 0, 0, nullptr, nullptr) == 0, "recorded solve");
+        rt().capturing = false;
+        CHECK(alpa_dp_last_timing(h, &a, &b, &c) == ALPA_DP_EHIP, "times of a solve that was recorded");
+        const int rc = eager == 2 ? alpa_dp_solve_sweep(h, nullptr, 0, 0, Bs, 2, plans) : alpa_dp_solve(h, nullptr, 0, 0, nullptr, &plan);
+        CHECK(rc == 0 && alpa_dp_last_timing(h, &a, &b, &c) == 0, "times of a solve: %s", alpa_dp_last_error());
+    }
+    alpa_dp_destroy(h);
+}
+
 // memory too short for old and new arrays together: without a graph the old ones make room
 static void short_memory()
 {
@@ -490,6 +510,7 @@ int main(int argc, char **argv)
     else if (what == "recorded_solve") recorded_solve();
     else if (what == "long_lists") long_lists();
     else if (what == "short_memory") short_memory();
+    else if (what == "timing") timing();
     else if (what == "routes") routes();
     else if (what == "sweep_memory") sweep_memory();
     else { printf("unknown scenario\n"); return 1; }

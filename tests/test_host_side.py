@@ -23,7 +23,7 @@ def driver(tmp_path_factory):
     return str(out)
 
 
-@pytest.mark.parametrize("scenario", ["out_of_memory", "ordinary_lists", "recorded_solve", "long_lists", "short_memory", "routes", "sweep_memory"])
+@pytest.mark.parametrize("scenario", ["out_of_memory", "ordinary_lists", "recorded_solve", "long_lists", "short_memory", "timing", "routes", "sweep_memory"])
 def test_host_side_of_a_handle(driver, scenario):
     env = dict(os.environ)
     env["LD_LIBRARY_PATH"] = os.path.dirname(B.LIB_PATH) + ":" + env.get("LD_LIBRARY_PATH", "")
