@@ -508,8 +508,11 @@ __global__ __launch_bounds__(WAVE) void plan_walk_kernel(Problem p, const int32_
     const int K = p.K, D = p.D, S = p.S;
     const int LS = (K + 2) * (D + 1);
     state += blockIdx.x;
-    if (blockIdx.x == 0 && lane == 0) solve->clock[3] = wall_clock64();    // (again behind a plan that has to be walked)
-    if (state->plan_done) return;
+    auto ends = [&] { if (lane == 0) atomicMax((unsigned long long *)&solve->clock[3], (unsigned long long)wall_clock64()); };
+    if (state->plan_done) {
+        ends();
+        return;
+    }
     F_all += blockIdx.x * slab;
     plan += blockIdx.x;
     const bool feasible = state->best_idx >= 0;
@@ -574,7 +577,7 @@ __global__ __launch_bounds__(WAVE) void plan_walk_kernel(Problem p, const int32_
         if (plan_out) ((int32_t *)plan_out)[x] = v;
         if (better) ((int32_t *)best_plan)[x] = v;
     }
-    if (blockIdx.x == 0 && lane == 0) solve->clock[3] = wall_clock64();
+    ends();                                            // (the last of a sweep's blocks counts)
 }
 
 // (and `words` of a bitmap to clear)
@@ -583,6 +586,7 @@ __global__ void init_state_kernel(SolveState *state, int64_t *chunk_min, int n_c
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t == 0) {
         state->clock[0] = wall_clock64();
+        state->clock[3] = 0;
         state->ticket = 0;
         state->n_processed = 0;
         state->best_idx = -1;
