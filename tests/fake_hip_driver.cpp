@@ -37,7 +37,7 @@ struct Runtime {
     int waits_for_capture = 0;                     // synchronisation, allocation or release in a capture
     int mallocs = 0, syncs = 0;
     int fail_from = 0, fail_to = 0, failed = 0;    // the allocations [from, to) fail
-    int32_t n_distinct = 100, largest = 5000;      // what the kernels would have found in the table
+    int32_t n_distinct = 100, largest = 5000, falls = 0;      // what the kernels would have found in the table
     Dim3 grid{}, block{};
     size_t shared = 0;
     Stream stream = nullptr;
@@ -126,7 +126,8 @@ int hipMemcpyAsync(void *dst, const void *src, size_t bytes, int kind, Stream)
     if (kind != D2H) return OK;
     memset(dst, 0, bytes);
     if (bytes == 4) memcpy(dst, &rt().n_distinct, 4);
-    if (bytes == 8) ((int32_t *)dst)[1] = rt().largest;
+    if (bytes == 12) ((int32_t *)dst)[1] = rt().largest;       // (smallest, largest, does one fall)
+    if (bytes == 12) ((int32_t *)dst)[2] = rt().falls;
     return OK;
 }
 int hipMemsetAsync(void *, int, size_t, Stream) { return OK; }
@@ -419,6 +420,30 @@ static void routes()
         CHECK(k.find(c.has) != std::string::npos, "%d layers on %dx%d, %d: no%sin%s", c.K, c.N, c.M, c.n, c.has, k.c_str());
         CHECK(k.find(c.has_not) == std::string::npos, "%d layers on %dx%d, %d: %s in%s", c.K, c.N, c.M, c.n, c.has_not,
               k.c_str());
+        alpa_dp_destroy(h);
+    }
+    // graphs where the band kernel serves, no shape is repeated and no latency falls with the stages behind: made with the bounds (by
+    // a kernel that makes none where one falls, but the bounds), gone through in each round in front of the recurrence; not behind a
+    // restriction
+    struct { int K, N, M, repeat, falls; bool makes, graphs; } graphs[] = {
+        {24, 2, 8, 0, 0, true, true}, {24, 2, 8, 0, 1, true, false}, {24, 2, 8, 8, 0, false, false}, {24, 1, 8, 0, 0, false, false},
+        {64, 16, 8, 0, 0, true, true}, {60, 32, 8, 0, 0, false, false}};
+    for (auto &c : graphs) {
+        rt().falls = c.falls;
+        alpa_dp_t *h = create_problem(c.K, c.N, c.M, c.repeat);
+        rt().falls = 0;
+        for (int n : {0, 600}) {                   // (5000 values: two rounds)
+            for (int solve = 0; solve < 2; ++solve) {
+                const std::string k = kernels_of(h, n);
+                int made = 0, gone = 0;
+                for (size_t at = 0; (at = k.find(" sparse_graph_kernel<", at)) != std::string::npos; ++at) ++made;
+                for (size_t at = 0; (at = k.find(" sparse_eval_kernel<false> recurrence_band_kernel<", at)) != std::string::npos; ++at) ++gone;
+                CHECK(made == (c.makes && n == 0 && solve == 0) && gone == (c.graphs ? n == 0 ? 2 : 1 : 0),
+                      "%d layers on %dx%d, %d, %d: %d made, %d gone through in%s", c.K, c.N, c.M, c.repeat, c.falls, made, gone, k.c_str());
+            }
+        }
+        CHECK(alpa_dp_restrict_equal_layers(h) == 0, "restriction");
+        CHECK(kernels_of(h, 0).find(" sparse_eval") == std::string::npos, "%d layers on %dx%d: graphs of stages of equal layers", c.K, c.N, c.M);
         alpa_dp_destroy(h);
     }
     // forms that the tuning call asks for, on the meshes of the register/LDS kernel
