@@ -31,6 +31,13 @@ _BATCH_INSTANCE = re.compile(r"recurrence_fast_kernelILi[1-4]ELi1ELi1ELb0ELb0ELb
 # The band kernel has a compute unit to itself (its layers fill the LDS): sixteen waves, four per SIMD, in all its
 # instances, and where it computes a table's bounds.
 _BAND_INSTANCE = re.compile(r"(recurrence_band|band_exact_bounds)_kernelI")
+# The kernels of graphs, front costs and clustering: the waves per SIMD that their workgroups make (sixteen waves in a
+# compute unit for a graph and for front costs, three workgroups of four by the labels in LDS, eight waves of clustering),
+# and bytes of scratch memory.  A graph on more than 64 devices spills two registers,
+# outside its loops.
+_OTHER_INSTANCES = [(re.compile(r"sparse_eval_kernelI"), 3, 0), (re.compile(r"sparse_graph_kernelILi1E"), 4, 0),
+                    (re.compile(r"sparse_graph_kernelILi[24]E"), 4, 12), (re.compile(r"band_thresholds_kernelI"), 4, 0),
+                    (re.compile(r"cluster_rows_kernelI"), 2, 0)]
 
 
 def parse_resource_remarks(text: str) -> dict:
@@ -71,6 +78,9 @@ def check_resources(kernels: dict) -> list:
         # accumulation register: neither may appear.
         if "recurrence_fast_kernel" in name and r.get("agprs", 0) != 0:
             bad.append(f"{name}: {r} (accumulation registers in the recurrence kernel: a spill)")
+        for pat, waves, scratch in _OTHER_INSTANCES:
+            if pat.search(name) and (r.get("occupancy", 0) < waves or r.get("scratch", 0) > scratch or r.get("agprs", 0) != 0):
+                bad.append(f"{name}: {r} ({waves} waves/SIMD and at most {scratch} bytes of scratch expected)")
     return bad
 
 
@@ -168,7 +178,7 @@ def build(verbose: bool = True, extra=()) -> str:
             j.result()
     bad = check_resources(kernels) + asm_bad
     if bad:
-        raise RuntimeError("register budget of the recurrence kernel not met:\n  " + "\n  ".join(bad))
+        raise RuntimeError("register budget not met:\n  " + "\n  ".join(bad))
     if verbose:
         n_batch = sum(1 for k in kernels if _BATCH_INSTANCE.search(k))
         print(f"resource check: {len(kernels)} kernels, {n_batch} instances at 8 waves/SIMD, "

@@ -46,6 +46,16 @@ def test_band_kernel_must_keep_four_waves_and_no_spills(name):
     assert check(136, 0, 3) == check(128, 8, 4) == check(128, 0, 4, 4) == 1
 
 
+@pytest.mark.parametrize("name, waves, scratch", [
+    ("_ZN4alpa18sparse_eval_kernelILb0EEEvNS_10SparseArgsE", 3, 0), ("_ZN4alpa19sparse_graph_kernelILi1EEEvNS_10FrontTableE", 4, 0),
+    ("_ZN4alpa19sparse_graph_kernelILi4EEEvNS_10FrontTableE", 4, 12), ("_ZN4alpa22band_thresholds_kernelILi1ELi3EEEvNS_10FrontTableE", 4, 0),
+    ("_ZN4alpa19cluster_rows_kernelILb0ENS_7RowFormILi16ELi512ELi2EEEEEvPKl", 2, 0)])
+def test_kernels_of_graphs_front_costs_and_clustering(name, waves, scratch):
+    check = lambda *r: len(B.check_resources(B.parse_resource_remarks(remarks(name, *r))))
+    assert check(90, scratch, waves) == 0
+    assert check(90, scratch, waves - 1) == check(90, scratch + 4, waves) == check(90, scratch, waves, 4) == 1
+
+
 ASM_HEAD = "\t.text\n_ZN4alpa22recurrence_fast_kernelILi4ELi1ELi1ELb0ELb0ELb0ELb0EEEvNS_7ProblemE: ; @x\n"
 
 
