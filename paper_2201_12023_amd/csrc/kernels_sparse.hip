@@ -264,11 +264,12 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
         if (sh_plan[1] > feasible || sh_plan[0] >= U) return none();
         U = __builtin_amdgcn_readfirstlane(sh_plan[0]);
     }
-    if (tid == 0) {                                // (what does not fit takes no room, not even for a moment; a swap fails only if another succeeds)
-        int at = __hip_atomic_load(g.used, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        while (at + n_stages <= g.room &&
-               !__hip_atomic_compare_exchange_strong(g.used, &at, at + n_stages, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {}
-        sh_first = at + n_stages <= g.room ? at : -1;
+    if (tid == 0) {                                // (what does not fit gives it back)
+        sh_first = atomicAdd(g.used, n_stages);
+        if (sh_first + n_stages > g.room) {
+            atomicSub(g.used, n_stages);
+            sh_first = -1;
+        }
     }
     __syncthreads();
     const int first = sh_first;
