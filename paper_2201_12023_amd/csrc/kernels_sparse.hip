@@ -325,10 +325,15 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
                 for (int y = lane; y < n_cells; y += WAVE) fewest[y] = y == 0 ? 0 : 1 << 20;
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
                 int4 w[4];                         // of chunks, as they are asked for
-                int count[4];
+                int count[4], starts = 0, ends = 0;        // (a lane for each of 64 chunks, as in sparse_eval_kernel: a read in turn before each is
+                                                   // 0.5 us a chunk)
                 auto load = [&](int ch, int u) {
-                    const int e = __builtin_amdgcn_readfirstlane(chunks[min(ch, n_chunks)]);
-                    count[u] = __builtin_amdgcn_readfirstlane(chunks[min(ch + 1, n_chunks)]) - e;
+                    if ((ch & (WAVE - 1)) == 0) {
+                        starts = chunks[min(ch + lane, n_chunks)];
+                        ends = chunks[min(ch + lane + 1, n_chunks)];
+                    }
+                    const int e = __builtin_amdgcn_readlane(starts, ch & (WAVE - 1));
+                    count[u] = __builtin_amdgcn_readlane(ends, ch & (WAVE - 1)) - e;
                     w[u] = all[e + lane];          // (there is room behind the last)
                 };
 #pragma unroll
