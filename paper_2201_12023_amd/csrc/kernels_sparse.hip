@@ -95,8 +95,8 @@ __device__ __forceinline__ int graph_scan(int v, int *sh, int &total)
 }
 
 // The graph of interval j.  Bound by what is looked at of each cell's stages, so that is done once, up to the last layer that the
-// filter lets a stage reach, by as many neighbouring cells to a wave as to any other, with the latencies of their first layer in
-// registers; what is found is listed in LDS, and only a graph of more stages than the list holds is looked at again.  (64 layers on
+// filter lets a stage reach, by as many neighbouring cells to a wave as to any other, with 256 latencies of their first layer at a time in
+// registers for all of them (read again for each cell: 57 layers on 32 x 8 522 us, now 399); what is found is listed in LDS, and only a graph of more stages than the list holds is looked at again.  (64 layers on
 // 8 x 8: every cell twice and to the last layer 156 us, listed 78, latencies kept 73; on 16 x 8 209, 86 and 72; 128 layers 308, 174 and
 // 127; 48 layers on 32 x 8, with front costs of its own for the lowest interval, 520, 210 and 191.)
 template <int W>
@@ -161,34 +161,48 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
         }
         if (lane == 0) sh_reach[k] = (int16_t)(reach < 0 ? -1 : k + reach / SP);
     }
-    // the stages of a cell, in order: found(lanes that have one, whether this one has, its number).  Neighbouring cells mostly begin
-    // with the same layer, whose latencies stay in registers
-    struct Row { int32_t t[4]; int at[4], have = -1; };      // at: last layer << 16 | devices
-    auto stages = [&](Row &r, int cell, auto found) {
-        const int x0 = sh_cell[cell], k = x0 / RS, d = x0 % RS + 1, n = (sh_reach[k] + 1 - k) * S;
-        const int32_t room = sh_room[cell];
-        const int32_t *const row = ft.least + (uint32_t)((k * K + k) * SP);
-        for (int y0 = 0; y0 < n; y0 += 4 * WAVE) {
-            if (r.have != (k << 16 | y0)) {
+    // The stages of the wave's cells: found(cell, how many it has so far, lanes that have one, whether this one has, its number), each cell's
+    // in order.  Neighbouring cells mostly begin with the same layer: up to 64 of them are gone through with 256 of its latencies in
+    // registers before the next 256 are read.  counts: zeros
+    auto stages = [&](int *counts, auto found) {
+        const int to = 1 + (n_cells - 1) * (wid + 1) / FRONT_WAVES;
+        for (int a = 1 + (n_cells - 1) * wid / FRONT_WAVES; a < to;) {
+            const int k = __builtin_amdgcn_readfirstlane(sh_cell[a] / RS);
+            const uint64_t others = __ballot(a + lane >= to || sh_cell[min(a + lane, to - 1)] / RS != k);
+            const int b = a + (others ? __ffsll((unsigned long long)others) - 1 : WAVE), n = (sh_reach[k] + 1 - k) * S;
+            const int32_t *const row = ft.least + (uint32_t)((k * K + k) * SP);
+            for (int y0 = 0; y0 < n; y0 += 4 * WAVE) {
+                int32_t t[4];
+                int at[4];                         // last layer << 16 | devices
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int y = min(y0 + u * WAVE + lane, n - 1), l = (int)(((int64_t)y * inv) >> 20);
                     const int q = y - l * S;
-                    r.t[u] = y0 + u * WAVE + lane < n ? row[(uint32_t)(l * SP + q)] : INF_I32;
-                    r.at[u] = (k + l) << 16 | sh_size[q];
+                    t[u] = y0 + u * WAVE + lane < n ? row[(uint32_t)(l * SP + q)] : INF_I32;
+                    at[u] = (k + l) << 16 | sh_size[q];
                 }
-                r.have = k << 16 | y0;
-            }
+                for (int cell = a; cell < b; ++cell) {
+                    const int d = sh_cell[cell] % RS + 1, before = __builtin_amdgcn_readfirstlane(counts[cell]);
+                    const int32_t room = sh_room[cell];
+                    int m = before;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (y0 + u * WAVE >= n) continue;  // (uniform)
-                const int i = r.at[u] >> 16, left = d - (r.at[u] & 0xffff), behind = (i + 1) * RS + left - 1;
-                const bool end = i == K - 1;
-                bool ok = r.t[u] <= c && (end ? left == 0 : left > 0);
-                const int32_t f = ok && !end ? Q[behind] : 0;
-                ok = ok && f < DEV_INF && r.t[u] + f <= room;
-                found(__ballot(ok), ok, y0 + u * WAVE + lane);
+                    for (int u = 0; u < 4; ++u) {
+                        if (y0 + u * WAVE >= n) continue;          // (uniform)
+                        const int i = at[u] >> 16, left = d - (at[u] & 0xffff), behind = (i + 1) * RS + left - 1;
+                        const bool end = i == K - 1;
+                        bool ok = t[u] <= c && (end ? left == 0 : left > 0);
+                        const int32_t f = ok && !end ? Q[behind] : 0;
+                        ok = ok && f < DEV_INF && t[u] + f <= room;
+                        const uint64_t lanes = __ballot(ok);
+                        if (lanes == 0) continue;
+                        found(cell, m, lanes, ok, y0 + u * WAVE + lane);
+                        m += __popcll(lanes);
+                    }
+                    if (m != before && lane == 0) counts[cell] = m;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
             }
+            a = b;
         }
     };
     for (int turn = 0;; ++turn) {
@@ -212,28 +226,22 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
                 const int x = place(y);
                 if (Q[x] < DEV_INF) {
                     sh_cell[at] = (uint16_t)x;
+                    sh_at[at] = 0;
                     sh_room[at] = U - front_of(x);
                     id[x] = (uint16_t)at++;
                 }
             }
             __syncthreads();
             // how many stages each has: as many cells for every wave
-            Row row;
-            for (int cell = 1 + (n_cells - 1) * wid / FRONT_WAVES; cell < 1 + (n_cells - 1) * (wid + 1) / FRONT_WAVES; ++cell) {
-                int n = 0;
-                stages(row, cell, [&](uint64_t lanes, bool ok, int y) {
-                    if (lanes == 0) return;
-                    int to = 0;
-                    if (lane == 0) to = atomicAdd(&sh_listed, __popcll(lanes));
-                    const int before = __popcll(lanes & ((1ull << lane) - 1)), e = __builtin_amdgcn_readfirstlane(to) + before;
-                    if (ok && e < list_room) {
-                        listed[e] = (uint32_t)cell << 14 | (uint32_t)y;
-                        listed_at[e] = (uint16_t)(n + before);
-                    }
-                    n += __popcll(lanes);
-                });
-                if (lane == 0) sh_at[cell] = n < 1 << 13 ? n : GRAPH_STAGES + 1;     // (a label has 13 bits for its number)
-            }
+            stages(sh_at, [&](int cell, int n, uint64_t lanes, bool ok, int y) {
+                int to = 0;
+                if (lane == 0) to = atomicAdd(&sh_listed, __popcll(lanes));
+                const int before = __popcll(lanes & ((1ull << lane) - 1)), e = __builtin_amdgcn_readfirstlane(to) + before;
+                if (ok && e < list_room) {
+                    listed[e] = (uint32_t)cell << 14 | (uint32_t)y;
+                    listed_at[e] = (uint16_t)(n + before);
+                }
+            });
             __syncthreads();
             constexpr int EACH = (GRAPH_CELLS + GRAPH_THREADS - 1) / GRAPH_THREADS;
             int own[EACH], sum = 0;
@@ -241,6 +249,7 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
             for (int u = 0; u < EACH; ++u) {
                 const int x = me * EACH + u;
                 own[u] = x >= 1 && x < n_cells ? sh_at[x] : 0;
+                if (own[u] >= 1 << 13) own[u] = GRAPH_STAGES + 1;          // (a label has 13 bits for its number)
                 sum += own[u];
             }
             at = graph_scan(sum, sh_scan, n_stages);
@@ -283,15 +292,14 @@ __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const 
     };
     if (n_stages <= list_room)
         for (int e = tid; e < n_stages; e += GRAPH_THREADS) write((int)(listed[e] >> 14), listed_at[e], (int)(listed[e] & 0x3fff));
-    Row row;
-    if (n_stages > list_room)
-        for (int cell = 1 + (n_cells - 1) * wid / FRONT_WAVES; cell < 1 + (n_cells - 1) * (wid + 1) / FRONT_WAVES; ++cell) {
-            int to = 0;
-            stages(row, cell, [&](uint64_t lanes, bool ok, int y) {
-                if (ok) write(cell, to + __popcll(lanes & ((1ull << lane) - 1)), y);
-                to += __popcll(lanes);
-            });
-        }
+    if (n_stages > list_room) {
+        int *const counts = (int *)listed;             // (the list is of no use, and has room for GRAPH_CELLS: see launch_sparse_graph)
+        for (int x = tid; x < n_cells; x += GRAPH_THREADS) counts[x] = 0;
+        __syncthreads();
+        stages(counts, [&](int cell, int n, uint64_t lanes, bool ok, int y) {
+            if (ok) write(cell, n + __popcll(lanes & ((1ull << lane) - 1)), y);
+        });
+    }
     for (int x = tid; x < n_cells; x += GRAPH_THREADS) g.cells[j * GRAPH_CELLS + x] = sh_at[x];
     // chunks: a thread per first layer, r = K - 1 - k
     auto row_start = [&](int r) {                  // where the stages that begin with layer K - 1 - r start
