@@ -463,7 +463,7 @@ __global__ void cluster_walk_kernel(const int64_t *__restrict__ G, const int64_t
     int n = K, r = L;
     if (lane == 0) first_op[L] = K;
     // A layer has at most `width` operators: where they fit a wave, what any of the next three rows can be asked for is
-    // loaded along with the present one (a load a row in turn: 23 us for 96 rows)
+    // loaded along with the present one (96 rows: 21 us, a load a row in turn 23)
     const int width = meta[0];
     const size_t ld = (size_t)K + 1;
     while (r >= 1) {

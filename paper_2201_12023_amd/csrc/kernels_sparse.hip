@@ -25,6 +25,13 @@
 
 namespace alpa {
 
+// Limits (first call on a table and later ones, us):
+// * GRAPH_CELLS (graph_label.hpp): 96 layers on 8 x 8, all values 541 and 215, with 1024 cells 709 and 365; with 2048, and two
+//   workgroups of labels to a compute unit instead of three, 560 and 220.
+// * GRAPH_STAGES: a pass over so many is some 300 chunks of 0.25 us, about what the recurrence takes of a candidate.
+// * GRAPH_SEARCH: 25 layers on 12 x 16, the plan out of 440 candidates 321 and 114, with 1024 and with 512 350 and 170, where those below the
+//   least t_max with a plan go to the recurrence; 64 on 8 x 8 354 and 149, with 512 347 and 156; 16384 takes first calls longer (5 of 354).
+// * GRAPH_LAYERS: with 128 and with 2048 the same within 3 % on 29 calls.
 constexpr int GRAPH_STAGES = 1 << 14;          // of one graph
 constexpr int GRAPH_CHUNKS = 512;              // of up to 64 stages that begin with one layer (at most 248 + 16384 / 64)
 constexpr int GRAPH_THREADS = WAVE * FRONT_WAVES;
