@@ -4,7 +4,7 @@
 // through the stage of layers k .. i on a devices with d behind its beginning is not below
 //     P(k, D - d) + least(k, i, a) + Q(i + 1, d - a),
 // and a plan whose stages pass the lower threshold bounds the best one from above, by U.  What is not above U is a
-// graph of some ten to some thousand stages between as many cells (k, d) (64 layers on 8 x 8 of an expert model: 10 to 4300 of
+// graph of some ten to some thousand stages between as many cells (k, d) (64 layers on 8 x 8 of an expert model: 10 to 5100 of
 // 23 000 stages on up to 64 device counts each), and every best plan of every candidate between the two is a way through
 // it.  So a candidate is one pass over the graph from the last layer to the first by one wave, with its filter:
 // for each cell the least sum, the fewest stages that reach it, and of those the first stage in Eq. 3's order.
@@ -104,8 +104,8 @@ __device__ __forceinline__ int graph_scan(int v, int *sh, int &total)
 // The graph of interval j.  Bound by what is looked at of each cell's stages, so that is done once, up to the last layer that the
 // filter lets a stage reach, by as many neighbouring cells to a wave as to any other, with 256 latencies of their first layer at a time in
 // registers for all of them (read again for each cell: 57 layers on 32 x 8 522 us, now 399); what is found is listed in LDS, and only a graph of more stages than the list holds is looked at again.  (64 layers on
-// 8 x 8: every cell twice and to the last layer 156 us, listed 78, latencies kept 73; on 16 x 8 209, 86 and 72; 128 layers 308, 174 and
-// 127; 48 layers on 32 x 8, with front costs of its own for the lowest interval, 520, 210 and 191.)
+// 8 x 8: every cell twice and to the last layer 156 us, listed 78, now 71; on 16 x 8 209, 86 and 75; 128 layers 308, 174 and
+// 118; 48 layers on 32 x 8, with front costs of its own for the lowest interval, 520, 210 and 198.)
 template <int W>
 __device__ __forceinline__ void sparse_graph(int j, const FrontTable &ft, const int32_t *__restrict__ table, const BandShapes &bs, int K, int D,
                                              int32_t max_finite, const int32_t *__restrict__ fronts, const int32_t *__restrict__ backs,
